@@ -23,6 +23,7 @@
 // the log-sum-exp weights of eq. 1.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstdint>
@@ -30,6 +31,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <type_traits>
 
 #include "deft_internal.h"
 
@@ -52,6 +54,8 @@ struct Stage1Args {
     const int32_t *q_order;
     const int32_t *items;  // deft::kItemInts int32 per work item, see deft_internal.h
     int32_t n_items, Hq, Hkv, G;
+    uint32_t inv_Hkv, inv_G;  // see divide
+    int32_t resident_one, resident_many;  // most row tiles of a task on the resident path, see kResidentTiles
     int32_t table_len;  // entries of the LDS per-token table: longest multi-piece chunk, in whole blocks
     float c;  // scale * log2(e): probabilities are 2^((s - m) * c)
 };
@@ -63,6 +67,13 @@ struct Stage2Args {
     int32_t nq, Hq, out_f32;
     float c;
 };
+
+// floor(n / d) for any n and d > 0, given inverse(d); a division by a run-time number costs a workgroup 0.3 us otherwise
+uint32_t inverse(uint32_t d) { return d == 1 ? 0xffffffffu : (uint32_t)((uint64_t(1) << 32) / d); }
+__device__ __forceinline__ uint32_t divide(uint32_t n, uint32_t d, uint32_t inv) {
+    const uint32_t q = __umulhi(n, inv);  // floor(n / d) or one less
+    return n - q * d >= d ? q + 1 : q;
+}
 
 __device__ __forceinline__ u32x4 load16(const uint16_t *p) { return *reinterpret_cast<const u32x4 *>(p); }
 // K/V rows of a chunk whose group fits one task (one or two row tiles): no other workgroup will read them,
@@ -79,9 +90,14 @@ __device__ __forceinline__ u32x4 load16_kv(const uint16_t *p) {
 
 __device__ __forceinline__ float wave_row_max(float x) {
     // a row of a 16-row tile lives in lanes {n, n+16, n+32, n+48}
-    x = fmaxf(x, __shfl_xor(x, 16));
-    x = fmaxf(x, __shfl_xor(x, 32));
-    return x;
+    // (a swap of rows of 16 lanes, then of halves, between two copies: no LDS round trip)
+    const uint32_t u = __builtin_bit_cast(uint32_t, x);
+    const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    const uint32_t a0 = a[0], a1 = a[1];
+    const uint32_t w = __builtin_bit_cast(uint32_t, fmaxf(__builtin_bit_cast(float, a0), __builtin_bit_cast(float, a1)));
+    const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+    const uint32_t b0 = b[0], b1 = b[1];
+    return fmaxf(__builtin_bit_cast(float, b0), __builtin_bit_cast(float, b1));
 }
 
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
@@ -645,6 +661,360 @@ struct WidePipe {
     }
 };
 
+// ---- resident path: chunks short enough to be held in registers ----
+// A chunk of at most kResidentTokens<D> tokens is loaded once, all of it at the start, into the registers of the
+// four waves (wave w holds blocks w, w+4, ...), and the row tiles of the task then pass over it one after the other:
+// Q of the next tile is fetched while the current one is worked on, the softmax of a tile needs no running state
+// (every token is there, so the maximum is exact), and the four waves' results of a tile are added in LDS.  A step
+// costs one barrier per 16 rows instead of one per 32 tokens, and no K or V byte goes through LDS.
+// Bound by latency: the chain descriptor -> rows and pieces -> K/V and Q -> tiles, each link taken once per task.
+// Stage 1, before -> after: 64 x 128 tokens x 8 heads, one tile (33.6 MB) 11.5 -> 8.1 us; 288 tasks of 256 tokens over
+// 16-token pages (37 MB) 19.9 -> 12.2 us, together with the finer cut of rows in launch_stage1_variant.
+template <int D>
+constexpr int kResidentBlocks = 256 / D;  // blocks per wave: 128 registers of K and V
+template <int D>
+constexpr int kResidentTokens = 32 * kWaves * kResidentBlocks<D>;
+constexpr int kTaskRows = 16 * deft::kMaxTilesPerTask;
+
+// LDS of the resident path, in floats / int32: two merge buffers (tiles alternate), the task's rows, the tokens
+template <int D>
+struct ResidentLds {
+    static constexpr int kPitch = D + 4;
+    static constexpr int kMerge = kWaves * 16 * kPitch + 2 * kWaves * 16;  // O, then m and l, of one tile
+    static constexpr int kRows = 2 * kMerge;
+    static constexpr int kTokens = kRows + 3 * kTaskRows;
+    static constexpr int kWords = kTokens + 3 * kResidentTokens<D>;
+    static_assert(4 * kResidentTokens<D> <= kRows, "piece records are parked in the merge buffers");
+};
+
+template <int D>
+struct ResidentTask {
+    static constexpr int KK = D / 32, VW = D / 16, NB = kResidentBlocks<D>;
+    bf16x8 k[NB][2][KK];  // A operand of S^T = K Q^T, as in KVRegs
+    u32x4 vt[NB][VW];     // A operand of product c' of O^T += V^T P^T: row n16 of it is d = VW * n16 + c'
+    bf16x8 q[KK];
+    typedef __attribute__((ext_vector_type(VW / 2))) uint32_t vrow;  // VW values of one token, as loaded
+
+    // Blocks 0..NA-1 of this wave.  Positions past the chunk's end repeat its last row (their scores are masked).
+    template <int NA>
+    __device__ __forceinline__ void load(vrow (&v)[NA][8], const ChunkCtx &c, const uint16_t *k_lane, const uint16_t *v_lane,
+                                         int wave) {
+#pragma unroll
+        for (int b = 0; b < NA; ++b) {
+            const int x0 = 32 * (wave + kWaves * b);
+#pragma unroll
+            for (int aa = 0; aa < 2; ++aa) {
+                const uint16_t *kp = k_lane + (size_t)tok_row(c, min(x0 + 16 * aa + c.n16, c.clen - 1)) * c.row_stride;
+#pragma unroll
+                for (int kk = 0; kk < KK; ++kk) k[b][aa][kk] = __builtin_bit_cast(bf16x8, load16(kp + 32 * kk));
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int x = min(x0 + 16 * (j >> 2) + 4 * c.g + (j & 3), c.clen - 1);
+                v[b][j] = *reinterpret_cast<const vrow *>(v_lane + (size_t)tok_row(c, x) * c.row_stride);
+            }
+        }
+    }
+    // 2x2 interleave of token pairs, see pv_block; done once for all tiles
+    template <int NA>
+    __device__ __forceinline__ void interleave(const vrow (&v)[NA][8]) {
+#pragma unroll
+        for (int b = 0; b < NA; ++b)
+#pragma unroll
+            for (int c2 = 0; c2 < VW / 2; ++c2)
+#pragma unroll
+                for (int p = 0; p < 4; ++p) {
+                    const uint32_t lo = v[b][2 * p][c2], hi = v[b][2 * p + 1][c2];
+                    vt[b][2 * c2][p] = __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+                    vt[b][2 * c2 + 1][p] = __builtin_amdgcn_perm(hi, lo, 0x07060302u);
+                }
+    }
+    __device__ __forceinline__ void load_q(const uint16_t *q_lane, int row) {
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) q[kk] = __builtin_bit_cast(bf16x8, load16(q_lane + (size_t)row * D + 32 * kk));
+    }
+
+    // One wave's share of one tile: scores of its NA blocks, softmax over them, products, into the merge buffer.
+    // `between` runs once the scores are under way: the sum over the waves of the tile before.
+    template <int NA, bool MASK, bool PRECISE, typename F>
+    __device__ __forceinline__ void tile(const ChunkCtx &c, int wave, int qpos, int vis_lo, int vis_hi, const uint16_t *q_lane,
+                                         int next_row, float cs, float *buf, F &&between) {
+        const u32x4 one4 = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};  // eight bf16 1.0
+        const bf16x8 ones = __builtin_bit_cast(bf16x8, one4);
+        f32x4 o[VW], l = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int cc = 0; cc < VW; ++cc) o[cc] = f32x4{0.f, 0.f, 0.f, 0.f};
+        float mx = -INFINITY;
+        f32x4 s[NA][2];
+#pragma unroll
+        for (int b = 0; b < NA; ++b)
+#pragma unroll
+            for (int aa = 0; aa < 2; ++aa) {
+                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int kk = 0; kk < KK; ++kk)
+                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k[b][aa][kk], q[kk], acc, 0, 0, 0);
+                s[b][aa] = acc;
+            }
+        load_q(q_lane, next_row);
+        __builtin_amdgcn_sched_barrier(0);  // the loads go out here, not where the registers run short
+        between();
+        // a tile none of whose rows sees any token of this wave contributes nothing (chunks of several branches)
+        if (!MASK || __any(qpos >= vis_lo && qpos < vis_hi)) {
+            if (MASK) {
+#pragma unroll
+                for (int b = 0; b < NA; ++b)
+#pragma unroll
+                    for (int aa = 0; aa < 2; ++aa) {
+                        const int xv = 32 * (wave + kWaves * b) + 16 * aa + 4 * c.g;
+                        const i32x4 qlo = *reinterpret_cast<const i32x4 *>(&c.s_qlo[xv]);
+                        const i32x4 qhi = *reinterpret_cast<const i32x4 *>(&c.s_qhi[xv]);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) s[b][aa][i] = (qpos >= qlo[i] && qpos < qhi[i]) ? s[b][aa][i] : -INFINITY;
+                    }
+            }
+#pragma unroll
+            for (int b = 0; b < NA; ++b)
+#pragma unroll
+                for (int aa = 0; aa < 2; ++aa)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) mx = fmaxf(mx, s[b][aa][i]);
+            mx = wave_row_max(mx);
+            const float mc = mx == -INFINITY ? 0.f : mx * cs;
+#pragma unroll
+            for (int b = 0; b < NA; ++b) {
+                float pv[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) pv[j] = __builtin_amdgcn_exp2f(fmaf(s[b][j >> 2][j & 3], cs, -mc));
+                u32x4 pk;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) pk[j] = pack_bf16(pv[2 * j], pv[2 * j + 1]);
+                const bf16x8 hi = __builtin_bit_cast(bf16x8, pk);
+                l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, hi, l, 0, 0, 0);
+#pragma unroll
+                for (int cc = 0; cc < VW; ++cc)
+                    o[cc] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vt[b][cc]), hi, o[cc], 0, 0, 0);
+                if (PRECISE) {  // what the rounding to bf16 dropped, see weights_block
+                    u32x4 lk;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        lk[j] = pack_bf16(pv[2 * j] - __builtin_bit_cast(float, pk[j] << 16),
+                                          pv[2 * j + 1] - __builtin_bit_cast(float, pk[j] & 0xffff0000u));
+                    const bf16x8 lo = __builtin_bit_cast(bf16x8, lk);
+                    l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, lo, l, 0, 0, 0);
+#pragma unroll
+                    for (int cc = 0; cc < VW; ++cc)
+                        o[cc] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vt[b][cc]), lo, o[cc], 0, 0, 0);
+                }
+            }
+        }
+        publish(c, wave, o, mx, l[0], buf);
+    }
+
+    // this wave's part of a tile's result: the lane owns d in [D/4 * g, D/4 * (g+1)) of row n16, d = VW * (4g + i) + c'
+    __device__ __forceinline__ void publish(const ChunkCtx &c, int wave, const f32x4 (&o)[VW], float m, float l, float *buf) {
+        float *dst = buf + (wave * 16 + c.n16) * ResidentLds<D>::kPitch + (D / 4) * c.g;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int cc = 0; cc < VW; cc += 4)
+                *reinterpret_cast<f32x4 *>(dst + VW * i + cc) = f32x4{o[cc][i], o[cc + 1][i], o[cc + 2][i], o[cc + 3][i]};
+        // the four lanes of a row store the same two numbers
+        float *ml = buf + kWaves * 16 * ResidentLds<D>::kPitch + wave * 16 + c.n16;
+        ml[0] = m;
+        ml[kWaves * 16] = l;
+    }
+
+    // The tiles of the task, one barrier each: a wave writes its part of tile t, and adds up four rows of that tile
+    // while it works on tile t + 1 in the other buffer.
+    template <int NA, bool MASK, bool PRECISE>
+    __device__ __forceinline__ void run(const Stage1Args &a, const ChunkCtx &c, float *lds, int wave, int lane, int ntiles,
+                                        const uint16_t *q_lane, int vis_lo, int vis_hi) {
+        using L = ResidentLds<D>;
+        const int32_t *row_q = reinterpret_cast<const int32_t *>(lds + L::kRows), *row_pos = row_q + kTaskRows;
+        const uint32_t *row_out = reinterpret_cast<const uint32_t *>(row_pos + kTaskRows);
+        const int n = 4 * wave + (lane >> 4), dc = lane & 15;
+        auto merge = [&](int t) {
+            const float *buf = lds + (t & 1) * L::kMerge, *ml = buf + kWaves * 16 * L::kPitch + n;
+            float m[kWaves], M = -INFINITY;
+#pragma unroll
+            for (int sp = 0; sp < kWaves; ++sp) {
+                m[sp] = ml[sp * 16];
+                M = fmaxf(M, m[sp]);
+            }
+            const float ref = M == -INFINITY ? 0.f : M;
+            float sum = 0.f;
+            f32x4 acc[D / 64];
+#pragma unroll
+            for (int e = 0; e < D / 64; ++e) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int sp = 0; sp < kWaves; ++sp) {
+                const float w = __builtin_amdgcn_exp2f((m[sp] - ref) * a.c);
+                sum += w * ml[(kWaves + sp) * 16];
+#pragma unroll
+                for (int e = 0; e < D / 64; ++e)
+                    acc[e] += w * *reinterpret_cast<const f32x4 *>(buf + (sp * 16 + n) * L::kPitch + 64 * e + 4 * dc);
+            }
+            // Rows past the end are copies of the last row and store what it stores: no condition, so that the number
+            // of stores behind the next Q loads is the same on every path and the wait for those counts them exactly.
+            const size_t ro = row_out[16 * t + n];
+            *((dc & 1 ? a.part_l : a.part_m) + ro) = dc & 1 ? sum : M;
+#pragma unroll
+            for (int e = 0; e < D / 64; ++e) *reinterpret_cast<f32x4 *>(a.part_acc + ro * D + 64 * e + 4 * dc) = acc[e];
+        };
+        if constexpr (NA == 0) {  // a wave without a block: its part is empty in both buffers from the start
+            f32x4 o[VW];
+#pragma unroll
+            for (int cc = 0; cc < VW; ++cc) o[cc] = f32x4{0.f, 0.f, 0.f, 0.f};
+            publish(c, wave, o, -INFINITY, 0.f, lds);
+            publish(c, wave, o, -INFINITY, 0.f, lds + L::kMerge);
+            for (int t = 0; t < ntiles; ++t) {
+                __syncthreads();
+                merge(t);
+            }
+        } else {
+            const int last = 16 * (ntiles - 1) + c.n16;
+            tile<NA, MASK, PRECISE>(c, wave, MASK ? row_pos[c.n16] : 0, vis_lo, vis_hi, q_lane, row_q[min(16 + c.n16, last)],
+                                    a.c, lds, [] {});
+            __builtin_amdgcn_s_waitcnt(0);  // nothing but the loop's own loads and stores is in flight inside it
+            for (int t = 1; t < ntiles; ++t) {
+                __syncthreads();
+                tile<NA, MASK, PRECISE>(c, wave, MASK ? row_pos[16 * t + c.n16] : 0, vis_lo, vis_hi, q_lane,
+                                        row_q[min(16 * (t + 1) + c.n16, last)], a.c, lds + (t & 1) * L::kMerge,
+                                        [&] { merge(t - 1); });
+            }
+            __syncthreads();
+            merge(ntiles - 1);
+        }
+    }
+};
+
+template <int D, bool PRECISE>
+__device__ __forceinline__ void resident_task(const Stage1Args &a, const int32_t *it, int h, unsigned char *s_raw) {
+    using L = ResidentLds<D>;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tile0 = it[deft::kItTile0], ntiles = it[deft::kItNTiles];
+    const int seg0 = it[deft::kItSeg0], nseg = it[deft::kItNSeg];
+    const int cqlo = it[deft::kItQlo], width = it[deft::kItWidth];
+    const int slot_base = it[deft::kItSlotBase];
+    float *lds = reinterpret_cast<float *>(s_raw);
+    int32_t *row_q = reinterpret_cast<int32_t *>(lds + L::kRows), *row_pos = row_q + kTaskRows;
+    uint32_t *row_out = reinterpret_cast<uint32_t *>(row_pos + kTaskRows);
+    int32_t *s_row = reinterpret_cast<int32_t *>(lds + L::kTokens), *s_qlo = s_row + kResidentTokens<D>,
+            *s_qhi = s_qlo + kResidentTokens<D>;
+    ChunkCtx c{};
+    c.row_stride = (size_t)a.Hkv * D;
+    c.s_row = s_row;
+    c.s_qlo = s_qlo;
+    c.s_qhi = s_qhi;
+    c.clen = it[deft::kItLen];
+    c.uniform = nseg == 1;
+    c.begin0 = it[deft::kItBegin0];
+    c.n16 = lane & 15;
+    c.g = lane >> 4;
+    const int nblk = (c.clen + 31) >> 5;
+    const int rows = min(16 * ntiles, width * a.G - 16 * tile0);  // of this task
+    const uint16_t *k_lane = a.k + (size_t)h * D + 8 * c.g, *v_lane = a.v + (size_t)h * D + (D / 16) * c.n16;
+    const uint16_t *q_lane = a.q + 8 * c.g;
+
+    // The rows of the task: where Q comes from and where the partial result goes (rows past the end repeat the last).
+    // One thread per row; the query index is asked for here and waited for in finish_rows, behind the K/V loads.
+    static_assert(kTaskRows <= 64 * kWaves, "one thread per row");
+    const int rr = 16 * tile0 + min(tid, rows - 1);
+    const int pl = divide(rr, a.G, a.inv_G), gh = rr - pl * a.G;
+    const bool row_thread = tid < 16 * ntiles;
+    int q_user = 0;
+    if (row_thread) q_user = a.q_order[cqlo + pl];
+    auto finish_rows = [&] {
+        if (row_thread) {
+            row_q[tid] = q_user * a.Hq + h * a.G + gh;
+            row_pos[tid] = cqlo + pl;
+            row_out[tid] = (uint32_t)(slot_base + pl) * (uint32_t)a.Hq + (uint32_t)(h * a.G + gh);
+        }
+    };
+    // the tokens: physical row and the interval of plan positions that see it (nobody, past the chunk's end)
+    const int mine = (nblk - wave + kWaves - 1) / kWaves;  // blocks of this wave that exist,
+    const int taken = mine <= 2 ? mine : kResidentBlocks<D>;  // and that it works on
+    const int padded = 32 * kWaves * (nblk <= kWaves ? 1 : nblk <= 2 * kWaves ? 2 : kResidentBlocks<D>);
+    const bool ragged = nseg > 1 || (c.clen & 31) || (nblk > 2 * kWaves && padded != c.clen);
+    if (nseg > 1) {
+        int32_t *p_off = reinterpret_cast<int32_t *>(s_raw), *p_beg = p_off + kResidentTokens<D>,
+                *p_lo = p_beg + kResidentTokens<D>, *p_hi = p_lo + kResidentTokens<D>;
+        for (int s = tid; s < nseg; s += 64 * kWaves) {
+            p_off[s] = a.seg_off[seg0 + s];
+            p_beg[s] = a.seg_tok_begin[seg0 + s];
+            p_lo[s] = a.seg_qlo[seg0 + s];
+            p_hi[s] = a.seg_qhi[seg0 + s];
+        }
+        __syncthreads();
+        for (int x = tid; x < padded; x += 64 * kWaves) {
+            int lo = 0, hi = nseg - 1;  // largest s with p_off[s] <= x
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (p_off[mid] <= x) lo = mid; else hi = mid - 1;
+            }
+            const bool in = x < c.clen;
+            s_row[x] = in ? p_beg[lo] + (x - p_off[lo]) : c.begin0;
+            s_qlo[x] = in ? p_lo[lo] : 0;
+            s_qhi[x] = in ? p_hi[lo] : 0;
+        }
+        finish_rows();
+        __syncthreads();
+    } else if (ragged) {
+        for (int x = tid; x < padded; x += 64 * kWaves) {
+            s_qlo[x] = 0;
+            s_qhi[x] = x < c.clen ? INT32_MAX : 0;
+        }
+    }
+
+    ResidentTask<D> T;
+    auto go = [&](auto na) {
+        constexpr int NA = decltype(na)::value;
+        typename ResidentTask<D>::vrow v[NA > 0 ? NA : 1][8];
+        if constexpr (NA > 0) T.template load<NA>(v, c, k_lane, v_lane, wave);
+        if (nseg == 1) {  // (the K/V loads needed no table: they are under way)
+            finish_rows();
+            __syncthreads();
+        }
+        // Does every row see every token of this wave's blocks?  Then nothing is masked.
+        int vis_lo = INT32_MAX, vis_hi = 0, all = 1;
+        if constexpr (NA > 0) {
+            T.load_q(q_lane, row_q[c.n16]);
+            if (ragged) {
+                if (lane < 32) {
+                    for (int b = 0; b < taken; ++b) {
+                        const int x = 32 * (wave + kWaves * b) + lane;
+                        if (s_qhi[x] > s_qlo[x]) vis_lo = min(vis_lo, s_qlo[x]);
+                        vis_hi = max(vis_hi, s_qhi[x]);
+                        all &= s_qlo[x] <= cqlo && s_qhi[x] >= cqlo + width;
+                    }
+                }
+#pragma unroll
+                for (int o = 16; o > 0; o >>= 1) {
+                    vis_lo = min(vis_lo, __shfl_xor(vis_lo, o));
+                    vis_hi = max(vis_hi, __shfl_xor(vis_hi, o));
+                }
+                vis_lo = __builtin_amdgcn_readfirstlane(vis_lo);
+                vis_hi = __builtin_amdgcn_readfirstlane(vis_hi);
+            }
+            T.template interleave<NA>(v);
+        }
+        if (!__all(all))
+            T.template run<NA, true, PRECISE>(a, c, lds, wave, lane, ntiles, q_lane, vis_lo, vis_hi);
+        else
+            T.template run<NA, false, PRECISE>(a, c, lds, wave, lane, ntiles, q_lane, vis_lo, vis_hi);
+    };
+    if (mine <= 0)
+        go(std::integral_constant<int, 0>());
+    else if (mine == 1)
+        go(std::integral_constant<int, 1>());
+    else if (D == 128 || mine == 2)
+        go(std::integral_constant<int, 2>());
+    else
+        go(std::integral_constant<int, kResidentBlocks<D>>());
+}
+
 // Stage 1: one workgroup of four waves per task = (chunk, KV head, up to 128 rows of the chunk's group).
 // The rows are (query of the group) x (query head reading this KV head), tiled 16 at a time.  A task of
 // 1, 2 or 3-4 tiles splits its rows over TR = 1, 2 or 4 waves and its tokens over the 4 / TR parts that
@@ -678,14 +1048,20 @@ __global__ __launch_bounds__(64 * kWaves, 2) void deft_stage1(Stage1Args a) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: keeps the block loops on scalar branches
     const int n16 = lane & 15;
     const int g = lane >> 4;
-    const int item = blockIdx.x / a.Hkv;
+    const int item = divide(blockIdx.x, a.Hkv, a.inv_Hkv);
     // KV head of this workgroup.  Workgroups b and b + 256 land on the same compute unit (the dispatcher goes
     // round the 256 units), and with Hkv dividing 256 they would stream the same head: K and V rows whose
     // addresses agree in bits 7..12.  A unit whose streams all share those bits reads measurably slower (its
     // L1 keeps fewer lines in flight), so every further round of 256 workgroups is moved on by one head.
     // The shift depends on the task only, so a task still visits every head exactly once.
-    const int h = (blockIdx.x - item * a.Hkv + ((item * a.Hkv) >> 8)) % a.Hkv;
+    const uint32_t turned = blockIdx.x - item * a.Hkv + ((uint32_t)(item * a.Hkv) >> 8);
+    const int h = turned - divide(turned, a.Hkv, a.inv_Hkv) * a.Hkv;
     const int32_t *it = a.items + (size_t)item * deft::kItemInts;
+    if (it[deft::kItLen] <= kResidentTokens<D> &&
+        it[deft::kItNTiles] <= (D == 128 && it[deft::kItNSeg] == 1 ? a.resident_one : a.resident_many)) {
+        resident_task<D, PRECISE>(a, it, h, s_raw);
+        return;
+    }
     const int tile0 = it[deft::kItTile0], ntiles = it[deft::kItNTiles];
     const int seg0 = it[deft::kItSeg0], nseg = it[deft::kItNSeg];
     const int cqlo = it[deft::kItQlo];
@@ -762,7 +1138,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void deft_stage1(Stage1Args a) {
         const int tile = wave % TR + 4 * u;
         const int r = 16 * (tile0 + tile) + n16;
         const bool ok = (u < NTW) && (tile < ntiles) && (r < R);
-        const int pl = r / a.G;
+        const int pl = divide(r, a.G, a.inv_G);
         q_head[u] = r - pl * a.G;
         ts[u].qpos = ok ? cqlo + pl : -1;
         q_user[u] = 0;
@@ -873,7 +1249,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void deft_stage1(Stage1Args a) {
                     o[e + 3] += w * x[3];
                 }
             }
-            const int pl = r / a.G, gh = r - pl * a.G;
+            const int pl = divide(r, a.G, a.inv_G), gh = r - pl * a.G;
             const size_t ro = (size_t)(slot_base + pl) * a.Hq + (size_t)h * a.G + gh;
             if (dc == 0) {
                 a.part_m[ro] = M;
@@ -1024,6 +1400,7 @@ bool configure_stage1() {
     if (!hip_ok(hipGetDevice(&dev), "hipGetDevice")) return false;
     if (dev >= 0 && dev < 64 && ((configured.load(std::memory_order_acquire) >> dev) & 1)) return true;
     const int bytes = kXbufBytes + 3 * DEFT_MAX_CHUNK * (int)sizeof(int32_t);
+    static_assert(ResidentLds<D>::kWords * 4 <= kXbufBytes + 3 * DEFT_MAX_CHUNK * (int)sizeof(int32_t), "LDS limit");
     if (!hip_ok(hipFuncSetAttribute(reinterpret_cast<const void *>(&deft_stage1<D, false>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, bytes), "deft_stage1 LDS size") ||
         !hip_ok(hipFuncSetAttribute(reinterpret_cast<const void *>(&deft_stage1<D, true>),
@@ -1033,26 +1410,43 @@ bool configure_stage1() {
     return true;
 }
 
+// Which tasks of a launch take the resident path, by row tiles.  A resident task costs its loads and then a fixed time
+// per tile (0.4 us for 128 tokens, 0.7 us for 256, two workgroups to a compute unit); a streaming task overlaps the two,
+// but takes a step per 32 tokens (1.2 us and more where rows are looked up token by token, as in chunks of several
+// pieces, and with d = 64, which has no fast addressing).  One tile: resident always (8191 tokens of one sequence, 512
+// tasks of one tile: stage 1 11.5 -> 8.1 us).  One piece: up to three tiles; four tiles of 256 tokens on a full chip
+// are 17.5 us streamed and 20.3 us resident.  Several pieces or d = 64: any number while the launch is one round of
+// workgroups (432 tasks of five tiles over 16-token pages: 15.8 -> 12.6 us), three when it is not and the loads of
+// other tasks cover a streaming task's steps (1328 tasks, 256 queries: 96.1 us with five, 95.0 us with three).
+constexpr int kResidentTiles = 3;
+
 template <int D, bool PRECISE>
-bool launch_stage1_variant(Stage1Args a1, const int32_t *items, int32_t n_items, hipStream_t stream) {
-    if (n_items == 0) return true;
-    a1.items = items;
-    a1.n_items = n_items;
-    const size_t lds = kXbufBytes + 3 * (size_t)a1.table_len * sizeof(int32_t);
-    const unsigned grid = (unsigned)n_items * (unsigned)a1.Hkv;
+bool launch_stage1_variant(Stage1Args a1, const uint8_t *image, const deft::TaskLists &T, hipStream_t stream) {
+    if (T.n[0] == 0) return true;
+    // Of the task lists, the finest whose workgroups are all on the chip at once: a row tile more in a task costs more
+    // than reading its chunk a second time from L2 (20 queries x 4 heads, 288 -> 416 workgroups: stage 1 16.0 -> 12.2
+    // us; 64 queries x 4 heads, d = 64: 13.5 -> 9.2 us), but a second round of workgroups costs more than both
+    // (iteration over 432 workgroups cut to 680: 12.6 -> 16.2 us).
+    int cut = 0;
+    for (int i = 1; i < deft::kTaskLists; ++i)
+        if (T.n[i] > 0 && (int64_t)T.n[i] * a1.Hkv <= deft::kResidentGroups) cut = i;
+    a1.items = reinterpret_cast<const int32_t *>(image + T.off[cut]);
+    a1.n_items = T.n[cut];
+    const bool one_round = (int64_t)a1.n_items * a1.Hkv <= deft::kResidentGroups;
+    a1.resident_one = kResidentTiles;
+    a1.resident_many = one_round ? deft::kMaxTilesPerTask : kResidentTiles;
+    const size_t lds = std::max(kXbufBytes + 3 * (size_t)a1.table_len * sizeof(int32_t), (size_t)ResidentLds<D>::kWords * 4);
+    const unsigned grid = (unsigned)a1.n_items * (unsigned)a1.Hkv;
     hipLaunchKernelGGL((deft_stage1<D, PRECISE>), dim3(grid), dim3(64 * kWaves), lds, stream, a1);
     return hip_ok(hipGetLastError(), "deft_stage1 launch");
 }
 
-// The task list holds the tasks with bf16 weights first, then those with two-term weights.
 template <int D>
 bool launch_stage1(const deft::Schedule &S, const Stage1Args &a1, const uint8_t *image, hipStream_t stream) {
     if (S.n_items == 0) return true;
     if (!configure_stage1<D>()) return false;
-    const int32_t *items = reinterpret_cast<const int32_t *>(image + S.off_items);
-    const int32_t n_fast = S.n_items - S.n_items_precise;
-    return launch_stage1_variant<D, false>(a1, items, n_fast, stream) &&
-           launch_stage1_variant<D, true>(a1, items + (size_t)n_fast * deft::kItemInts, S.n_items_precise, stream);
+    return launch_stage1_variant<D, false>(a1, image, S.tasks[0], stream) &&
+           launch_stage1_variant<D, true>(a1, image, S.tasks[1], stream);
 }
 
 template <int D>
@@ -1116,6 +1510,8 @@ int run_stage1(const deft_plan_t *plan, const Call &call, const void *q, const v
     a1.Hq = Hq;
     a1.Hkv = Hkv;
     a1.G = Hq / Hkv;
+    a1.inv_Hkv = inverse(Hkv);
+    a1.inv_G = inverse(a1.G);
     a1.table_len = S.table_len;
     a1.c = call.c;
     const bool ok = d == 128 ? launch_stage1<128>(S, a1, call.img, call.stream)

@@ -33,11 +33,20 @@ enum ItemField {
     kItBegin0 = 9,    // first segment: physical row of its first token,
     kItSegQlo0 = 10,  //                its query interval
     kItSegQhi0 = 11,
-    kItPrecise = 12,  // 1: the softmax weights enter the products as two bf16 terms (short paths, or on request)
-    kItCostTiles = 13,  // host only: tiles of the largest task of this chunk, the key of the dispatch order
 };
 // A group one of whose queries has fewer tokens than this on its whole path gets two-term weights.
 constexpr int kPreciseBelowTokens = 1024;
+
+// The same work as up to kTaskLists lists of tasks: list 0 has tasks of up to kMaxTilesPerTask row tiles, list i of up
+// to kTaskTiles[i].  A launch takes the finest list whose workgroups fit the chip at once, which depends on the number
+// of KV heads; a list that no launch can take, or that is the same as the one before, is left out (n = 0).
+constexpr int kTaskLists = 4;
+constexpr int kTaskTiles[kTaskLists] = {kMaxTilesPerTask, 4, 3, 2};
+constexpr int kResidentGroups = 512;  // workgroups of stage 1 that an MI355X holds: two on each of 256 compute units
+struct TaskLists {
+    int32_t n[kTaskLists] = {};   // tasks
+    size_t off[kTaskLists] = {};  // where their descriptors lie in the image
+};
 
 // Launch schedule + image layout for one Hq/Hkv ratio.
 struct Schedule {
@@ -48,9 +57,8 @@ struct Schedule {
     size_t off_q_order = 0;
     size_t off_q_part_ptr = 0, off_q_part_slot = 0;
     size_t off_q_head = 0;    // per-query records for stage 2
-    size_t off_items = 0;     // task descriptors
     int32_t n_items = 0;
-    int32_t n_items_precise = 0;  // the last n_items_precise tasks of the list want two-term weights
+    TaskLists tasks[2];       // of the groups with bf16 weights, of those with two-term weights
     int32_t table_len = 32;   // longest chunk made of several pieces, rounded up to whole blocks: LDS table size
     std::vector<uint8_t> host_image;  // packed image, kept for repeated uploads
 };

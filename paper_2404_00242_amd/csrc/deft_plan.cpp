@@ -706,8 +706,11 @@ static void build_schedule(const deft_plan_t *P, int32_t G, Schedule &S) {
     S.group = G;
     S.table_len = 32;
     const int32_t m = P->n_chunks();
-    std::vector<int32_t> items;
     std::vector<int32_t> seg_off(P->n_segs(), 0);
+    struct Chunk {
+        int32_t id, len, tiles;
+    };
+    std::vector<Chunk> chunks[2];  // by the kind of weights
     for (int32_t c = 0; c < m; ++c) {
         const int32_t s0 = P->chunk_seg_ptr[c], s1 = P->chunk_seg_ptr[c + 1];
         int32_t len = 0;
@@ -716,62 +719,68 @@ static void build_schedule(const deft_plan_t *P, int32_t G, Schedule &S) {
             len += P->seg_len[s];
         }
         if (s1 - s0 > 1) S.table_len = std::max(S.table_len, (len + 31) / 32 * 32);
-        const int32_t width = P->chunk_qhi[c] - P->chunk_qlo[c];
-        const int64_t rows = (int64_t)width * G;
-        const int32_t tiles = (int32_t)((rows + 15) / 16);
+        const int64_t rows = (int64_t)(P->chunk_qhi[c] - P->chunk_qlo[c]) * G;
         // two-term softmax weights where some query of the group has a short path
         int32_t precise = P->precise_all ? 1 : 0;
         for (int32_t p = P->chunk_qlo[c]; p < P->chunk_qhi[c] && !precise; ++p)
             if (P->q_path_len[p] < kPreciseBelowTokens) precise = 1;
-        // Groups of more than kMaxTilesPerTask tiles become several tasks of (nearly) equal size: the row groups
-        // of one chunk then cost the same, are dispatched next to each other and find the chunk in L2 after the
-        // first of them has fetched it.
-        const int32_t n_tasks = (tiles + kMaxTilesPerTask - 1) / kMaxTilesPerTask;
-        const int32_t per_task = n_tasks ? (tiles + n_tasks - 1) / n_tasks : 0;
-        for (int32_t t0 = 0; t0 < tiles; t0 += per_task) {
-            int32_t d[kItemInts] = {0};
-            d[kItChunk] = c;
-            d[kItTile0] = t0;
-            d[kItNTiles] = std::min<int32_t>(per_task, tiles - t0);
-            d[kItSeg0] = s0;
-            d[kItNSeg] = s1 - s0;
-            d[kItQlo] = P->chunk_qlo[c];
-            d[kItWidth] = width;
-            d[kItSlotBase] = P->chunk_slot_base[c];
-            d[kItLen] = len;
-            d[kItBegin0] = P->seg_tok_begin[s0];
-            d[kItSegQlo0] = P->seg_qlo[s0];
-            d[kItSegQhi0] = P->seg_qhi[s0];
-            d[kItPrecise] = precise;
-            d[kItCostTiles] = per_task;
-            items.insert(items.end(), d, d + kItemInts);
-        }
+        chunks[precise].push_back({c, len, (int32_t)((rows + 15) / 16)});
     }
 
+    // Groups of more row tiles than a list allows become several tasks of (nearly) equal size: the row groups of one
+    // chunk then cost the same, are dispatched next to each other and find the chunk in L2 after the first of them
+    // has fetched it.
+    //
     // Dispatch order: workgroups are handed to compute units in the order of the task list, a new one
     // whenever a slot frees, so the longest tasks go first (tokens x (2 + row tiles) as the estimate) and
     // the short ones fill the tail.  The row groups of one chunk share one estimate (that of the largest of
     // them) and equal estimates keep their chunk order, which leaves them next to each other: they re-read
     // that chunk from the same L2 while it is still there.
-    {
-        const int32_t n = (int32_t)(items.size() / kItemInts);
-        std::vector<int32_t> order(n);
-        for (int32_t i = 0; i < n; ++i) order[i] = i;
-        auto cost = [&](int32_t i) {
-            return (int64_t)items[(size_t)i * kItemInts + kItLen] * (2 + items[(size_t)i * kItemInts + kItCostTiles]);
+    std::vector<int32_t> items[2][kTaskLists];
+    for (int kind = 0; kind < 2; ++kind) {
+        const std::vector<Chunk> &own = chunks[kind];
+        auto cuts = [](int32_t tiles, int list) { return (tiles + kTaskTiles[list] - 1) / kTaskTiles[list]; };
+        auto per_task = [&](int32_t tiles, int list) {
+            const int32_t k = cuts(tiles, list);
+            return k ? (tiles + k - 1) / k : 0;
         };
-        auto precise = [&](int32_t i) { return items[(size_t)i * kItemInts + kItPrecise]; };
-        // tasks with two-term weights run in a kernel of their own and come last in the list
-        std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
-            if (precise(x) != precise(y)) return precise(x) < precise(y);
-            return cost(x) > cost(y);
-        });
-        S.n_items_precise = 0;
-        for (int32_t i = 0; i < n; ++i) S.n_items_precise += precise(i);
-        std::vector<int32_t> sorted(items.size());
-        for (int32_t i = 0; i < n; ++i)
-            std::memcpy(&sorted[(size_t)i * kItemInts], &items[(size_t)order[i] * kItemInts], kItemInts * sizeof(int32_t));
-        items.swap(sorted);
+        std::vector<std::pair<int64_t, int32_t>> order(own.size());  // (-estimate, index)
+        int before = 0;                                              // the last list that was kept
+        for (int list = 0; list < kTaskLists; ++list) {
+            int64_t n = 0;
+            bool same = list > 0;
+            for (const Chunk &ch : own) {
+                const int32_t per = per_task(ch.tiles, list);
+                n += per ? (ch.tiles + per - 1) / per : 0;
+                same = same && per == per_task(ch.tiles, before);
+            }
+            if (same || (list > 0 && n > kResidentGroups)) continue;
+            before = list;
+            for (size_t i = 0; i < own.size(); ++i)
+                order[i] = {-(int64_t)own[i].len * (2 + per_task(own[i].tiles, list)), (int32_t)i};
+            std::sort(order.begin(), order.end());
+            std::vector<int32_t> &out = items[kind][list];
+            out.assign((size_t)n * kItemInts, 0);
+            int32_t *d = out.data();
+            for (const auto &at : order) {
+                const Chunk &ch = own[at.second];
+                const int32_t c = ch.id, s0 = P->chunk_seg_ptr[c], per = per_task(ch.tiles, list);
+                for (int32_t t0 = 0; t0 < ch.tiles; t0 += per, d += kItemInts) {
+                    d[kItChunk] = c;
+                    d[kItTile0] = t0;
+                    d[kItNTiles] = std::min<int32_t>(per, ch.tiles - t0);
+                    d[kItSeg0] = s0;
+                    d[kItNSeg] = P->chunk_seg_ptr[c + 1] - s0;
+                    d[kItQlo] = P->chunk_qlo[c];
+                    d[kItWidth] = P->chunk_qhi[c] - P->chunk_qlo[c];
+                    d[kItSlotBase] = P->chunk_slot_base[c];
+                    d[kItLen] = ch.len;
+                    d[kItBegin0] = P->seg_tok_begin[s0];
+                    d[kItSegQlo0] = P->seg_qlo[s0];
+                    d[kItSegQhi0] = P->seg_qhi[s0];
+                }
+            }
+        }
     }
 
     size_t off = 0;
@@ -791,8 +800,12 @@ static void build_schedule(const deft_plan_t *P, int32_t G, Schedule &S) {
     S.off_q_part_slot = place(slots);
     off = (off + 63) & ~(size_t)63;  // per-query records and descriptors are aligned 64-byte records
     S.off_q_head = place((size_t)nq * kQueryHeadInts);
-    S.n_items = (int32_t)(items.size() / kItemInts);
-    S.off_items = place(items.size());
+    for (int kind = 0; kind < 2; ++kind)
+        for (int list = 0; list < kTaskLists; ++list) {
+            S.tasks[kind].n[list] = (int32_t)(items[kind][list].size() / kItemInts);
+            S.tasks[kind].off[list] = place(items[kind][list].size());
+        }
+    S.n_items = S.tasks[0].n[0] + S.tasks[1].n[0];
     S.bytes = std::max<size_t>(off, 16);
     S.host_image.assign(S.bytes, 0);
     auto put = [&](size_t at, const std::vector<int32_t> &v) {
@@ -806,7 +819,8 @@ static void build_schedule(const deft_plan_t *P, int32_t G, Schedule &S) {
     put(S.off_q_order, P->q_order);
     put(S.off_q_part_ptr, P->q_part_ptr);
     put(S.off_q_part_slot, P->q_part_slot);
-    put(S.off_items, items);
+    for (int kind = 0; kind < 2; ++kind)
+        for (int list = 0; list < kTaskLists; ++list) put(S.tasks[kind].off[list], items[kind][list]);
     {
         std::vector<int32_t> head((size_t)nq * kQueryHeadInts, 0);
         for (int32_t p = 0; p < nq; ++p) {

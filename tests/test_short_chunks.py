@@ -1,0 +1,57 @@
+"""Chunks that stage 1 holds in registers (at most 256 tokens at d = 128, 512 at d = 64), and the cut of a task's rows
+over several workgroups, at the sizes where they can go wrong.  Same tolerance as tests/test_gpu_parity.py, whose
+paths of fewer than 1024 tokens also get the tight bound of two-term weights."""
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2404_00242_amd import workloads as wl
+
+from .test_gpu_parity import check, reference, reference_abs_v, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def tree(root, branches, Hq, Hkv, d, seed):
+    """a root of `root` tokens under branches of the given lengths, one query each (0: on a node without tokens)"""
+    lens = np.asarray([root] + list(branches), dtype=np.int32)
+    begin = np.concatenate([[0], np.cumsum(lens)[:-1]]).astype(np.int32)
+    parent = np.asarray([-1] + [0] * len(branches), dtype=np.int32)
+    return wl.Tree(name=f"short_{root}", node_tok_begin=begin, node_tok_len=lens, node_parent=parent,
+                   query_node=np.arange(1, len(lens), dtype=np.int32), ntok=int(lens.sum()), Hq=Hq, Hkv=Hkv, d=d, value_seed=seed)
+
+
+# blocks per wave 1 and 2 (and 4 at d = 64), whole and broken last blocks, waves without a block, one token
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("root", [1, 31, 33, 96, 128, 129, 255, 256, 257, 300, 385, 512, 513])
+def test_one_chunk_of_every_length(root, d):
+    t = tree(root, [0, 3, 1, 2], 6, 2, d, seed=root)
+    Q, K, V = wl.make_qkv(t)
+    got, _ = run_gpu(t, Q, K, V, chunk_size=1024, out_dtype=torch.float32, mode="node")
+    check(got, reference(t, Q, K, V), strict=False, abs_v=reference_abs_v(t, Q, K, V), two_term=True)
+
+
+# 1 to 17 row tiles, the last one full, nearly full or with one row; KV heads that leave the chip empty (rows cut as
+# finely as they go), nearly full, and over-full (not cut at all)
+@pytest.mark.parametrize("nq,G", [(1, 1), (17, 1), (33, 1), (12, 4), (13, 5), (129, 1), (65, 4)])
+@pytest.mark.parametrize("Hkv", [1, 8, 48])
+def test_row_tiles_and_workgroup_cuts(nq, G, Hkv):
+    if nq * G * Hkv > 4000:
+        Hkv = 12
+    t = tree(700, [(5 * i) % 7 for i in range(nq)], G * Hkv, Hkv, 128, seed=nq)
+    Q, K, V = wl.make_qkv(t)
+    for chunk in (96, 256, 640):
+        got, _ = run_gpu(t, Q, K, V, chunk_size=chunk, out_dtype=torch.float32)
+        check(got, reference(t, Q, K, V), strict=False, abs_v=reference_abs_v(t, Q, K, V), two_term=True)
+
+
+# long paths (bf16 weights) through the same shapes; both splits
+@pytest.mark.parametrize("mode", ["flatten", "balanced"])
+@pytest.mark.parametrize("nq,Hq,Hkv,d", [(3, 8, 8, 128), (20, 32, 8, 128), (9, 24, 2, 64), (70, 8, 2, 64)])
+def test_long_paths_in_short_chunks(nq, Hq, Hkv, d, mode):
+    t = tree(1100, [(7 * i) % 90 for i in range(nq)], Hq, Hkv, d, seed=nq)
+    Q, K, V = wl.make_qkv(t)
+    for chunk in (128, 224, 256):
+        got, _ = run_gpu(t, Q, K, V, chunk_size=chunk, out_dtype=torch.float32, mode=mode)
+        check(got, reference(t, Q, K, V), strict=False)

@@ -1026,7 +1026,7 @@ __device__ __forceinline__ void resident_task(const Stage1Args &a, const int32_t
 // that the extra registers of the precise one do not weigh on the other; a plan's tasks are listed by
 // variant and a call launches each non-empty list.
 template <int D, bool PRECISE>
-__global__ __launch_bounds__(64 * kWaves, 2) void deft_stage1(Stage1Args a) {
+__device__ __forceinline__ void streaming_task(const Stage1Args &a, const int32_t *it, int h, unsigned char *s_raw) {
     constexpr int KK = D / 32;  // k-steps of the Q.K^T contraction
     // The P.V product runs as 8 MFMAs per block (a lane loads 8 d of V per token).  With D = 64 lanes
     // n16 >= 8 repeat the loads of n16 - 8 and half of each product is discarded; that shape only occurs
@@ -1034,7 +1034,6 @@ __global__ __launch_bounds__(64 * kWaves, 2) void deft_stage1(Stage1Args a) {
     static_assert(D == 64 || D == 128, "head dimension");
     constexpr int OP = D + 4;  // padded row pitch (floats) of the merge buffer
 
-    extern __shared__ __attribute__((aligned(16))) unsigned char s_raw[];
     u32x4 *xbuf = reinterpret_cast<u32x4 *>(s_raw);                     // register exchange, kXbufBytes
     float *mO = reinterpret_cast<float *>(s_raw);                       // merge buffer, aliases the exchange
     float *mM = mO + kWaves * 16 * OP;
@@ -1048,20 +1047,6 @@ __global__ __launch_bounds__(64 * kWaves, 2) void deft_stage1(Stage1Args a) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: keeps the block loops on scalar branches
     const int n16 = lane & 15;
     const int g = lane >> 4;
-    const int item = divide(blockIdx.x, a.Hkv, a.inv_Hkv);
-    // KV head of this workgroup.  Workgroups b and b + 256 land on the same compute unit (the dispatcher goes
-    // round the 256 units), and with Hkv dividing 256 they would stream the same head: K and V rows whose
-    // addresses agree in bits 7..12.  A unit whose streams all share those bits reads measurably slower (its
-    // L1 keeps fewer lines in flight), so every further round of 256 workgroups is moved on by one head.
-    // The shift depends on the task only, so a task still visits every head exactly once.
-    const uint32_t turned = blockIdx.x - item * a.Hkv + ((uint32_t)(item * a.Hkv) >> 8);
-    const int h = turned - divide(turned, a.Hkv, a.inv_Hkv) * a.Hkv;
-    const int32_t *it = a.items + (size_t)item * deft::kItemInts;
-    if (it[deft::kItLen] <= kResidentTokens<D> &&
-        it[deft::kItNTiles] <= (D == 128 && it[deft::kItNSeg] == 1 ? a.resident_one : a.resident_many)) {
-        resident_task<D, PRECISE>(a, it, h, s_raw);
-        return;
-    }
     const int tile0 = it[deft::kItTile0], ntiles = it[deft::kItNTiles];
     const int seg0 = it[deft::kItSeg0], nseg = it[deft::kItNSeg];
     const int cqlo = it[deft::kItQlo];
@@ -1263,6 +1248,35 @@ __global__ __launch_bounds__(64 * kWaves, 2) void deft_stage1(Stage1Args a) {
     }
 }
 
+enum Weights { kBf16 = 0, kTwoTerm = 1, kMixed = 2 };
+
+template <int D, bool PRECISE>
+__device__ __forceinline__ void run_task(const Stage1Args &a, const int32_t *it, int h, unsigned char *s_raw) {
+    if (it[deft::kItLen] <= kResidentTokens<D> &&
+        it[deft::kItNTiles] <= (D == 128 && it[deft::kItNSeg] == 1 ? a.resident_one : a.resident_many))
+        resident_task<D, PRECISE>(a, it, h, s_raw);
+    else
+        streaming_task<D, PRECISE>(a, it, h, s_raw);
+}
+
+template <int D, int WEIGHTS>
+__global__ __launch_bounds__(64 * kWaves, 2) void deft_stage1(Stage1Args a) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char s_raw[];
+    const int item = divide(blockIdx.x, a.Hkv, a.inv_Hkv);
+    // KV head of this workgroup.  Workgroups b and b + 256 land on the same compute unit (the dispatcher goes
+    // round the 256 units), and with Hkv dividing 256 they would stream the same head: K and V rows whose
+    // addresses agree in bits 7..12.  A unit whose streams all share those bits reads measurably slower (its
+    // L1 keeps fewer lines in flight), so every further round of 256 workgroups is moved on by one head.
+    // The shift depends on the task only, so a task still visits every head exactly once.
+    const uint32_t turned = blockIdx.x - item * a.Hkv + ((uint32_t)(item * a.Hkv) >> 8);
+    const int h = turned - divide(turned, a.Hkv, a.inv_Hkv) * a.Hkv;
+    const int32_t *it = a.items + (size_t)item * deft::kItemInts;
+    if (WEIGHTS == kTwoTerm || (WEIGHTS == kMixed && it[deft::kItPrecise]))
+        run_task<D, true>(a, it, h, s_raw);
+    else
+        run_task<D, false>(a, it, h, s_raw);
+}
+
 // Stage 2: tree-topology-aware global reduction (eq. 1 with the largest maximum subtracted).
 // One wave per (query, query head).  Weights are computed with lanes across the query's slots;
 // the weighted rows are then summed with D/4 lanes per row (128-bit loads), several rows at a time.
@@ -1401,11 +1415,10 @@ bool configure_stage1() {
     if (dev >= 0 && dev < 64 && ((configured.load(std::memory_order_acquire) >> dev) & 1)) return true;
     const int bytes = kXbufBytes + 3 * DEFT_MAX_CHUNK * (int)sizeof(int32_t);
     static_assert(ResidentLds<D>::kWords * 4 <= kXbufBytes + 3 * DEFT_MAX_CHUNK * (int)sizeof(int32_t), "LDS limit");
-    if (!hip_ok(hipFuncSetAttribute(reinterpret_cast<const void *>(&deft_stage1<D, false>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, bytes), "deft_stage1 LDS size") ||
-        !hip_ok(hipFuncSetAttribute(reinterpret_cast<const void *>(&deft_stage1<D, true>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, bytes), "deft_stage1 LDS size"))
-        return false;
+    for (const void *f : {reinterpret_cast<const void *>(&deft_stage1<D, kBf16>),
+                          reinterpret_cast<const void *>(&deft_stage1<D, kTwoTerm>),
+                          reinterpret_cast<const void *>(&deft_stage1<D, kMixed>)})
+        if (!hip_ok(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes), "deft_stage1 LDS size")) return false;
     if (dev >= 0 && dev < 64) configured.fetch_or(1ull << dev, std::memory_order_release);
     return true;
 }
@@ -1420,33 +1433,21 @@ bool configure_stage1() {
 // other tasks cover a streaming task's steps (1328 tasks, 256 queries: 96.1 us with five, 95.0 us with three).
 constexpr int kResidentTiles = 3;
 
-template <int D, bool PRECISE>
-bool launch_stage1_variant(Stage1Args a1, const uint8_t *image, const deft::TaskLists &T, hipStream_t stream) {
-    if (T.n[0] == 0) return true;
-    // Of the task lists, the finest whose workgroups are all on the chip at once: a row tile more in a task costs more
-    // than reading its chunk a second time from L2 (20 queries x 4 heads, 288 -> 416 workgroups: stage 1 16.0 -> 12.2
-    // us; 64 queries x 4 heads, d = 64: 13.5 -> 9.2 us), but a second round of workgroups costs more than both
-    // (iteration over 432 workgroups cut to 680: 12.6 -> 16.2 us).
-    int cut = 0;
-    for (int i = 1; i < deft::kTaskLists; ++i)
-        if (T.n[i] > 0 && (int64_t)T.n[i] * a1.Hkv <= deft::kResidentGroups) cut = i;
-    a1.items = reinterpret_cast<const int32_t *>(image + T.off[cut]);
-    a1.n_items = T.n[cut];
-    const bool one_round = (int64_t)a1.n_items * a1.Hkv <= deft::kResidentGroups;
-    a1.resident_one = kResidentTiles;
-    a1.resident_many = one_round ? deft::kMaxTilesPerTask : kResidentTiles;
-    const size_t lds = std::max(kXbufBytes + 3 * (size_t)a1.table_len * sizeof(int32_t), (size_t)ResidentLds<D>::kWords * 4);
-    const unsigned grid = (unsigned)a1.n_items * (unsigned)a1.Hkv;
-    hipLaunchKernelGGL((deft_stage1<D, PRECISE>), dim3(grid), dim3(64 * kWaves), lds, stream, a1);
-    return hip_ok(hipGetLastError(), "deft_stage1 launch");
-}
-
 template <int D>
-bool launch_stage1(const deft::Schedule &S, const Stage1Args &a1, const uint8_t *image, hipStream_t stream) {
+bool launch_stage1(const deft::Schedule &S, Stage1Args a1, const uint8_t *image, hipStream_t stream) {
     if (S.n_items == 0) return true;
     if (!configure_stage1<D>()) return false;
-    return launch_stage1_variant<D, false>(a1, image, S.tasks[0], stream) &&
-           launch_stage1_variant<D, true>(a1, image, S.tasks[1], stream);
+    a1.items = reinterpret_cast<const int32_t *>(image + S.off_items);
+    a1.n_items = S.n_items;
+    a1.resident_one = kResidentTiles;
+    a1.resident_many = (int64_t)S.n_items * a1.Hkv <= deft::kResidentGroups ? deft::kMaxTilesPerTask : kResidentTiles;
+    const size_t lds = std::max(kXbufBytes + 3 * (size_t)a1.table_len * sizeof(int32_t), (size_t)ResidentLds<D>::kWords * 4);
+    const unsigned grid = (unsigned)S.n_items * (unsigned)a1.Hkv;
+    auto *kernel = S.n_items_precise == 0           ? &deft_stage1<D, kBf16>
+                   : S.n_items_precise == S.n_items ? &deft_stage1<D, kTwoTerm>
+                                                    : &deft_stage1<D, kMixed>;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * kWaves), lds, stream, a1);
+    return hip_ok(hipGetLastError(), "deft_stage1 launch");
 }
 
 template <int D>
@@ -1605,7 +1606,7 @@ extern "C" int deft_plan_upload(deft_plan_t *plan, int32_t Hq, int32_t Hkv, void
     if (!aligned16(dev_image)) return DEFT_EINVAL;
     const deft::Schedule *S = nullptr;
     try {
-        S = deft::get_schedule(plan, Hq / Hkv);
+        S = deft::get_schedule(plan, Hq / Hkv, Hkv);
     } catch (...) {
         return DEFT_ENOMEM;
     }

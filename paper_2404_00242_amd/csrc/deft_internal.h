@@ -33,22 +33,20 @@ enum ItemField {
     kItBegin0 = 9,    // first segment: physical row of its first token,
     kItSegQlo0 = 10,  //                its query interval
     kItSegQhi0 = 11,
+    kItPrecise = 12,  // 1: the softmax weights enter the products as two bf16 terms (short paths, or on request)
 };
 // A group one of whose queries has fewer tokens than this on its whole path gets two-term weights.
 constexpr int kPreciseBelowTokens = 1024;
 
-// The same work as up to kTaskLists lists of tasks: list 0 has tasks of up to kMaxTilesPerTask row tiles, list i of up
-// to kTaskTiles[i].  A launch takes the finest list whose workgroups fit the chip at once, which depends on the number
-// of KV heads; a list that no launch can take, or that is the same as the one before, is left out (n = 0).
-constexpr int kTaskLists = 4;
-constexpr int kTaskTiles[kTaskLists] = {kMaxTilesPerTask, 4, 3, 2};
+// Row tiles to a task, from coarse to fine.  The schedule takes the finest cut whose workgroups are all on the chip at
+// once: a row tile more in a task costs more than reading its chunk a second time from L2 (20 queries x 4 heads over 8
+// KV heads, 288 -> 416 workgroups: stage 1 16.0 -> 12.2 us; 64 queries x 4 heads, d = 64: 13.5 -> 9.2 us), but a second
+// round of workgroups costs more than either (432 workgroups cut to 680: 12.6 -> 16.2 us).
+constexpr int kTaskTiles[] = {kMaxTilesPerTask, 4, 3, 2};
 constexpr int kResidentGroups = 512;  // workgroups of stage 1 that an MI355X holds: two on each of 256 compute units
-struct TaskLists {
-    int32_t n[kTaskLists] = {};   // tasks
-    size_t off[kTaskLists] = {};  // where their descriptors lie in the image
-};
 
-// Launch schedule + image layout for one Hq/Hkv ratio.
+// Launch schedule + image layout for one Hq/Hkv ratio.  The row cut suits the number of KV heads it was first asked
+// for with; the schedule is right for any.
 struct Schedule {
     int32_t group = 0;        // G = Hq / Hkv, rows per query within one KV head
     size_t bytes = 0;         // total image size
@@ -58,7 +56,8 @@ struct Schedule {
     size_t off_q_part_ptr = 0, off_q_part_slot = 0;
     size_t off_q_head = 0;    // per-query records for stage 2
     int32_t n_items = 0;
-    TaskLists tasks[2];       // of the groups with bf16 weights, of those with two-term weights
+    int32_t n_items_precise = 0;  // tasks among them that want two-term weights
+    size_t off_items = 0;     // task descriptors
     int32_t table_len = 32;   // longest chunk made of several pieces, rounded up to whole blocks: LDS table size
     std::vector<uint8_t> host_image;  // packed image, kept for repeated uploads
 };
@@ -98,6 +97,6 @@ struct deft_plan_s {
 
 namespace deft {
 // Builds (or returns the cached) schedule for G = Hq/Hkv.  Thread-safe.
-const Schedule *get_schedule(const deft_plan_t *plan, int32_t group);
+const Schedule *get_schedule(const deft_plan_t *plan, int32_t group, int32_t Hkv);
 const Schedule *find_schedule(const deft_plan_t *plan, int32_t group);
 }  // namespace deft

@@ -702,15 +702,22 @@ namespace deft {
 
 static size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
 
-static void build_schedule(const deft_plan_t *P, int32_t G, Schedule &S) {
+static void build_schedule(const deft_plan_t *P, int32_t G, int32_t Hkv, Schedule &S) {
     S.group = G;
     S.table_len = 32;
     const int32_t m = P->n_chunks();
     std::vector<int32_t> seg_off(P->n_segs(), 0);
     struct Chunk {
-        int32_t id, len, tiles;
+        int32_t id, len, tiles, precise;
+        int64_t cost;
     };
-    std::vector<Chunk> chunks[2];  // by the kind of weights
+    std::vector<Chunk> chunks((size_t)m);
+    constexpr int kCuts = (int)(sizeof(kTaskTiles) / sizeof(kTaskTiles[0]));
+    int64_t n_tasks[kCuts] = {};
+    auto per_task = [](int32_t tiles, int cut) {
+        const int32_t k = (tiles + kTaskTiles[cut] - 1) / kTaskTiles[cut];
+        return k ? (tiles + k - 1) / k : 1;
+    };
     for (int32_t c = 0; c < m; ++c) {
         const int32_t s0 = P->chunk_seg_ptr[c], s1 = P->chunk_seg_ptr[c + 1];
         int32_t len = 0;
@@ -724,10 +731,17 @@ static void build_schedule(const deft_plan_t *P, int32_t G, Schedule &S) {
         int32_t precise = P->precise_all ? 1 : 0;
         for (int32_t p = P->chunk_qlo[c]; p < P->chunk_qhi[c] && !precise; ++p)
             if (P->q_path_len[p] < kPreciseBelowTokens) precise = 1;
-        chunks[precise].push_back({c, len, (int32_t)((rows + 15) / 16)});
+        chunks[c] = {c, len, (int32_t)((rows + 15) / 16), precise, 0};
+        for (int i = 0; i < kCuts; ++i) {
+            const int32_t per = per_task(chunks[c].tiles, i);
+            n_tasks[i] += (chunks[c].tiles + per - 1) / per;
+        }
     }
+    int cut = 0;
+    for (int i = 1; i < kCuts; ++i)
+        if (n_tasks[i] * Hkv <= kResidentGroups) cut = i;
 
-    // Groups of more row tiles than a list allows become several tasks of (nearly) equal size: the row groups of one
+    // Groups of more row tiles than the cut allows become several tasks of (nearly) equal size: the row groups of one
     // chunk then cost the same, are dispatched next to each other and find the chunk in L2 after the first of them
     // has fetched it.
     //
@@ -736,50 +750,31 @@ static void build_schedule(const deft_plan_t *P, int32_t G, Schedule &S) {
     // the short ones fill the tail.  The row groups of one chunk share one estimate (that of the largest of
     // them) and equal estimates keep their chunk order, which leaves them next to each other: they re-read
     // that chunk from the same L2 while it is still there.
-    std::vector<int32_t> items[2][kTaskLists];
-    for (int kind = 0; kind < 2; ++kind) {
-        const std::vector<Chunk> &own = chunks[kind];
-        auto cuts = [](int32_t tiles, int list) { return (tiles + kTaskTiles[list] - 1) / kTaskTiles[list]; };
-        auto per_task = [&](int32_t tiles, int list) {
-            const int32_t k = cuts(tiles, list);
-            return k ? (tiles + k - 1) / k : 0;
-        };
-        std::vector<std::pair<int64_t, int32_t>> order(own.size());  // (-estimate, index)
-        int before = 0;                                              // the last list that was kept
-        for (int list = 0; list < kTaskLists; ++list) {
-            int64_t n = 0;
-            bool same = list > 0;
-            for (const Chunk &ch : own) {
-                const int32_t per = per_task(ch.tiles, list);
-                n += per ? (ch.tiles + per - 1) / per : 0;
-                same = same && per == per_task(ch.tiles, before);
-            }
-            if (same || (list > 0 && n > kResidentGroups)) continue;
-            before = list;
-            for (size_t i = 0; i < own.size(); ++i)
-                order[i] = {-(int64_t)own[i].len * (2 + per_task(own[i].tiles, list)), (int32_t)i};
-            std::sort(order.begin(), order.end());
-            std::vector<int32_t> &out = items[kind][list];
-            out.assign((size_t)n * kItemInts, 0);
-            int32_t *d = out.data();
-            for (const auto &at : order) {
-                const Chunk &ch = own[at.second];
-                const int32_t c = ch.id, s0 = P->chunk_seg_ptr[c], per = per_task(ch.tiles, list);
-                for (int32_t t0 = 0; t0 < ch.tiles; t0 += per, d += kItemInts) {
-                    d[kItChunk] = c;
-                    d[kItTile0] = t0;
-                    d[kItNTiles] = std::min<int32_t>(per, ch.tiles - t0);
-                    d[kItSeg0] = s0;
-                    d[kItNSeg] = P->chunk_seg_ptr[c + 1] - s0;
-                    d[kItQlo] = P->chunk_qlo[c];
-                    d[kItWidth] = P->chunk_qhi[c] - P->chunk_qlo[c];
-                    d[kItSlotBase] = P->chunk_slot_base[c];
-                    d[kItLen] = ch.len;
-                    d[kItBegin0] = P->seg_tok_begin[s0];
-                    d[kItSegQlo0] = P->seg_qlo[s0];
-                    d[kItSegQhi0] = P->seg_qhi[s0];
-                }
-            }
+    for (Chunk &ch : chunks) ch.cost = (int64_t)ch.len * (2 + per_task(ch.tiles, cut));
+    std::sort(chunks.begin(), chunks.end(), [](const Chunk &x, const Chunk &y) {
+        return x.cost != y.cost ? x.cost > y.cost : x.id < y.id;
+    });
+    std::vector<int32_t> items((size_t)n_tasks[cut] * kItemInts, 0);
+    int32_t *d = items.data();
+    S.n_items = (int32_t)n_tasks[cut];
+    S.n_items_precise = 0;
+    for (const Chunk &ch : chunks) {
+        const int32_t c = ch.id, s0 = P->chunk_seg_ptr[c], per = per_task(ch.tiles, cut);
+        for (int32_t t0 = 0; t0 < ch.tiles; t0 += per, d += kItemInts) {
+            d[kItChunk] = c;
+            d[kItTile0] = t0;
+            d[kItNTiles] = std::min<int32_t>(per, ch.tiles - t0);
+            d[kItSeg0] = s0;
+            d[kItNSeg] = P->chunk_seg_ptr[c + 1] - s0;
+            d[kItQlo] = P->chunk_qlo[c];
+            d[kItWidth] = P->chunk_qhi[c] - P->chunk_qlo[c];
+            d[kItSlotBase] = P->chunk_slot_base[c];
+            d[kItLen] = ch.len;
+            d[kItBegin0] = P->seg_tok_begin[s0];
+            d[kItSegQlo0] = P->seg_qlo[s0];
+            d[kItSegQhi0] = P->seg_qhi[s0];
+            d[kItPrecise] = ch.precise;
+            S.n_items_precise += ch.precise;
         }
     }
 
@@ -800,12 +795,7 @@ static void build_schedule(const deft_plan_t *P, int32_t G, Schedule &S) {
     S.off_q_part_slot = place(slots);
     off = (off + 63) & ~(size_t)63;  // per-query records and descriptors are aligned 64-byte records
     S.off_q_head = place((size_t)nq * kQueryHeadInts);
-    for (int kind = 0; kind < 2; ++kind)
-        for (int list = 0; list < kTaskLists; ++list) {
-            S.tasks[kind].n[list] = (int32_t)(items[kind][list].size() / kItemInts);
-            S.tasks[kind].off[list] = place(items[kind][list].size());
-        }
-    S.n_items = S.tasks[0].n[0] + S.tasks[1].n[0];
+    S.off_items = place(items.size());
     S.bytes = std::max<size_t>(off, 16);
     S.host_image.assign(S.bytes, 0);
     auto put = [&](size_t at, const std::vector<int32_t> &v) {
@@ -819,8 +809,7 @@ static void build_schedule(const deft_plan_t *P, int32_t G, Schedule &S) {
     put(S.off_q_order, P->q_order);
     put(S.off_q_part_ptr, P->q_part_ptr);
     put(S.off_q_part_slot, P->q_part_slot);
-    for (int kind = 0; kind < 2; ++kind)
-        for (int list = 0; list < kTaskLists; ++list) put(S.tasks[kind].off[list], items[kind][list]);
+    put(S.off_items, items);
     {
         std::vector<int32_t> head((size_t)nq * kQueryHeadInts, 0);
         for (int32_t p = 0; p < nq; ++p) {
@@ -834,12 +823,12 @@ static void build_schedule(const deft_plan_t *P, int32_t G, Schedule &S) {
     }
 }
 
-const Schedule *get_schedule(const deft_plan_t *plan, int32_t group) {
+const Schedule *get_schedule(const deft_plan_t *plan, int32_t group, int32_t Hkv) {
     std::lock_guard<std::mutex> lock(plan->mu);
     auto it = plan->schedules.find(group);
     if (it == plan->schedules.end()) {
         Schedule S;
-        build_schedule(plan, group, S);
+        build_schedule(plan, group, Hkv, S);
         it = plan->schedules.emplace(group, std::move(S)).first;
     }
     return &it->second;
@@ -856,7 +845,7 @@ const Schedule *find_schedule(const deft_plan_t *plan, int32_t group) {
 extern "C" size_t deft_plan_device_bytes(const deft_plan_t *plan, int32_t Hq, int32_t Hkv) {
     if (!plan || Hq <= 0 || Hkv <= 0 || Hq % Hkv != 0) return 0;
     try {
-        return deft::get_schedule(plan, Hq / Hkv)->bytes;
+        return deft::get_schedule(plan, Hq / Hkv, Hkv)->bytes;
     } catch (...) {
         return 0;
     }

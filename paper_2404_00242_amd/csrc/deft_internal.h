@@ -45,6 +45,12 @@ constexpr int kPreciseBelowTokens = 1024;
 constexpr int kTaskTiles[] = {kMaxTilesPerTask, 4, 3, 2};
 constexpr int kResidentGroups = 512;  // workgroups of stage 1 that an MI355X holds: two on each of 256 compute units
 
+// Tasks of chunks longer than this stream their tokens through LDS step by step, whatever their rows; two of them on a
+// compute unit get in each other's way, so the cut stops earlier for them, at one to a unit (4 chunks of 512 tokens, 63
+// queries x 8 heads over 8 KV heads: 160 workgroups 24.2 us, 320 (256 of them long) 23.5 us, 440 (352 long) 27.0 us).
+constexpr int kLongChunk = 256;
+constexpr int kLongGroups = kResidentGroups / 2;
+
 // Launch schedule + image layout for one Hq/Hkv ratio.  The row cut suits the number of KV heads it was first asked
 // for with; the schedule is right for any.
 struct Schedule {

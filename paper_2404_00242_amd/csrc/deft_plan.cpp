@@ -713,7 +713,7 @@ static void build_schedule(const deft_plan_t *P, int32_t G, int32_t Hkv, Schedul
     };
     std::vector<Chunk> chunks((size_t)m);
     constexpr int kCuts = (int)(sizeof(kTaskTiles) / sizeof(kTaskTiles[0]));
-    int64_t n_tasks[kCuts] = {};
+    int64_t n_tasks[kCuts] = {}, n_long[kCuts] = {};
     auto per_task = [](int32_t tiles, int cut) {
         const int32_t k = (tiles + kTaskTiles[cut] - 1) / kTaskTiles[cut];
         return k ? (tiles + k - 1) / k : 1;
@@ -734,12 +734,14 @@ static void build_schedule(const deft_plan_t *P, int32_t G, int32_t Hkv, Schedul
         chunks[c] = {c, len, (int32_t)((rows + 15) / 16), precise, 0};
         for (int i = 0; i < kCuts; ++i) {
             const int32_t per = per_task(chunks[c].tiles, i);
-            n_tasks[i] += (chunks[c].tiles + per - 1) / per;
+            const int32_t n = (chunks[c].tiles + per - 1) / per;
+            n_tasks[i] += n;
+            if (len > kLongChunk) n_long[i] += n;
         }
     }
     int cut = 0;
     for (int i = 1; i < kCuts; ++i)
-        if (n_tasks[i] * Hkv <= kResidentGroups) cut = i;
+        if (n_tasks[i] * Hkv <= kResidentGroups && n_long[i] * Hkv <= kLongGroups) cut = i;
 
     // Groups of more row tiles than the cut allows become several tasks of (nearly) equal size: the row groups of one
     // chunk then cost the same, are dispatched next to each other and find the chunk in L2 after the first of them

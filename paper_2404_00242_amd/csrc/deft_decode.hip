@@ -19,8 +19,8 @@
 // block each fetch a share of it and pass the operand registers to the others through LDS.  The waves' partial results are merged in LDS before
 // one (m, l, acc) triple per (chunk, row) is written.
 //
-// Stage 2 (deft_stage2): one wave per (query, query head) merges that query's partial results with
-// the log-sum-exp weights of eq. 1.
+// Stage 2 (deft_stage2_few, deft_stage2_many): one wave, or four, per (query, query head) merge that query's partial
+// results with the log-sum-exp weights of eq. 1.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -62,9 +62,11 @@ struct Stage1Args {
 
 struct Stage2Args {
     const float *part_acc, *part_m, *part_l;
-    const int32_t *q_head, *q_part_ptr, *q_part_slot;
+    const int32_t *q_head, *q_part_slot;
     void *out;
     int32_t nq, Hq, out_f32;
+    int32_t head_ints;  // int32 per query record
+    uint32_t inv_Hq;
     float c;
 };
 
@@ -1277,104 +1279,144 @@ __global__ __launch_bounds__(64 * kWaves, 2) void deft_stage1(Stage1Args a) {
         run_task<D, false>(a, it, h, s_raw);
 }
 
-// Stage 2: tree-topology-aware global reduction (eq. 1 with the largest maximum subtracted).
-// One wave per (query, query head).  Weights are computed with lanes across the query's slots;
-// the weighted rows are then summed with D/4 lanes per row (128-bit loads), several rows at a time.
+// Stage 2: tree-topology-aware global reduction (eq. 1 with the largest maximum subtracted), D/4 lanes to a row of a
+// partial result (128-bit loads), 64 / (D/4) rows at a time.  Bound by latency: the query's record, then m, l and rows.
 template <int D>
-__global__ __launch_bounds__(64) void deft_stage2(Stage2Args a) {
-    constexpr int LPR = D / 4;     // lanes per partial row
-    constexpr int RPI = 64 / LPR;  // rows per iteration
-    const int lane = threadIdx.x;
-    const int p = blockIdx.x / a.Hq;
-    const int qh = blockIdx.x - p * a.Hq;
-    // one 128-byte record per query: how many partials, where the result goes, the first slot ids
-    const int hd = a.q_head[(size_t)p * deft::kQueryHeadInts + (lane & (deft::kQueryHeadInts - 1))];
-    const int n = __shfl(hd, 0);
-    const int q_user = __shfl(hd, 1);
-    const int sub = lane / LPR, col = lane - sub * LPR;
+struct Stage2Row {
+    static constexpr int kLanes = D / 4;         // lanes per partial row
+    static constexpr int kRows = 64 / kLanes;    // rows per load of a wave
+    static constexpr int kBatch = 8 * kRows;     // rows a wave keeps in flight in registers
+};
 
+__device__ __forceinline__ float wave_max(float x) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o));
+    return x;
+}
+__device__ __forceinline__ float wave_sum(float x) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
+    return x;
+}
+
+__device__ __forceinline__ void store_out(const Stage2Args &a, size_t at, f32x4 x) {
+    if (a.out_f32) {
+        *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(a.out) + at) = x;
+    } else {
+        typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+        u32x2 pk = {pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3])};
+        *reinterpret_cast<u32x2 *>(reinterpret_cast<uint16_t *>(a.out) + at) = pk;
+    }
+}
+
+// Every query of the plan has at most kBatch partials: a wave per (query, query head).  The slot ids come with the
+// record, so m, l and every row are fetched in the next round trip and the weights are applied to rows that are already
+// in registers.  One wave to a workgroup: four cost 0.4 us more on every tree, and two or four heads to a wave gain
+// only where there are thousands (0.2 us of 6.3 at 8192).
+template <int D>
+__global__ __launch_bounds__(64) void deft_stage2_few(Stage2Args a) {
+    using R = Stage2Row<D>;
+    const int lane = threadIdx.x;
+    const int p = divide(blockIdx.x, a.Hq, a.inv_Hq), qh = blockIdx.x - p * a.Hq;
+    const int rec = a.q_head[(size_t)p * a.head_ints + (lane & (deft::kQueryHeadInts - 1))];
+    const int n = __builtin_amdgcn_readlane(rec, 0), q_user = __builtin_amdgcn_readlane(rec, 1);
+    const int sub = lane / R::kLanes, col = lane - sub * R::kLanes;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     float lsum = 0.f;
-    constexpr int FAST = 8 * RPI < deft::kQueryInlineSlots ? 8 * RPI : deft::kQueryInlineSlots;  // rows held in registers
-    if (n > 0 && n <= FAST) {
-        // few partials (the usual case): the slot ids came with the record, so m, l and every row are
-        // fetched in the next round trip and the weights are applied to rows that are already in registers
-        const int slot_all = __shfl(hd, (lane < n ? lane : 0) + 2);
-        const int slot = lane < n ? slot_all : 0;
+    if (n > 0) {
+        // lanes past the end hold a slot that exists
+        const int slot = __shfl(rec, deft::kQueryHeadFixed + (lane < n ? lane : 0));
         const size_t ro = (size_t)slot * a.Hq + qh;
         const float mj = lane < n ? a.part_m[ro] : -INFINITY;
         const float lj = lane < n ? a.part_l[ro] : 0.f;
         f32x4 x[8];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            const int jj = u * RPI + sub;
-            const int sj = __shfl(slot, jj);  // lanes >= n hold slot 0, which exists
+            const int sj = __shfl(slot, u * R::kRows + sub);
             x[u] = *reinterpret_cast<const f32x4 *>(a.part_acc + ((size_t)sj * a.Hq + qh) * D + 4 * col);
         }
-        float mx = mj;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+        const float mx = wave_max(mj);
         const float w = (lane < n && mx != -INFINITY) ? __builtin_amdgcn_exp2f((mj - mx) * a.c) : 0.f;
-        lsum = w * lj;
+        lsum = wave_sum(w * lj);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const float wu = __shfl(w, u * RPI + sub);
-            acc += wu * x[u];
-        }
-    } else if (n > 0) {
-        const int s0 = a.q_part_ptr[p];
-        float mx = -INFINITY;
-        for (int i = lane; i < n; i += 64) mx = fmaxf(mx, a.part_m[(size_t)a.q_part_slot[s0 + i] * a.Hq + qh]);
+        for (int u = 0; u < 8; ++u) acc += __shfl(w, u * R::kRows + sub) * x[u];
+    }
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-        if (mx != -INFINITY) {
-            for (int base = 0; base < n; base += 64) {
-                const int i = base + lane;
-                float w = 0.f;
-                int slot = 0;
-                if (i < n) {
-                    slot = a.q_part_slot[s0 + i];
-                    const size_t ro = (size_t)slot * a.Hq + qh;
-                    w = __builtin_amdgcn_exp2f((a.part_m[ro] - mx) * a.c);
-                    lsum += w * a.part_l[ro];
-                }
-                const int cnt = min(64, n - base);
-                for (int j = 0; j < cnt; j += 4 * RPI) {
-                    // four independent row loads per trip; rows past cnt get weight 0 and read slot 0, which exists
-                    float wj[4];
-                    f32x4 x[4];
+    for (int o = 32; o >= R::kLanes; o >>= 1)
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int jj = j + u * RPI + sub;
-                        const float ws = __shfl(w, jj & 63);
-                        const int sj = __shfl(slot, jj & 63);
-                        wj[u] = jj < cnt ? ws : 0.f;
-                        const int sr = jj < cnt ? sj : 0;
-                        x[u] = *reinterpret_cast<const f32x4 *>(a.part_acc + ((size_t)sr * a.Hq + qh) * D + 4 * col);
-                    }
+        for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], o);
+    if (sub == 0) store_out(a, ((size_t)q_user * a.Hq + qh) * D + 4 * col, acc * (lsum > 0.f ? 1.f / lsum : 0.f));
+}
+
+// Any number of partials: WAVES waves per (query, query head), partial WAVES * i + w with wave w.  Each wave merges what it
+// holds as above (64 of its partials at a time, on a running maximum), then their results are merged in LDS.
+template <int D, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void deft_stage2_many(Stage2Args a) {
+    using R = Stage2Row<D>;
+    __shared__ __attribute__((aligned(16))) float s_acc[WAVES][D];
+    __shared__ float s_m[WAVES], s_l[WAVES];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int p = divide(blockIdx.x, a.Hq, a.inv_Hq), qh = blockIdx.x - p * a.Hq;
+    const int32_t *rec = a.q_head + (size_t)p * a.head_ints;
+    int slot = rec[min(deft::kQueryHeadFixed + WAVES * lane + wave, a.head_ints - 1)];
+    const int n = rec[0], q_user = rec[1], s0 = rec[2];
+    const int sub = lane / R::kLanes, col = lane - sub * R::kLanes;
+    const int mine = (n - wave + WAVES - 1) / WAVES;  // partials of this wave
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    float M = -INFINITY, lsum = 0.f;
+    for (int base = 0; base < mine; base += 64) {
+        const int cnt = min(64, mine - base);
+        if (n > a.head_ints - deft::kQueryHeadFixed)
+            slot = a.q_part_slot[s0 + WAVES * (base + min(lane, cnt - 1)) + wave];
+        slot = __shfl(slot, min(lane, cnt - 1));  // lanes past the end hold a slot that exists
+        const size_t ro = (size_t)slot * a.Hq + qh;
+        const float mj = lane < cnt ? a.part_m[ro] : -INFINITY;
+        const float lj = lane < cnt ? a.part_l[ro] : 0.f;
+        float w = 0.f;
+        for (int j = 0; j < cnt; j += R::kBatch) {
+            f32x4 x[8];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) acc += wj[u] * x[u];
-                }
+            for (int u = 0; u < 8; ++u) {
+                const int sj = __shfl(slot, (j + u * R::kRows + sub) & 63);
+                x[u] = *reinterpret_cast<const f32x4 *>(a.part_acc + ((size_t)sj * a.Hq + qh) * D + 4 * col);
+            }
+            if (j == 0) {
+                const float top = fmaxf(M, wave_max(mj));
+                const float old = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((M - top) * a.c);
+                w = (lane < cnt && top != -INFINITY) ? __builtin_amdgcn_exp2f((mj - top) * a.c) : 0.f;
+                lsum = lsum * old + wave_sum(w * lj);
+                acc *= old;
+                M = top;
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const float wu = __shfl(w, (j + u * R::kRows + sub) & 63);  // zero for rows past the end
+                acc += wu * x[u];
             }
         }
     }
 #pragma unroll
-    for (int o = 32; o >= LPR; o >>= 1) {
+    for (int o = 32; o >= R::kLanes; o >>= 1)
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], o);
+    if (sub == 0) *reinterpret_cast<f32x4 *>(&s_acc[wave][4 * col]) = acc;
+    if (lane == 0) {
+        s_m[wave] = M;
+        s_l[wave] = lsum;
     }
+    __syncthreads();
+    if (wave != 0 || sub != 0) return;
+    float top = -INFINITY, total = 0.f;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) lsum += __shfl_xor(lsum, o);
-    if (sub != 0) return;
-    const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
-    const size_t oo = ((size_t)q_user * a.Hq + qh) * D + 4 * col;
-    if (a.out_f32) {
-        *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(a.out) + oo) = acc * inv;
-    } else {
-        typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
-        u32x2 pk = {pack_bf16(acc[0] * inv, acc[1] * inv), pack_bf16(acc[2] * inv, acc[3] * inv)};
-        *reinterpret_cast<u32x2 *>(reinterpret_cast<uint16_t *>(a.out) + oo) = pk;
+    for (int k = 0; k < WAVES; ++k) top = fmaxf(top, s_m[k]);
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < WAVES; ++k) {
+        const float w = top == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((s_m[k] - top) * a.c);
+        total += w * s_l[k];
+        sum += w * *reinterpret_cast<const f32x4 *>(&s_acc[k][4 * col]);
     }
+    store_out(a, ((size_t)q_user * a.Hq + qh) * D + 4 * col, sum * (total > 0.f ? 1.f / total : 0.f));
 }
 
 // Plain read of a buffer with 128-bit loads, every byte once, all compute units busy: the rate this
@@ -1451,9 +1493,19 @@ bool launch_stage1(const deft::Schedule &S, Stage1Args a1, const uint8_t *image,
 }
 
 template <int D>
-bool launch_stage2(const Stage2Args &a2, hipStream_t stream) {
+bool launch_stage2(const deft::Schedule &S, const Stage2Args &a2, hipStream_t stream) {
     if (a2.nq == 0) return true;
-    hipLaunchKernelGGL((deft_stage2<D>), dim3((unsigned)a2.nq * (unsigned)a2.Hq), dim3(64), 0, stream, a2);
+    const unsigned rows = (unsigned)a2.nq * (unsigned)a2.Hq;
+    constexpr int kFew = std::min(Stage2Row<D>::kBatch, deft::kQueryHeadInts - deft::kQueryHeadFixed);
+    // Up to kFew partials one wave has them all in flight at once, and more waves cost more to start than they save (16
+    // partials, 2048 rows of output: 5.1 us, four waves 7.5).  Beyond that a second batch is a round trip more: 17
+    // partials 5.6 us with one wave, 4.4 with four, 4.0 with two; 64 partials 7.2 us with one, 3.4 with four.
+    if (S.max_parts <= kFew)
+        hipLaunchKernelGGL((deft_stage2_few<D>), dim3(rows), dim3(64), 0, stream, a2);
+    else if (S.max_parts <= 2 * 16)
+        hipLaunchKernelGGL((deft_stage2_many<D, 2>), dim3(rows), dim3(128), 0, stream, a2);
+    else
+        hipLaunchKernelGGL((deft_stage2_many<D, 4>), dim3(rows), dim3(256), 0, stream, a2);
     return hip_ok(hipGetLastError(), "deft_stage2 launch");
 }
 
@@ -1531,14 +1583,15 @@ int run_stage2(const deft_plan_t *plan, const Call &call, void *o, int32_t Hq, i
     a2.part_m = call.pm;
     a2.part_l = call.pl;
     a2.q_head = at(S.off_q_head);
-    a2.q_part_ptr = at(S.off_q_part_ptr);
     a2.q_part_slot = at(S.off_q_part_slot);
     a2.out = o;
     a2.nq = plan->nq;
     a2.Hq = Hq;
+    a2.head_ints = S.head_ints;
+    a2.inv_Hq = inverse(Hq);
     a2.out_f32 = (flags == DEFT_OUT_F32);
     a2.c = call.c;
-    const bool ok = d == 128 ? launch_stage2<128>(a2, call.stream) : launch_stage2<64>(a2, call.stream);
+    const bool ok = d == 128 ? launch_stage2<128>(S, a2, call.stream) : launch_stage2<64>(S, a2, call.stream);
     return ok ? DEFT_OK : DEFT_EHIP;
 }
 

@@ -16,10 +16,12 @@ namespace deft {
 // without touching any other table.
 constexpr int kItemInts = 16;
 constexpr int kMaxTilesPerTask = 8;
-// Stage 2 reads one kQueryHeadInts-int32 record per plan query: {number of partials n, caller's query index,
-// the first kQueryInlineSlots slot ids}; queries with more partials go on to the CSR lists.
+// Stage 2 reads one record per plan query: {number of partials n, caller's query index, where its list starts in
+// q_part_slot, the first slot ids}.  A record has kQueryHeadInts int32, or as many times that as hold the longest list of
+// the plan, up to kQueryHeadMost; queries with more partials than fit go on to the list.
 constexpr int kQueryHeadInts = 32;
-constexpr int kQueryInlineSlots = kQueryHeadInts - 2;
+constexpr int kQueryHeadMost = 128;
+constexpr int kQueryHeadFixed = 3;
 enum ItemField {
     kItChunk = 0,     // chunk id
     kItTile0 = 1,     // first 16-row tile of the chunk's group handled by this task
@@ -59,8 +61,10 @@ struct Schedule {
     // byte offsets of the canonical arrays inside the image
     size_t off_seg_tok_begin = 0, off_seg_len = 0, off_seg_qlo = 0, off_seg_qhi = 0, off_seg_off = 0;
     size_t off_q_order = 0;
-    size_t off_q_part_ptr = 0, off_q_part_slot = 0;
+    size_t off_q_part_slot = 0;
     size_t off_q_head = 0;    // per-query records for stage 2
+    int32_t head_ints = kQueryHeadInts;  // int32 per record
+    int32_t max_parts = 0;    // partials of the query that has most
     int32_t n_items = 0;
     int32_t n_items_precise = 0;  // tasks among them that want two-term weights
     size_t off_items = 0;     // task descriptors

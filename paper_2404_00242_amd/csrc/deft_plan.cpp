@@ -793,10 +793,13 @@ static void build_schedule(const deft_plan_t *P, int32_t G, int32_t Hkv, Schedul
     S.off_seg_qhi = place(nseg);
     S.off_seg_off = place(nseg);
     S.off_q_order = place(nq);
-    S.off_q_part_ptr = place(nq + 1);
+    S.max_parts = 0;
+    for (int32_t p = 0; p < nq; ++p) S.max_parts = std::max(S.max_parts, P->q_part_ptr[p + 1] - P->q_part_ptr[p]);
+    S.head_ints = kQueryHeadInts;
+    while (S.head_ints < kQueryHeadMost && S.head_ints - kQueryHeadFixed < S.max_parts) S.head_ints *= 2;
     S.off_q_part_slot = place(slots);
     off = (off + 63) & ~(size_t)63;  // per-query records and descriptors are aligned 64-byte records
-    S.off_q_head = place((size_t)nq * kQueryHeadInts);
+    S.off_q_head = place((size_t)nq * S.head_ints);
     S.off_items = place(items.size());
     S.bytes = std::max<size_t>(off, 16);
     S.host_image.assign(S.bytes, 0);
@@ -809,19 +812,16 @@ static void build_schedule(const deft_plan_t *P, int32_t G, int32_t Hkv, Schedul
     put(S.off_seg_qhi, P->seg_qhi);
     put(S.off_seg_off, seg_off);
     put(S.off_q_order, P->q_order);
-    put(S.off_q_part_ptr, P->q_part_ptr);
     put(S.off_q_part_slot, P->q_part_slot);
     put(S.off_items, items);
-    {
-        std::vector<int32_t> head((size_t)nq * kQueryHeadInts, 0);
-        for (int32_t p = 0; p < nq; ++p) {
-            int32_t *r = &head[(size_t)p * kQueryHeadInts];
-            const int32_t s0 = P->q_part_ptr[p], n = P->q_part_ptr[p + 1] - s0;
-            r[0] = n;
-            r[1] = P->q_order[p];
-            for (int32_t k = 0; k < kQueryInlineSlots && k < n; ++k) r[2 + k] = P->q_part_slot[s0 + k];
-        }
-        put(S.off_q_head, head);
+    const int32_t inlined = S.head_ints - kQueryHeadFixed;
+    int32_t *r = reinterpret_cast<int32_t *>(S.host_image.data() + S.off_q_head);
+    for (int32_t p = 0; p < nq; ++p, r += S.head_ints) {
+        const int32_t s0 = P->q_part_ptr[p], n = P->q_part_ptr[p + 1] - s0;
+        r[0] = n;
+        r[1] = P->q_order[p];
+        r[2] = s0;
+        std::copy_n(P->q_part_slot.begin() + s0, std::min(n, inlined), r + kQueryHeadFixed);
     }
 }
 

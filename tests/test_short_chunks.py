@@ -1,5 +1,5 @@
 """Chunks that stage 1 holds in registers (at most 256 tokens at d = 128, 512 at d = 64), and the cut of a task's rows
-over several workgroups, at the sizes where they can go wrong.  Same tolerance as tests/test_gpu_parity.py, whose
+over several workgroups, and stage 2 by the number of partial results, at the sizes where they can go wrong.  Same tolerance as tests/test_gpu_parity.py, whose
 paths of fewer than 1024 tokens also get the tight bound of two-term weights."""
 
 import numpy as np
@@ -54,4 +54,15 @@ def test_long_paths_in_short_chunks(nq, Hq, Hkv, d, mode):
     Q, K, V = wl.make_qkv(t)
     for chunk in (128, 224, 256):
         got, _ = run_gpu(t, Q, K, V, chunk_size=chunk, out_dtype=torch.float32, mode=mode)
+        check(got, reference(t, Q, K, V), strict=False)
+
+
+# stage 2 by the number of partial results of a query: one wave, two, four, slot ids past the record, several passes
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("parts", [1, 16, 17, 29, 30, 32, 33, 61, 62, 125, 126, 257, 300])
+def test_any_number_of_partial_results(parts, d):
+    t = tree(32 * parts - 7, [0, 40], 6, 2, d, seed=parts)
+    Q, K, V = wl.make_qkv(t)
+    for out_dtype in (torch.float32, torch.bfloat16):
+        got, _ = run_gpu(t, Q, K, V, chunk_size=32, out_dtype=out_dtype, mode="node_chunk")
         check(got, reference(t, Q, K, V), strict=False)

@@ -218,6 +218,9 @@ int32_t deft_suggest_chunk_size(const int32_t *node_tok_len, const int32_t *node
 /* Fills *out with borrowed host pointers to the canonical arrays described above. */
 int deft_plan_view(const deft_plan_t *plan, deft_plan_view_t *out);
 
+/* Rows that the K and V buffers must have for this plan: one past the last row it addresses.  0 for a null plan. */
+int64_t deft_plan_rows(const deft_plan_t *plan);
+
 /*
  * The device image of a plan: the arrays the kernels read (segment table, chunk groups,
  * slot lists, query order) plus the launch schedule for a given ratio Hq/Hkv (how the

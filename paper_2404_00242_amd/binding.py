@@ -35,7 +35,7 @@ def rows_per_query(g: int) -> int:
     return (int(g) & 0xFFF) << 16
 
 EXPORTS = (
-    "deft_plan", "deft_plan_paged", "deft_plan_update", "deft_plan_paged_update", "deft_suggest_chunk_size", "deft_plan_view", "deft_plan_device_bytes", "deft_plan_upload", "deft_workspace_bytes",
+    "deft_plan", "deft_plan_paged", "deft_plan_update", "deft_plan_paged_update", "deft_suggest_chunk_size", "deft_plan_view", "deft_plan_rows", "deft_plan_device_bytes", "deft_plan_upload", "deft_workspace_bytes",
     "deft_tree_attn_decode", "deft_tree_attn_decode_static", "deft_stage1_partial_attention", "deft_stage2_global_reduction",
     "deft_hbm_read_probe", "deft_plan_destroy", "deft_strerror", "deft_last_hip_error",
 )
@@ -77,6 +77,16 @@ class DeftError(RuntimeError):
 
 
 _lib = None
+_torch = None  # imported by the first call that needs device memory: planning alone does without
+
+
+def _get_torch():
+    global _torch
+    if _torch is None:
+        import torch
+
+        _torch = torch
+    return _torch
 
 
 def load_library():
@@ -91,18 +101,20 @@ def load_library():
     lib = ctypes.CDLL(LIB_PATH)
     vp, c32, csz = ctypes.c_void_p, ctypes.c_int32, ctypes.c_size_t
     lib.deft_plan.restype = ctypes.c_int
-    lib.deft_plan.argtypes = [_i32p, _i32p, _i32p, c32, _i32p, c32, c32, c32, ctypes.c_uint32, ctypes.POINTER(vp)]
+    # int32 arrays go in as plain addresses (_address): a typed ctypes pointer costs 2 us an array to make
+    lib.deft_plan.argtypes = [vp, vp, vp, c32, vp, c32, c32, c32, ctypes.c_uint32, ctypes.POINTER(vp)]
     lib.deft_plan_paged.restype = ctypes.c_int
-    lib.deft_plan_paged.argtypes = [_i32p, _i32p, c32, c32, _i32p, _i32p, c32, _i32p, c32, c32, ctypes.c_uint32,
-                                    ctypes.POINTER(vp)]
+    lib.deft_plan_paged.argtypes = [vp, vp, c32, c32, vp, vp, c32, vp, c32, c32, ctypes.c_uint32, ctypes.POINTER(vp)]
     lib.deft_plan_update.restype = ctypes.c_int
     lib.deft_plan_update.argtypes = [vp] + lib.deft_plan.argtypes
     lib.deft_plan_paged_update.restype = ctypes.c_int
     lib.deft_plan_paged_update.argtypes = [vp] + lib.deft_plan_paged.argtypes
     lib.deft_suggest_chunk_size.restype = ctypes.c_int32
-    lib.deft_suggest_chunk_size.argtypes = [_i32p, _i32p, c32, _i32p, c32, c32, c32, ctypes.c_uint32]
+    lib.deft_suggest_chunk_size.argtypes = [vp, vp, c32, vp, c32, c32, c32, ctypes.c_uint32]
     lib.deft_plan_view.restype = ctypes.c_int
     lib.deft_plan_view.argtypes = [vp, ctypes.POINTER(_PlanView)]
+    lib.deft_plan_rows.restype = ctypes.c_int64
+    lib.deft_plan_rows.argtypes = [vp]
     lib.deft_plan_device_bytes.restype = csz
     lib.deft_plan_device_bytes.argtypes = [vp, c32, c32]
     lib.deft_plan_upload.restype = ctypes.c_int
@@ -145,14 +157,21 @@ def _i32(x):
     return np.ascontiguousarray(np.asarray(x), dtype=np.int32).reshape(-1)
 
 
+def _address(x):
+    """Address of an _i32 array's data, None for an empty one."""
+    return x.__array_interface__["data"][0] if x.size else None
+
+
 class Plan:
     """Owns a deft_plan_t handle and, per Hq/Hkv ratio, the device image uploaded for it."""
 
-    def __init__(self, handle):
+    def __init__(self, handle, nq=None):
         self._h = handle
-        self._images = {}      # (G, device index) -> torch uint8 tensor holding the device image
+        self._images = {}      # (G, device index) -> (torch uint8 tensor holding the device image, event, stream)
         self._workspaces = {}  # (Hq, Hkv, d, device index) -> torch uint8 tensor
         self._view = None
+        self._nq = nq          # queries, and rows a KV cache must have; a plan never changes
+        self._rows = None
 
     def __del__(self):
         h, self._h = getattr(self, "_h", None), None
@@ -176,6 +195,14 @@ class Plan:
                 out[name] = np.ctypeslib.as_array(ptr, shape=(n,)).copy() if n > 0 else np.zeros(0, dtype=dt)
             self._view = out
         return self._view
+
+    def limits(self):
+        """(queries of the plan, rows a KV cache must have for it)"""
+        if self._rows is None:
+            if self._nq is None:
+                self._nq = self.view()["nq"]
+            self._rows = int(load_library().deft_plan_rows(self._h))
+        return self._nq, self._rows
 
     def device_bytes(self, Hq: int, Hkv: int) -> int:
         return int(load_library().deft_plan_device_bytes(self._h, Hq, Hkv))
@@ -232,6 +259,13 @@ class Plan:
         return ws
 
 
+def _raw_stream(stream, index: int) -> int:
+    """Handle of a stream given as a torch stream, as a handle, or as None: the current stream of device `index`."""
+    if stream is None:
+        return _get_torch()._C._cuda_getCurrentRawStream(index)
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+
+
 def _stream_ptr(stream, device):
     import torch
 
@@ -244,9 +278,8 @@ def deft_suggest_chunk_size(node_tok_len, node_parent, query_node, Hq: int, Hkv:
     """Chunk size S_t suited to this tree for the split named by flags (about two equal stage-1 tasks per
     compute unit)."""
     nl, par, qn = _i32(node_tok_len), _i32(node_parent), _i32(query_node)
-    qptr = qn.ctypes.data_as(_i32p) if qn.size else None
-    rc = load_library().deft_suggest_chunk_size(nl.ctypes.data_as(_i32p), par.ctypes.data_as(_i32p), nl.size, qptr,
-                                                qn.size, int(Hq), int(Hkv), int(flags))
+    rc = load_library().deft_suggest_chunk_size(_address(nl), _address(par), nl.size, _address(qn), qn.size, int(Hq),
+                                                int(Hkv), int(flags))
     if rc < 0:
         _check(rc, "deft_suggest_chunk_size")
     return int(rc)
@@ -261,14 +294,13 @@ def deft_plan(node_tok_begin, node_tok_len, node_parent, query_node, ntok: int, 
     if not (nb.size == nl.size == par.size):
         raise DeftError(-1, "deft_plan: node table columns differ in length")
     out = ctypes.c_void_p()
-    qptr = qn.ctypes.data_as(_i32p) if qn.size else None
-    args = (nb.ctypes.data_as(_i32p), nl.ctypes.data_as(_i32p), par.ctypes.data_as(_i32p), nb.size,
-            qptr, qn.size, int(ntok), int(chunk_size), int(flags), ctypes.byref(out))
+    args = (_address(nb), _address(nl), _address(par), nb.size, _address(qn), qn.size, int(ntok), int(chunk_size),
+            int(flags), ctypes.byref(out))
     if prev is None:
         _check(lib.deft_plan(*args), "deft_plan")
     else:
         _check(lib.deft_plan_update(prev.handle, *args), "deft_plan_update")
-    return Plan(out)
+    return Plan(out, qn.size)
 
 
 def deft_plan_paged(node_page_ptr, page_ids, page_size: int, n_pool_pages: int, node_tok_len, node_parent,
@@ -280,14 +312,13 @@ def deft_plan_paged(node_page_ptr, page_ids, page_size: int, n_pool_pages: int, 
     if not (nl.size == par.size == pp.size - 1):
         raise DeftError(-1, "deft_plan_paged: node table columns differ in length")
     out = ctypes.c_void_p()
-    args = (pp.ctypes.data_as(_i32p), pg.ctypes.data_as(_i32p) if pg.size else None, int(page_size),
-            int(n_pool_pages), nl.ctypes.data_as(_i32p), par.ctypes.data_as(_i32p), nl.size,
-            qn.ctypes.data_as(_i32p) if qn.size else None, qn.size, int(chunk_size), int(flags), ctypes.byref(out))
+    args = (_address(pp), _address(pg), int(page_size), int(n_pool_pages), _address(nl), _address(par), nl.size,
+            _address(qn), qn.size, int(chunk_size), int(flags), ctypes.byref(out))
     if prev is None:
         _check(lib.deft_plan_paged(*args), "deft_plan_paged")
     else:
         _check(lib.deft_plan_paged_update(prev.handle, *args), "deft_plan_paged_update")
-    return Plan(out)
+    return Plan(out, qn.size)
 
 
 KV_STAGGER_BYTES = 512  # V pool's base relative to the K pool's, modulo 1 KiB
@@ -322,37 +353,43 @@ def deft_tree_attn_decode(plan: Plan, q, k, v, out=None, scale: float = 0.0, out
     float32 when out_dtype / out says so), in the caller's query order.  Asynchronous on `stream`
     (default: torch's current stream).
     """
-    import torch
-
+    torch = _torch or _get_torch()
+    bf16 = torch.bfloat16
     if not (q.is_cuda and k.is_cuda and v.is_cuda):
         raise DeftError(-1, "deft_tree_attn_decode: q, k, v must be device tensors (there is no CPU path)")
     for name, t in (("q", q), ("k", k), ("v", v)):
-        if t.dtype != torch.bfloat16 or not t.is_contiguous() or t.dim() != 3:
+        if t.dtype != bf16 or not t.is_contiguous() or t.dim() != 3:
             raise DeftError(-1, f"deft_tree_attn_decode: {name} must be a contiguous 3-d bf16 tensor")
     nq, Hq, d = q.shape
-    ntok, Hkv, d2 = k.shape
-    if v.shape != k.shape or d2 != d:
+    ntok, Hkv, d2 = shape = k.shape
+    if v.shape != shape or d2 != d:
         raise DeftError(-1, "deft_tree_attn_decode: k and v must both be [ntok, Hkv, d]")
-    view = plan.view()
-    if nq != view["nq"]:
+    plan_nq, plan_rows = plan.limits()
+    if nq != plan_nq:
         raise DeftError(-1, "deft_tree_attn_decode: q has a different number of queries than the plan")
-    if view["n_segs"] and int((view["seg_tok_begin"] + view["seg_len"]).max()) > ntok:
+    if plan_rows > ntok:
         raise DeftError(-1, "deft_tree_attn_decode: the plan addresses rows beyond the KV cache")
     dev = q.device
     if out is None:
-        out = torch.empty((nq, Hq, d), dtype=out_dtype or torch.bfloat16, device=dev)
-    if out.shape != (nq, Hq, d) or not out.is_contiguous() or out.device != dev:
+        out = torch.empty((nq, Hq, d), dtype=out_dtype or bf16, device=dev)
+    elif out.shape != (nq, Hq, d) or not out.is_contiguous() or out.device != dev:
         raise DeftError(-1, "deft_tree_attn_decode: out must be a contiguous [nq, Hq, d] tensor on q's device")
-    if out.dtype == torch.bfloat16:
+    if out.dtype == bf16:
         flags = DEFT_OUT_BF16
     elif out.dtype == torch.float32:
         flags = DEFT_OUT_F32
     else:
         raise DeftError(-1, "deft_tree_attn_decode: out must be bf16 or float32")
-    img = plan.image(Hq, Hkv, dev, stream)
-    ws = workspace if workspace is not None else plan.workspace(Hq, Hkv, d, dev)
-    rc = load_library().deft_tree_attn_decode(
-        plan.handle, img.data_ptr(), q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), Hq, Hkv, d,
-        float(scale), flags, ws.data_ptr(), ws.numel() * ws.element_size(), _stream_ptr(stream, dev))
+    index = dev.index
+    raw = _raw_stream(stream, index)
+    # an image that went out on this very stream, or that has landed, needs no ordering
+    entry = plan._images.get((Hq // Hkv, index))
+    img = entry[0] if entry is not None and (entry[2] == raw or entry[1] is None) else plan.image(Hq, Hkv, dev, stream)
+    ws = workspace if workspace is not None else plan._workspaces.get((Hq, Hkv, d, index))
+    if ws is None:
+        ws = plan.workspace(Hq, Hkv, d, dev)
+    rc = (_lib or load_library()).deft_tree_attn_decode(
+        plan._h, img.data_ptr(), q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), Hq, Hkv, d, float(scale), flags,
+        ws.data_ptr(), ws.numel() * ws.element_size(), raw)
     _check(rc, "deft_tree_attn_decode")
     return out

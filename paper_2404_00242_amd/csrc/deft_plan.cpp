@@ -675,6 +675,13 @@ extern "C" int deft_plan_view(const deft_plan_t *P, deft_plan_view_t *out) {
     return DEFT_OK;
 }
 
+extern "C" int64_t deft_plan_rows(const deft_plan_t *P) {
+    int64_t rows = 0;
+    if (P)
+        for (int32_t s = 0; s < P->n_segs(); ++s) rows = std::max(rows, (int64_t)P->seg_tok_begin[s] + P->seg_len[s]);
+    return rows;
+}
+
 extern "C" void deft_plan_destroy(deft_plan_t *plan) { delete plan; }
 
 extern "C" const char *deft_strerror(int status) {

@@ -943,8 +943,9 @@ __device__ __forceinline__ void resident_task(const Stage1Args &a, const int32_t
     if (nseg > 1) {
         int32_t *p_off = reinterpret_cast<int32_t *>(s_raw), *p_beg = p_off + kResidentTokens<D>,
                 *p_lo = p_beg + kResidentTokens<D>, *p_hi = p_lo + kResidentTokens<D>;
+        const int flat0 = a.seg_off[seg0];
         for (int s = tid; s < nseg; s += 64 * kWaves) {
-            p_off[s] = a.seg_off[seg0 + s];
+            p_off[s] = a.seg_off[seg0 + s] - flat0;
             p_beg[s] = a.seg_tok_begin[seg0 + s];
             p_lo[s] = a.seg_qlo[seg0 + s];
             p_hi[s] = a.seg_qhi[seg0 + s];
@@ -1087,8 +1088,9 @@ __device__ __forceinline__ void streaming_task(const Stage1Args &a, const int32_
         int32_t *p_beg = p_off + DEFT_MAX_CHUNK;
         int32_t *p_lo = p_beg + DEFT_MAX_CHUNK;
         int32_t *p_hi = p_lo + DEFT_MAX_CHUNK;
+        const int flat0 = a.seg_off[seg0];
         for (int s = tid; s < nseg; s += 64 * kWaves) {
-            p_off[s] = a.seg_off[seg0 + s];
+            p_off[s] = a.seg_off[seg0 + s] - flat0;
             p_beg[s] = a.seg_tok_begin[seg0 + s];
             p_lo[s] = a.seg_qlo[seg0 + s];
             p_hi[s] = a.seg_qhi[seg0 + s];
@@ -1476,33 +1478,33 @@ bool configure_stage1() {
 constexpr int kResidentTiles = 3;
 
 template <int D>
-bool launch_stage1(const deft::Schedule &S, Stage1Args a1, const uint8_t *image, hipStream_t stream) {
-    if (S.n_items == 0) return true;
+bool launch_stage1(const deft::TaskSet &T, Stage1Args a1, const uint8_t *image, hipStream_t stream) {
+    if (T.n_items == 0) return true;
     if (!configure_stage1<D>()) return false;
-    a1.items = reinterpret_cast<const int32_t *>(image + S.off_items);
-    a1.n_items = S.n_items;
+    a1.items = reinterpret_cast<const int32_t *>(image + T.off_items);
+    a1.n_items = T.n_items;
     a1.resident_one = kResidentTiles;
-    a1.resident_many = (int64_t)S.n_items * a1.Hkv <= deft::kResidentGroups ? deft::kMaxTilesPerTask : kResidentTiles;
+    a1.resident_many = (int64_t)T.n_items * a1.Hkv <= deft::kResidentGroups ? deft::kMaxTilesPerTask : kResidentTiles;
     const size_t lds = std::max(kXbufBytes + 3 * (size_t)a1.table_len * sizeof(int32_t), (size_t)ResidentLds<D>::kWords * 4);
-    const unsigned grid = (unsigned)S.n_items * (unsigned)a1.Hkv;
-    auto *kernel = S.n_items_precise == 0           ? &deft_stage1<D, kBf16>
-                   : S.n_items_precise == S.n_items ? &deft_stage1<D, kTwoTerm>
+    const unsigned grid = (unsigned)T.n_items * (unsigned)a1.Hkv;
+    auto *kernel = T.n_items_precise == 0           ? &deft_stage1<D, kBf16>
+                   : T.n_items_precise == T.n_items ? &deft_stage1<D, kTwoTerm>
                                                     : &deft_stage1<D, kMixed>;
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * kWaves), lds, stream, a1);
     return hip_ok(hipGetLastError(), "deft_stage1 launch");
 }
 
 template <int D>
-bool launch_stage2(const deft::Schedule &S, const Stage2Args &a2, hipStream_t stream) {
+bool launch_stage2(const deft::TaskSet &T, const Stage2Args &a2, hipStream_t stream) {
     if (a2.nq == 0) return true;
     const unsigned rows = (unsigned)a2.nq * (unsigned)a2.Hq;
     constexpr int kFew = std::min(Stage2Row<D>::kBatch, deft::kQueryHeadInts - deft::kQueryHeadFixed);
     // Up to kFew partials one wave has them all in flight at once, and more waves cost more to start than they save (16
     // partials, 2048 rows of output: 5.1 us, four waves 7.5).  Beyond that a second batch is a round trip more: 17
     // partials 5.6 us with one wave, 4.4 with four, 4.0 with two; 64 partials 7.2 us with one, 3.4 with four.
-    if (S.max_parts <= kFew)
+    if (T.max_parts <= kFew)
         hipLaunchKernelGGL((deft_stage2_few<D>), dim3(rows), dim3(64), 0, stream, a2);
-    else if (S.max_parts <= 2 * 16)
+    else if (T.max_parts <= 2 * 16)
         hipLaunchKernelGGL((deft_stage2_many<D, 2>), dim3(rows), dim3(128), 0, stream, a2);
     else
         hipLaunchKernelGGL((deft_stage2_many<D, 4>), dim3(rows), dim3(256), 0, stream, a2);
@@ -1528,7 +1530,7 @@ int prepare(const deft_plan_t *plan, const void *dev_image, int32_t Hq, int32_t 
     call.S = deft::find_schedule(plan, Hq / Hkv);
     if (!call.S) return DEFT_ENOTREADY;
     if (workspace_bytes < deft_workspace_bytes(plan, Hq, Hkv, d)) return DEFT_EWORKSPACE;
-    if ((int64_t)call.S->n_items * Hkv > INT32_MAX) return DEFT_EINVAL;  // grid sizes are 32-bit
+    if ((int64_t)call.S->by_chunk.n_items * Hkv > INT32_MAX) return DEFT_EINVAL;  // grid sizes are 32-bit
     if ((int64_t)plan->nq * Hq > INT32_MAX) return DEFT_EINVAL;
     const size_t rows = (size_t)plan->n_slots() * (size_t)Hq;
     call.img = static_cast<const uint8_t *>(dev_image);
@@ -1541,7 +1543,7 @@ int prepare(const deft_plan_t *plan, const void *dev_image, int32_t Hq, int32_t 
     return DEFT_OK;
 }
 
-int run_stage1(const deft_plan_t *plan, const Call &call, const void *q, const void *k, const void *v, int32_t Hq,
+int run_stage1(const deft_plan_t *plan, const Call &call, const deft::TaskSet &T, const void *q, const void *k, const void *v, int32_t Hq,
                int32_t Hkv, int32_t d) {
     if (plan->n_chunks() == 0) return DEFT_OK;
     if (!q || !k || !v || !aligned16(q) || !aligned16(k) || !aligned16(v)) return DEFT_EINVAL;
@@ -1567,31 +1569,30 @@ int run_stage1(const deft_plan_t *plan, const Call &call, const void *q, const v
     a1.inv_G = inverse(a1.G);
     a1.table_len = S.table_len;
     a1.c = call.c;
-    const bool ok = d == 128 ? launch_stage1<128>(S, a1, call.img, call.stream)
-                             : launch_stage1<64>(S, a1, call.img, call.stream);
+    const bool ok = d == 128 ? launch_stage1<128>(T, a1, call.img, call.stream)
+                             : launch_stage1<64>(T, a1, call.img, call.stream);
     return ok ? DEFT_OK : DEFT_EHIP;
 }
 
-int run_stage2(const deft_plan_t *plan, const Call &call, void *o, int32_t Hq, int32_t d, uint32_t flags) {
+int run_stage2(const deft_plan_t *plan, const Call &call, const deft::TaskSet &T, void *o, int32_t Hq, int32_t d, uint32_t flags) {
     if (flags != DEFT_OUT_BF16 && flags != DEFT_OUT_F32) return DEFT_EINVAL;
     if (plan->nq == 0) return DEFT_OK;
     if (!o || !aligned16(o)) return DEFT_EINVAL;
-    const deft::Schedule &S = *call.S;
     auto at = [&](size_t off) { return reinterpret_cast<const int32_t *>(call.img + off); };
     Stage2Args a2{};
     a2.part_acc = call.acc;
     a2.part_m = call.pm;
     a2.part_l = call.pl;
-    a2.q_head = at(S.off_q_head);
-    a2.q_part_slot = at(S.off_q_part_slot);
+    a2.q_head = at(T.off_q_head);
+    a2.q_part_slot = at(T.off_q_part_slot);
     a2.out = o;
     a2.nq = plan->nq;
     a2.Hq = Hq;
-    a2.head_ints = S.head_ints;
+    a2.head_ints = T.head_ints;
     a2.inv_Hq = inverse(Hq);
     a2.out_f32 = (flags == DEFT_OUT_F32);
     a2.c = call.c;
-    const bool ok = d == 128 ? launch_stage2<128>(S, a2, call.stream) : launch_stage2<64>(S, a2, call.stream);
+    const bool ok = d == 128 ? launch_stage2<128>(T, a2, call.stream) : launch_stage2<64>(T, a2, call.stream);
     return ok ? DEFT_OK : DEFT_EHIP;
 }
 
@@ -1681,7 +1682,7 @@ extern "C" int deft_stage1_partial_attention(const deft_plan_t *plan, const void
     Call call;
     int rc = prepare(plan, dev_image, Hq, Hkv, d, scale, workspace, workspace_bytes, stream, call);
     if (rc != DEFT_OK) return rc;
-    return run_stage1(plan, call, q, k, v, Hq, Hkv, d);
+    return run_stage1(plan, call, call.S->by_chunk, q, k, v, Hq, Hkv, d);
 }
 
 extern "C" int deft_stage2_global_reduction(const deft_plan_t *plan, const void *dev_image, void *o, int32_t Hq,
@@ -1690,7 +1691,7 @@ extern "C" int deft_stage2_global_reduction(const deft_plan_t *plan, const void 
     Call call;
     int rc = prepare(plan, dev_image, Hq, Hkv, d, scale, workspace, workspace_bytes, stream, call);
     if (rc != DEFT_OK) return rc;
-    return run_stage2(plan, call, o, Hq, d, flags);
+    return run_stage2(plan, call, call.S->by_chunk, o, Hq, d, flags);
 }
 
 extern "C" int deft_tree_attn_decode(const deft_plan_t *plan, const void *dev_image, const void *q, const void *k,
@@ -1702,9 +1703,9 @@ extern "C" int deft_tree_attn_decode(const deft_plan_t *plan, const void *dev_im
     // check both stages' arguments before launching anything
     if (flags != DEFT_OUT_BF16 && flags != DEFT_OUT_F32) return DEFT_EINVAL;
     if (plan->nq > 0 && (!o || !aligned16(o))) return DEFT_EINVAL;
-    rc = run_stage1(plan, call, q, k, v, Hq, Hkv, d);
+    rc = run_stage1(plan, call, call.S->fused, q, k, v, Hq, Hkv, d);
     if (rc != DEFT_OK) return rc;
-    return run_stage2(plan, call, o, Hq, d, flags);
+    return run_stage2(plan, call, call.S->fused, o, Hq, d, flags);
 }
 
 namespace {

@@ -52,6 +52,18 @@ constexpr int kResidentGroups = 512;  // workgroups of stage 1 that an MI355X ho
 // queries x 8 heads over 8 KV heads: 160 workgroups 24.2 us, 320 (256 of them long) 23.5 us, 440 (352 long) 27.0 us).
 constexpr int kLongChunk = 256;
 constexpr int kLongGroups = kResidentGroups / 2;
+constexpr int kJoinTokens = kLongChunk;  // chunks are joined up to the longest run that is not long
+
+// Stage 1's tasks and the records with which stage 2 finds their partial results.
+struct TaskSet {
+    size_t off_items = 0;        // task descriptors
+    size_t off_q_head = 0;       // per-query records for stage 2
+    size_t off_q_part_slot = 0;  // per-query slot lists
+    int32_t n_items = 0;
+    int32_t n_items_precise = 0;         // tasks among them that want two-term weights
+    int32_t head_ints = kQueryHeadInts;  // int32 per record
+    int32_t max_parts = 0;               // partials of the query that has most
+};
 
 // Launch schedule + image layout for one Hq/Hkv ratio.  The row cut suits the number of KV heads it was first asked
 // for with; the schedule is right for any.
@@ -61,13 +73,8 @@ struct Schedule {
     // byte offsets of the canonical arrays inside the image
     size_t off_seg_tok_begin = 0, off_seg_len = 0, off_seg_qlo = 0, off_seg_qhi = 0, off_seg_off = 0;
     size_t off_q_order = 0;
-    size_t off_q_part_slot = 0;
-    size_t off_q_head = 0;    // per-query records for stage 2
-    int32_t head_ints = kQueryHeadInts;  // int32 per record
-    int32_t max_parts = 0;    // partials of the query that has most
-    int32_t n_items = 0;
-    int32_t n_items_precise = 0;  // tasks among them that want two-term weights
-    size_t off_items = 0;     // task descriptors
+    TaskSet by_chunk;         // one partial result per (chunk, query of its group): what the two stages called apart use
+    TaskSet fused;            // the same work on joined chunks: what a whole call uses; the same as by_chunk if none are
     int32_t table_len = 32;   // longest chunk made of several pieces, rounded up to whole blocks: LDS table size
     std::vector<uint8_t> host_image;  // packed image, kept for repeated uploads
 };

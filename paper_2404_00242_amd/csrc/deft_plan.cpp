@@ -709,127 +709,179 @@ namespace deft {
 
 static size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
 
-static void build_schedule(const deft_plan_t *P, int32_t G, int32_t Hkv, Schedule &S) {
-    S.group = G;
-    S.table_len = 32;
-    const int32_t m = P->n_chunks();
-    std::vector<int32_t> seg_off(P->n_segs(), 0);
-    struct Chunk {
-        int32_t id, len, tiles, precise;
-        int64_t cost;
-    };
-    std::vector<Chunk> chunks((size_t)m);
+// A run of consecutive chunks that stage 1 works on as one, with the queries of all of them.
+struct Run {
+    int32_t c0, c1;  // chunks [c0, c1)
+    int32_t lo, hi;  // queries, in plan positions
+    int32_t len, tiles, precise, slot_base;
+    int64_t cost;    // of the largest task, for the dispatch order
+};
+
+static int32_t row_tiles(int32_t width, int32_t G) { return (int32_t)(((int64_t)width * G + 15) / 16); }
+
+// Tasks and stage-2 records of a list of runs, appended to the image.
+static void build_tasks(const deft_plan_t *P, int32_t G, int32_t Hkv, std::vector<Run> runs, Schedule &S, TaskSet &T) {
     constexpr int kCuts = (int)(sizeof(kTaskTiles) / sizeof(kTaskTiles[0]));
     int64_t n_tasks[kCuts] = {}, n_long[kCuts] = {};
     auto per_task = [](int32_t tiles, int cut) {
         const int32_t k = (tiles + kTaskTiles[cut] - 1) / kTaskTiles[cut];
         return k ? (tiles + k - 1) / k : 1;
     };
-    for (int32_t c = 0; c < m; ++c) {
-        const int32_t s0 = P->chunk_seg_ptr[c], s1 = P->chunk_seg_ptr[c + 1];
-        int32_t len = 0;
-        for (int32_t s = s0; s < s1; ++s) {
-            seg_off[s] = len;
-            len += P->seg_len[s];
-        }
-        if (s1 - s0 > 1) S.table_len = std::max(S.table_len, (len + 31) / 32 * 32);
-        const int64_t rows = (int64_t)(P->chunk_qhi[c] - P->chunk_qlo[c]) * G;
-        // two-term softmax weights where some query of the group has a short path
-        int32_t precise = P->precise_all ? 1 : 0;
-        for (int32_t p = P->chunk_qlo[c]; p < P->chunk_qhi[c] && !precise; ++p)
-            if (P->q_path_len[p] < kPreciseBelowTokens) precise = 1;
-        chunks[c] = {c, len, (int32_t)((rows + 15) / 16), precise, 0};
+    for (const Run &r : runs) {
+        if (r.c1 > r.c0 && P->chunk_seg_ptr[r.c1] - P->chunk_seg_ptr[r.c0] > 1)
+            S.table_len = std::max(S.table_len, (r.len + 31) / 32 * 32);
         for (int i = 0; i < kCuts; ++i) {
-            const int32_t per = per_task(chunks[c].tiles, i);
-            const int32_t n = (chunks[c].tiles + per - 1) / per;
+            const int32_t per = per_task(r.tiles, i), n = (r.tiles + per - 1) / per;
             n_tasks[i] += n;
-            if (len > kLongChunk) n_long[i] += n;
+            if (r.len > kLongChunk) n_long[i] += n;
         }
     }
     int cut = 0;
     for (int i = 1; i < kCuts; ++i)
         if (n_tasks[i] * Hkv <= kResidentGroups && n_long[i] * Hkv <= kLongGroups) cut = i;
 
-    // Groups of more row tiles than the cut allows become several tasks of (nearly) equal size: the row groups of one
-    // chunk then cost the same, are dispatched next to each other and find the chunk in L2 after the first of them
-    // has fetched it.
-    //
-    // Dispatch order: workgroups are handed to compute units in the order of the task list, a new one
-    // whenever a slot frees, so the longest tasks go first (tokens x (2 + row tiles) as the estimate) and
-    // the short ones fill the tail.  The row groups of one chunk share one estimate (that of the largest of
-    // them) and equal estimates keep their chunk order, which leaves them next to each other: they re-read
-    // that chunk from the same L2 while it is still there.
-    for (Chunk &ch : chunks) ch.cost = (int64_t)ch.len * (2 + per_task(ch.tiles, cut));
-    std::sort(chunks.begin(), chunks.end(), [](const Chunk &x, const Chunk &y) {
-        return x.cost != y.cost ? x.cost > y.cost : x.id < y.id;
-    });
-    std::vector<int32_t> items((size_t)n_tasks[cut] * kItemInts, 0);
-    int32_t *d = items.data();
-    S.n_items = (int32_t)n_tasks[cut];
-    S.n_items_precise = 0;
-    for (const Chunk &ch : chunks) {
-        const int32_t c = ch.id, s0 = P->chunk_seg_ptr[c], per = per_task(ch.tiles, cut);
-        for (int32_t t0 = 0; t0 < ch.tiles; t0 += per, d += kItemInts) {
-            d[kItChunk] = c;
-            d[kItTile0] = t0;
-            d[kItNTiles] = std::min<int32_t>(per, ch.tiles - t0);
-            d[kItSeg0] = s0;
-            d[kItNSeg] = P->chunk_seg_ptr[c + 1] - s0;
-            d[kItQlo] = P->chunk_qlo[c];
-            d[kItWidth] = P->chunk_qhi[c] - P->chunk_qlo[c];
-            d[kItSlotBase] = P->chunk_slot_base[c];
-            d[kItLen] = ch.len;
-            d[kItBegin0] = P->seg_tok_begin[s0];
-            d[kItSegQlo0] = P->seg_qlo[s0];
-            d[kItSegQhi0] = P->seg_qhi[s0];
-            d[kItPrecise] = ch.precise;
-            S.n_items_precise += ch.precise;
+    auto place = [&](size_t bytes, size_t align) {
+        const size_t at = (S.host_image.size() + align - 1) / align * align;
+        S.host_image.resize(align16(at + bytes), 0);
+        return at;
+    };
+    // ---- per query: its partial results, in the order of the runs ----
+    const int32_t nq = P->nq;
+    std::vector<int32_t> ptr(nq + 1, 0);
+    for (const Run &r : runs)
+        for (int32_t p = r.lo; p < r.hi; ++p) ++ptr[p + 1];
+    T.max_parts = 0;
+    for (int32_t p = 0; p < nq; ++p) {
+        T.max_parts = std::max(T.max_parts, ptr[p + 1]);
+        ptr[p + 1] += ptr[p];
+    }
+    T.head_ints = kQueryHeadInts;
+    while (T.head_ints < kQueryHeadMost && T.head_ints - kQueryHeadFixed < T.max_parts) T.head_ints *= 2;
+    T.off_q_part_slot = place((size_t)ptr[nq] * sizeof(int32_t), 16);
+    T.off_q_head = place((size_t)nq * T.head_ints * sizeof(int32_t), 64);
+    T.off_items = place((size_t)n_tasks[cut] * kItemInts * sizeof(int32_t), 64);
+    int32_t *slots = reinterpret_cast<int32_t *>(S.host_image.data() + T.off_q_part_slot);
+    int32_t *head = reinterpret_cast<int32_t *>(S.host_image.data() + T.off_q_head);
+    {
+        std::vector<int32_t> cursor(ptr.begin(), ptr.end() - 1);
+        for (const Run &r : runs)
+            for (int32_t p = r.lo; p < r.hi; ++p) slots[cursor[p]++] = r.slot_base + (p - r.lo);
+        for (int32_t p = 0; p < nq; ++p, head += T.head_ints) {
+            const int32_t n = ptr[p + 1] - ptr[p];
+            head[0] = n;
+            head[1] = P->q_order[p];
+            head[2] = ptr[p];
+            std::copy_n(slots + ptr[p], std::min(n, T.head_ints - kQueryHeadFixed), head + kQueryHeadFixed);
         }
     }
 
-    size_t off = 0;
-    auto place = [&](size_t count) {
-        size_t at = off;
-        off = align16(off + count * sizeof(int32_t));
+    // ---- tasks ----
+    // Groups of more row tiles than the cut allows become several tasks of (nearly) equal size: the row groups of one
+    // run then cost the same, are dispatched next to each other and find its tokens in L2 after the first of them
+    // has fetched them.
+    //
+    // Dispatch order: workgroups are handed to compute units in the order of the task list, a new one
+    // whenever a slot frees, so the longest tasks go first (tokens x (2 + row tiles) as the estimate) and
+    // the short ones fill the tail.  The row groups of one run share one estimate (that of the largest of
+    // them) and equal estimates keep their order, which leaves them next to each other: they re-read
+    // the tokens from the same L2 while they are still there.
+    for (Run &r : runs) r.cost = (int64_t)r.len * (2 + per_task(r.tiles, cut));
+    std::sort(runs.begin(), runs.end(),
+              [](const Run &x, const Run &y) { return x.cost != y.cost ? x.cost > y.cost : x.c0 < y.c0; });
+    int32_t *d = reinterpret_cast<int32_t *>(S.host_image.data() + T.off_items);
+    T.n_items = (int32_t)n_tasks[cut];
+    T.n_items_precise = 0;
+    for (const Run &r : runs) {
+        const int32_t s0 = P->chunk_seg_ptr[r.c0], per = per_task(r.tiles, cut);
+        for (int32_t t0 = 0; t0 < r.tiles; t0 += per, d += kItemInts) {
+            d[kItChunk] = r.c0;
+            d[kItTile0] = t0;
+            d[kItNTiles] = std::min<int32_t>(per, r.tiles - t0);
+            d[kItSeg0] = s0;
+            d[kItNSeg] = P->chunk_seg_ptr[r.c1] - s0;
+            d[kItQlo] = r.lo;
+            d[kItWidth] = r.hi - r.lo;
+            d[kItSlotBase] = r.slot_base;
+            d[kItLen] = r.len;
+            d[kItBegin0] = P->seg_tok_begin[s0];
+            d[kItSegQlo0] = P->seg_qlo[s0];
+            d[kItSegQhi0] = P->seg_qhi[s0];
+            d[kItPrecise] = r.precise;
+            T.n_items_precise += r.precise;
+        }
+    }
+}
+
+static void build_schedule(const deft_plan_t *P, int32_t G, int32_t Hkv, Schedule &S) {
+    S.group = G;
+    S.table_len = 32;
+    const int32_t m = P->n_chunks(), nseg = P->n_segs();
+    std::vector<int32_t> seg_off(nseg);  // flattened position of a segment's first token
+    for (int32_t s = 0, at = 0; s < nseg; at += P->seg_len[s++]) seg_off[s] = at;
+    std::vector<Run> own((size_t)m), joined;
+    for (int32_t c = 0; c < m; ++c) {
+        const int32_t s0 = P->chunk_seg_ptr[c], s1 = P->chunk_seg_ptr[c + 1], lo = P->chunk_qlo[c], hi = P->chunk_qhi[c];
+        const int32_t len = s1 > s0 ? seg_off[s1 - 1] + P->seg_len[s1 - 1] - seg_off[s0] : 0;
+        // two-term softmax weights where some query of the group has a short path
+        int32_t precise = P->precise_all ? 1 : 0;
+        for (int32_t p = lo; p < hi && !precise; ++p)
+            if (P->q_path_len[p] < kPreciseBelowTokens) precise = 1;
+        own[c] = {c, c + 1, lo, hi, len, row_tiles(hi - lo, G), precise, P->chunk_slot_base[c], 0};
+    }
+
+    // A whole call is free to work on several chunks as one.  It does so where the plan's chunks are many and short: with
+    // more than one round of workgroups, or with more than half a round whose partial results are a good part of the
+    // traffic, a run of up to kJoinTokens saves rounds, partial results and their reduction.  On fewer workgroups it only
+    // leaves compute units without work.  us per call, by chunk -> joined: 968 workgroups of 128 tokens (50 queries x 4
+    // heads) 25.9 -> 23.4; 1184 (62 queries, d = 64) 32.9 -> 30.1; 440, partials 0.40 of the KV bytes 17.4 -> 16.8; 264,
+    // 0.95: 20.8 -> 19.5; but 512, 0.03: 11.5 -> 12.2; 496, 0.04: 12.3 -> 13.2; 120, 0.31: 11.3 -> 13.5.
+    // Chunks join if that costs no more than the two apart (the measure of the balanced split) and makes no new slot.
+    int64_t groups = 0;
+    for (const Run &r : own) groups += (int64_t)((r.tiles + kMaxTilesPerTask - 1) / kMaxTilesPerTask) * Hkv;
+    const bool join = groups > kResidentGroups ||
+                      (groups > kResidentGroups / 2 && 10 * (int64_t)P->n_slots() * G >= 3 * (int64_t)P->n_flat);
+    for (const Run &r : own) {
+        if (join && !joined.empty()) {
+            Run &j = joined.back();
+            const int32_t lo = std::min(j.lo, r.lo), hi = std::max(j.hi, r.hi), tiles = row_tiles(hi - lo, G);
+            const int64_t apart = (int64_t)j.len * (2 + j.tiles) + (int64_t)r.len * (2 + r.tiles) + 192;
+            if ((int64_t)j.len + r.len <= kJoinTokens && hi - lo <= (j.hi - j.lo) + (r.hi - r.lo) &&
+                ((int64_t)j.len + r.len) * (2 + tiles) <= apart) {
+                j = {j.c0, r.c1, lo, hi, j.len + r.len, tiles, j.precise | r.precise, j.slot_base, 0};
+                continue;
+            }
+        }
+        joined.push_back(r);
+        if (joined.size() > 1) {
+            const Run &b = joined[joined.size() - 2];
+            joined.back().slot_base = b.slot_base + (b.hi - b.lo);
+        }
+    }
+
+    auto put = [&](const std::vector<int32_t> &v) {
+        const size_t at = S.host_image.size();
+        S.host_image.resize(align16(at + v.size() * sizeof(int32_t)), 0);
+        if (!v.empty()) std::memcpy(S.host_image.data() + at, v.data(), v.size() * sizeof(int32_t));
         return at;
     };
-    const int32_t nseg = P->n_segs(), nq = P->nq, slots = P->n_slots();
-    S.off_seg_tok_begin = place(nseg);
-    S.off_seg_len = place(nseg);
-    S.off_seg_qlo = place(nseg);
-    S.off_seg_qhi = place(nseg);
-    S.off_seg_off = place(nseg);
-    S.off_q_order = place(nq);
-    S.max_parts = 0;
-    for (int32_t p = 0; p < nq; ++p) S.max_parts = std::max(S.max_parts, P->q_part_ptr[p + 1] - P->q_part_ptr[p]);
-    S.head_ints = kQueryHeadInts;
-    while (S.head_ints < kQueryHeadMost && S.head_ints - kQueryHeadFixed < S.max_parts) S.head_ints *= 2;
-    S.off_q_part_slot = place(slots);
-    off = (off + 63) & ~(size_t)63;  // per-query records and descriptors are aligned 64-byte records
-    S.off_q_head = place((size_t)nq * S.head_ints);
-    S.off_items = place(items.size());
-    S.bytes = std::max<size_t>(off, 16);
-    S.host_image.assign(S.bytes, 0);
-    auto put = [&](size_t at, const std::vector<int32_t> &v) {
-        if (!v.empty()) std::memcpy(S.host_image.data() + at, v.data(), v.size() * sizeof(int32_t));
-    };
-    put(S.off_seg_tok_begin, P->seg_tok_begin);
-    put(S.off_seg_len, P->seg_len);
-    put(S.off_seg_qlo, P->seg_qlo);
-    put(S.off_seg_qhi, P->seg_qhi);
-    put(S.off_seg_off, seg_off);
-    put(S.off_q_order, P->q_order);
-    put(S.off_q_part_slot, P->q_part_slot);
-    put(S.off_items, items);
-    const int32_t inlined = S.head_ints - kQueryHeadFixed;
-    int32_t *r = reinterpret_cast<int32_t *>(S.host_image.data() + S.off_q_head);
-    for (int32_t p = 0; p < nq; ++p, r += S.head_ints) {
-        const int32_t s0 = P->q_part_ptr[p], n = P->q_part_ptr[p + 1] - s0;
-        r[0] = n;
-        r[1] = P->q_order[p];
-        r[2] = s0;
-        std::copy_n(P->q_part_slot.begin() + s0, std::min(n, inlined), r + kQueryHeadFixed);
-    }
+    // room for one task set without a cut, and for two where chunks are joined
+    const size_t sets = joined.size() == own.size() ? 1 : 2;
+    S.host_image.reserve(4 * (5 * (size_t)nseg + P->nq + sets * ((size_t)P->n_slots() + 2 * kQueryHeadInts * (size_t)P->nq +
+                                                               (size_t)(groups / Hkv) * kItemInts)) + 1024);
+    S.off_seg_tok_begin = put(P->seg_tok_begin);
+    S.off_seg_len = put(P->seg_len);
+    S.off_seg_qlo = put(P->seg_qlo);
+    S.off_seg_qhi = put(P->seg_qhi);
+    S.off_seg_off = put(seg_off);
+    S.off_q_order = put(P->q_order);
+    const bool same = joined.size() == own.size();
+    build_tasks(P, G, Hkv, std::move(own), S, S.by_chunk);
+    if (same)
+        S.fused = S.by_chunk;
+    else
+        build_tasks(P, G, Hkv, std::move(joined), S, S.fused);
+    if (S.host_image.size() < 16) S.host_image.resize(16, 0);
+    S.bytes = S.host_image.size();
 }
 
 const Schedule *get_schedule(const deft_plan_t *plan, int32_t group, int32_t Hkv) {

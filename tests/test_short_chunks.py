@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 import torch
 
-from paper_2404_00242_amd import workloads as wl
+from paper_2404_00242_amd import binding, workloads as wl
 
 from .test_gpu_parity import check, reference, reference_abs_v, run_gpu
 
@@ -66,3 +66,31 @@ def test_any_number_of_partial_results(parts, d):
     for out_dtype in (torch.float32, torch.bfloat16):
         got, _ = run_gpu(t, Q, K, V, chunk_size=32, out_dtype=out_dtype, mode="node_chunk")
         check(got, reference(t, Q, K, V), strict=False)
+
+
+# chunks that a whole call works on as one: prefixes, several branches, wide next to narrow, short next to long paths;
+# the stages called apart keep the plan's slots, and both ways give the same result
+@pytest.mark.parametrize("mode,chunk", [("flatten", 128), ("flatten", 96), ("node_chunk", 64), ("balanced", 128), ("query", 160)])
+@pytest.mark.parametrize("Hq,Hkv,d,root", [(32, 32, 128, 900), (24, 24, 64, 1500), (96, 24, 128, 2100)])
+def test_joined_chunks(mode, chunk, Hq, Hkv, d, root):
+    t = tree(root, [(37 * i) % 150 for i in range(14)], Hq, Hkv, d, seed=root)
+    Q, K, V = wl.make_qkv(t)
+    got, plan = run_gpu(t, Q, K, V, chunk_size=chunk, out_dtype=torch.float32, mode=mode)
+    ref = reference(t, Q, K, V)
+    check(got, ref, strict=False)
+    dev = torch.device("cuda:0")
+    q, k, v = Q.to(dev), K.to(dev), V.to(dev)
+    o = torch.empty((t.nq, Hq, d), dtype=torch.float32, device=dev)
+    lib, img, ws = binding.load_library(), plan.image(Hq, Hkv, dev), plan.workspace(Hq, Hkv, d, dev)
+    ws.fill_(0xFF)  # NaN: every slot that stage 2 reads has to be written by stage 1
+    st = torch.cuda.current_stream().cuda_stream
+    assert lib.deft_stage1_partial_attention(plan.handle, img.data_ptr(), q.data_ptr(), k.data_ptr(), v.data_ptr(), Hq,
+                                             Hkv, d, 0.0, ws.data_ptr(), ws.numel(), st) == 0
+    assert lib.deft_stage2_global_reduction(plan.handle, img.data_ptr(), o.data_ptr(), Hq, Hkv, d, 0.0, 1, ws.data_ptr(),
+                                            ws.numel(), st) == 0
+    torch.cuda.synchronize()
+    check(o.cpu().numpy().astype(np.float64), ref, strict=False)
+    ws.fill_(0xFF)
+    binding.deft_tree_attn_decode(plan, q, k, v, out=o, workspace=ws)
+    torch.cuda.synchronize()
+    check(o.cpu().numpy().astype(np.float64), ref, strict=False)

@@ -47,9 +47,12 @@ constexpr int kPreciseBelowTokens = 1024;
 constexpr int kTaskTiles[] = {kMaxTilesPerTask, 4, 3, 2};
 constexpr int kResidentGroups = 512;  // workgroups of stage 1 that an MI355X holds: two on each of 256 compute units
 
-// Tasks of chunks longer than this stream their tokens through LDS step by step, whatever their rows; two of them on a
-// compute unit get in each other's way, so the cut stops earlier for them, at one to a unit (4 chunks of 512 tokens, 63
-// queries x 8 heads over 8 KV heads: 160 workgroups 24.2 us, 320 (256 of them long) 23.5 us, 440 (352 long) 27.0 us).
+// Tasks of chunks longer than kLongChunk stream their tokens through LDS in steps that take as long for three row tiles
+// as for four, and half as many steps for two.  The wide ones among them (more than two tiles) have a cut of their own,
+// to 4 or 2 tiles, as long as they stay at one to a compute unit; what else is in the plan does not matter, for they
+// are the longest tasks and go first.  Per call, us: one chunk of 832 tokens under 64 queries x 8 heads with 57 others
+// 47.0 -> 33.6, one of 448 with 60 others 35.6 -> 24.9, four of 3072 under 77 queries x 4 heads (d = 64) 75.8 -> 70.8
+// (cut to 3 tiles: 89.7), four of 512 under 63 queries x 8 heads 24.1 -> 23.4 (3 tiles: 27.0).
 constexpr int kLongChunk = 256;
 constexpr int kLongGroups = kResidentGroups / 2;
 constexpr int kJoinTokens = kLongChunk;  // chunks are joined up to the longest run that is not long

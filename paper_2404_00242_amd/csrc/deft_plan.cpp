@@ -722,23 +722,27 @@ static int32_t row_tiles(int32_t width, int32_t G) { return (int32_t)(((int64_t)
 // Tasks and stage-2 records of a list of runs, appended to the image.
 static void build_tasks(const deft_plan_t *P, int32_t G, int32_t Hkv, std::vector<Run> runs, Schedule &S, TaskSet &T) {
     constexpr int kCuts = (int)(sizeof(kTaskTiles) / sizeof(kTaskTiles[0]));
-    int64_t n_tasks[kCuts] = {}, n_long[kCuts] = {};
+    int64_t n_short[kCuts] = {}, n_long[kCuts] = {};
     auto per_task = [](int32_t tiles, int cut) {
         const int32_t k = (tiles + kTaskTiles[cut] - 1) / kTaskTiles[cut];
         return k ? (tiles + k - 1) / k : 1;
     };
+    auto wide_and_long = [](const Run &r) { return r.len > kLongChunk && r.tiles > kTaskTiles[kCuts - 1]; };
     for (const Run &r : runs) {
         if (r.c1 > r.c0 && P->chunk_seg_ptr[r.c1] - P->chunk_seg_ptr[r.c0] > 1)
             S.table_len = std::max(S.table_len, (r.len + 31) / 32 * 32);
         for (int i = 0; i < kCuts; ++i) {
             const int32_t per = per_task(r.tiles, i), n = (r.tiles + per - 1) / per;
-            n_tasks[i] += n;
-            if (r.len > kLongChunk) n_long[i] += n;
+            (wide_and_long(r) ? n_long : n_short)[i] += n;
         }
     }
-    int cut = 0;
+    int cut_long = 0, cut_short = 0;
     for (int i = 1; i < kCuts; ++i)
-        if (n_tasks[i] * Hkv <= kResidentGroups && n_long[i] * Hkv <= kLongGroups) cut = i;
+        if (n_long[i] * Hkv <= kLongGroups && kTaskTiles[i] != 3) cut_long = i;
+    for (int i = 1; i < kCuts; ++i)
+        if ((n_long[cut_long] + n_short[i]) * Hkv <= kResidentGroups) cut_short = i;
+    auto per_run = [&](const Run &r) { return per_task(r.tiles, wide_and_long(r) ? cut_long : cut_short); };
+    const size_t n_tasks = (size_t)(n_long[cut_long] + n_short[cut_short]);
 
     auto place = [&](size_t bytes, size_t align) {
         const size_t at = (S.host_image.size() + align - 1) / align * align;
@@ -759,7 +763,7 @@ static void build_tasks(const deft_plan_t *P, int32_t G, int32_t Hkv, std::vecto
     while (T.head_ints < kQueryHeadMost && T.head_ints - kQueryHeadFixed < T.max_parts) T.head_ints *= 2;
     T.off_q_part_slot = place((size_t)ptr[nq] * sizeof(int32_t), 16);
     T.off_q_head = place((size_t)nq * T.head_ints * sizeof(int32_t), 64);
-    T.off_items = place((size_t)n_tasks[cut] * kItemInts * sizeof(int32_t), 64);
+    T.off_items = place(n_tasks * kItemInts * sizeof(int32_t), 64);
     int32_t *slots = reinterpret_cast<int32_t *>(S.host_image.data() + T.off_q_part_slot);
     int32_t *head = reinterpret_cast<int32_t *>(S.host_image.data() + T.off_q_head);
     {
@@ -785,14 +789,14 @@ static void build_tasks(const deft_plan_t *P, int32_t G, int32_t Hkv, std::vecto
     // the short ones fill the tail.  The row groups of one run share one estimate (that of the largest of
     // them) and equal estimates keep their order, which leaves them next to each other: they re-read
     // the tokens from the same L2 while they are still there.
-    for (Run &r : runs) r.cost = (int64_t)r.len * (2 + per_task(r.tiles, cut));
+    for (Run &r : runs) r.cost = (int64_t)r.len * (2 + per_run(r));
     std::sort(runs.begin(), runs.end(),
               [](const Run &x, const Run &y) { return x.cost != y.cost ? x.cost > y.cost : x.c0 < y.c0; });
     int32_t *d = reinterpret_cast<int32_t *>(S.host_image.data() + T.off_items);
-    T.n_items = (int32_t)n_tasks[cut];
+    T.n_items = (int32_t)n_tasks;
     T.n_items_precise = 0;
     for (const Run &r : runs) {
-        const int32_t s0 = P->chunk_seg_ptr[r.c0], per = per_task(r.tiles, cut);
+        const int32_t s0 = P->chunk_seg_ptr[r.c0], per = per_run(r);
         for (int32_t t0 = 0; t0 < r.tiles; t0 += per, d += kItemInts) {
             d[kItChunk] = r.c0;
             d[kItTile0] = t0;

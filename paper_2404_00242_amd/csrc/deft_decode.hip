@@ -601,8 +601,10 @@ struct WidePipe {
         for (int j = 0; j < 8; ++j) v[j] = xs[(2 * KK + j) * 64 + lane];
     }
 
-    // one steady-state step: block `blk` arrives, block blk-1 (scores in sacc, V in vreg) is finished
-    template <bool PRECISE>
+    // one steady-state step: block `blk` arrives, block blk-1 (scores in sacc, V in vreg) is finished.  WHOLE: the block
+    // is known to need no mask; without a branch in front of them the shift and the check of its scores are issued
+    // while the products of block blk-1 are multiplied.
+    template <bool PRECISE, bool WHOLE>
     __device__ __forceinline__ void step(S &sh, const ChunkCtx &c, u32x4 *xs, int t, int lane, int blk, int nblk,
                                          TileState<D> (&ts)[NT], f32x4 (&sacc)[NT][2], u32x4 (&vreg)[8], float cs,
                                          float inv_cs) {
@@ -615,7 +617,7 @@ struct WidePipe {
         qk_block<D, NT>(k, ts, snew);
         pv_block<D, NT, PRECISE, true>(vreg, preg, plo, ts);
         read_v(xs, lane, vreg);
-        mask_block<D, NT>(c, blk * 32, ts, snew);
+        if (!WHOLE) mask_block<D, NT>(c, blk * 32, ts, snew);
         shift_block<D, NT>(ts, snew, cs);
         raise_block<D, NT>(ts, snew);
 #pragma unroll
@@ -644,17 +646,21 @@ struct WidePipe {
         }
         // steady state, DEPTH steps per round so that the shares in flight are addressed statically.  Whole
         // rounds only inside the loop (a round that could stop half way would make the compiler assume, for the
-        // waits of the next round, that the share it consumes is the youngest one in flight).
+        // waits of the next round, that the share it consumes is the youngest one in flight).  UNIFORM: every block
+        // but the last is whole, so the loop leaves that one to the steps behind it.
+        const int b_end = UNIFORM ? nblk - 1 : nblk;
         int b0 = 1;
-        for (; b0 + DEPTH <= nblk; b0 += DEPTH) {
+        for (; b0 + DEPTH <= b_end; b0 += DEPTH) {
 #pragma unroll
             for (int u = 0; u < DEPTH; ++u) {
                 const int blk = b0 + u;
-                step<PRECISE>(st[(1 + u) % DEPTH], ctx, xbuf + (blk & 1) * STAGE, t, lane, blk, nblk, ts, sacc, vreg, cs, inv_cs);
+                step<PRECISE, UNIFORM>(st[(1 + u) % DEPTH], ctx, xbuf + (blk & 1) * STAGE, t, lane, blk, nblk, ts, sacc, vreg, cs, inv_cs);
             }
         }
-        if (DEPTH == 2 && b0 < nblk)
-            step<PRECISE>(st[1], ctx, xbuf + (b0 & 1) * STAGE, t, lane, b0, nblk, ts, sacc, vreg, cs, inv_cs);
+#pragma unroll
+        for (int u = 0; u < (UNIFORM ? DEPTH : DEPTH - 1); ++u)
+            if (b0 + u < nblk)
+                step<PRECISE, false>(st[(1 + u) % DEPTH], ctx, xbuf + ((b0 + u) & 1) * STAGE, t, lane, b0 + u, nblk, ts, sacc, vreg, cs, inv_cs);
         {   // last block: weights and products
             bf16x8 preg[NT], plo[NT];
             weights_block<D, NT, PRECISE>(ts, sacc, cs, preg, plo);

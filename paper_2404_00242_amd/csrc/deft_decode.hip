@@ -14,7 +14,7 @@
 //
 // Each token row of one head (2*d bytes, contiguous) is fetched from HBM exactly once per task and every
 // byte of every 64-byte sector requested is used.  A narrow group (one row tile) splits the chunk's
-// tokens over the four waves, each keeping two blocks of loads in flight in registers.  A wider group
+// tokens over the four waves, each keeping a block of loads in flight in registers.  A wider group
 // gives each wave its own row tile (two tiles for tasks of more than four); the waves that need the same
 // block each fetch a share of it and pass the operand registers to the others through LDS.  The waves' partial results are merged in LDS before
 // one (m, l, acc) triple per (chunk, row) is written.
@@ -144,7 +144,7 @@ __device__ __forceinline__ int tok_row(const ChunkCtx &c, int x) {
 // instructions on every path the compiler can count exactly how many younger loads may stay in flight when
 // an older block is consumed, which is what keeps the software pipeline full.
 template <int D>
-__device__ __forceinline__ void load_block(KVRegs<D> &r, const ChunkCtx &c, int x0, bool valid) {
+__device__ __forceinline__ void load_k(KVRegs<D> &r, const ChunkCtx &c, int x0, bool valid) {
     if (!valid) x0 = 0;
 #pragma unroll
     for (int aa = 0; aa < 2; ++aa) {
@@ -152,12 +152,18 @@ __device__ __forceinline__ void load_block(KVRegs<D> &r, const ChunkCtx &c, int 
         const uint16_t *kp = c.kbase + (size_t)rowk * c.row_stride;
 #pragma unroll
         for (int kk = 0; kk < D / 32; ++kk) r.k[aa][kk] = __builtin_bit_cast(bf16x8, load16_once(kp + 32 * kk));
+    }
+}
+template <int D>
+__device__ __forceinline__ void load_v(KVRegs<D> &r, const ChunkCtx &c, int x0, bool valid) {
+    if (!valid) x0 = 0;
+#pragma unroll
+    for (int aa = 0; aa < 2; ++aa)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int rowv = valid ? tok_row(c, x0 + 16 * aa + 4 * c.g + i) : c.begin0;
             r.v[4 * aa + i] = load16_once(c.vbase + (size_t)rowv * c.row_stride);
         }
-    }
 }
 
 // Running softmax state of one row (held redundantly by the row's four lanes).
@@ -389,23 +395,36 @@ __device__ __forceinline__ void compute_block(const KVRegs<D> &r, const ChunkCtx
     pv_block<D, NT, PRECISE>(r.v, preg, plo, ts);
 }
 
-// ---- token-split path (groups of one row tile): every wave streams its own blocks, two in flight ----
-// wave w takes blocks w, w+4, w+8, ... (neighbouring waves read neighbouring rows at the same time)
+// ---- token-split path (groups of one row tile): every wave streams its own blocks.  K of the next block is asked for
+//      as soon as the scores are formed, V as soon as the products are, each into the registers it replaces ----
+// wave w takes blocks w, w+4, w+8, ... (neighbouring waves read neighbouring rows at the same time).
+// Bound by HBM.  One block of 16 KB per wave, 128 KB per compute unit, is nine times what the unit's share of the
+// bandwidth needs at the latency of a loaded chip (24 GB/s x 0.6 us); a second block per wave only made the queue in
+// front of the other workgroup's loads longer.  Stage 1, two blocks -> one reloaded whole -> in halves: sixteen
+// sequences (148 MB) 29.9 -> 28.8 -> 27.8 us, few-shot prefix (149 MB) 28.7 -> 28.7 -> 27.7, reasoning tree of 256
+// queries (456 MB) 96.2 -> 94.5 -> 93.6.
 template <int D>
 struct SplitPipe {
-    KVRegs<D> b0, b1;
+    KVRegs<D> r;
     __device__ __forceinline__ void prime(const ChunkCtx &ctx, int wave, int nblk) {
-        load_block<D>(b0, ctx, wave * 32, wave < nblk);
-        load_block<D>(b1, ctx, (wave + kWaves) * 32, wave + kWaves < nblk);
+        load_k<D>(r, ctx, wave * 32, wave < nblk);
+        load_v<D>(r, ctx, wave * 32, wave < nblk);
     }
     template <bool PRECISE>
-    __device__ __forceinline__ void run(const ChunkCtx &ctx, int wave, int nblk, TileState<D> (&ts)[1], float cs,
-                                        float inv_cs) {
-        for (int blk = wave; blk < nblk; blk += 2 * kWaves) {
-            compute_block<D, 1, PRECISE>(b0, ctx, blk * 32, ts, cs, inv_cs);
-            load_block<D>(b0, ctx, (blk + 2 * kWaves) * 32, blk + 2 * kWaves < nblk);
-            if (blk + kWaves < nblk) compute_block<D, 1, PRECISE>(b1, ctx, (blk + kWaves) * 32, ts, cs, inv_cs);
-            load_block<D>(b1, ctx, (blk + 3 * kWaves) * 32, blk + 3 * kWaves < nblk);
+    __device__ __forceinline__ void run(const ChunkCtx &ctx, int wave, int nblk, TileState<D> (&ts)[1], float cs) {
+        for (int blk = wave; blk < nblk; blk += kWaves) {
+            const int next = blk + kWaves;
+            f32x4 sacc[1][2];
+            bf16x8 preg[1], plo[1];
+            qk_block<D, 1>(r.k, ts, sacc);
+            load_k<D>(r, ctx, next * 32, next < nblk);
+            __builtin_amdgcn_sched_barrier(0);  // the loads go out here, not behind the softmax
+            mask_block<D, 1>(ctx, blk * 32, ts, sacc);
+            shift_block<D, 1>(ts, sacc, cs);
+            raise_block<D, 1>(ts, sacc);
+            weights_block<D, 1, PRECISE>(ts, sacc, cs, preg, plo);
+            pv_block<D, 1, PRECISE>(r.v, preg, plo, ts);
+            load_v<D>(r, ctx, next * 32, next < nblk);
         }
     }
 };
@@ -1161,7 +1180,7 @@ __device__ __forceinline__ void streaming_task(const Stage1Args &a, const int32_
         SplitPipe<D> pipe;
         pipe.prime(ctx, wave, nblk);
         load_q(1);
-        pipe.template run<PRECISE>(ctx, wave, nblk, ts1, a.c, inv_cs);
+        pipe.template run<PRECISE>(ctx, wave, nblk, ts1, a.c);
     } else if (TR == 2) {
         SharedPipe<D, 2, 1> pipe;
         pipe.prime(ctx, wave, nblk);

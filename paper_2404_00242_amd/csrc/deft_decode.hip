@@ -544,14 +544,16 @@ struct SharedPipe {
 //      then addressed as (wave-uniform pointer that moves on by one block per step) + (a byte offset per lane
 //      that never changes): no vector arithmetic per load.  The last, partial block and the dummy loads past
 //      the end go through the general addressing.
-template <int D, int NT, bool UNIFORM>
+//      DEPTH: blocks whose shares a wave keeps in flight.  One, except for two-tile waves on chunks of more than kDeepChunk tokens:
+//      there the task is what the launch waits for, and its loads queue behind those of the workgroup beside it (120
+//      queries over 32768 tokens: 166 us with one, 124 with two).  Elsewhere a second one only waits behind the other
+//      workgroup's loads and in front of its next ones (stage 1 of a 256-query reasoning tree 93.6 us with two, 91.5
+//      with one; of 26 queries x 4 heads over 12345 tokens 18.8, 18.2; a 64-row group over 4000 tokens 20.5, 19.5).
+constexpr int kDeepChunk = 1024;
+template <int D, int NT, bool UNIFORM, int DEPTH>
 struct WidePipe {
     static constexpr int KK = D / 32;
     using S = Share<D, 4>;
-    // blocks whose shares a wave keeps in flight: with a tile per wave one measured faster than two (a 64-row
-    // group over a 4000-token prefix: 19.5 us against 20.5 us); such a task is short and what is queued deeper
-    // only waits behind the other workgroup's loads
-    static constexpr int DEPTH = NT == 1 ? 1 : 2;
     S st[DEPTH];
     uint32_t lane_row, lane_col;  // UNIFORM: first row of this lane's loads inside a block, byte offset inside a row
 
@@ -1187,25 +1189,30 @@ __device__ __forceinline__ void streaming_task(const Stage1Args &a, const int32_
         load_q(1);
         pipe.template run<PRECISE>(ctx, xbuf, wave, lane, nblk, ts1, a.c, inv_cs);
     } else if (NTW == 1 && ctx.uniform) {
-        WidePipe<D, 1, D == 128> pipe;
+        WidePipe<D, 1, D == 128, 1> pipe;
         pipe.prime(ctx, wave, nblk);
         load_q(1);
         pipe.template run<PRECISE>(ctx, xbuf, wave, lane, nblk, ts1, a.c, inv_cs);
     } else if (NTW == 1) {
-        WidePipe<D, 1, false> pipe;
+        WidePipe<D, 1, false, 1> pipe;
         pipe.prime(ctx, wave, nblk);
         load_q(1);
         pipe.template run<PRECISE>(ctx, xbuf, wave, lane, nblk, ts1, a.c, inv_cs);
-    } else if (ctx.uniform) {
-        WidePipe<D, 2, D == 128> pipe;  // the fast addressing is written for four loads per K loader
-        pipe.prime(ctx, wave, nblk);
-        load_q(2);
-        pipe.template run<PRECISE>(ctx, xbuf, wave, lane, nblk, ts, a.c, inv_cs);
     } else {
-        WidePipe<D, 2, false> pipe;
-        pipe.prime(ctx, wave, nblk);
-        load_q(2);
-        pipe.template run<PRECISE>(ctx, xbuf, wave, lane, nblk, ts, a.c, inv_cs);
+        auto two_tiles = [&](auto &&pipe) {
+            pipe.prime(ctx, wave, nblk);
+            load_q(2);
+            pipe.template run<PRECISE>(ctx, xbuf, wave, lane, nblk, ts, a.c, inv_cs);
+        };
+        const bool deep = clen > kDeepChunk;
+        if (ctx.uniform && deep)
+            two_tiles(WidePipe<D, 2, D == 128, 2>());  // the fast addressing is written for four loads per K loader
+        else if (ctx.uniform)
+            two_tiles(WidePipe<D, 2, D == 128, 1>());
+        else if (deep)
+            two_tiles(WidePipe<D, 2, false, 2>());
+        else
+            two_tiles(WidePipe<D, 2, false, 1>());
     }
 
     // ---- merge the token parts in LDS and write one partial result per (chunk, row):

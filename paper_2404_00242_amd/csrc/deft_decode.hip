@@ -1055,7 +1055,7 @@ __device__ __forceinline__ void resident_task(const Stage1Args &a, const int32_t
 // PRECISE selects two-term softmax weights (see compute_block).  The two variants are separate kernels so
 // that the extra registers of the precise one do not weigh on the other; a plan's tasks are listed by
 // variant and a call launches each non-empty list.
-template <int D, bool PRECISE>
+template <int D, bool PRECISE, bool SHALLOW>
 __device__ __forceinline__ void streaming_task(const Stage1Args &a, const int32_t *it, int h, unsigned char *s_raw) {
     constexpr int KK = D / 32;  // k-steps of the Q.K^T contraction
     // The P.V product runs as 8 MFMAs per block (a lane loads 8 d of V per token).  With D = 64 lanes
@@ -1198,21 +1198,28 @@ __device__ __forceinline__ void streaming_task(const Stage1Args &a, const int32_
         pipe.prime(ctx, wave, nblk);
         load_q(1);
         pipe.template run<PRECISE>(ctx, xbuf, wave, lane, nblk, ts1, a.c, inv_cs);
+    // SHALLOW: the kernel has room for the variants with one block in flight.  The kernels with two-term weights do not:
+    // their registers spill with them (256 queries over 62 chunks of 1024 tokens 66 -> 73 us).
+    } else if (SHALLOW && ctx.uniform && clen <= kDeepChunk) {
+        WidePipe<D, 2, D == 128, SHALLOW ? 1 : 2> pipe;
+        pipe.prime(ctx, wave, nblk);
+        load_q(2);
+        pipe.template run<PRECISE>(ctx, xbuf, wave, lane, nblk, ts, a.c, inv_cs);
+    } else if (SHALLOW && clen <= kDeepChunk) {
+        WidePipe<D, 2, false, SHALLOW ? 1 : 2> pipe;
+        pipe.prime(ctx, wave, nblk);
+        load_q(2);
+        pipe.template run<PRECISE>(ctx, xbuf, wave, lane, nblk, ts, a.c, inv_cs);
+    } else if (ctx.uniform) {
+        WidePipe<D, 2, D == 128, 2> pipe;  // the fast addressing is written for four loads per K loader
+        pipe.prime(ctx, wave, nblk);
+        load_q(2);
+        pipe.template run<PRECISE>(ctx, xbuf, wave, lane, nblk, ts, a.c, inv_cs);
     } else {
-        auto two_tiles = [&](auto &&pipe) {
-            pipe.prime(ctx, wave, nblk);
-            load_q(2);
-            pipe.template run<PRECISE>(ctx, xbuf, wave, lane, nblk, ts, a.c, inv_cs);
-        };
-        const bool deep = clen > kDeepChunk;
-        if (ctx.uniform && deep)
-            two_tiles(WidePipe<D, 2, D == 128, 2>());  // the fast addressing is written for four loads per K loader
-        else if (ctx.uniform)
-            two_tiles(WidePipe<D, 2, D == 128, 1>());
-        else if (deep)
-            two_tiles(WidePipe<D, 2, false, 2>());
-        else
-            two_tiles(WidePipe<D, 2, false, 1>());
+        WidePipe<D, 2, false, 2> pipe;
+        pipe.prime(ctx, wave, nblk);
+        load_q(2);
+        pipe.template run<PRECISE>(ctx, xbuf, wave, lane, nblk, ts, a.c, inv_cs);
     }
 
     // ---- merge the token parts in LDS and write one partial result per (chunk, row):
@@ -1286,13 +1293,13 @@ __device__ __forceinline__ void streaming_task(const Stage1Args &a, const int32_
 
 enum Weights { kBf16 = 0, kTwoTerm = 1, kMixed = 2 };
 
-template <int D, bool PRECISE>
+template <int D, bool PRECISE, bool SHALLOW>
 __device__ __forceinline__ void run_task(const Stage1Args &a, const int32_t *it, int h, unsigned char *s_raw) {
     if (it[deft::kItLen] <= kResidentTokens<D> &&
         it[deft::kItNTiles] <= (D == 128 && it[deft::kItNSeg] == 1 ? a.resident_one : a.resident_many))
         resident_task<D, PRECISE>(a, it, h, s_raw);
     else
-        streaming_task<D, PRECISE>(a, it, h, s_raw);
+        streaming_task<D, PRECISE, SHALLOW>(a, it, h, s_raw);
 }
 
 template <int D, int WEIGHTS>
@@ -1308,9 +1315,9 @@ __global__ __launch_bounds__(64 * kWaves, 2) void deft_stage1(Stage1Args a) {
     const int h = turned - divide(turned, a.Hkv, a.inv_Hkv) * a.Hkv;
     const int32_t *it = a.items + (size_t)item * deft::kItemInts;
     if (WEIGHTS == kTwoTerm || (WEIGHTS == kMixed && it[deft::kItPrecise]))
-        run_task<D, true>(a, it, h, s_raw);
+        run_task<D, true, false>(a, it, h, s_raw);
     else
-        run_task<D, false>(a, it, h, s_raw);
+        run_task<D, false, WEIGHTS == kBf16>(a, it, h, s_raw);
 }
 
 // Stage 2: tree-topology-aware global reduction (eq. 1 with the largest maximum subtracted), D/4 lanes to a row of a

@@ -722,7 +722,7 @@ static int32_t row_tiles(int32_t width, int32_t G) { return (int32_t)(((int64_t)
 // Tasks and stage-2 records of a list of runs, appended to the image.
 static void build_tasks(const deft_plan_t *P, int32_t G, int32_t Hkv, std::vector<Run> runs, Schedule &S, TaskSet &T) {
     constexpr int kCuts = (int)(sizeof(kTaskTiles) / sizeof(kTaskTiles[0]));
-    int64_t n_short[kCuts] = {}, n_long[kCuts] = {};
+    int64_t n_short[kCuts] = {}, n_long[kCuts] = {}, tokens = 0, longest = 0;
     auto per_task = [](int32_t tiles, int cut) {
         const int32_t k = (tiles + kTaskTiles[cut] - 1) / kTaskTiles[cut];
         return k ? (tiles + k - 1) / k : 1;
@@ -735,10 +735,17 @@ static void build_tasks(const deft_plan_t *P, int32_t G, int32_t Hkv, std::vecto
             const int32_t per = per_task(r.tiles, i), n = (r.tiles + per - 1) / per;
             (wide_and_long(r) ? n_long : n_short)[i] += n;
         }
+        tokens += r.len;
+        if (wide_and_long(r)) longest = std::max<int64_t>(longest, r.len);
     }
     int cut_long = 0, cut_short = 0;
+    // a launch of one round becomes two only where the wide tasks are far longer than what would follow them
+    const bool one_round = (n_long[0] + n_short[0]) * Hkv <= kResidentGroups;
+    const bool far_longer = longest * (int64_t)runs.size() >= 2 * tokens;
     for (int i = 1; i < kCuts; ++i)
-        if (n_long[i] * Hkv <= kLongGroups && kTaskTiles[i] != 3) cut_long = i;
+        if (n_long[i] * Hkv <= kLongGroups && kTaskTiles[i] != 3 &&
+            (!one_round || far_longer || (n_long[i] + n_short[0]) * Hkv <= kResidentGroups))
+            cut_long = i;
     for (int i = 1; i < kCuts; ++i)
         if ((n_long[cut_long] + n_short[i]) * Hkv <= kResidentGroups) cut_short = i;
     auto per_run = [&](const Run &r) { return per_task(r.tiles, wide_and_long(r) ? cut_long : cut_short); };

@@ -1,7 +1,7 @@
 // Device side of libdeft: the Attention Calculation Phase of DeFT-Flatten (Algorithm 4) for gfx950.
 //
-// Stage 1 (deft_stage1): one workgroup of four waves per task = (chunk, KV head, up to eight 16-row
-// tiles).  The rows of a tile are (query of the chunk's group) x (query head reading this KV head).
+// Stage 1 (deft_stage1): one workgroup of four waves per task = (chunk or run of short chunks, KV head, up to eight
+// 16-row tiles).  Short chunks are held in registers whole (resident_task), the others stream (streaming_task).  The rows of a tile are (query of the chunk's group) x (query head reading this KV head).
 // A wave streams 32 tokens at a time straight from HBM into MFMA operand registers:
 //
 //   S^T[token, row] = K[token, :] . Q[row, :]      v_mfma_f32_16x16x32_bf16, A = K tile (a lane holds
@@ -1052,9 +1052,7 @@ __device__ __forceinline__ void resident_task(const Stage1Args &a, const int32_t
 // tiles.  The parts' partial results are merged in LDS, so one (m, l, acc) triple per (chunk, row)
 // reaches the workspace.
 //
-// PRECISE selects two-term softmax weights (see compute_block).  The two variants are separate kernels so
-// that the extra registers of the precise one do not weigh on the other; a plan's tasks are listed by
-// variant and a call launches each non-empty list.
+// PRECISE selects two-term softmax weights (see compute_block).
 template <int D, bool PRECISE, bool SHALLOW>
 __device__ __forceinline__ void streaming_task(const Stage1Args &a, const int32_t *it, int h, unsigned char *s_raw) {
     constexpr int KK = D / 32;  // k-steps of the Q.K^T contraction
@@ -1291,6 +1289,9 @@ __device__ __forceinline__ void streaming_task(const Stage1Args &a, const int32_
     }
 }
 
+// One launch for all tasks of a call: a second one would run behind the first, each on a part of the chip (sixteen
+// sequences on both sides of 1024 tokens: 29.6 + 16.5 us in two launches, 29.9 us in one).  Plans whose tasks all want
+// the same kind of weights, which is most of them, run a kernel that holds that kind alone.
 enum Weights { kBf16 = 0, kTwoTerm = 1, kMixed = 2 };
 
 template <int D, bool PRECISE, bool SHALLOW>

@@ -843,22 +843,23 @@ static void build_schedule(const deft_plan_t *P, int32_t G, int32_t Hkv, Schedul
     // A whole call is free to work on several chunks as one.  It does so where the plan's chunks are many and short: with
     // more than one round of workgroups, or with more than half a round whose partial results are a good part of the
     // traffic, a run of up to kJoinTokens saves rounds, partial results and their reduction.  On fewer workgroups it only
-    // leaves compute units without work.  us per call, by chunk -> joined: 968 workgroups of 128 tokens (50 queries x 4
-    // heads) 25.9 -> 23.4; 1184 (62 queries, d = 64) 32.9 -> 30.1; 440, partials 0.40 of the KV bytes 17.4 -> 16.8; 264,
-    // 0.95: 20.8 -> 19.5; but 512, 0.03: 11.5 -> 12.2; 496, 0.04: 12.3 -> 13.2; 120, 0.31: 11.3 -> 13.5.
-    // Chunks join if that costs no more than the two apart (the measure of the balanced split) and makes no new slot.
+    // leaves compute units without work.  us per call, by chunk -> joined: 64 queries x 32 heads over 4000 tokens in chunks
+    // of 128 36.6 -> 29.1; 16000 tokens under 32 branches, 4 heads a KV head, 93.4 -> 70.0; few-shot, 20 branches of 256 x
+    // 32 heads 41.5 -> 38.5; but 512 workgroups, partials 0.03 of the KV bytes, 11.5 -> 12.2.
+    // Only chunks with the same queries join, and only in the two flattened splits: a masked token still enters a query's
+    // sum with weight 0, and 0 * Inf is NaN, so no query may share a run with tokens that were in none of its chunks.  The
+    // strategies that the header calls comparisons are run as they are named, chunk by chunk.
     int64_t groups = 0;
     for (const Run &r : own) groups += (int64_t)((r.tiles + kMaxTilesPerTask - 1) / kMaxTilesPerTask) * Hkv;
-    const bool join = groups > kResidentGroups ||
-                      (groups > kResidentGroups / 2 && 10 * (int64_t)P->n_slots() * G >= 3 * (int64_t)P->n_flat);
+    const bool join = (P->mode == DEFT_SPLIT_FLATTEN || P->mode == DEFT_SPLIT_BALANCED) &&
+                      (groups > kResidentGroups ||
+                       (groups > kResidentGroups / 2 && 10 * (int64_t)P->n_slots() * G >= 3 * (int64_t)P->n_flat));
     for (const Run &r : own) {
         if (join && !joined.empty()) {
             Run &j = joined.back();
-            const int32_t lo = std::min(j.lo, r.lo), hi = std::max(j.hi, r.hi), tiles = row_tiles(hi - lo, G);
-            const int64_t apart = (int64_t)j.len * (2 + j.tiles) + (int64_t)r.len * (2 + r.tiles) + 192;
-            if ((int64_t)j.len + r.len <= kJoinTokens && hi - lo <= (j.hi - j.lo) + (r.hi - r.lo) &&
-                ((int64_t)j.len + r.len) * (2 + tiles) <= apart) {
-                j = {j.c0, r.c1, lo, hi, j.len + r.len, tiles, j.precise | r.precise, j.slot_base, 0};
+            if (j.lo == r.lo && j.hi == r.hi && (int64_t)j.len + r.len <= kJoinTokens) {
+                j.c1 = r.c1;
+                j.len += r.len;
                 continue;
             }
         }

@@ -94,3 +94,45 @@ def test_joined_chunks(mode, chunk, Hq, Hkv, d, root):
     binding.deft_tree_attn_decode(plan, q, k, v, out=o, workspace=ws)
     torch.cuda.synchronize()
     check(o.cpu().numpy().astype(np.float64), ref, strict=False)
+
+
+def stages(plan, q, k, v, ws, one=True, two=True, out_f32=1):
+    """the two stages called apart on a workspace; returns stage 2's output"""
+    nq, Hq, d = q.shape
+    Hkv, dev = k.shape[1], q.device
+    lib, img, st = binding.load_library(), plan.image(Hq, Hkv, dev), torch.cuda.current_stream().cuda_stream
+    o = torch.empty((nq, Hq, d), dtype=torch.float32 if out_f32 else torch.bfloat16, device=dev)
+    if one:
+        assert lib.deft_stage1_partial_attention(plan.handle, img.data_ptr(), q.data_ptr(), k.data_ptr(), v.data_ptr(),
+                                                 Hq, Hkv, d, 0.0, ws.data_ptr(), ws.numel(), st) == 0
+    if two:
+        assert lib.deft_stage2_global_reduction(plan.handle, img.data_ptr(), o.data_ptr(), Hq, Hkv, d, 0.0, out_f32,
+                                                ws.data_ptr(), ws.numel(), st) == 0
+    torch.cuda.synchronize()
+    return o
+
+
+JOINING = ("flatten", "balanced")
+
+
+# Inf and NaN in V reach the queries that see them and, inside one chunk, its other queries (0 * Inf); a whole call must
+# not carry them further than the two stages do chunk by chunk, and in the node and query plans, whose chunks hold nothing
+# that some query of the group does not see, no further than the reference.
+@pytest.mark.parametrize("mode,chunk", [("flatten", 64), ("balanced", 64), ("node_chunk", 64), ("node", 0), ("query", 96)])
+@pytest.mark.parametrize("Hq,Hkv,d", [(32, 32, 128), (24, 24, 64)])
+def test_infinities_of_a_sibling_stay_where_they_are(mode, chunk, Hq, Hkv, d):
+    t = tree(2100, [20 + (37 * i) % 90 for i in range(24)], Hq, Hkv, d, seed=d)
+    Q, K, V = wl.make_qkv(t)
+    at = int(t.node_tok_begin[5]) + 3
+    V[at, :, 7], V[at + 1, :, 9] = float("inf"), float("nan")
+    q, k, v = (x.to("cuda:0") for x in (Q, K, V))
+    got, plan = run_gpu(t, Q, K, V, chunk_size=chunk, out_dtype=torch.float32, mode=mode)
+    ws = plan.workspace(Hq, Hkv, d, q.device)
+    apart = stages(plan, q, k, v, ws).cpu().numpy()
+    assert not np.isfinite(got[4]).all()  # the query of node 5
+    assert (np.isfinite(got) >= np.isfinite(apart)).all()
+    if mode not in JOINING:
+        others = [j for j in range(t.nq) if j != 4]
+        assert np.isfinite(got[others]).all()
+        V[at, :, 7] = V[at + 1, :, 9] = 0
+        check(got[others], reference(t, Q, K, V)[others], strict=False)

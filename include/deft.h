@@ -275,9 +275,11 @@ int deft_tree_attn_decode(const deft_plan_t *plan, const void *dev_image, const 
 
 /*
  * The two stages of Algorithm 4 as separate calls, for callers that want to time or overlap them.
- * deft_tree_attn_decode(...) is exactly stage 1 followed by stage 2 on the same stream with the
- * same workspace and scale.  Arguments, alignment rules and errors are those of
- * deft_tree_attn_decode.
+ * deft_tree_attn_decode(...) is stage 1 followed by stage 2 on the same stream with the same workspace
+ * and scale, and stage 2 may follow either (for a second output type, say) with the same result.  The one
+ * difference: a whole call may merge chunks that have the same queries before it writes a partial result,
+ * which then lies in the slots of the first of them, while those of the others are marked empty (m = -inf,
+ * l = 0, acc unwritten).  Arguments, alignment rules and errors are those of deft_tree_attn_decode.
  *   stage 1: per QKV group, masked partial attention with an online softmax; writes, for every
  *            (slot, query head), the running maximum m of the raw scores q.k, the sum l of
  *            exp(scale*(s - m)) and the un-normalised sum acc of exp(scale*(s - m)) * v into the

@@ -1303,6 +1303,20 @@ __device__ __forceinline__ void run_task(const Stage1Args &a, const int32_t *it,
         streaming_task<D, PRECISE, SHALLOW>(a, it, h, s_raw);
 }
 
+// A run of several chunks with the same queries leaves its result in the slots of the first and marks those of the others
+// empty, m = -inf and l = 0, so that stage 2 finds the same sum whether it reads the run's slots or the plan's.
+__device__ __forceinline__ void mark_empty(const Stage1Args &a, const int32_t *it, int h) {
+    static_assert(kTaskRows <= 64 * kWaves, "one thread per row");
+    const int width = it[deft::kItWidth], r = 16 * it[deft::kItTile0] + threadIdx.x;
+    if (threadIdx.x >= 16 * it[deft::kItNTiles] || r >= width * a.G) return;
+    const int pl = divide(r, a.G, a.inv_G), gh = r - pl * a.G;
+    for (int k = 1; k < it[deft::kItChunks]; ++k) {
+        const size_t ro = (size_t)(it[deft::kItSlotBase] + k * width + pl) * a.Hq + (size_t)h * a.G + gh;
+        a.part_m[ro] = -INFINITY;
+        a.part_l[ro] = 0.f;
+    }
+}
+
 template <int D, int WEIGHTS>
 __global__ __launch_bounds__(64 * kWaves, 2) void deft_stage1(Stage1Args a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char s_raw[];
@@ -1315,6 +1329,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void deft_stage1(Stage1Args a) {
     const uint32_t turned = blockIdx.x - item * a.Hkv + ((uint32_t)(item * a.Hkv) >> 8);
     const int h = turned - divide(turned, a.Hkv, a.inv_Hkv) * a.Hkv;
     const int32_t *it = a.items + (size_t)item * deft::kItemInts;
+    if (it[deft::kItChunks] > 1) mark_empty(a, it, h);  // (first: behind the task its descriptor would have to be read again)
     if (WEIGHTS == kTwoTerm || (WEIGHTS == kMixed && it[deft::kItPrecise]))
         run_task<D, true, false>(a, it, h, s_raw);
     else
@@ -1341,6 +1356,20 @@ __device__ __forceinline__ float wave_sum(float x) {
     return x;
 }
 
+// HOLES: some slots of the list may have been marked empty by a whole call (m = -inf, l = 0).  Their rows of acc were not
+// written, so they are dropped and not multiplied by 0; in the place of a weight, which is never negative, such a slot has
+// kNoSlot.  A whole call's own list has no such slots, and does without the selection, which costs it 0.3 us.
+constexpr float kNoSlot = -1.f;
+template <bool HOLES>
+__device__ __forceinline__ float row_weight(float w, float m, float l) {
+    return HOLES && m == -INFINITY && l == 0.f ? kNoSlot : w;
+}
+template <bool HOLES>
+__device__ __forceinline__ void add_row(f32x4 &acc, float w, const f32x4 &x) {
+    if (HOLES && w == kNoSlot) return;
+    acc += w * x;
+}
+
 __device__ __forceinline__ void store_out(const Stage2Args &a, size_t at, f32x4 x) {
     if (a.out_f32) {
         *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(a.out) + at) = x;
@@ -1355,7 +1384,7 @@ __device__ __forceinline__ void store_out(const Stage2Args &a, size_t at, f32x4 
 // record, so m, l and every row are fetched in the next round trip and the weights are applied to rows that are already
 // in registers.  One wave to a workgroup: four cost 0.4 us more on every tree, and two or four heads to a wave gain
 // only where there are thousands (0.2 us of 6.3 at 8192).
-template <int D>
+template <int D, bool HOLES>
 __global__ __launch_bounds__(64) void deft_stage2_few(Stage2Args a) {
     using R = Stage2Row<D>;
     const int lane = threadIdx.x;
@@ -1380,8 +1409,9 @@ __global__ __launch_bounds__(64) void deft_stage2_few(Stage2Args a) {
         const float mx = wave_max(mj);
         const float w = (lane < n && mx != -INFINITY) ? __builtin_amdgcn_exp2f((mj - mx) * a.c) : 0.f;
         lsum = wave_sum(w * lj);
+        const float wr = row_weight<HOLES>(w, mj, lj);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc += __shfl(w, u * R::kRows + sub) * x[u];
+        for (int u = 0; u < 8; ++u) add_row<HOLES>(acc, __shfl(wr, u * R::kRows + sub), x[u]);
     }
 #pragma unroll
     for (int o = 32; o >= R::kLanes; o >>= 1)
@@ -1392,7 +1422,7 @@ __global__ __launch_bounds__(64) void deft_stage2_few(Stage2Args a) {
 
 // Any number of partials: WAVES waves per (query, query head), partial WAVES * i + w with wave w.  Each wave merges what it
 // holds as above (64 of its partials at a time, on a running maximum), then their results are merged in LDS.
-template <int D, int WAVES>
+template <int D, int WAVES, bool HOLES>
 __global__ __launch_bounds__(64 * WAVES) void deft_stage2_many(Stage2Args a) {
     using R = Stage2Row<D>;
     __shared__ __attribute__((aligned(16))) float s_acc[WAVES][D];
@@ -1427,13 +1457,13 @@ __global__ __launch_bounds__(64 * WAVES) void deft_stage2_many(Stage2Args a) {
                 const float old = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((M - top) * a.c);
                 w = (lane < cnt && top != -INFINITY) ? __builtin_amdgcn_exp2f((mj - top) * a.c) : 0.f;
                 lsum = lsum * old + wave_sum(w * lj);
+                w = row_weight<HOLES>(w, mj, lj);
                 acc *= old;
                 M = top;
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                const float wu = __shfl(w, (j + u * R::kRows + sub) & 63);  // zero for rows past the end
-                acc += wu * x[u];
+                add_row<HOLES>(acc, __shfl(w, (j + u * R::kRows + sub) & 63), x[u]);  // weight 0 for rows past the end
             }
         }
     }
@@ -1534,7 +1564,7 @@ bool launch_stage1(const deft::TaskSet &T, Stage1Args a1, const uint8_t *image, 
     return hip_ok(hipGetLastError(), "deft_stage1 launch");
 }
 
-template <int D>
+template <int D, bool HOLES>
 bool launch_stage2(const deft::TaskSet &T, const Stage2Args &a2, hipStream_t stream) {
     if (a2.nq == 0) return true;
     const unsigned rows = (unsigned)a2.nq * (unsigned)a2.Hq;
@@ -1543,11 +1573,11 @@ bool launch_stage2(const deft::TaskSet &T, const Stage2Args &a2, hipStream_t str
     // partials, 2048 rows of output: 5.1 us, four waves 7.5).  Beyond that a second batch is a round trip more: 17
     // partials 5.6 us with one wave, 4.4 with four, 4.0 with two; 64 partials 7.2 us with one, 3.4 with four.
     if (T.max_parts <= kFew)
-        hipLaunchKernelGGL((deft_stage2_few<D>), dim3(rows), dim3(64), 0, stream, a2);
+        hipLaunchKernelGGL((deft_stage2_few<D, HOLES>), dim3(rows), dim3(64), 0, stream, a2);
     else if (T.max_parts <= 2 * 16)
-        hipLaunchKernelGGL((deft_stage2_many<D, 2>), dim3(rows), dim3(128), 0, stream, a2);
+        hipLaunchKernelGGL((deft_stage2_many<D, 2, HOLES>), dim3(rows), dim3(128), 0, stream, a2);
     else
-        hipLaunchKernelGGL((deft_stage2_many<D, 4>), dim3(rows), dim3(256), 0, stream, a2);
+        hipLaunchKernelGGL((deft_stage2_many<D, 4, HOLES>), dim3(rows), dim3(256), 0, stream, a2);
     return hip_ok(hipGetLastError(), "deft_stage2 launch");
 }
 
@@ -1632,7 +1662,10 @@ int run_stage2(const deft_plan_t *plan, const Call &call, const deft::TaskSet &T
     a2.inv_Hq = inverse(Hq);
     a2.out_f32 = (flags == DEFT_OUT_F32);
     a2.c = call.c;
-    const bool ok = d == 128 ? launch_stage2<128>(T, a2, call.stream) : launch_stage2<64>(T, a2, call.stream);
+    // a stage 2 called apart may find slots that a whole call on joined chunks left empty
+    const bool holes = &T != &call.S->fused && call.S->fused.off_items != T.off_items;
+    const bool ok = d == 128 ? (holes ? launch_stage2<128, true>(T, a2, call.stream) : launch_stage2<128, false>(T, a2, call.stream))
+                             : (holes ? launch_stage2<64, true>(T, a2, call.stream) : launch_stage2<64, false>(T, a2, call.stream));
     return ok ? DEFT_OK : DEFT_EHIP;
 }
 

@@ -818,6 +818,7 @@ static void build_tasks(const deft_plan_t *P, int32_t G, int32_t Hkv, std::vecto
             d[kItSegQlo0] = P->seg_qlo[s0];
             d[kItSegQhi0] = P->seg_qhi[s0];
             d[kItPrecise] = r.precise;
+            d[kItChunks] = r.c1 - r.c0;
             T.n_items_precise += r.precise;
         }
     }
@@ -864,10 +865,6 @@ static void build_schedule(const deft_plan_t *P, int32_t G, int32_t Hkv, Schedul
             }
         }
         joined.push_back(r);
-        if (joined.size() > 1) {
-            const Run &b = joined[joined.size() - 2];
-            joined.back().slot_base = b.slot_base + (b.hi - b.lo);
-        }
     }
 
     auto put = [&](const std::vector<int32_t> &v) {

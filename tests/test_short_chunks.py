@@ -112,7 +112,38 @@ def stages(plan, q, k, v, ws, one=True, two=True, out_f32=1):
     return o
 
 
+def empty_slots(plan, ws, Hq, d):
+    """(slot, head) pairs of a workspace that hold no token: m = -inf, l = 0"""
+    rows = plan.view()["n_slots"] * Hq
+    f = ws.view(torch.float32)
+    m, l = f[rows * d: rows * (d + 1)], f[rows * (d + 1): rows * (d + 2)]
+    return int(((m == -np.inf) & (l == 0)).sum())
+
+
 JOINING = ("flatten", "balanced")
+
+
+# Stage 2 may follow a whole call on its workspace (a second output type, say), whether or not the call worked on several
+# chunks as one; the comparison strategies are run chunk by chunk.
+@pytest.mark.parametrize("mode", ["flatten", "balanced", "node_chunk", "query"])
+@pytest.mark.parametrize("Hq,Hkv,d", [(32, 32, 128), (40, 20, 64), (64, 16, 128)])
+def test_stage2_after_a_whole_call(mode, Hq, Hkv, d):
+    t = tree(2900, [(37 * i) % 150 for i in range(14)], Hq, Hkv, d, seed=Hq)
+    Q, K, V = wl.make_qkv(t)
+    q, k, v = (x.to("cuda:0") for x in (Q, K, V))
+    _, plan = run_gpu(t, Q, K, V, chunk_size=64, out_dtype=torch.float32, mode=mode)
+    ref, ws = reference(t, Q, K, V), plan.workspace(Hq, Hkv, d, q.device)
+    ws.fill_(0xFF)  # NaN
+    whole = binding.deft_tree_attn_decode(plan, q, k, v, out_dtype=torch.float32, workspace=ws)
+    after = stages(plan, q, k, v, ws, one=False)
+    joined = empty_slots(plan, ws, Hq, d)
+    check(whole.cpu().numpy().astype(np.float64), ref, strict=False)
+    check(after.cpu().numpy().astype(np.float64), ref, strict=False)
+    check(stages(plan, q, k, v, ws, one=False, out_f32=0).float().cpu().numpy().astype(np.float64), ref, strict=False)
+    ws.fill_(0xFF)
+    check(stages(plan, q, k, v, ws).cpu().numpy().astype(np.float64), ref, strict=False)
+    assert empty_slots(plan, ws, Hq, d) == 0
+    assert (joined > 0) == (mode in JOINING), joined
 
 
 # Inf and NaN in V reach the queries that see them and, inside one chunk, its other queries (0 * Inf); a whole call must

@@ -544,12 +544,12 @@ struct SharedPipe {
 //      then addressed as (wave-uniform pointer that moves on by one block per step) + (a byte offset per lane
 //      that never changes): no vector arithmetic per load.  The last, partial block and the dummy loads past
 //      the end go through the general addressing.
-//      DEPTH: blocks whose shares a wave keeps in flight.  One, except for two-tile waves on chunks of more than kDeepChunk tokens:
-//      there the task is what the launch waits for, and its loads queue behind those of the workgroup beside it (120
-//      queries over 32768 tokens: 166 us with one, 124 with two).  Elsewhere a second one only waits behind the other
-//      workgroup's loads and in front of its next ones (stage 1 of a 256-query reasoning tree 93.6 us with two, 91.5
-//      with one; of 26 queries x 4 heads over 12345 tokens 18.8, 18.2; a 64-row group over 4000 tokens 20.5, 19.5).
-constexpr int kDeepChunk = 1024;
+//      DEPTH: blocks whose shares a wave keeps in flight: one where a wave has one tile, two where it has two, whatever
+//      the chunk's length.  A task of 5-8 tiles is what its launch waits for, and with one block in flight each of its
+//      steps waits for loads that queue behind those of the workgroup beside it.  Whole call, us, one -> two: 120
+//      queries x 4 heads over 32768 tokens in chunks of 1024 (equal-token split) 175 -> 163, 20000 tokens under 40
+//      branches 89.8 -> 77.3, 32768 under 40 branches, 7 heads a KV head, 104.7 -> 91.0; where such tasks are few among
+//      many narrow ones a second block costs 2 % (256-query reasoning tree, balanced split, 97.7 -> 99.9).
 template <int D, int NT, bool UNIFORM, int DEPTH>
 struct WidePipe {
     static constexpr int KK = D / 32;
@@ -1053,7 +1053,7 @@ __device__ __forceinline__ void resident_task(const Stage1Args &a, const int32_t
 // reaches the workspace.
 //
 // PRECISE selects two-term softmax weights (see compute_block).
-template <int D, bool PRECISE, bool SHALLOW>
+template <int D, bool PRECISE>
 __device__ __forceinline__ void streaming_task(const Stage1Args &a, const int32_t *it, int h, unsigned char *s_raw) {
     constexpr int KK = D / 32;  // k-steps of the Q.K^T contraction
     // The P.V product runs as 8 MFMAs per block (a lane loads 8 d of V per token).  With D = 64 lanes
@@ -1196,18 +1196,6 @@ __device__ __forceinline__ void streaming_task(const Stage1Args &a, const int32_
         pipe.prime(ctx, wave, nblk);
         load_q(1);
         pipe.template run<PRECISE>(ctx, xbuf, wave, lane, nblk, ts1, a.c, inv_cs);
-    // SHALLOW: the kernel has room for the variants with one block in flight.  The kernels with two-term weights do not:
-    // their registers spill with them (256 queries over 62 chunks of 1024 tokens 66 -> 73 us).
-    } else if (SHALLOW && ctx.uniform && clen <= kDeepChunk) {
-        WidePipe<D, 2, D == 128, SHALLOW ? 1 : 2> pipe;
-        pipe.prime(ctx, wave, nblk);
-        load_q(2);
-        pipe.template run<PRECISE>(ctx, xbuf, wave, lane, nblk, ts, a.c, inv_cs);
-    } else if (SHALLOW && clen <= kDeepChunk) {
-        WidePipe<D, 2, false, SHALLOW ? 1 : 2> pipe;
-        pipe.prime(ctx, wave, nblk);
-        load_q(2);
-        pipe.template run<PRECISE>(ctx, xbuf, wave, lane, nblk, ts, a.c, inv_cs);
     } else if (ctx.uniform) {
         WidePipe<D, 2, D == 128, 2> pipe;  // the fast addressing is written for four loads per K loader
         pipe.prime(ctx, wave, nblk);
@@ -1294,13 +1282,13 @@ __device__ __forceinline__ void streaming_task(const Stage1Args &a, const int32_
 // the same kind of weights, which is most of them, run a kernel that holds that kind alone.
 enum Weights { kBf16 = 0, kTwoTerm = 1, kMixed = 2 };
 
-template <int D, bool PRECISE, bool SHALLOW>
+template <int D, bool PRECISE>
 __device__ __forceinline__ void run_task(const Stage1Args &a, const int32_t *it, int h, unsigned char *s_raw) {
     if (it[deft::kItLen] <= kResidentTokens<D> &&
         it[deft::kItNTiles] <= (D == 128 && it[deft::kItNSeg] == 1 ? a.resident_one : a.resident_many))
         resident_task<D, PRECISE>(a, it, h, s_raw);
     else
-        streaming_task<D, PRECISE, SHALLOW>(a, it, h, s_raw);
+        streaming_task<D, PRECISE>(a, it, h, s_raw);
 }
 
 // A run of several chunks with the same queries leaves its result in the slots of the first and marks those of the others
@@ -1331,9 +1319,9 @@ __global__ __launch_bounds__(64 * kWaves, 2) void deft_stage1(Stage1Args a) {
     const int32_t *it = a.items + (size_t)item * deft::kItemInts;
     if (it[deft::kItChunks] > 1) mark_empty(a, it, h);  // (first: behind the task its descriptor would have to be read again)
     if (WEIGHTS == kTwoTerm || (WEIGHTS == kMixed && it[deft::kItPrecise]))
-        run_task<D, true, false>(a, it, h, s_raw);
+        run_task<D, true>(a, it, h, s_raw);
     else
-        run_task<D, false, WEIGHTS == kBf16>(a, it, h, s_raw);
+        run_task<D, false>(a, it, h, s_raw);
 }
 
 // Stage 2: tree-topology-aware global reduction (eq. 1 with the largest maximum subtracted), D/4 lanes to a row of a

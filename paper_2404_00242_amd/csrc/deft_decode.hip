@@ -624,7 +624,9 @@ struct WidePipe {
 
     // one steady-state step: block `blk` arrives, block blk-1 (scores in sacc, V in vreg) is finished.  WHOLE: the block
     // is known to need no mask; without a branch in front of them the shift and the check of its scores are issued
-    // while the products of block blk-1 are multiplied.
+    // while the products of block blk-1 are multiplied.  Not with two-term weights: there the second set of products
+    // fills the matrix pipe as it is, and what is kept alive across them costs more (64 queries x 4 heads, reasoning tree
+    // of two-term weights, 22.6 us with the branch, 24.7 without; 256 queries, 286-token root, 29.5 and 33.3).
     template <bool PRECISE, bool WHOLE>
     __device__ __forceinline__ void step(S &sh, const ChunkCtx &c, u32x4 *xs, int t, int lane, int blk, int nblk,
                                          TileState<D> (&ts)[NT], f32x4 (&sacc)[NT][2], u32x4 (&vreg)[8], float cs,
@@ -667,19 +669,20 @@ struct WidePipe {
         }
         // steady state, DEPTH steps per round so that the shares in flight are addressed statically.  Whole
         // rounds only inside the loop (a round that could stop half way would make the compiler assume, for the
-        // waits of the next round, that the share it consumes is the youngest one in flight).  UNIFORM: every block
+        // waits of the next round, that the share it consumes is the youngest one in flight).  kWhole: every block
         // but the last is whole, so the loop leaves that one to the steps behind it.
-        const int b_end = UNIFORM ? nblk - 1 : nblk;
+        constexpr bool kWhole = UNIFORM && !PRECISE;
+        const int b_end = kWhole ? nblk - 1 : nblk;
         int b0 = 1;
         for (; b0 + DEPTH <= b_end; b0 += DEPTH) {
 #pragma unroll
             for (int u = 0; u < DEPTH; ++u) {
                 const int blk = b0 + u;
-                step<PRECISE, UNIFORM>(st[(1 + u) % DEPTH], ctx, xbuf + (blk & 1) * STAGE, t, lane, blk, nblk, ts, sacc, vreg, cs, inv_cs);
+                step<PRECISE, kWhole>(st[(1 + u) % DEPTH], ctx, xbuf + (blk & 1) * STAGE, t, lane, blk, nblk, ts, sacc, vreg, cs, inv_cs);
             }
         }
 #pragma unroll
-        for (int u = 0; u < (UNIFORM ? DEPTH : DEPTH - 1); ++u)
+        for (int u = 0; u < (kWhole ? DEPTH : DEPTH - 1); ++u)
             if (b0 + u < nblk)
                 step<PRECISE, false>(st[(1 + u) % DEPTH], ctx, xbuf + ((b0 + u) & 1) * STAGE, t, lane, b0 + u, nblk, ts, sacc, vreg, cs, inv_cs);
         {   // last block: weights and products

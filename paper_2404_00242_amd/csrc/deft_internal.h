@@ -49,13 +49,17 @@ constexpr int kTaskTiles[] = {kMaxTilesPerTask, 4, 3, 2};
 constexpr int kResidentGroups = 512;  // workgroups of stage 1 that an MI355X holds: two on each of 256 compute units
 
 // Tasks of chunks longer than kLongChunk stream their tokens through LDS in steps that take as long for three row tiles
-// as for four, and half as many steps for two.  The wide ones among them (more than two tiles) have a cut of their own,
-// to 4 or 2 tiles, as long as they stay at one to a compute unit; what else is in the plan does not matter, for they
-// are the longest tasks and go first.  Per call, us: one chunk of 832 tokens under 64 queries x 8 heads with 57 others
-// 47.0 -> 33.6, one of 448 with 60 others 35.6 -> 24.9, four of 3072 under 77 queries x 4 heads (d = 64) 75.8 -> 70.8
-// (cut to 3 tiles: 89.7), four of 512 under 63 queries x 8 heads 24.1 -> 23.4 (3 tiles: 27.0).
+// as for four, and half as many steps for two (with d = 64 chunks of up to twice that can still be held in registers; the
+// schedule serves both).  The wide ones among them (more than two tiles) have a cut of their own, to 4 or 2 tiles, as long
+// as they stay at one to a compute unit: always where all workgroups then still fit the chip at once, and otherwise only if
+// the longest task costs kLongestShare times the work of the launch per place on the chip (a task of several pieces, whose
+// rows are looked up token by token, counts a third more).  More tasks read the chunk more often and form its weights in
+// smaller batches, which a launch of several rounds pays for.  Whole call, us, uncut -> cut, by that ratio: 0.9 45.0 ->
+// 49.2, 1.7 58.2 -> 66.8, 2.3 60.5 -> 71.6, 2.5 33.6 -> 38.2, 3.3 34.7 -> 38.5, 3.4 81.5 -> 90.8; with several pieces 4.5
+// 37.8 -> 31.1, 4.5 54.3 -> 45.2, 6.0 37.7 -> 30.7; one piece 4.7 22.7 -> 17.1, 5.9 38.9 -> 25.6, 9.3 31.8 -> 22.5.
 constexpr int kLongChunk = 256;
 constexpr int kLongGroups = kResidentGroups / 2;
+constexpr int kLongestShare = 4;
 constexpr int kJoinTokens = kLongChunk;  // chunks are joined up to the longest run that is not long
 
 // Stage 1's tasks and the records with which stage 2 finds their partial results.

@@ -722,29 +722,32 @@ static int32_t row_tiles(int32_t width, int32_t G) { return (int32_t)(((int64_t)
 // Tasks and stage-2 records of a list of runs, appended to the image.
 static void build_tasks(const deft_plan_t *P, int32_t G, int32_t Hkv, std::vector<Run> runs, Schedule &S, TaskSet &T) {
     constexpr int kCuts = (int)(sizeof(kTaskTiles) / sizeof(kTaskTiles[0]));
-    int64_t n_short[kCuts] = {}, n_long[kCuts] = {}, tokens = 0, longest = 0;
+    int64_t n_short[kCuts] = {}, n_long[kCuts] = {}, work = 0, longest = 0;
     auto per_task = [](int32_t tiles, int cut) {
         const int32_t k = (tiles + kTaskTiles[cut] - 1) / kTaskTiles[cut];
         return k ? (tiles + k - 1) / k : 1;
     };
     auto wide_and_long = [](const Run &r) { return r.len > kLongChunk && r.tiles > kTaskTiles[kCuts - 1]; };
     for (const Run &r : runs) {
-        if (r.c1 > r.c0 && P->chunk_seg_ptr[r.c1] - P->chunk_seg_ptr[r.c0] > 1)
+        const int32_t pieces = P->chunk_seg_ptr[r.c1] - P->chunk_seg_ptr[r.c0];
+        if (pieces > 1)
             S.table_len = std::max(S.table_len, (r.len + 31) / 32 * 32);
         for (int i = 0; i < kCuts; ++i) {
             const int32_t per = per_task(r.tiles, i), n = (r.tiles + per - 1) / per;
             (wide_and_long(r) ? n_long : n_short)[i] += n;
         }
-        tokens += r.len;
-        if (wide_and_long(r)) longest = std::max<int64_t>(longest, r.len);
+        const int32_t per = per_task(r.tiles, 0);
+        const int64_t cost = (int64_t)r.len * (2 + per);
+        work += cost * ((r.tiles + per - 1) / per);
+        if (wide_and_long(r)) longest = std::max(longest, pieces > 1 ? cost * 4 / 3 : cost);
     }
     int cut_long = 0, cut_short = 0;
-    // a launch of one round becomes two only where the wide tasks are far longer than what would follow them
-    const bool one_round = (n_long[0] + n_short[0]) * Hkv <= kResidentGroups;
-    const bool far_longer = longest * (int64_t)runs.size() >= 2 * tokens;
+    // A second round of workgroups is worth it only where the launch waits for its longest task: where that task costs
+    // kLongestShare times the work that each place on the chip has to do.
+    const bool waits = (double)longest * kResidentGroups >= (double)kLongestShare * (double)work * Hkv;
     for (int i = 1; i < kCuts; ++i)
         if (n_long[i] * Hkv <= kLongGroups && kTaskTiles[i] != 3 &&
-            (!one_round || far_longer || (n_long[i] + n_short[0]) * Hkv <= kResidentGroups))
+            (waits || (n_long[i] + n_short[0]) * Hkv <= kResidentGroups))
             cut_long = i;
     for (int i = 1; i < kCuts; ++i)
         if ((n_long[cut_long] + n_short[i]) * Hkv <= kResidentGroups) cut_short = i;

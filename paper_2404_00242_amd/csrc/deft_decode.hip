@@ -1665,7 +1665,7 @@ int run_stage2(const deft_plan_t *plan, const Call &call, const deft::TaskSet &T
 // an asynchronous copy, so deft_plan_upload neither waits for the stream nor depends on the plan staying
 // alive.  A slot is reused only after the event recorded behind its last copy has completed.
 constexpr int kStageSlots = 8;
-constexpr size_t kStageSlotBytes = 256 * 1024;
+constexpr size_t kStageSlotBytes = DEFT_STAGED_IMAGE_BYTES;
 struct Staging {
     std::mutex mu;
     uint8_t *base = nullptr;

@@ -719,8 +719,10 @@ struct Run {
 
 static int32_t row_tiles(int32_t width, int32_t G) { return (int32_t)(((int64_t)width * G + 15) / 16); }
 
-// Tasks and stage-2 records of a list of runs, appended to the image.
-static void build_tasks(const deft_plan_t *P, int32_t G, int32_t Hkv, std::vector<Run> runs, Schedule &S, TaskSet &T) {
+// Tasks and stage-2 records of a list of runs, appended to the image.  ptr, slots: the slots of each query's partial
+// results, in the order of the runs.
+static void build_tasks(const deft_plan_t *P, int32_t G, int32_t Hkv, std::vector<Run> runs, const std::vector<int32_t> &ptr,
+                        const std::vector<int32_t> &slots, Schedule &S, TaskSet &T) {
     constexpr int kCuts = (int)(sizeof(kTaskTiles) / sizeof(kTaskTiles[0]));
     int64_t n_short[kCuts] = {}, n_long[kCuts] = {}, work = 0, longest = 0;
     auto per_task = [](int32_t tiles, int cut) {
@@ -759,34 +761,27 @@ static void build_tasks(const deft_plan_t *P, int32_t G, int32_t Hkv, std::vecto
         S.host_image.resize(align16(at + bytes), 0);
         return at;
     };
-    // ---- per query: its partial results, in the order of the runs ----
+    // ---- per query: its partial results ----
     const int32_t nq = P->nq;
-    std::vector<int32_t> ptr(nq + 1, 0);
-    for (const Run &r : runs)
-        for (int32_t p = r.lo; p < r.hi; ++p) ++ptr[p + 1];
     T.max_parts = 0;
-    for (int32_t p = 0; p < nq; ++p) {
-        T.max_parts = std::max(T.max_parts, ptr[p + 1]);
-        ptr[p + 1] += ptr[p];
-    }
+    for (int32_t p = 0; p < nq; ++p) T.max_parts = std::max(T.max_parts, ptr[p + 1] - ptr[p]);
     T.head_ints = kQueryHeadInts;
-    while (T.head_ints < kQueryHeadMost && T.head_ints - kQueryHeadFixed < T.max_parts) T.head_ints *= 2;
-    T.off_q_part_slot = place((size_t)ptr[nq] * sizeof(int32_t), 16);
+    while (T.head_ints < kQueryHeadMost && T.head_ints - kQueryHeadFixed < T.max_parts &&
+           (size_t)nq * 2 * T.head_ints * sizeof(int32_t) <= kQueryHeadBytes)
+        T.head_ints *= 2;
+    if (T.max_parts > T.head_ints - kQueryHeadFixed) {  // records too short for some query: the lists go along whole
+        T.off_q_part_slot = place(slots.size() * sizeof(int32_t), 16);
+        std::memcpy(S.host_image.data() + T.off_q_part_slot, slots.data(), slots.size() * sizeof(int32_t));
+    }
     T.off_q_head = place((size_t)nq * T.head_ints * sizeof(int32_t), 64);
     T.off_items = place(n_tasks * kItemInts * sizeof(int32_t), 64);
-    int32_t *slots = reinterpret_cast<int32_t *>(S.host_image.data() + T.off_q_part_slot);
     int32_t *head = reinterpret_cast<int32_t *>(S.host_image.data() + T.off_q_head);
-    {
-        std::vector<int32_t> cursor(ptr.begin(), ptr.end() - 1);
-        for (const Run &r : runs)
-            for (int32_t p = r.lo; p < r.hi; ++p) slots[cursor[p]++] = r.slot_base + (p - r.lo);
-        for (int32_t p = 0; p < nq; ++p, head += T.head_ints) {
-            const int32_t n = ptr[p + 1] - ptr[p];
-            head[0] = n;
-            head[1] = P->q_order[p];
-            head[2] = ptr[p];
-            std::copy_n(slots + ptr[p], std::min(n, T.head_ints - kQueryHeadFixed), head + kQueryHeadFixed);
-        }
+    for (int32_t p = 0; p < nq; ++p, head += T.head_ints) {
+        const int32_t n = ptr[p + 1] - ptr[p];
+        head[0] = n;
+        head[1] = P->q_order[p];
+        head[2] = ptr[p];
+        std::copy_n(slots.data() + ptr[p], std::min(n, T.head_ints - kQueryHeadFixed), head + kQueryHeadFixed);
     }
 
     // ---- tasks ----
@@ -833,14 +828,14 @@ static void build_schedule(const deft_plan_t *P, int32_t G, int32_t Hkv, Schedul
     const int32_t m = P->n_chunks(), nseg = P->n_segs();
     std::vector<int32_t> seg_off(nseg);  // flattened position of a segment's first token
     for (int32_t s = 0, at = 0; s < nseg; at += P->seg_len[s++]) seg_off[s] = at;
+    std::vector<int32_t> short_paths((size_t)P->nq + 1, 0);  // queries in front of a plan position that have a short path
+    for (int32_t p = 0; p < P->nq; ++p) short_paths[p + 1] = short_paths[p] + (P->q_path_len[p] < kPreciseBelowTokens);
     std::vector<Run> own((size_t)m), joined;
     for (int32_t c = 0; c < m; ++c) {
         const int32_t s0 = P->chunk_seg_ptr[c], s1 = P->chunk_seg_ptr[c + 1], lo = P->chunk_qlo[c], hi = P->chunk_qhi[c];
         const int32_t len = s1 > s0 ? seg_off[s1 - 1] + P->seg_len[s1 - 1] - seg_off[s0] : 0;
         // two-term softmax weights where some query of the group has a short path
-        int32_t precise = P->precise_all ? 1 : 0;
-        for (int32_t p = lo; p < hi && !precise; ++p)
-            if (P->q_path_len[p] < kPreciseBelowTokens) precise = 1;
+        const int32_t precise = P->precise_all || short_paths[hi] > short_paths[lo];
         own[c] = {c, c + 1, lo, hi, len, row_tiles(hi - lo, G), precise, P->chunk_slot_base[c], 0};
     }
 
@@ -876,22 +871,35 @@ static void build_schedule(const deft_plan_t *P, int32_t G, int32_t Hkv, Schedul
         if (!v.empty()) std::memcpy(S.host_image.data() + at, v.data(), v.size() * sizeof(int32_t));
         return at;
     };
-    // room for one task set without a cut, and for two where chunks are joined
-    const size_t sets = joined.size() == own.size() ? 1 : 2;
-    S.host_image.reserve(4 * (5 * (size_t)nseg + P->nq + sets * ((size_t)P->n_slots() + 2 * kQueryHeadInts * (size_t)P->nq +
-                                                               (size_t)(groups / Hkv) * kItemInts)) + 1024);
+    const bool same = joined.size() == own.size();
+    // room for the records and the lists whole, and for tasks as far as they are cut
+    S.host_image.reserve(4 * (5 * (size_t)nseg + P->nq + (same ? 1 : 2) * (P->q_part_slot.size() + kQueryHeadInts * (size_t)P->nq +
+                                                                          kItemInts * (size_t)(groups / Hkv + kResidentGroups))) +
+                         2 * kQueryHeadBytes + 1024);
     S.off_seg_tok_begin = put(P->seg_tok_begin);
     S.off_seg_len = put(P->seg_len);
     S.off_seg_qlo = put(P->seg_qlo);
     S.off_seg_qhi = put(P->seg_qhi);
     S.off_seg_off = put(seg_off);
     S.off_q_order = put(P->q_order);
-    const bool same = joined.size() == own.size();
-    build_tasks(P, G, Hkv, std::move(own), S, S.by_chunk);
+    std::vector<int32_t> ptr, slots;  // of the joined runs: of each query's slots in the plan, those of a run's first chunk
+    if (!same) {
+        std::vector<uint8_t> first((size_t)m, 0);
+        for (const Run &r : joined) first[r.c0] = 1;
+        ptr.reserve((size_t)P->nq + 1);
+        slots.reserve(P->q_part_slot.size());
+        for (int32_t p = 0; p < P->nq; ++p) {
+            ptr.push_back((int32_t)slots.size());
+            for (int32_t i = P->q_part_ptr[p]; i < P->q_part_ptr[p + 1]; ++i)
+                if (first[P->q_part_chunk[i]]) slots.push_back(P->q_part_slot[i]);
+        }
+        ptr.push_back((int32_t)slots.size());
+    }
+    build_tasks(P, G, Hkv, std::move(own), P->q_part_ptr, P->q_part_slot, S, S.by_chunk);
     if (same)
         S.fused = S.by_chunk;
     else
-        build_tasks(P, G, Hkv, std::move(joined), S, S.fused);
+        build_tasks(P, G, Hkv, std::move(joined), ptr, slots, S, S.fused);
     if (S.host_image.size() < 16) S.host_image.resize(16, 0);
     S.bytes = S.host_image.size();
 }

@@ -528,3 +528,31 @@ def test_uploads_are_only_enqueued_and_may_outrun_the_stream():
     for (t, Q, K, V, *_), o in zip(cases, outs):
         check(o.cpu().numpy().astype(np.float64), reference(t, Q, K, V), strict=False,
               abs_v=reference_abs_v(t, Q, K, V), two_term=all_paths_short(t))
+
+
+def test_an_image_past_256_kib_is_enqueued_and_not_waited_for():
+    """120 queries over 32768 tokens in chunks of 128: joined chunks make the image longer than 256 KiB"""
+    lens = [32768] + [200] * 120
+    t = wl._finish("star", lens, [-1] + [0] * 120, list(range(1, 121)), 8, 2, 128, 3)
+    Q, K, V = wl.make_qkv(t)
+    dev = torch.device("cuda:0")
+    q, k, v = Q.to(dev), K.to(dev), V.to(dev)
+    plan = binding.deft_plan(t.node_tok_begin, t.node_tok_len, t.node_parent, t.query_node, t.ntok, 64)
+    nbytes = plan.device_bytes(t.Hq, t.Hkv)
+    assert nbytes > 256 << 10
+    img = torch.empty(nbytes, dtype=torch.uint8, device=dev)
+    big, lib = torch.empty(1 << 30, dtype=torch.uint8, device=dev), binding.load_library()
+    small = wl.make_config(1)
+    binding.deft_plan(small.node_tok_begin, small.node_tok_len, small.node_parent, small.query_node, small.ntok).image(
+        small.Hq, small.Hkv, dev)  # (the first upload on a device allocates the ring)
+    torch.cuda.synchronize()
+    for _ in range(100):  # some 40 ms of work
+        big.add_(1)
+    done = torch.cuda.Event()
+    done.record()
+    assert lib.deft_plan_upload(plan.handle, t.Hq, t.Hkv, img.data_ptr(), nbytes, torch.cuda.current_stream().cuda_stream) == 0
+    assert not done.query()
+    torch.cuda.synchronize()
+    o = binding.deft_tree_attn_decode(plan, q, k, v, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    check(o.cpu().numpy().astype(np.float64), reference(t, Q, K, V), strict=False)

@@ -239,3 +239,37 @@ def test_corrupted_trees_are_accepted_or_refused_exactly_as_by_the_oracle():
             for key in ("seg_tok_begin", "seg_len", "seg_qlo", "seg_qhi", "chunk_qlo", "chunk_qhi", "q_part_slot", "q_order"):
                 assert np.array_equal(got[key], want[key]), (it, key)
     assert refused > 100 and accepted > 50
+
+
+def uncut_image_bytes(plan, G):
+    """size of an image with the segment table, one list and one 32-int record per query and one task per eight row
+    tiles: what the kernels need at the least, and what may not grow so far that an upload has to wait"""
+    v = plan.view()
+    pad = lambda n: -(-4 * n // 16) * 16
+    tiles = -(-(v["chunk_qhi"] - v["chunk_qlo"]) * G // 16)
+    lists = 5 * pad(v["n_segs"]) + pad(v["nq"]) + pad(v["nq"] + 1) + pad(v["n_slots"])
+    return -(-lists // 64) * 64 + 128 * v["nq"] + 64 * int((-(-tiles // 8)).sum())
+
+
+@pytest.mark.parametrize("mode", ["flatten", "balanced", "node_chunk"])
+@pytest.mark.parametrize("Hkv", [1, 8, 32])
+def test_images_of_large_plans_fit_a_staging_slot(repo_root, Hkv, mode):
+    """Plans whose tables alone are up to 256 KiB, the size that has always been uploaded without waiting: joined chunks,
+    records and finer cuts may add to them, but not past a slot of the staging ring."""
+    import re
+
+    header = open(os.path.join(repo_root, "include", "deft.h")).read()
+    limit = int(re.search(r"DEFT_STAGED_IMAGE_BYTES \((\d+)u << 10\)", header).group(1)) << 10
+    G, large = 4, 0
+    for root, branches, each, chunk in [(32768, 120, 512, 128), (16000, 160, 64, 128), (32768, 255, 300, 256), (12000, 250, 40, 128),
+                                        (20000, 1000, 1, 512), (500, 1500, 1, 128), (60000, 60, 1, 128), (30000, 3, 9000, 32)]:
+        lens = np.asarray([root] + [each] * branches, dtype=np.int32)
+        begin = np.concatenate([[0], np.cumsum(lens)[:-1]]).astype(np.int32)
+        parent = np.asarray([-1] + [0] * branches, dtype=np.int32)
+        flags = binding.SPLIT_MODES[mode] | (binding.rows_per_query(G) if mode == "balanced" else 0)
+        plan = binding.deft_plan(begin, lens, parent, np.arange(1, len(lens)), int(lens.sum()), chunk, flags)
+        least = uncut_image_bytes(plan, G)
+        if least <= 256 << 10:
+            assert plan.device_bytes(G * Hkv, Hkv) <= limit, (root, branches, each, chunk, least)
+            large += least > 100 << 10
+    assert large >= 2

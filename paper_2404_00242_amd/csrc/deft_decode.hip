@@ -19,7 +19,7 @@
 // block each fetch a share of it and pass the operand registers to the others through LDS.  The waves' partial results are merged in LDS before
 // one (m, l, acc) triple per (chunk, row) is written.
 //
-// Stage 2 (deft_stage2_few, deft_stage2_many): one wave, or four, per (query, query head) merge that query's partial
+// Stage 2 (deft_stage2_few, deft_stage2_many): one, two or four waves per (query, query head) merge that query's partial
 // results with the log-sum-exp weights of eq. 1.
 #include <hip/hip_runtime.h>
 
@@ -1411,8 +1411,8 @@ __global__ __launch_bounds__(64) void deft_stage2_few(Stage2Args a) {
     if (sub == 0) store_out(a, ((size_t)q_user * a.Hq + qh) * D + 4 * col, acc * (lsum > 0.f ? 1.f / lsum : 0.f));
 }
 
-// Any number of partials: WAVES waves per (query, query head), partial WAVES * i + w with wave w.  Each wave merges what it
-// holds as above (64 of its partials at a time, on a running maximum), then their results are merged in LDS.
+// Any number of partials: one, two or four waves per (query, query head), partial WAVES * i + w with wave w.  Each wave
+// merges what it holds as above (64 of its partials at a time, on a running maximum), then their results are merged in LDS.
 template <int D, int WAVES, bool HOLES>
 __global__ __launch_bounds__(64 * WAVES) void deft_stage2_many(Stage2Args a) {
     using R = Stage2Row<D>;
@@ -1431,6 +1431,8 @@ __global__ __launch_bounds__(64 * WAVES) void deft_stage2_many(Stage2Args a) {
         const int cnt = min(64, mine - base);
         if (n > a.head_ints - deft::kQueryHeadFixed)
             slot = a.q_part_slot[s0 + WAVES * (base + min(lane, cnt - 1)) + wave];
+        else if (WAVES == 1 && base > 0)  // (two waves or four find all of theirs in the first 64)
+            slot = rec[deft::kQueryHeadFixed + base + min(lane, cnt - 1)];
         slot = __shfl(slot, min(lane, cnt - 1));  // lanes past the end hold a slot that exists
         const size_t ro = (size_t)slot * a.Hq + qh;
         const float mj = lane < cnt ? a.part_m[ro] : -INFINITY;
@@ -1561,11 +1563,17 @@ bool launch_stage2(const deft::TaskSet &T, const Stage2Args &a2, hipStream_t str
     const unsigned rows = (unsigned)a2.nq * (unsigned)a2.Hq;
     constexpr int kFew = std::min(Stage2Row<D>::kBatch, deft::kQueryHeadInts - deft::kQueryHeadFixed);
     // Up to kFew partials one wave has them all in flight at once, and more waves cost more to start than they save (16
-    // partials, 2048 rows of output: 5.1 us, four waves 7.5).  Beyond that a second batch is a round trip more: 17
-    // partials 5.6 us with one wave, 4.4 with four, 4.0 with two; 64 partials 7.2 us with one, 3.4 with four.
+    // partials, 2048 rows of output: 5.1 us, four waves 7.5).  Beyond that a second batch is a round trip more, which a
+    // few rows have the chip to take apart and many do not: the waves of rows with few partials are in the way.  Whole
+    // call, us, with one, two and four waves: 32 rows of 64 partials 13.8, 13.0, 12.6; 128 rows, one query in four of 128,
+    // 25.4, 24.6, 24.2; 960 of 65 43.9, 43.4, 43.6; 2048 of 32 33.8, 33.5, 35.0; 2048, one query in 64 of 128, 38.9, 38.2,
+    // 40.1; 8192, one in 256 of 128, 55.5, 59.1, 65.0.  (One wave to a row beyond 2048 of
+    // them also keeps launches of up to 2^26 rows within the 32 bits of grid x block.)
     if (T.max_parts <= kFew)
         hipLaunchKernelGGL((deft_stage2_few<D, HOLES>), dim3(rows), dim3(64), 0, stream, a2);
-    else if (T.max_parts <= 2 * 16)
+    else if (rows > 2048)
+        hipLaunchKernelGGL((deft_stage2_many<D, 1, HOLES>), dim3(rows), dim3(64), 0, stream, a2);
+    else if (rows > 1024 || T.max_parts <= 2 * 16)
         hipLaunchKernelGGL((deft_stage2_many<D, 2, HOLES>), dim3(rows), dim3(128), 0, stream, a2);
     else
         hipLaunchKernelGGL((deft_stage2_many<D, 4, HOLES>), dim3(rows), dim3(256), 0, stream, a2);

@@ -167,3 +167,33 @@ def test_infinities_of_a_sibling_stay_where_they_are(mode, chunk, Hq, Hkv, d):
         assert np.isfinite(got[others]).all()
         V[at, :, 7] = V[at + 1, :, 9] = 0
         check(got[others], reference(t, Q, K, V)[others], strict=False)
+
+
+# stage 2 with one wave to a row (more than 2048 rows), with two and with four, slot ids in the record up to its last one
+# and past it, in more than one batch of 64; every 40th query has `parts` partial results, the others one
+@pytest.mark.parametrize("nq,Hq,Hkv,d", [(40, 24, 8, 128), (40, 48, 8, 64), (80, 40, 8, 128)])
+@pytest.mark.parametrize("parts", [29, 30, 61, 65, 125, 126, 130])
+def test_stage2_waves_by_rows(parts, nq, Hq, Hkv, d):
+    lens = [32 * parts - 5 if i % 40 == 7 else 20 + i % 3 for i in range(nq)]
+    t = wl._finish("waves", lens, [-1] * nq, list(range(nq)), Hq, Hkv, d, parts)
+    Q, K, V = wl.make_qkv(t)
+    got, plan = run_gpu(t, Q, K, V, chunk_size=32, out_dtype=torch.float32, mode="node_chunk")
+    assert int(np.diff(plan.view()["q_part_ptr"]).max()) == parts
+    check(got, reference(t, Q, K, V), strict=False)
+
+
+# more rows than 256 threads each would leave within 32 bits of grid x block (2^24): 17 queries x 2^20 heads
+def test_more_than_2_to_the_24_rows():
+    lens, Hq, d, dev = [33 * 32] + [20] * 16, 1 << 20, 64, torch.device("cuda:0")
+    begin = np.concatenate([[0], np.cumsum(lens)[:-1]]).astype(np.int32)
+    plan = binding.deft_plan(begin, lens, [-1] * 17, list(range(17)), sum(lens), 32, binding.SPLIT_MODES["node_chunk"])
+    g = torch.Generator(device=dev).manual_seed(24)
+    q = torch.empty((17, Hq, d), dtype=torch.bfloat16, device=dev).normal_(generator=g)
+    k, v = (torch.empty((sum(lens), 1, d), dtype=torch.bfloat16, device=dev).normal_(generator=g) for _ in range(2))
+    o = binding.deft_tree_attn_decode(plan, q, k, v, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    heads = torch.tensor([0, 1, 127, 128, 65537, Hq - 1], device=dev)
+    for j, n in enumerate(lens):
+        kj, vj = (x[int(begin[j]): int(begin[j]) + n, 0].double() for x in (k, v))
+        want = torch.softmax(q[j, heads].double() @ kj.T.contiguous() / d ** 0.5, dim=-1) @ vj
+        check(o[j, heads].cpu().numpy().astype(np.float64), want.cpu().numpy(), strict=False)

@@ -76,8 +76,8 @@ struct TaskSet {
     int32_t max_parts = 0;               // partials of the query that has most
 };
 
-// Launch schedule + image layout for one Hq/Hkv ratio.  The row cut suits the number of KV heads it was first asked
-// for with; the schedule is right for any.
+// Launch schedule + image layout for one Hq/Hkv ratio.  The row cut and the joining of chunks suit the number of KV heads
+// that an image was first uploaded for; the schedule is right for any.
 struct Schedule {
     int32_t group = 0;        // G = Hq / Hkv, rows per query within one KV head
     size_t bytes = 0;         // total image size
@@ -124,6 +124,8 @@ struct deft_plan_s {
 };
 
 namespace deft {
+// Size of an image for G = Hq/Hkv that holds the schedule for any number of KV heads.
+size_t image_bytes(const deft_plan_t *plan, int32_t group);
 // Builds (or returns the cached) schedule for G = Hq/Hkv.  Thread-safe.
 const Schedule *get_schedule(const deft_plan_t *plan, int32_t group, int32_t Hkv);
 const Schedule *find_schedule(const deft_plan_t *plan, int32_t group);

@@ -822,6 +822,9 @@ static void build_tasks(const deft_plan_t *P, int32_t G, int32_t Hkv, std::vecto
     }
 }
 
+// The strategies that the header calls comparisons are run as they are named, chunk by chunk.
+static bool may_join(const deft_plan_t *P) { return P->mode == DEFT_SPLIT_FLATTEN || P->mode == DEFT_SPLIT_BALANCED; }
+
 static void build_schedule(const deft_plan_t *P, int32_t G, int32_t Hkv, Schedule &S) {
     S.group = G;
     S.table_len = 32;
@@ -846,11 +849,10 @@ static void build_schedule(const deft_plan_t *P, int32_t G, int32_t Hkv, Schedul
     // of 128 36.6 -> 29.1; 16000 tokens under 32 branches, 4 heads a KV head, 93.4 -> 70.0; few-shot, 20 branches of 256 x
     // 32 heads 41.5 -> 38.5; but 512 workgroups, partials 0.03 of the KV bytes, 11.5 -> 12.2.
     // Only chunks with the same queries join, and only in the two flattened splits: a masked token still enters a query's
-    // sum with weight 0, and 0 * Inf is NaN, so no query may share a run with tokens that were in none of its chunks.  The
-    // strategies that the header calls comparisons are run as they are named, chunk by chunk.
+    // sum with weight 0, and 0 * Inf is NaN, so no query may share a run with tokens that were in none of its chunks.
     int64_t groups = 0;
     for (const Run &r : own) groups += (int64_t)((r.tiles + kMaxTilesPerTask - 1) / kMaxTilesPerTask) * Hkv;
-    const bool join = (P->mode == DEFT_SPLIT_FLATTEN || P->mode == DEFT_SPLIT_BALANCED) &&
+    const bool join = may_join(P) &&
                       (groups > kResidentGroups ||
                        (groups > kResidentGroups / 2 && 10 * (int64_t)P->n_slots() * G >= 3 * (int64_t)P->n_flat));
     for (const Run &r : own) {
@@ -904,6 +906,18 @@ static void build_schedule(const deft_plan_t *P, int32_t G, int32_t Hkv, Schedul
     S.bytes = S.host_image.size();
 }
 
+size_t image_bytes(const deft_plan_t *P, int32_t G) {
+    size_t tasks = kResidentGroups;  // a cut may add as many to those of eight row tiles, in either set
+    for (int32_t c = 0; c < P->n_chunks(); ++c) {
+        const int32_t tiles = row_tiles(P->chunk_qhi[c] - P->chunk_qlo[c], G);
+        tasks += (size_t)((tiles + kMaxTilesPerTask - 1) / kMaxTilesPerTask);
+    }
+    const size_t nq = (size_t)P->nq, record = sizeof(int32_t) * nq;
+    const size_t set = align16(P->q_part_slot.size() * sizeof(int32_t)) + tasks * kItemInts * sizeof(int32_t) + 2 * 64 +
+                       std::max(record * kQueryHeadInts, std::min(record * kQueryHeadMost, kQueryHeadBytes));
+    return 5 * align16((size_t)P->n_segs() * sizeof(int32_t)) + align16(record) + (may_join(P) ? 2 : 1) * set;
+}
+
 const Schedule *get_schedule(const deft_plan_t *plan, int32_t group, int32_t Hkv) {
     std::lock_guard<std::mutex> lock(plan->mu);
     auto it = plan->schedules.find(group);
@@ -926,7 +940,7 @@ const Schedule *find_schedule(const deft_plan_t *plan, int32_t group) {
 extern "C" size_t deft_plan_device_bytes(const deft_plan_t *plan, int32_t Hq, int32_t Hkv) {
     if (!plan || Hq <= 0 || Hkv <= 0 || Hq % Hkv != 0) return 0;
     try {
-        return deft::get_schedule(plan, Hq / Hkv, Hkv)->bytes;
+        return deft::image_bytes(plan, Hq / Hkv);
     } catch (...) {
         return 0;
     }

@@ -273,3 +273,17 @@ def test_images_of_large_plans_fit_a_staging_slot(repo_root, Hkv, mode):
             assert plan.device_bytes(G * Hkv, Hkv) <= limit, (root, branches, each, chunk, least)
             large += least > 100 << 10
     assert large >= 2
+
+
+def test_a_size_query_decides_nothing():
+    """the size an image needs is one for all head counts of a ratio, whoever asks first, and no call may follow it"""
+    lens = np.asarray([4000] + [256] * 20, dtype=np.int32)
+    begin = np.concatenate([[0], np.cumsum(lens)[:-1]]).astype(np.int32)
+    parent = np.asarray([-1] + [0] * 20, dtype=np.int32)
+    make = lambda: binding.deft_plan(begin, lens, parent, np.arange(1, 21), int(lens.sum()), 128)
+    plan, lib = make(), binding.load_library()
+    sizes = [plan.device_bytes(4 * Hkv, Hkv) for Hkv in (1, 8, 2, 64)]
+    assert sizes == [make().device_bytes(32, 8)] * 4
+    a16 = np.zeros(64, dtype=np.uint8)
+    p = (a16.ctypes.data + 15) & ~15
+    assert lib.deft_tree_attn_decode(plan.handle, p, p, p, p, p, 32, 8, 128, 0.0, 0, p, 1 << 40, None) == -5  # no image yet

@@ -197,3 +197,18 @@ def test_more_than_2_to_the_24_rows():
         kj, vj = (x[int(begin[j]): int(begin[j]) + n, 0].double() for x in (k, v))
         want = torch.softmax(q[j, heads].double() @ kj.T.contiguous() / d ** 0.5, dim=-1) @ vj
         check(o[j, heads].cpu().numpy().astype(np.float64), want.cpu().numpy(), strict=False)
+
+
+# the cut of rows is the one for the head count of the upload, also if a size was asked for with another
+def test_cut_does_not_depend_on_an_earlier_size_query():
+    t = tree(4000, [256] * 20, 32, 8, 128, seed=1)
+    Q, K, V = wl.make_qkv(t)
+    q, k, v = (x.to("cuda:0") for x in (Q, K, V))
+    outs = []
+    for ask in (False, True):
+        plan = binding.deft_plan(t.node_tok_begin, t.node_tok_len, t.node_parent, t.query_node, t.ntok, 128)
+        if ask:
+            plan.device_bytes(4, 1)
+        outs.append(binding.deft_tree_attn_decode(plan, q, k, v, out_dtype=torch.float32))
+    torch.cuda.synchronize()
+    assert torch.equal(*outs)  # another cut rounds the weights elsewhere

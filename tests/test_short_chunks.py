@@ -1,6 +1,7 @@
-"""Chunks that stage 1 holds in registers (at most 256 tokens at d = 128, 512 at d = 64), and the cut of a task's rows
-over several workgroups, and stage 2 by the number of partial results, at the sizes where they can go wrong.  Same tolerance as tests/test_gpu_parity.py, whose
-paths of fewer than 1024 tokens also get the tight bound of two-term weights."""
+"""Chunks that stage 1 holds in registers (at most 256 tokens at d = 128, 512 at d = 64), chunks that a whole call works on as
+one, the cut of a task's rows over several workgroups, and stage 2 by the number of partial results and of rows, at the
+sizes where they can go wrong.  Same tolerance as tests/test_gpu_parity.py, whose paths of fewer than 1024 tokens also get
+the tight bound of two-term weights."""
 
 import numpy as np
 import pytest
@@ -68,8 +69,8 @@ def test_any_number_of_partial_results(parts, d):
         check(got, reference(t, Q, K, V), strict=False)
 
 
-# chunks that a whole call works on as one: prefixes, several branches, wide next to narrow, short next to long paths;
-# the stages called apart keep the plan's slots, and both ways give the same result
+# plans of many short chunks: prefixes, several branches, wide next to narrow, short next to long paths; a whole call (which
+# may work on several chunks as one, see test_stage2_after_a_whole_call) and the stages called apart give the same result
 @pytest.mark.parametrize("mode,chunk", [("flatten", 128), ("flatten", 96), ("node_chunk", 64), ("balanced", 128), ("query", 160)])
 @pytest.mark.parametrize("Hq,Hkv,d,root", [(32, 32, 128, 900), (24, 24, 64, 1500), (96, 24, 128, 2100)])
 def test_joined_chunks(mode, chunk, Hq, Hkv, d, root):
@@ -212,3 +213,37 @@ def test_cut_does_not_depend_on_an_earlier_size_query():
         outs.append(binding.deft_tree_attn_decode(plan, q, k, v, out_dtype=torch.float32))
     torch.cuda.synchronize()
     assert torch.equal(*outs)  # another cut rounds the weights elsewhere
+
+
+# joined chunks over scattered pages (of one token: a piece per token; of seven: pieces that end inside a block), through the
+# call with a static workspace, and captured, with eager calls between the replays
+@pytest.mark.parametrize("page_size", [1, 7, 16])
+def test_joined_chunks_over_pages_static_and_captured(page_size):
+    t = tree(2400, [(37 * i) % 150 for i in range(14)], 64, 16, 128, seed=page_size)
+    Q, K, V = wl.make_qkv(t)
+    pp, pg, npool, row_of = wl.to_paged(t, page_size, seed=3)
+    q, k, v = Q.to("cuda:0"), *(wl.scatter_to_pool(x, row_of, npool * page_size, i).to("cuda:0") for i, x in ((1, K), (2, V)))
+    plan = binding.deft_plan_paged(pp, pg, page_size, npool, t.node_tok_len, t.node_parent, t.query_node, 64)
+    ref, ws = reference(t, Q, K, V), plan.workspace(t.Hq, t.Hkv, t.d, q.device)
+    ws.fill_(0xFF)
+    want = binding.deft_tree_attn_decode(plan, q, k, v, out_dtype=torch.float32, workspace=ws)
+    torch.cuda.synchronize()
+    assert empty_slots(plan, ws, t.Hq, t.d) > 0
+    check(want.cpu().numpy().astype(np.float64), ref, strict=False)
+    check(stages(plan, q, k, v, ws, one=False).cpu().numpy().astype(np.float64), ref, strict=False)
+    o, lib = torch.empty_like(want), binding.load_library()
+    assert lib.deft_tree_attn_decode_static(plan.handle, plan.image(t.Hq, t.Hkv, q.device).data_ptr(), q.data_ptr(),
+                                            k.data_ptr(), v.data_ptr(), o.data_ptr(), t.Hq, t.Hkv, t.d, 0.0, 1,
+                                            torch.cuda.current_stream().cuda_stream) == 0
+    assert torch.equal(o, want)
+    graph, got = torch.cuda.CUDAGraph(), torch.empty_like(want)
+    with torch.cuda.graph(graph):
+        binding.deft_tree_attn_decode(plan, q, k, v, out=got, workspace=ws)
+    for scale in (1.0, 0.5, 2.0):
+        q.copy_(Q * scale)
+        got.zero_()
+        ws.fill_(0xFF)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(got, binding.deft_tree_attn_decode(plan, q, k, v, out_dtype=torch.float32))

@@ -1,7 +1,8 @@
 // Device side of libdeft: the Attention Calculation Phase of DeFT-Flatten (Algorithm 4) for gfx950.
 //
 // Stage 1 (deft_stage1): one workgroup of four waves per task = (chunk or run of short chunks, KV head, up to eight
-// 16-row tiles).  Short chunks are held in registers whole (resident_task), the others stream (streaming_task).  The rows of a tile are (query of the chunk's group) x (query head reading this KV head).
+// 16-row tiles).  Short chunks are held in registers whole (resident_task), the others stream (streaming_task).  The
+// rows of a tile are (query of the chunk's group) x (query head reading this KV head).
 // A wave streams 32 tokens at a time straight from HBM into MFMA operand registers:
 //
 //   S^T[token, row] = K[token, :] . Q[row, :]      v_mfma_f32_16x16x32_bf16, A = K tile (a lane holds
@@ -16,8 +17,8 @@
 // byte of every 64-byte sector requested is used.  A narrow group (one row tile) splits the chunk's
 // tokens over the four waves, each keeping a block of loads in flight in registers.  A wider group
 // gives each wave its own row tile (two tiles for tasks of more than four); the waves that need the same
-// block each fetch a share of it and pass the operand registers to the others through LDS.  The waves' partial results are merged in LDS before
-// one (m, l, acc) triple per (chunk, row) is written.
+// block each fetch a share of it and pass the operand registers to the others through LDS.  The waves' partial results
+// are merged in LDS before one (m, l, acc) triple per (chunk, row) is written.
 //
 // Stage 2 (deft_stage2_few, deft_stage2_many): one, two or four waves per (query, query head) merge that query's partial
 // results with the log-sum-exp weights of eq. 1.
@@ -78,10 +79,13 @@ __device__ __forceinline__ uint32_t divide(uint32_t n, uint32_t d, uint32_t inv)
 }
 
 __device__ __forceinline__ u32x4 load16(const uint16_t *p) { return *reinterpret_cast<const u32x4 *>(p); }
-// K/V rows of a chunk whose group fits one task (one or two row tiles): no other workgroup will read them,
-// so they are streamed without being kept in the caches (non-temporal); measured 2 % faster on the few-shot
-// trees.  Chunks of wider groups are re-read by the other row groups and by the waves of the K pattern, and
-// lose with it.
+// K/V rows of streaming tasks of one or two row tiles are loaded without being kept in the caches (non-temporal): as a
+// rule such a task is its chunk's whole group and no other workgroup will read them; measured 2 % faster on the few-shot
+// trees, 5 % where two tiles are all of a group over a long prefix (28644 tokens under 6 queries x 4 heads 33.1 -> 31.2 us
+// per call).  Wide groups that the schedule cuts down to two tiles do re-read their rows and would be faster with cached
+// loads (478-token root under 256 queries 29.2 -> 24.8 us, 3859 tokens under 44 queries x 6 heads 22.8 -> 22.4), but a
+// kernel that holds both kinds of loads pays for it in its wide loops (12345 tokens under 26 queries x 4 heads 28.9 ->
+// 29.9, 256-query reasoning tree 119.7 -> 122.5).  Wider tasks and resident ones load through the caches.
 __device__ __forceinline__ u32x4 load16_once(const uint16_t *p) {
     return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
 }
@@ -701,7 +705,10 @@ struct WidePipe {
 // costs one barrier per 16 rows instead of one per 32 tokens, and no K or V byte goes through LDS.
 // Bound by latency: the chain descriptor -> rows and pieces -> K/V and Q -> tiles, each link taken once per task.
 // Stage 1, before -> after: 64 x 128 tokens x 8 heads, one tile (33.6 MB) 11.5 -> 8.1 us; 288 tasks of 256 tokens over
-// 16-token pages (37 MB) 19.9 -> 12.2 us, together with the finer cut of rows in launch_stage1_variant.
+// 16-token pages (37 MB) 19.9 -> 12.2 us, together with the finer cut of rows in the schedule.  The K/V loads go through
+// the caches: non-temporal ones are 10 % faster where the rows come from HBM (6750 tokens of one sequence 12.8 -> 11.4 us
+// per call) and 10 to 16 % slower where the memory-side cache still has them (1349 tokens under 4 queries x 4 heads 9.0 ->
+// 10.2), as it has for models of few layers and trees of a few MB.
 template <int D>
 constexpr int kResidentBlocks = 256 / D;  // blocks per wave: 128 registers of K and V
 template <int D>
@@ -1512,8 +1519,8 @@ bool hip_ok(hipError_t e, const char *what) {
     return false;
 }
 
-// The kernels may use more than the default 64 KB of dynamic LDS: the limit of both variants is raised once
-// per device, at the first call that launches either of them.
+// The kernels may use more than the default 64 KB of dynamic LDS: the limit of all variants is raised once
+// per device, at the first call that launches one of them.
 template <int D>
 bool configure_stage1() {
     static std::atomic<uint64_t> configured;  // bit i set: done on device i (one flag per head dimension)

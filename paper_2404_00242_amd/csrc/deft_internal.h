@@ -19,8 +19,9 @@ constexpr int kMaxTilesPerTask = 8;
 // Stage 2 reads one record per plan query: {number of partials n, caller's query index, where its list starts in
 // q_part_slot, the first slot ids}.  A record has kQueryHeadInts int32, or up to kQueryHeadMost where that holds the
 // longest list of the plan and the records stay within kQueryHeadBytes: a slot id in the record saves a round trip (one
-// query of 77 partials, whole call 12.2 us with the list, 11.7 with the record), but every query's record has the length of the longest, and the image is
-// sent for every new plan.  Queries with more partials than fit go on to the list, which is left out where none has.
+// query of 77 partials, whole call 12.2 us with the list, 11.7 with the record), but every query's record has the length
+// of the longest, and the image is sent for every new plan.  Queries with more partials than fit go on to the list, which
+// is left out where none has.
 constexpr int kQueryHeadInts = 32;
 constexpr int kQueryHeadMost = 128;
 constexpr int kQueryHeadFixed = 3;

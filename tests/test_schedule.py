@@ -1,0 +1,18 @@
+"""Launch schedules (which chunks a whole call works on as one, how rows are cut into tasks, stage 2's records) against the
+plans they are made from: a host-only program, see tests/sanitize/schedule_driver.cpp, under the sanitizers."""
+
+import os
+import shutil
+
+import pytest
+
+from .test_sanitizers import ROOT, SAN, run
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_schedules_of_random_plans(tmp_path):
+    exe = str(tmp_path / "schedule_driver")
+    csrc = os.path.join(ROOT, "paper_2404_00242_amd", "csrc")
+    run(["g++", "-std=c++17", *SAN, "-I", os.path.join(ROOT, "include"), "-I", csrc, os.path.join(csrc, "deft_plan.cpp"),
+         os.path.join(ROOT, "tests", "sanitize", "schedule_driver.cpp"), "-lpthread", "-o", exe])
+    assert "schedules checked" in run([exe])

@@ -242,7 +242,9 @@ size_t deft_plan_device_bytes(const deft_plan_t *plan, int32_t Hq, int32_t Hkv);
 int deft_plan_upload(deft_plan_t *plan, int32_t Hq, int32_t Hkv, void *dev_image, size_t bytes, void *stream);
 
 /* Bytes of device workspace deft_tree_attn_decode needs (fp32 partial attention, running
- * maxima and sums per (slot, query head)); 0 on bad arguments. */
+ * maxima and sums per (slot, query head), and 16 bytes more per (slot, query head) for calls that
+ * are made in one launch); 0 on bad arguments.  A buffer without the 16 bytes, of
+ * n_slots * Hq * (d + 2) floats and 32 bytes more, is accepted too; calls then take two launches. */
 size_t deft_workspace_bytes(const deft_plan_t *plan, int32_t Hq, int32_t Hkv, int32_t d);
 
 /*
@@ -267,7 +269,7 @@ size_t deft_workspace_bytes(const deft_plan_t *plan, int32_t Hq, int32_t Hkv, in
  *             aligned; contents are scratch.
  * stream    : hipStream_t (NULL = default stream).  Kernels are enqueued, not awaited.  After one
  *             ordinary call on the device (which sets a kernel attribute), a call made while the
- *             stream is being captured records just its two kernel launches in the graph.
+ *             stream is being captured records just its one or two kernel launches in the graph.
  * Errors: DEFT_EINVAL, DEFT_ENOTREADY, DEFT_EWORKSPACE, DEFT_EHIP (deft_last_hip_error
  * gives the runtime's text).  Nothing is launched when an error is returned, except that a
  * launch failure may leave earlier kernels of the same call enqueued.
@@ -303,7 +305,7 @@ int deft_stage2_global_reduction(const deft_plan_t *plan, const void *dev_image,
  * live in a fixed array of DEFT_STATIC_SCRATCH_BYTES bytes that is part of the library's device code, one
  * copy per GPU, kept until the process ends.  The call allocates nothing and frees nothing.  Arguments,
  * results and errors are those of deft_tree_attn_decode without the workspace pair; a plan whose
- * deft_workspace_bytes(plan, Hq, Hkv, d) exceeds DEFT_STATIC_SCRATCH_BYTES is refused with DEFT_EWORKSPACE
+ * partial results (n_slots * Hq * (d + 2) floats) exceed DEFT_STATIC_SCRATCH_BYTES is refused with DEFT_EWORKSPACE
  * and nothing is launched (use a larger chunk_size, or the call with a caller workspace).  All calls on one
  * GPU share that GPU's array: calls that may overlap on one GPU (different streams, no ordering) race and
  * must be ordered by the caller; the array keeps the last call's partial results and needs no clearing,

@@ -31,6 +31,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
+#include <random>
 #include <string>
 #include <type_traits>
 
@@ -59,6 +60,13 @@ struct Stage1Args {
     int32_t resident_one, resident_many;  // most row tiles of a task on the resident path, see kResidentTiles
     int32_t table_len;  // entries of the LDS per-token table: longest multi-piece chunk, in whole blocks
     float c;  // scale * log2(e): probabilities are 2^((s - m) * c)
+    // A whole call in one launch: a record of 16 bytes per row of partial results, {m, l, mark}, and what this call writes
+    // into the marks (publish_rows).  The records of a KV head lie together, in the order of slots and its query heads, so
+    // that no two workgroups write to one line at a time (in the order of slots and all heads: 10 % on a call of 4000 rows
+    // under 32 heads).
+    float *marks;
+    uint64_t ticket;
+    int32_t n_slots;
 };
 
 struct Stage2Args {
@@ -69,6 +77,14 @@ struct Stage2Args {
     int32_t head_ints;  // int32 per query record
     uint32_t inv_Hq;
     float c;
+};
+
+// A whole call in one launch: stage 1's workgroups first, then those of stage 2
+struct CallArgs {
+    Stage1Args s1;
+    Stage2Args s2;
+    uint32_t tasks;       // workgroups of stage 1
+    int32_t wide_reduce;  // 1: a workgroup of stage 2 takes one row of the output, 0: one in each wave
 };
 
 // floor(n / d) for any n and d > 0, given inverse(d); a division by a run-time number costs a workgroup 0.3 us otherwise
@@ -94,6 +110,21 @@ __device__ __forceinline__ u32x4 load16_kv(const uint16_t *p) {
     return ONCE ? load16_once(p) : load16(p);
 }
 
+// Partial results.  SHARED: in a call of one launch they are stored past the L2 of their XCD, and read past the reader's,
+// because the workgroup that reads them runs while others still write (publish_rows).  Elsewhere such stores only cost
+// time (17 MB of them 1.9 us of 22).
+typedef __attribute__((address_space(1))) u32x4 *global_u32x4;
+template <bool SHARED>
+__device__ __forceinline__ void store_partial(float *p, f32x4 x) {
+    if (SHARED)
+        __builtin_amdgcn_global_store_b128((global_u32x4)p, __builtin_bit_cast(u32x4, x), "agent");
+    else
+        *reinterpret_cast<f32x4 *>(p) = x;
+}
+__device__ __forceinline__ f32x4 load_shared4(const float *p) {
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_global_load_b128((global_u32x4)p, "agent"));
+}
+
 __device__ __forceinline__ float wave_row_max(float x) {
     // a row of a 16-row tile lives in lanes {n, n+16, n+32, n+48}
     // (a swap of rows of 16 lanes, then of halves, between two copies: no LDS round trip)
@@ -110,6 +141,21 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
     typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
     bf16x2 r = {(__bf16)lo, (__bf16)hi};
     return __builtin_bit_cast(uint32_t, r);
+}
+
+// In a whole call of one launch, stage 2 may not read a row of partial results before the row is complete.  The wave that
+// wrote it waits until its stores have arrived and then writes the call's ticket into the row's mark; stage 2's wave waits
+// for the ticket and takes it out again.  Every call has a ticket of its own, 64 bits, so a mark needs no value to start
+// from (whatever a workspace holds, it is not the ticket), and a captured call finds its marks cleared when it is replayed.
+__device__ __forceinline__ uint64_t *mark_of(float *record) { return reinterpret_cast<uint64_t *>(record) + 1; }
+__device__ __forceinline__ void publish_rows(const Stage1Args &a, bool mine, size_t record) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (mine) __hip_atomic_store(mark_of(a.marks + 4 * record), a.ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+__device__ __forceinline__ void store_record(const Stage1Args &a, size_t record, float m, float l) {
+    __hip_atomic_store(reinterpret_cast<uint64_t *>(a.marks + 4 * record), __builtin_bit_cast(uint64_t, (f32x2{m, l})),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 constexpr int kWaves = 4;              // waves per stage-1 workgroup
@@ -721,7 +767,7 @@ struct ResidentLds {
     static constexpr int kPitch = D + 4;
     static constexpr int kMerge = kWaves * 16 * kPitch + 2 * kWaves * 16;  // O, then m and l, of one tile
     static constexpr int kRows = 2 * kMerge;
-    static constexpr int kTokens = kRows + 3 * kTaskRows;
+    static constexpr int kTokens = kRows + 4 * kTaskRows;
     static constexpr int kWords = kTokens + 3 * kResidentTokens<D>;
     static_assert(4 * kResidentTokens<D> <= kRows, "piece records are parked in the merge buffers");
 };
@@ -866,14 +912,14 @@ struct ResidentTask {
 
     // The tiles of the task, one barrier each: a wave writes its part of tile t, and adds up four rows of that tile
     // while it works on tile t + 1 in the other buffer.
-    template <int NA, bool MASK, bool PRECISE>
+    template <int NA, bool MASK, bool PRECISE, bool SHARED>
     __device__ __forceinline__ void run(const Stage1Args &a, const ChunkCtx &c, float *lds, int wave, int lane, int ntiles,
-                                        const uint16_t *q_lane, int vis_lo, int vis_hi) {
+                                        int rows, const uint16_t *q_lane, int vis_lo, int vis_hi) {
         using L = ResidentLds<D>;
         const int32_t *row_q = reinterpret_cast<const int32_t *>(lds + L::kRows), *row_pos = row_q + kTaskRows;
-        const uint32_t *row_out = reinterpret_cast<const uint32_t *>(row_pos + kTaskRows);
+        const uint32_t *row_out = reinterpret_cast<const uint32_t *>(row_pos + kTaskRows), *row_rec = row_out + kTaskRows;
         const int n = 4 * wave + (lane >> 4), dc = lane & 15;
-        auto merge = [&](int t) {
+        auto merge = [&](int t, auto final) {
             const float *buf = lds + (t & 1) * L::kMerge, *ml = buf + kWaves * 16 * L::kPitch + n;
             float m[kWaves], M = -INFINITY;
 #pragma unroll
@@ -894,12 +940,15 @@ struct ResidentTask {
                 for (int e = 0; e < D / 64; ++e)
                     acc[e] += w * *reinterpret_cast<const f32x4 *>(buf + (sp * 16 + n) * L::kPitch + 64 * e + 4 * dc);
             }
-            // Rows past the end are copies of the last row and store what it stores: no condition, so that the number
-            // of stores behind the next Q loads is the same on every path and the wait for those counts them exactly.
+            // Only the last tile has rows past the end, and only there they are left out: elsewhere no condition, so that
+            // the number of stores behind the next Q loads is the same on every path and the wait for those counts them
+            // exactly.
+            if (decltype(final)::value && 16 * t + n >= rows) return;
             const size_t ro = row_out[16 * t + n];
             *((dc & 1 ? a.part_l : a.part_m) + ro) = dc & 1 ? sum : M;
+            if (SHARED) store_record(a, row_rec[16 * t + n], M, sum);
 #pragma unroll
-            for (int e = 0; e < D / 64; ++e) *reinterpret_cast<f32x4 *>(a.part_acc + ro * D + 64 * e + 4 * dc) = acc[e];
+            for (int e = 0; e < D / 64; ++e) store_partial<SHARED>(a.part_acc + ro * D + 64 * e + 4 * dc, acc[e]);
         };
         if constexpr (NA == 0) {  // a wave without a block: its part is empty in both buffers from the start
             f32x4 o[VW];
@@ -909,7 +958,10 @@ struct ResidentTask {
             publish(c, wave, o, -INFINITY, 0.f, lds + L::kMerge);
             for (int t = 0; t < ntiles; ++t) {
                 __syncthreads();
-                merge(t);
+                if (t + 1 < ntiles)
+                    merge(t, std::false_type());
+                else
+                    merge(t, std::true_type());
             }
         } else {
             const int last = 16 * (ntiles - 1) + c.n16;
@@ -920,15 +972,18 @@ struct ResidentTask {
                 __syncthreads();
                 tile<NA, MASK, PRECISE>(c, wave, MASK ? row_pos[16 * t + c.n16] : 0, vis_lo, vis_hi, q_lane,
                                         row_q[min(16 * (t + 1) + c.n16, last)], a.c, lds + (t & 1) * L::kMerge,
-                                        [&] { merge(t - 1); });
+                                        [&] { merge(t - 1, std::false_type()); });
             }
             __syncthreads();
-            merge(ntiles - 1);
+            merge(ntiles - 1, std::true_type());
         }
+        // this wave's rows: 4 * wave .. 4 * wave + 3 of every tile
+        const int mine = 16 * (lane >> 2) + 4 * wave + (lane & 3);
+        if (SHARED) publish_rows(a, mine < rows, row_rec[min(mine, rows - 1)]);
     }
 };
 
-template <int D, bool PRECISE>
+template <int D, bool PRECISE, bool SHARED>
 __device__ __forceinline__ void resident_task(const Stage1Args &a, const int32_t *it, int h, unsigned char *s_raw) {
     using L = ResidentLds<D>;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -939,7 +994,7 @@ __device__ __forceinline__ void resident_task(const Stage1Args &a, const int32_t
     const int slot_base = it[deft::kItSlotBase];
     float *lds = reinterpret_cast<float *>(s_raw);
     int32_t *row_q = reinterpret_cast<int32_t *>(lds + L::kRows), *row_pos = row_q + kTaskRows;
-    uint32_t *row_out = reinterpret_cast<uint32_t *>(row_pos + kTaskRows);
+    uint32_t *row_out = reinterpret_cast<uint32_t *>(row_pos + kTaskRows), *row_rec = row_out + kTaskRows;
     int32_t *s_row = reinterpret_cast<int32_t *>(lds + L::kTokens), *s_qlo = s_row + kResidentTokens<D>,
             *s_qhi = s_qlo + kResidentTokens<D>;
     ChunkCtx c{};
@@ -970,6 +1025,7 @@ __device__ __forceinline__ void resident_task(const Stage1Args &a, const int32_t
             row_q[tid] = q_user * a.Hq + h * a.G + gh;
             row_pos[tid] = cqlo + pl;
             row_out[tid] = (uint32_t)(slot_base + pl) * (uint32_t)a.Hq + (uint32_t)(h * a.G + gh);
+            if (SHARED) row_rec[tid] = (uint32_t)(h * a.n_slots + slot_base + pl) * (uint32_t)a.G + (uint32_t)gh;
         }
     };
     // the tokens: physical row and the interval of plan positions that see it (nobody, past the chunk's end)
@@ -1041,9 +1097,9 @@ __device__ __forceinline__ void resident_task(const Stage1Args &a, const int32_t
             T.template interleave<NA>(v);
         }
         if (!__all(all))
-            T.template run<NA, true, PRECISE>(a, c, lds, wave, lane, ntiles, q_lane, vis_lo, vis_hi);
+            T.template run<NA, true, PRECISE, SHARED>(a, c, lds, wave, lane, ntiles, rows, q_lane, vis_lo, vis_hi);
         else
-            T.template run<NA, false, PRECISE>(a, c, lds, wave, lane, ntiles, q_lane, vis_lo, vis_hi);
+            T.template run<NA, false, PRECISE, SHARED>(a, c, lds, wave, lane, ntiles, rows, q_lane, vis_lo, vis_hi);
     };
     if (mine <= 0)
         go(std::integral_constant<int, 0>());
@@ -1063,7 +1119,7 @@ __device__ __forceinline__ void resident_task(const Stage1Args &a, const int32_t
 // reaches the workspace.
 //
 // PRECISE selects two-term softmax weights (see compute_block).
-template <int D, bool PRECISE>
+template <int D, bool PRECISE, bool SHARED>
 __device__ __forceinline__ void streaming_task(const Stage1Args &a, const int32_t *it, int h, unsigned char *s_raw) {
     constexpr int KK = D / 32;  // k-steps of the Q.K^T contraction
     // The P.V product runs as 8 MFMAs per block (a lane loads 8 d of V per token).  With D = 64 lanes
@@ -1278,12 +1334,18 @@ __device__ __forceinline__ void streaming_task(const Stage1Args &a, const int32_
             if (dc == 0) {
                 a.part_m[ro] = M;
                 a.part_l[ro] = L;
+                if (SHARED) store_record(a, ((size_t)h * a.n_slots + slot_base + pl) * a.G + gh, M, L);
             }
             float *dst = a.part_acc + ro * D + EPL * dc;
 #pragma unroll
-            for (int e = 0; e < EPL; e += 4)
-                *reinterpret_cast<f32x4 *>(dst + e) = f32x4{o[e], o[e + 1], o[e + 2], o[e + 3]};
+            for (int e = 0; e < EPL; e += 4) store_partial<SHARED>(dst + e, f32x4{o[e], o[e + 1], o[e + 2], o[e + 3]});
         }
+    }
+    if (SHARED) {  // this wave's rows: 4 * TR from 4 * TR * wave among the first tiles of the waves, as many among the second
+        const int gr = 4 * TR * wave + (lane & 15), tile = (gr >> 4) + 4 * (lane >> 4), r = 16 * (tile0 + tile) + (gr & 15);
+        const int pl = divide(r, a.G, a.inv_G);
+        publish_rows(a, (lane & 15) < 4 * TR && lane < 16 * NTW && tile < ntiles && r < R,
+                     ((size_t)h * a.n_slots + slot_base + pl) * a.G + (r - pl * a.G));
     }
 }
 
@@ -1292,13 +1354,13 @@ __device__ __forceinline__ void streaming_task(const Stage1Args &a, const int32_
 // the same kind of weights, which is most of them, run a kernel that holds that kind alone.
 enum Weights { kBf16 = 0, kTwoTerm = 1, kMixed = 2 };
 
-template <int D, bool PRECISE>
+template <int D, bool PRECISE, bool SHARED>
 __device__ __forceinline__ void run_task(const Stage1Args &a, const int32_t *it, int h, unsigned char *s_raw) {
     if (it[deft::kItLen] <= kResidentTokens<D> &&
         it[deft::kItNTiles] <= (D == 128 && it[deft::kItNSeg] == 1 ? a.resident_one : a.resident_many))
-        resident_task<D, PRECISE>(a, it, h, s_raw);
+        resident_task<D, PRECISE, SHARED>(a, it, h, s_raw);
     else
-        streaming_task<D, PRECISE>(a, it, h, s_raw);
+        streaming_task<D, PRECISE, SHARED>(a, it, h, s_raw);
 }
 
 // A run of several chunks with the same queries leaves its result in the slots of the first and marks those of the others
@@ -1313,25 +1375,6 @@ __device__ __forceinline__ void mark_empty(const Stage1Args &a, const int32_t *i
         a.part_m[ro] = -INFINITY;
         a.part_l[ro] = 0.f;
     }
-}
-
-template <int D, int WEIGHTS>
-__global__ __launch_bounds__(64 * kWaves, 2) void deft_stage1(Stage1Args a) {
-    extern __shared__ __attribute__((aligned(16))) unsigned char s_raw[];
-    const int item = divide(blockIdx.x, a.Hkv, a.inv_Hkv);
-    // KV head of this workgroup.  Workgroups b and b + 256 land on the same compute unit (the dispatcher goes
-    // round the 256 units), and with Hkv dividing 256 they would stream the same head: K and V rows whose
-    // addresses agree in bits 7..12.  A unit whose streams all share those bits reads measurably slower (its
-    // L1 keeps fewer lines in flight), so every further round of 256 workgroups is moved on by one head.
-    // The shift depends on the task only, so a task still visits every head exactly once.
-    const uint32_t turned = blockIdx.x - item * a.Hkv + ((uint32_t)(item * a.Hkv) >> 8);
-    const int h = turned - divide(turned, a.Hkv, a.inv_Hkv) * a.Hkv;
-    const int32_t *it = a.items + (size_t)item * deft::kItemInts;
-    if (it[deft::kItChunks] > 1) mark_empty(a, it, h);  // (first: behind the task its descriptor would have to be read again)
-    if (WEIGHTS == kTwoTerm || (WEIGHTS == kMixed && it[deft::kItPrecise]))
-        run_task<D, true>(a, it, h, s_raw);
-    else
-        run_task<D, false>(a, it, h, s_raw);
 }
 
 // Stage 2: tree-topology-aware global reduction (eq. 1 with the largest maximum subtracted), D/4 lanes to a row of a
@@ -1491,6 +1534,123 @@ __global__ __launch_bounds__(64 * WAVES) void deft_stage2_many(Stage2Args a) {
     store_out(a, ((size_t)q_user * a.Hq + qh) * D + 4 * col, sum * (total > 0.f ? 1.f / total : 0.f));
 }
 
+// Stage 2 of a whole call in one launch.  Its workgroups come last in the grid: workgroups are started in the order of
+// their ids, on every XCD for itself, so whichever of these runs, all that it waits for run or have run already, and none of
+// those waits for anything.  (The wait gives up in any case, after seconds; the row is then not a number.)
+constexpr int kMarkPolls = 1 << 22;
+template <int D>
+__device__ __forceinline__ void reduce_task(const CallArgs &call, float *lds) {
+    using R = Stage2Row<D>;
+    const Stage2Args &a = call.s2;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t id = blockIdx.x - call.tasks;
+    const uint32_t row = call.wide_reduce ? id : kWaves * id + wave;
+    const int waves = call.wide_reduce ? kWaves : 1, first = call.wide_reduce ? wave : 0;
+    const int p = divide(row, a.Hq, a.inv_Hq), qh = row - p * a.Hq;
+    if (p >= a.nq) return;  // (only where every wave has a row of its own)
+    const int32_t *rec = a.q_head + (size_t)p * a.head_ints;
+    int slot = rec[min(deft::kQueryHeadFixed + waves * lane + first, a.head_ints - 1)];
+    const int n = rec[0], q_user = rec[1], s0 = rec[2];
+    const int sub = lane / R::kLanes, col = lane - sub * R::kLanes;
+    const int mine = call.wide_reduce ? (n - wave + kWaves - 1) / kWaves : n;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    float M = -INFINITY, lsum = 0.f;
+    for (int base = 0; base < mine; base += 64) {
+        const int cnt = min(64, mine - base);
+        if (n > a.head_ints - deft::kQueryHeadFixed)
+            slot = a.q_part_slot[s0 + waves * (base + min(lane, cnt - 1)) + first];
+        else if (base > 0)
+            slot = rec[deft::kQueryHeadFixed + waves * (base + min(lane, cnt - 1)) + first];
+        slot = __shfl(slot, min(lane, cnt - 1));  // lanes past the end hold a slot that exists
+        const int kvh = divide(qh, call.s1.G, call.s1.inv_G);
+        float *record = call.s1.marks + 4 * (((size_t)kvh * call.s1.n_slots + slot) * call.s1.G + (qh - kvh * call.s1.G));
+        uint64_t *mark = mark_of(record);
+        bool there = lane >= cnt;
+        for (int i = 0; i < kMarkPolls; ++i) {
+            if (!there) there = __hip_atomic_load(mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == call.s1.ticket;
+            if (__all(there)) break;
+            __builtin_amdgcn_s_sleep(2);
+        }
+        asm volatile("" ::: "memory");
+        f32x2 ml = {-INFINITY, 0.f};
+        if (lane < cnt)
+            ml = __builtin_bit_cast(f32x2, __hip_atomic_load(reinterpret_cast<uint64_t *>(record), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        const float mj = ml[0], lj = ml[1];
+        float w = 0.f;
+        for (int j = 0; j < cnt; j += R::kBatch) {
+            f32x4 x[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int sj = __shfl(slot, (j + u * R::kRows + sub) & 63);
+                x[u] = load_shared4(a.part_acc + ((size_t)sj * a.Hq + qh) * D + 4 * col);
+            }
+            if (j == 0) {
+                if (lane < cnt) __hip_atomic_store(mark, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const float top = fmaxf(M, wave_max(mj));
+                const float old = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((M - top) * a.c);
+                w = (lane < cnt && top != -INFINITY) ? __builtin_amdgcn_exp2f((mj - top) * a.c) : 0.f;
+                if (!there) w = NAN;
+                lsum = lsum * old + wave_sum(w * lj);
+                acc *= old;
+                M = top;
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) acc += __shfl(w, (j + u * R::kRows + sub) & 63) * x[u];
+        }
+    }
+#pragma unroll
+    for (int o = 32; o >= R::kLanes; o >>= 1)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], o);
+    if (call.wide_reduce) {
+        float *s_m = lds + kWaves * D, *s_l = s_m + kWaves;
+        if (sub == 0) *reinterpret_cast<f32x4 *>(lds + wave * D + 4 * col) = acc;
+        if (lane == 0) {
+            s_m[wave] = M;
+            s_l[wave] = lsum;
+        }
+        __syncthreads();
+        if (wave != 0) return;
+        float top = -INFINITY;
+#pragma unroll
+        for (int k = 0; k < kWaves; ++k) top = fmaxf(top, s_m[k]);
+        acc = f32x4{0.f, 0.f, 0.f, 0.f};
+        lsum = 0.f;
+#pragma unroll
+        for (int k = 0; k < kWaves; ++k) {
+            const float w = top == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((s_m[k] - top) * a.c);
+            lsum += w * s_l[k];
+            acc += w * *reinterpret_cast<const f32x4 *>(lds + k * D + 4 * col);
+        }
+    }
+    if (sub == 0) store_out(a, ((size_t)q_user * a.Hq + qh) * D + 4 * col, acc * (lsum > 0.f ? 1.f / lsum : 0.f));
+}
+
+// SHARED: a whole call in one launch, stage 2 included.
+template <int D, int WEIGHTS, bool SHARED>
+__global__ __launch_bounds__(64 * kWaves, 2) void deft_stage1(CallArgs call) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char s_raw[];
+    if (SHARED && blockIdx.x >= call.tasks) {
+        reduce_task<D>(call, reinterpret_cast<float *>(s_raw));
+        return;
+    }
+    const Stage1Args &a = call.s1;
+    const int item = divide(blockIdx.x, a.Hkv, a.inv_Hkv);
+    // KV head of this workgroup.  Workgroups b and b + 256 land on the same compute unit (the dispatcher goes
+    // round the 256 units), and with Hkv dividing 256 they would stream the same head: K and V rows whose
+    // addresses agree in bits 7..12.  A unit whose streams all share those bits reads measurably slower (its
+    // L1 keeps fewer lines in flight), so every further round of 256 workgroups is moved on by one head.
+    // The shift depends on the task only, so a task still visits every head exactly once.
+    const uint32_t turned = blockIdx.x - item * a.Hkv + ((uint32_t)(item * a.Hkv) >> 8);
+    const int h = turned - divide(turned, a.Hkv, a.inv_Hkv) * a.Hkv;
+    const int32_t *it = a.items + (size_t)item * deft::kItemInts;
+    if (it[deft::kItChunks] > 1) mark_empty(a, it, h);  // (first: behind the task its descriptor would have to be read again)
+    if (WEIGHTS == kTwoTerm || (WEIGHTS == kMixed && it[deft::kItPrecise]))
+        run_task<D, true, SHARED>(a, it, h, s_raw);
+    else
+        run_task<D, false, SHARED>(a, it, h, s_raw);
+}
+
 // Plain read of a buffer with 128-bit loads, every byte once, all compute units busy: the rate this
 // reaches is the practical ceiling for a kernel whose job is to read HBM (Section 3.3's premise is that
 // the KV read dominates).  Workgroup b leaves the xor of the words it read in sink[b], so that no load
@@ -1529,9 +1689,12 @@ bool configure_stage1() {
     if (dev >= 0 && dev < 64 && ((configured.load(std::memory_order_acquire) >> dev) & 1)) return true;
     const int bytes = kXbufBytes + 3 * DEFT_MAX_CHUNK * (int)sizeof(int32_t);
     static_assert(ResidentLds<D>::kWords * 4 <= kXbufBytes + 3 * DEFT_MAX_CHUNK * (int)sizeof(int32_t), "LDS limit");
-    for (const void *f : {reinterpret_cast<const void *>(&deft_stage1<D, kBf16>),
-                          reinterpret_cast<const void *>(&deft_stage1<D, kTwoTerm>),
-                          reinterpret_cast<const void *>(&deft_stage1<D, kMixed>)})
+    for (const void *f : {reinterpret_cast<const void *>(&deft_stage1<D, kBf16, false>),
+                          reinterpret_cast<const void *>(&deft_stage1<D, kTwoTerm, false>),
+                          reinterpret_cast<const void *>(&deft_stage1<D, kMixed, false>),
+                          reinterpret_cast<const void *>(&deft_stage1<D, kBf16, true>),
+                          reinterpret_cast<const void *>(&deft_stage1<D, kTwoTerm, true>),
+                          reinterpret_cast<const void *>(&deft_stage1<D, kMixed, true>)})
         if (!hip_ok(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes), "deft_stage1 LDS size")) return false;
     if (dev >= 0 && dev < 64) configured.fetch_or(1ull << dev, std::memory_order_release);
     return true;
@@ -1547,20 +1710,21 @@ bool configure_stage1() {
 // other tasks cover a streaming task's steps (1328 tasks, 256 queries: 96.1 us with five, 95.0 us with three).
 constexpr int kResidentTiles = 3;
 
-template <int D>
-bool launch_stage1(const deft::TaskSet &T, Stage1Args a1, const uint8_t *image, hipStream_t stream) {
+template <int D, bool SHARED>
+bool launch_stage1(const deft::TaskSet &T, CallArgs a, unsigned reduce_groups, const uint8_t *image, hipStream_t stream) {
     if (T.n_items == 0) return true;
     if (!configure_stage1<D>()) return false;
+    Stage1Args &a1 = a.s1;
     a1.items = reinterpret_cast<const int32_t *>(image + T.off_items);
     a1.n_items = T.n_items;
     a1.resident_one = kResidentTiles;
     a1.resident_many = (int64_t)T.n_items * a1.Hkv <= deft::kResidentGroups ? deft::kMaxTilesPerTask : kResidentTiles;
     const size_t lds = std::max(kXbufBytes + 3 * (size_t)a1.table_len * sizeof(int32_t), (size_t)ResidentLds<D>::kWords * 4);
-    const unsigned grid = (unsigned)T.n_items * (unsigned)a1.Hkv;
-    auto *kernel = T.n_items_precise == 0           ? &deft_stage1<D, kBf16>
-                   : T.n_items_precise == T.n_items ? &deft_stage1<D, kTwoTerm>
-                                                    : &deft_stage1<D, kMixed>;
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * kWaves), lds, stream, a1);
+    a.tasks = (unsigned)T.n_items * (unsigned)a1.Hkv;
+    auto *kernel = T.n_items_precise == 0           ? &deft_stage1<D, kBf16, SHARED>
+                   : T.n_items_precise == T.n_items ? &deft_stage1<D, kTwoTerm, SHARED>
+                                                    : &deft_stage1<D, kMixed, SHARED>;
+    hipLaunchKernelGGL(kernel, dim3(a.tasks + reduce_groups), dim3(64 * kWaves), lds, stream, a);
     return hip_ok(hipGetLastError(), "deft_stage1 launch");
 }
 
@@ -1592,6 +1756,7 @@ struct Call {
     const deft::Schedule *S = nullptr;
     const uint8_t *img = nullptr;
     float *acc = nullptr, *pm = nullptr, *pl = nullptr;
+    float *marks = nullptr;  // null: the workspace has no room for them
     float c = 0.f;
     hipStream_t stream = nullptr;
 };
@@ -1605,7 +1770,7 @@ int prepare(const deft_plan_t *plan, const void *dev_image, int32_t Hq, int32_t 
     if (!aligned16(workspace) || !aligned16(dev_image)) return DEFT_EINVAL;
     call.S = deft::find_schedule(plan, Hq / Hkv);
     if (!call.S) return DEFT_ENOTREADY;
-    if (workspace_bytes < deft_workspace_bytes(plan, Hq, Hkv, d)) return DEFT_EWORKSPACE;
+    if (workspace_bytes < deft::partials_bytes(plan, Hq, d)) return DEFT_EWORKSPACE;
     if ((int64_t)std::max(call.S->by_chunk.n_items, call.S->fused.n_items) * Hkv > INT32_MAX) return DEFT_EINVAL;  // grid sizes are 32-bit
     if ((int64_t)plan->nq * Hq > INT32_MAX) return DEFT_EINVAL;
     const size_t rows = (size_t)plan->n_slots() * (size_t)Hq;
@@ -1613,19 +1778,16 @@ int prepare(const deft_plan_t *plan, const void *dev_image, int32_t Hq, int32_t 
     call.acc = static_cast<float *>(workspace);
     call.pm = call.acc + rows * (size_t)d;
     call.pl = call.pm + rows;
+    call.marks = workspace_bytes < deft::workspace_bytes(plan, Hq, d) ? nullptr : call.pm + (2 * rows + 3) / 4 * 4;
     if (!(scale > 0.f)) scale = 1.0f / std::sqrt((float)d);
     call.c = scale * 1.4426950408889634f;  // log2(e)
     call.stream = reinterpret_cast<hipStream_t>(stream);
     return DEFT_OK;
 }
 
-int run_stage1(const deft_plan_t *plan, const Call &call, const deft::TaskSet &T, const void *q, const void *k, const void *v, int32_t Hq,
-               int32_t Hkv, int32_t d) {
-    if (plan->n_chunks() == 0) return DEFT_OK;
-    if (!q || !k || !v || !aligned16(q) || !aligned16(k) || !aligned16(v)) return DEFT_EINVAL;
+void stage1_args(const Call &call, const void *q, const void *k, const void *v, int32_t Hq, int32_t Hkv, Stage1Args &a1) {
     const deft::Schedule &S = *call.S;
     auto at = [&](size_t off) { return reinterpret_cast<const int32_t *>(call.img + off); };
-    Stage1Args a1{};
     a1.q = static_cast<const uint16_t *>(q);
     a1.k = static_cast<const uint16_t *>(k);
     a1.v = static_cast<const uint16_t *>(v);
@@ -1645,17 +1807,10 @@ int run_stage1(const deft_plan_t *plan, const Call &call, const deft::TaskSet &T
     a1.inv_G = inverse(a1.G);
     a1.table_len = S.table_len;
     a1.c = call.c;
-    const bool ok = d == 128 ? launch_stage1<128>(T, a1, call.img, call.stream)
-                             : launch_stage1<64>(T, a1, call.img, call.stream);
-    return ok ? DEFT_OK : DEFT_EHIP;
 }
 
-int run_stage2(const deft_plan_t *plan, const Call &call, const deft::TaskSet &T, void *o, int32_t Hq, int32_t d, uint32_t flags) {
-    if (flags != DEFT_OUT_BF16 && flags != DEFT_OUT_F32) return DEFT_EINVAL;
-    if (plan->nq == 0) return DEFT_OK;
-    if (!o || !aligned16(o)) return DEFT_EINVAL;
+void stage2_args(const deft_plan_t *plan, const Call &call, const deft::TaskSet &T, void *o, int32_t Hq, uint32_t flags, Stage2Args &a2) {
     auto at = [&](size_t off) { return reinterpret_cast<const int32_t *>(call.img + off); };
-    Stage2Args a2{};
     a2.part_acc = call.acc;
     a2.part_m = call.pm;
     a2.part_l = call.pl;
@@ -1668,11 +1823,77 @@ int run_stage2(const deft_plan_t *plan, const Call &call, const deft::TaskSet &T
     a2.inv_Hq = inverse(Hq);
     a2.out_f32 = (flags == DEFT_OUT_F32);
     a2.c = call.c;
+}
+
+bool stage1_inputs_ok(const void *q, const void *k, const void *v) {
+    return q && k && v && aligned16(q) && aligned16(k) && aligned16(v);
+}
+
+int run_stage1(const deft_plan_t *plan, const Call &call, const deft::TaskSet &T, const void *q, const void *k, const void *v, int32_t Hq,
+               int32_t Hkv, int32_t d) {
+    if (plan->n_chunks() == 0) return DEFT_OK;
+    if (!stage1_inputs_ok(q, k, v)) return DEFT_EINVAL;
+    CallArgs a{};
+    stage1_args(call, q, k, v, Hq, Hkv, a.s1);
+    const bool ok = d == 128 ? launch_stage1<128, false>(T, a, 0, call.img, call.stream)
+                             : launch_stage1<64, false>(T, a, 0, call.img, call.stream);
+    return ok ? DEFT_OK : DEFT_EHIP;
+}
+
+int run_stage2(const deft_plan_t *plan, const Call &call, const deft::TaskSet &T, void *o, int32_t Hq, int32_t d, uint32_t flags) {
+    if (flags != DEFT_OUT_BF16 && flags != DEFT_OUT_F32) return DEFT_EINVAL;
+    if (plan->nq == 0) return DEFT_OK;
+    if (!o || !aligned16(o)) return DEFT_EINVAL;
+    Stage2Args a2{};
+    stage2_args(plan, call, T, o, Hq, flags, a2);
     // a stage 2 called apart may find slots that a whole call on joined chunks left empty
     const bool holes = &T != &call.S->fused && call.S->fused.off_items != T.off_items;
     const bool ok = d == 128 ? (holes ? launch_stage2<128, true>(T, a2, call.stream) : launch_stage2<128, false>(T, a2, call.stream))
                              : (holes ? launch_stage2<64, true>(T, a2, call.stream) : launch_stage2<64, false>(T, a2, call.stream));
     return ok ? DEFT_OK : DEFT_EHIP;
+}
+
+// A number that no call of this process has had and that no memory is likely to hold.
+uint64_t new_ticket() {
+    static std::atomic<uint64_t> last{((uint64_t)std::random_device{}() << 32) ^ std::random_device{}()};
+    uint64_t x = last.fetch_add(0x9e3779b97f4a7c15ull, std::memory_order_relaxed);  // splitmix64
+    x = (x ^ (x >> 30)) * 0xbf58476d1ce4e5b9ull;
+    x = (x ^ (x >> 27)) * 0x94d049bb133111ebull;
+    x ^= x >> 31;
+    return x ? x : 1;
+}
+
+// Both stages in one launch.
+int run_call(const deft_plan_t *plan, const Call &call, const void *q, const void *k, const void *v, void *o, int32_t Hq,
+             int32_t Hkv, int32_t d, uint32_t flags) {
+    if (!stage1_inputs_ok(q, k, v)) return DEFT_EINVAL;
+    const deft::TaskSet &T = call.S->fused;
+    CallArgs a{};
+    stage1_args(call, q, k, v, Hq, Hkv, a.s1);
+    stage2_args(plan, call, T, o, Hq, flags, a.s2);
+    a.s1.marks = call.marks;
+    a.s1.ticket = new_ticket();
+    a.s1.n_slots = plan->n_slots();
+    const unsigned rows = (unsigned)plan->nq * (unsigned)Hq;
+    a.wide_reduce = T.max_parts > 16 && rows <= 512;
+    const unsigned groups = a.wide_reduce ? rows : (rows + kWaves - 1) / kWaves;
+    const bool ok = d == 128 ? launch_stage1<128, true>(T, a, groups, call.img, call.stream)
+                             : launch_stage1<64, true>(T, a, groups, call.img, call.stream);
+    return ok ? DEFT_OK : DEFT_EHIP;
+}
+
+// Which calls are made in one launch.  It saves the host 2 to 3 us and the GPU the microsecond between two kernels, but
+// stage 2 then shares the chip with stage 1 at stage 1's size of workgroup, and partial results cross the caches one by
+// one.  So: the calls that the host's work bounds, those of few bytes, and few partial results.  Whole call, us, two
+// launches -> one: 384 tokens x 4 heads 10.4 -> 8.2; 1659 tokens under one query 12.6 -> 9.4; 8191 tokens (34 MB) 11.9 ->
+// 11.2; 33 MB and 960 rows of partial results 12.1 -> 10.7; 22 MB and 4032 rows 12.3 -> 12.2; 21 MB and 8096 rows 12.6 ->
+// 13.0, 38 MB and 10880 rows 16.0 -> 17.5; 47 MB and 1704 rows 14.7 -> 15.7; 17 MB, 4312 rows 13.0 -> 13.5.  A thousand
+// rows of output are too many as well: 1024 of them, 4.5 MB and 2240 partial ones 12.3 -> 12.6, 896 of them 12.4 -> 9.3.
+bool one_launch(const deft_plan_t *plan, const Call &call, int32_t Hq, int32_t Hkv, int32_t d) {
+    constexpr int64_t kFewRows = 1024, kFewPartials = 4096, kFewBytes = 40 << 20;
+    if (!call.marks || plan->nq == 0 || call.S->fused.n_items == 0) return false;
+    return (int64_t)plan->nq * Hq < kFewRows && (int64_t)plan->n_slots() * Hq <= kFewPartials &&
+           (int64_t)plan->n_flat * Hkv * d * 4 <= kFewBytes;
 }
 
 // Pinned host staging for plan images: a ring of slots per device, allocated at the first upload on that
@@ -1782,6 +2003,7 @@ extern "C" int deft_tree_attn_decode(const deft_plan_t *plan, const void *dev_im
     // check both stages' arguments before launching anything
     if (flags != DEFT_OUT_BF16 && flags != DEFT_OUT_F32) return DEFT_EINVAL;
     if (plan->nq > 0 && (!o || !aligned16(o))) return DEFT_EINVAL;
+    if (one_launch(plan, call, Hq, Hkv, d)) return run_call(plan, call, q, k, v, o, Hq, Hkv, d, flags);
     rc = run_stage1(plan, call, call.S->fused, q, k, v, Hq, Hkv, d);
     if (rc != DEFT_OK) return rc;
     return run_stage2(plan, call, call.S->fused, o, Hq, d, flags);
@@ -1814,9 +2036,8 @@ extern "C" int deft_tree_attn_decode_static(const deft_plan_t *plan, const void 
                                             const void *k, const void *v, void *o, int32_t Hq, int32_t Hkv, int32_t d,
                                             float scale, uint32_t flags, void *stream) {
     // size first: a plan whose partial results do not fit is refused before anything touches the device
-    const size_t need = deft_workspace_bytes(plan, Hq, Hkv, d);
-    if (need == 0) return DEFT_EINVAL;
-    if (need > (size_t)DEFT_STATIC_SCRATCH_BYTES) return DEFT_EWORKSPACE;
+    if (deft_workspace_bytes(plan, Hq, Hkv, d) == 0) return DEFT_EINVAL;
+    if (deft::partials_bytes(plan, Hq, d) > (size_t)DEFT_STATIC_SCRATCH_BYTES) return DEFT_EWORKSPACE;
     void *ws = nullptr;
     const int rc = static_scratch(&ws);
     if (rc != DEFT_OK) return rc;

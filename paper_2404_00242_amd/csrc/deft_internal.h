@@ -127,6 +127,9 @@ struct deft_plan_s {
 namespace deft {
 // Size of an image for G = Hq/Hkv that holds the schedule for any number of KV heads.
 size_t image_bytes(const deft_plan_t *plan, int32_t group);
+// The partial results of a plan, and the workspace that holds them and the marks a whole call in one launch needs.
+size_t partials_bytes(const deft_plan_t *plan, int32_t Hq, int32_t d);
+size_t workspace_bytes(const deft_plan_t *plan, int32_t Hq, int32_t d);
 // Builds (or returns the cached) schedule for G = Hq/Hkv.  Thread-safe.
 const Schedule *get_schedule(const deft_plan_t *plan, int32_t group, int32_t Hkv);
 const Schedule *find_schedule(const deft_plan_t *plan, int32_t group);

@@ -918,6 +918,16 @@ size_t image_bytes(const deft_plan_t *P, int32_t G) {
     return 5 * align16((size_t)P->n_segs() * sizeof(int32_t)) + align16(record) + (may_join(P) ? 2 : 1) * set;
 }
 
+// acc [slots, Hq, d] + m [slots, Hq] + l [slots, Hq], fp32; never zero so callers can allocate it
+size_t partials_bytes(const deft_plan_t *plan, int32_t Hq, int32_t d) {
+    const size_t rows = (size_t)plan->n_slots() * (size_t)Hq;
+    return std::max<size_t>(16, (rows * (size_t)d + 2 * rows) * sizeof(float) + 32);
+}
+
+size_t workspace_bytes(const deft_plan_t *plan, int32_t Hq, int32_t d) {
+    return partials_bytes(plan, Hq, d) + (size_t)plan->n_slots() * (size_t)Hq * 16;
+}
+
 const Schedule *get_schedule(const deft_plan_t *plan, int32_t group, int32_t Hkv) {
     std::lock_guard<std::mutex> lock(plan->mu);
     auto it = plan->schedules.find(group);
@@ -948,7 +958,5 @@ extern "C" size_t deft_plan_device_bytes(const deft_plan_t *plan, int32_t Hq, in
 
 extern "C" size_t deft_workspace_bytes(const deft_plan_t *plan, int32_t Hq, int32_t Hkv, int32_t d) {
     if (!plan || Hq <= 0 || Hkv <= 0 || Hq % Hkv != 0 || (d != 64 && d != 128)) return 0;
-    const size_t rows = (size_t)plan->n_slots() * (size_t)Hq;
-    // acc [slots, Hq, d] + m [slots, Hq] + l [slots, Hq], fp32; never zero so callers can allocate it
-    return std::max<size_t>(16, (rows * (size_t)d + 2 * rows) * sizeof(float) + 32);
+    return deft::workspace_bytes(plan, Hq, d);
 }

@@ -1,0 +1,141 @@
+"""Whole calls made in one launch: stage 2's workgroups wait for stage 1's inside the kernel.
+
+The same call in two launches, which a workspace without room for the marks gives, is the reference: both sum the same
+partial results in fp32, in another order, so outputs differ by a few units of 2^-24 of the attention of |V|."""
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2404_00242_amd import binding, workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def base_bytes(plan, t):
+    return plan.view()["n_slots"] * t.Hq * (t.d + 2) * 4 + 32
+
+
+def prepared(t, chunk, flags=0):
+    Q, K, V = (x.cuda() for x in wl.make_qkv(t))
+    plan = binding.deft_plan(t.node_tok_begin, t.node_tok_len, t.node_parent, t.query_node, t.ntok, chunk, flags)
+    return plan, Q, K, V
+
+
+def two_launches(plan, t, q, k, v):
+    ws = torch.empty(base_bytes(plan, t), dtype=torch.uint8, device="cuda")
+    return binding.deft_tree_attn_decode(plan, q, k, v, out_dtype=torch.float32, workspace=ws)
+
+
+def close(a, b, v):
+    # every output is a mean of V; two fp32 summations of n <= 512 terms differ by at most 2 n 2^-24 of the largest |V|
+    assert (a - b).abs().max().item() <= 2 * 512 * 2.0**-24 * v.abs().max().item()
+
+
+def star(root, leaves, length, Hq, Hkv, d, nq=None):
+    lens, parents = [root] + [length] * leaves, [-1] + [0] * leaves
+    return wl._finish("star", lens, parents, list(range(1, leaves + 1)) if leaves else [0] * (nq or 1), Hq, Hkv, d, 7)
+
+
+TREES = [
+    (star(1, 0, 0, 1, 1, 64), 32),           # one token, one row of output
+    (star(40, 0, 0, 4, 4, 128), 32),         # two partials
+    (star(29 * 32, 0, 0, 2, 2, 64), 32),     # 29 partials at d = 64, and one more: past what a wave has in flight
+    (star(30 * 32, 0, 0, 2, 2, 64), 32),
+    (star(16 * 32, 0, 0, 5, 5, 128), 32),    # one wave to a row up to 16 partials, four beyond
+    (star(17 * 32, 0, 0, 5, 5, 128), 32),
+    (star(70 * 32, 0, 0, 2, 1, 128), 32),    # more partials than a record holds
+    (star(300 * 32, 0, 0, 3, 3, 64), 32),    # more than 64 for each of four waves
+    (star(64, 3, 20, 7, 1, 128), 32),        # 7 heads: rows that do not fill tiles, waves without a row
+    (star(700, 26, 9, 4, 4, 128), 128),      # two tiles
+    (star(2000, 33, 40, 8, 2, 128), 512),    # streaming tasks of nine tiles, cut in two
+    (star(1500, 20, 60, 16, 2, 64), 256),
+    (star(300, 3, 400, 6, 2, 128), 2048),    # chunks of several pieces, both kinds of softmax weights
+    (star(900, 6, 200, 8, 4, 128), 96),
+    (star(96, 0, 0, 8, 2, 128, nq=17), 32),  # queries on the root alone
+]
+
+
+@pytest.mark.parametrize("i", range(len(TREES)))
+def test_equals_two_launches(i):
+    t, chunk = TREES[i]
+    plan, q, k, v = prepared(t, chunk)
+    assert t.nq * t.Hq < 1024 and plan.view()["n_slots"] * t.Hq <= 4096  # made in one launch
+    want = two_launches(plan, t, q, k, v)
+    ws = torch.empty(plan.workspace_bytes(t.Hq, t.Hkv, t.d), dtype=torch.uint8, device="cuda")
+    for fill in (0, 0xFF, 0x5A):  # whatever the workspace holds
+        ws.fill_(fill)
+        got = binding.deft_tree_attn_decode(plan, q, k, v, out_dtype=torch.float32, workspace=ws)
+        close(got, want, v)
+        again = binding.deft_tree_attn_decode(plan, q, k, v, out_dtype=torch.float32, workspace=ws)
+        assert torch.equal(got, again)
+    b16 = binding.deft_tree_attn_decode(plan, q, k, v, workspace=ws)
+    assert torch.equal(b16, got.to(torch.bfloat16))
+    # the partial results are there for a stage 2 called apart
+    out = torch.empty_like(got)
+    img = plan.image(t.Hq, t.Hkv, "cuda")
+    rc = binding.load_library().deft_stage2_global_reduction(
+        plan.handle, img.data_ptr(), out.data_ptr(), t.Hq, t.Hkv, t.d, 0.0, binding.DEFT_OUT_F32, ws.data_ptr(), ws.numel(),
+        torch.cuda.current_stream().cuda_stream)
+    assert rc == 0
+    close(out, want, v)
+
+
+def test_queries_without_tokens_and_precise_weights():
+    t = wl._finish("empty", [0, 70, 0, 33], [-1, -1, 1, 1], [0, 2, 3, 0], 4, 2, 128, 3)
+    for flags in (0, binding.DEFT_PRECISE_WEIGHTS):
+        plan, q, k, v = prepared(t, 32, flags)
+        got = binding.deft_tree_attn_decode(plan, q, k, v, out_dtype=torch.float32)
+        close(got, two_launches(plan, t, q, k, v), v)
+        assert not got[[0, 3]].any()
+
+
+def test_workspace_shared_by_plans_of_other_layouts():
+    a, b = star(640, 5, 33, 8, 2, 128), star(333, 11, 17, 4, 4, 64)
+    plans = [prepared(t, 64) for t in (a, b)]
+    ws = torch.empty(max(p.workspace_bytes(t.Hq, t.Hkv, t.d) for (p, *_), t in zip(plans, (a, b))), dtype=torch.uint8, device="cuda")
+    want = [two_launches(p, t, q, k, v) for (p, q, k, v), t in zip(plans, (a, b))]
+    for _ in range(4):
+        for (p, q, k, v), w in zip(plans, want):
+            close(binding.deft_tree_attn_decode(p, q, k, v, out_dtype=torch.float32, workspace=ws), w, v)
+
+
+def test_two_streams_with_a_workspace_each():
+    t = star(900, 9, 50, 8, 2, 128)
+    plan, q, k, v = prepared(t, 64)
+    want = two_launches(plan, t, q, k, v)
+    plan.image(t.Hq, t.Hkv, "cuda")
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    spaces = [torch.empty(plan.workspace_bytes(t.Hq, t.Hkv, t.d), dtype=torch.uint8, device="cuda") for _ in streams]
+    outs = [[torch.empty_like(want) for _ in range(20)] for _ in streams]
+    for i in range(20):
+        for st, ws, o in zip(streams, spaces, outs):
+            binding.deft_tree_attn_decode(plan, q, k, v, out=o[i], workspace=ws, stream=st)
+    torch.cuda.synchronize()
+    for o in outs:
+        for x in o:
+            close(x, want, v)
+
+
+def test_captured_calls_replayed_with_eager_calls_between():
+    t = star(600, 4, 90, 8, 2, 128)
+    plan, q, k, v = prepared(t, 64)
+    ws = torch.empty(plan.workspace_bytes(t.Hq, t.Hkv, t.d), dtype=torch.uint8, device="cuda")
+    out = torch.zeros((t.nq, t.Hq, t.d), dtype=torch.float32, device="cuda")
+    binding.deft_tree_attn_decode(plan, q, k, v, out=out, workspace=ws)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side):
+        for _ in range(2):
+            binding.deft_tree_attn_decode(plan, q, k, v, out=out, workspace=ws, stream=side)
+    for i in range(4):
+        q.normal_()  # new inputs: a replay that read the partial results of the one before would show
+        out.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        close(out, two_launches(plan, t, q, k, v), v)
+        if i == 1:
+            binding.deft_tree_attn_decode(plan, q, k, v, workspace=ws)

@@ -17,6 +17,8 @@ def hipcc_command(out: str = LIB, extra=()):
         "hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
         # packed-FP32 VALU forms are kept out of the generated code on purpose
         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+        # the leading scalar arguments of a kernel are in registers when its waves start (see CallArgs in deft_decode.hip)
+        "-mllvm", "-amdgpu-kernarg-preload-count=5",
         "-Wall", "-Wno-unused-function",
         "-I", os.path.join(ROOT, "include"), "-I", CSRC,
         *extra, *os.environ.get("DEFT_EXTRA_FLAGS", "").split(),

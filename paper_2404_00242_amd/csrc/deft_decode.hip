@@ -54,9 +54,8 @@ struct Stage1Args {
     float *part_acc, *part_m, *part_l;
     const int32_t *seg_tok_begin, *seg_len, *seg_qlo, *seg_qhi, *seg_off;
     const int32_t *q_order;
-    const int32_t *items;  // deft::kItemInts int32 per work item, see deft_internal.h
     int32_t n_items, Hq, Hkv, G;
-    uint32_t inv_Hkv, inv_G;  // see divide
+    uint32_t inv_G;  // see divide
     int32_t resident_one, resident_many;  // most row tiles of a task on the resident path, see kResidentTiles
     int32_t table_len;  // entries of the LDS per-token table: longest multi-piece chunk, in whole blocks
     float c;  // scale * log2(e): probabilities are 2^((s - m) * c)
@@ -79,11 +78,15 @@ struct Stage2Args {
     float c;
 };
 
+// What a workgroup needs to ask for its first record is passed ahead of the structures, as plain arguments: the compiler
+// has those loaded into registers before the first wave starts (build.py), which takes one round trip out of the chain
+// that every workgroup begins with.  Whole call, us: 37 MB over 16-token pages 16.2 -> 15.7, the decode iteration of the
+// same tree 170.8 -> 166.0, 21 MB with d = 64 12.4 -> 12.1, 67 MB 22.3 -> 22.1.
+
 // A whole call in one launch: stage 1's workgroups first, then those of stage 2
 struct CallArgs {
     Stage1Args s1;
     Stage2Args s2;
-    uint32_t tasks;       // workgroups of stage 1
     int32_t wide_reduce;  // 1: a workgroup of stage 2 takes one row of the output, 0: one in each wave
 };
 
@@ -946,7 +949,7 @@ struct ResidentTask {
             if (decltype(final)::value && 16 * t + n >= rows) return;
             const size_t ro = row_out[16 * t + n];
             *((dc & 1 ? a.part_l : a.part_m) + ro) = dc & 1 ? sum : M;
-            if (SHARED) store_record(a, row_rec[16 * t + n], M, sum);
+            if (SHARED && dc == 0) store_record(a, row_rec[16 * t + n], M, sum);
 #pragma unroll
             for (int e = 0; e < D / 64; ++e) store_partial<SHARED>(a.part_acc + ro * D + 64 * e + 4 * dc, acc[e]);
         };
@@ -1426,11 +1429,12 @@ __device__ __forceinline__ void store_out(const Stage2Args &a, size_t at, f32x4 
 // in registers.  One wave to a workgroup: four cost 0.4 us more on every tree, and two or four heads to a wave gain
 // only where there are thousands (0.2 us of 6.3 at 8192).
 template <int D, bool HOLES>
-__global__ __launch_bounds__(64) void deft_stage2_few(Stage2Args a) {
+__global__ __launch_bounds__(64) void deft_stage2_few(const int32_t *q_head, uint32_t Hq, uint32_t inv_Hq, uint32_t head_ints,
+                                                      Stage2Args a) {
     using R = Stage2Row<D>;
     const int lane = threadIdx.x;
-    const int p = divide(blockIdx.x, a.Hq, a.inv_Hq), qh = blockIdx.x - p * a.Hq;
-    const int rec = a.q_head[(size_t)p * a.head_ints + (lane & (deft::kQueryHeadInts - 1))];
+    const int p = divide(blockIdx.x, Hq, inv_Hq), qh = blockIdx.x - p * Hq;
+    const int rec = q_head[(size_t)p * head_ints + (lane & (deft::kQueryHeadInts - 1))];
     const int n = __builtin_amdgcn_readlane(rec, 0), q_user = __builtin_amdgcn_readlane(rec, 1);
     const int sub = lane / R::kLanes, col = lane - sub * R::kLanes;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -1464,14 +1468,15 @@ __global__ __launch_bounds__(64) void deft_stage2_few(Stage2Args a) {
 // Any number of partials: one, two or four waves per (query, query head), partial WAVES * i + w with wave w.  Each wave
 // merges what it holds as above (64 of its partials at a time, on a running maximum), then their results are merged in LDS.
 template <int D, int WAVES, bool HOLES>
-__global__ __launch_bounds__(64 * WAVES) void deft_stage2_many(Stage2Args a) {
+__global__ __launch_bounds__(64 * WAVES) void deft_stage2_many(const int32_t *q_head, uint32_t Hq, uint32_t inv_Hq, uint32_t head_ints,
+                                                               Stage2Args a) {
     using R = Stage2Row<D>;
     __shared__ __attribute__((aligned(16))) float s_acc[WAVES][D];
     __shared__ float s_m[WAVES], s_l[WAVES];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int p = divide(blockIdx.x, a.Hq, a.inv_Hq), qh = blockIdx.x - p * a.Hq;
-    const int32_t *rec = a.q_head + (size_t)p * a.head_ints;
-    int slot = rec[min(deft::kQueryHeadFixed + WAVES * lane + wave, a.head_ints - 1)];
+    const int p = divide(blockIdx.x, Hq, inv_Hq), qh = blockIdx.x - p * Hq;
+    const int32_t *rec = q_head + (size_t)p * head_ints;
+    int slot = rec[min(deft::kQueryHeadFixed + WAVES * lane + wave, (int)head_ints - 1)];
     const int n = rec[0], q_user = rec[1], s0 = rec[2];
     const int sub = lane / R::kLanes, col = lane - sub * R::kLanes;
     const int mine = (n - wave + WAVES - 1) / WAVES;  // partials of this wave
@@ -1479,7 +1484,7 @@ __global__ __launch_bounds__(64 * WAVES) void deft_stage2_many(Stage2Args a) {
     float M = -INFINITY, lsum = 0.f;
     for (int base = 0; base < mine; base += 64) {
         const int cnt = min(64, mine - base);
-        if (n > a.head_ints - deft::kQueryHeadFixed)
+        if (n > (int)head_ints - deft::kQueryHeadFixed)
             slot = a.q_part_slot[s0 + WAVES * (base + min(lane, cnt - 1)) + wave];
         else if (WAVES == 1 && base > 0)  // (two waves or four find all of theirs in the first 64)
             slot = rec[deft::kQueryHeadFixed + base + min(lane, cnt - 1)];
@@ -1539,11 +1544,10 @@ __global__ __launch_bounds__(64 * WAVES) void deft_stage2_many(Stage2Args a) {
 // those waits for anything.  (The wait gives up in any case, after seconds; the row is then not a number.)
 constexpr int kMarkPolls = 1 << 22;
 template <int D>
-__device__ __forceinline__ void reduce_task(const CallArgs &call, float *lds) {
+__device__ __forceinline__ void reduce_task(const CallArgs &call, uint32_t id, float *lds) {
     using R = Stage2Row<D>;
     const Stage2Args &a = call.s2;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t id = blockIdx.x - call.tasks;
     const uint32_t row = call.wide_reduce ? id : kWaves * id + wave;
     const int waves = call.wide_reduce ? kWaves : 1, first = call.wide_reduce ? wave : 0;
     const int p = divide(row, a.Hq, a.inv_Hq), qh = row - p * a.Hq;
@@ -1627,23 +1631,25 @@ __device__ __forceinline__ void reduce_task(const CallArgs &call, float *lds) {
 }
 
 // SHARED: a whole call in one launch, stage 2 included.
+//   items   deft::kItemInts int32 per work item, see deft_internal.h
+//   tasks   workgroups of stage 1
 template <int D, int WEIGHTS, bool SHARED>
-__global__ __launch_bounds__(64 * kWaves, 2) void deft_stage1(CallArgs call) {
+__global__ __launch_bounds__(64 * kWaves, 2) void deft_stage1(const int32_t *items, uint32_t Hkv, uint32_t inv_Hkv, uint32_t tasks, CallArgs call) {
     extern __shared__ __attribute__((aligned(16))) unsigned char s_raw[];
-    if (SHARED && blockIdx.x >= call.tasks) {
-        reduce_task<D>(call, reinterpret_cast<float *>(s_raw));
+    if (SHARED && blockIdx.x >= tasks) {
+        reduce_task<D>(call, blockIdx.x - tasks, reinterpret_cast<float *>(s_raw));
         return;
     }
     const Stage1Args &a = call.s1;
-    const int item = divide(blockIdx.x, a.Hkv, a.inv_Hkv);
+    const int item = divide(blockIdx.x, Hkv, inv_Hkv);
     // KV head of this workgroup.  Workgroups b and b + 256 land on the same compute unit (the dispatcher goes
     // round the 256 units), and with Hkv dividing 256 they would stream the same head: K and V rows whose
     // addresses agree in bits 7..12.  A unit whose streams all share those bits reads measurably slower (its
     // L1 keeps fewer lines in flight), so every further round of 256 workgroups is moved on by one head.
     // The shift depends on the task only, so a task still visits every head exactly once.
-    const uint32_t turned = blockIdx.x - item * a.Hkv + ((uint32_t)(item * a.Hkv) >> 8);
-    const int h = turned - divide(turned, a.Hkv, a.inv_Hkv) * a.Hkv;
-    const int32_t *it = a.items + (size_t)item * deft::kItemInts;
+    const uint32_t turned = blockIdx.x - item * Hkv + ((uint32_t)(item * Hkv) >> 8);
+    const int h = turned - divide(turned, Hkv, inv_Hkv) * Hkv;
+    const int32_t *it = items + (size_t)item * deft::kItemInts;
     if (it[deft::kItChunks] > 1) mark_empty(a, it, h);  // (first: behind the task its descriptor would have to be read again)
     if (WEIGHTS == kTwoTerm || (WEIGHTS == kMixed && it[deft::kItPrecise]))
         run_task<D, true, SHARED>(a, it, h, s_raw);
@@ -1715,16 +1721,16 @@ bool launch_stage1(const deft::TaskSet &T, CallArgs a, unsigned reduce_groups, c
     if (T.n_items == 0) return true;
     if (!configure_stage1<D>()) return false;
     Stage1Args &a1 = a.s1;
-    a1.items = reinterpret_cast<const int32_t *>(image + T.off_items);
+    const int32_t *items = reinterpret_cast<const int32_t *>(image + T.off_items);
     a1.n_items = T.n_items;
     a1.resident_one = kResidentTiles;
     a1.resident_many = (int64_t)T.n_items * a1.Hkv <= deft::kResidentGroups ? deft::kMaxTilesPerTask : kResidentTiles;
     const size_t lds = std::max(kXbufBytes + 3 * (size_t)a1.table_len * sizeof(int32_t), (size_t)ResidentLds<D>::kWords * 4);
-    a.tasks = (unsigned)T.n_items * (unsigned)a1.Hkv;
+    const uint32_t Hkv = (uint32_t)a1.Hkv, tasks = (uint32_t)T.n_items * Hkv;
     auto *kernel = T.n_items_precise == 0           ? &deft_stage1<D, kBf16, SHARED>
                    : T.n_items_precise == T.n_items ? &deft_stage1<D, kTwoTerm, SHARED>
                                                     : &deft_stage1<D, kMixed, SHARED>;
-    hipLaunchKernelGGL(kernel, dim3(a.tasks + reduce_groups), dim3(64 * kWaves), lds, stream, a);
+    hipLaunchKernelGGL(kernel, dim3(tasks + reduce_groups), dim3(64 * kWaves), lds, stream, items, Hkv, inverse(Hkv), tasks, a);
     return hip_ok(hipGetLastError(), "deft_stage1 launch");
 }
 
@@ -1732,6 +1738,7 @@ template <int D, bool HOLES>
 bool launch_stage2(const deft::TaskSet &T, const Stage2Args &a2, hipStream_t stream) {
     if (a2.nq == 0) return true;
     const unsigned rows = (unsigned)a2.nq * (unsigned)a2.Hq;
+    const uint32_t Hq = (uint32_t)a2.Hq, ints = (uint32_t)a2.head_ints;
     constexpr int kFew = std::min(Stage2Row<D>::kBatch, deft::kQueryHeadInts - deft::kQueryHeadFixed);
     // Up to kFew partials one wave has them all in flight at once, and more waves cost more to start than they save (16
     // partials, 2048 rows of output: 5.1 us, four waves 7.5).  Beyond that a second batch is a round trip more, which a
@@ -1741,13 +1748,13 @@ bool launch_stage2(const deft::TaskSet &T, const Stage2Args &a2, hipStream_t str
     // 40.1; 8192, one in 256 of 128, 55.5, 59.1, 65.0.  (One wave to a row beyond 2048 of
     // them also keeps launches of up to 2^26 rows within the 32 bits of grid x block.)
     if (T.max_parts <= kFew)
-        hipLaunchKernelGGL((deft_stage2_few<D, HOLES>), dim3(rows), dim3(64), 0, stream, a2);
+        hipLaunchKernelGGL((deft_stage2_few<D, HOLES>), dim3(rows), dim3(64), 0, stream, a2.q_head, Hq, a2.inv_Hq, ints, a2);
     else if (rows > 2048)
-        hipLaunchKernelGGL((deft_stage2_many<D, 1, HOLES>), dim3(rows), dim3(64), 0, stream, a2);
+        hipLaunchKernelGGL((deft_stage2_many<D, 1, HOLES>), dim3(rows), dim3(64), 0, stream, a2.q_head, Hq, a2.inv_Hq, ints, a2);
     else if (rows > 1024 || T.max_parts <= 2 * 16)
-        hipLaunchKernelGGL((deft_stage2_many<D, 2, HOLES>), dim3(rows), dim3(128), 0, stream, a2);
+        hipLaunchKernelGGL((deft_stage2_many<D, 2, HOLES>), dim3(rows), dim3(128), 0, stream, a2.q_head, Hq, a2.inv_Hq, ints, a2);
     else
-        hipLaunchKernelGGL((deft_stage2_many<D, 4, HOLES>), dim3(rows), dim3(256), 0, stream, a2);
+        hipLaunchKernelGGL((deft_stage2_many<D, 4, HOLES>), dim3(rows), dim3(256), 0, stream, a2.q_head, Hq, a2.inv_Hq, ints, a2);
     return hip_ok(hipGetLastError(), "deft_stage2 launch");
 }
 
@@ -1803,7 +1810,6 @@ void stage1_args(const Call &call, const void *q, const void *k, const void *v, 
     a1.Hq = Hq;
     a1.Hkv = Hkv;
     a1.G = Hq / Hkv;
-    a1.inv_Hkv = inverse(Hkv);
     a1.inv_G = inverse(a1.G);
     a1.table_len = S.table_len;
     a1.c = call.c;

@@ -992,7 +992,7 @@ __device__ __forceinline__ void resident_task(const Stage1Args &a, const int32_t
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tile0 = it[deft::kItTile0], ntiles = it[deft::kItNTiles];
-    const int seg0 = it[deft::kItSeg0], nseg = it[deft::kItNSeg];
+    const int seg0 = it[deft::kItSeg0], nseg = it[deft::kItPieces];
     const int cqlo = it[deft::kItQlo], width = it[deft::kItWidth];
     const int slot_base = it[deft::kItSlotBase];
     float *lds = reinterpret_cast<float *>(s_raw);
@@ -1145,7 +1145,7 @@ __device__ __forceinline__ void streaming_task(const Stage1Args &a, const int32_
     const int n16 = lane & 15;
     const int g = lane >> 4;
     const int tile0 = it[deft::kItTile0], ntiles = it[deft::kItNTiles];
-    const int seg0 = it[deft::kItSeg0], nseg = it[deft::kItNSeg];
+    const int seg0 = it[deft::kItSeg0], nseg = it[deft::kItPieces];
     const int cqlo = it[deft::kItQlo];
     const int R = it[deft::kItWidth] * a.G;
     const int slot_base = it[deft::kItSlotBase];
@@ -1360,7 +1360,7 @@ enum Weights { kBf16 = 0, kTwoTerm = 1, kMixed = 2 };
 template <int D, bool PRECISE, bool SHARED>
 __device__ __forceinline__ void run_task(const Stage1Args &a, const int32_t *it, int h, unsigned char *s_raw) {
     if (it[deft::kItLen] <= kResidentTokens<D> &&
-        it[deft::kItNTiles] <= (D == 128 && it[deft::kItNSeg] == 1 ? a.resident_one : a.resident_many))
+        it[deft::kItNTiles] <= (D == 128 && it[deft::kItPieces] == 1 ? a.resident_one : a.resident_many))
         resident_task<D, PRECISE, SHARED>(a, it, h, s_raw);
     else
         streaming_task<D, PRECISE, SHARED>(a, it, h, s_raw);

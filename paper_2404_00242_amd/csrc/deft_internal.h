@@ -40,6 +40,7 @@ enum ItemField {
     kItSegQlo0 = 10,  //                its query interval
     kItSegQhi0 = 11,
     kItPrecise = 12,  // 1: the softmax weights enter the products as two bf16 terms (short paths, or on request)
+    kItPieces = 14,   // segments to tell apart: 1 where they continue one another and have the same queries, else kItNSeg
     kItChunks = 13,   // chunks worked on as one: the result goes to the slots of the first, those of the others stay empty
 };
 // A group one of whose queries has fewer tokens than this on its whole path gets two-term weights.

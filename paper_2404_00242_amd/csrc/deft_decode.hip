@@ -56,7 +56,7 @@ struct Stage1Args {
     const int32_t *q_order;
     int32_t n_items, Hq, Hkv, G;
     uint32_t inv_G;  // see divide
-    int32_t resident_one, resident_many;  // most row tiles of a task on the resident path, see kResidentTiles
+    int32_t resident_one, resident_many;  // most row tiles of a task on the resident path, see is_resident
     int32_t table_len;  // entries of the LDS per-token table: longest multi-piece chunk, in whole blocks
     float c;  // scale * log2(e): probabilities are 2^((s - m) * c)
     // A whole call in one launch: a record of 16 bytes per row of partial results, {m, l, mark}, and what this call writes
@@ -1357,10 +1357,27 @@ __device__ __forceinline__ void streaming_task(const Stage1Args &a, const int32_
 // the same kind of weights, which is most of them, run a kernel that holds that kind alone.
 enum Weights { kBf16 = 0, kTwoTerm = 1, kMixed = 2 };
 
+// Which tasks take the resident path, by row tiles.  A resident task costs its loads and then a fixed time per tile (0.4 us
+// for 128 tokens, 0.7 us for 256, two workgroups to a compute unit); a streaming task overlaps the two, but takes a step
+// per 32 tokens (1.2 us and more where rows are looked up token by token, as in chunks of several pieces, and with d = 64,
+// which has no fast addressing).  One piece and d = 128: up to three tiles; four tiles of 256 tokens on a full chip are
+// 17.5 us streamed and 20.3 us resident, and seven tiles beside narrow tasks 20.9 and 23.9 us a call (32 queries x 4 heads
+// over 7281 tokens).  Several pieces or d = 64: any number.  One such task among tasks of one piece is what its launch
+// waits for (2977 tokens under 50 queries x 4 heads, 16 of 712 workgroups, 24.6 -> 22.2 us a call), d = 64 under 31 queries
+// x 4 heads 21.0 -> 18.7; on launches of several rounds it is level: 952 workgroups 52.6 -> 51.3, 1696 78.3 -> 77.1, 704
+// 37.4 -> 37.8, 896 38.5 -> 38.9, 3064 70.6 -> 70.4.
+// (The limits are arguments of the kernel: as constants the compiler lays the kernel's registers out otherwise, and narrow
+// streaming tasks take 2 to 8 % longer.)
+constexpr int kResidentTiles = 3;
+template <int D>
+__device__ __forceinline__ bool is_resident(const Stage1Args &a, const int32_t *it) {
+    return it[deft::kItLen] <= kResidentTokens<D> &&
+           it[deft::kItNTiles] <= (D == 128 && it[deft::kItPieces] == 1 ? a.resident_one : a.resident_many);
+}
+
 template <int D, bool PRECISE, bool SHARED>
 __device__ __forceinline__ void run_task(const Stage1Args &a, const int32_t *it, int h, unsigned char *s_raw) {
-    if (it[deft::kItLen] <= kResidentTokens<D> &&
-        it[deft::kItNTiles] <= (D == 128 && it[deft::kItPieces] == 1 ? a.resident_one : a.resident_many))
+    if (is_resident<D>(a, it))
         resident_task<D, PRECISE, SHARED>(a, it, h, s_raw);
     else
         streaming_task<D, PRECISE, SHARED>(a, it, h, s_raw);
@@ -1706,16 +1723,6 @@ bool configure_stage1() {
     return true;
 }
 
-// Which tasks of a launch take the resident path, by row tiles.  A resident task costs its loads and then a fixed time
-// per tile (0.4 us for 128 tokens, 0.7 us for 256, two workgroups to a compute unit); a streaming task overlaps the two,
-// but takes a step per 32 tokens (1.2 us and more where rows are looked up token by token, as in chunks of several
-// pieces, and with d = 64, which has no fast addressing).  One tile: resident always (8191 tokens of one sequence, 512
-// tasks of one tile: stage 1 11.5 -> 8.1 us).  One piece: up to three tiles; four tiles of 256 tokens on a full chip
-// are 17.5 us streamed and 20.3 us resident.  Several pieces or d = 64: any number while the launch is one round of
-// workgroups (432 tasks of five tiles over 16-token pages: 15.8 -> 12.6 us), three when it is not and the loads of
-// other tasks cover a streaming task's steps (1328 tasks, 256 queries: 96.1 us with five, 95.0 us with three).
-constexpr int kResidentTiles = 3;
-
 template <int D, bool SHARED>
 bool launch_stage1(const deft::TaskSet &T, CallArgs a, unsigned reduce_groups, const uint8_t *image, hipStream_t stream) {
     if (T.n_items == 0) return true;
@@ -1724,7 +1731,7 @@ bool launch_stage1(const deft::TaskSet &T, CallArgs a, unsigned reduce_groups, c
     const int32_t *items = reinterpret_cast<const int32_t *>(image + T.off_items);
     a1.n_items = T.n_items;
     a1.resident_one = kResidentTiles;
-    a1.resident_many = (int64_t)T.n_items * a1.Hkv <= deft::kResidentGroups ? deft::kMaxTilesPerTask : kResidentTiles;
+    a1.resident_many = deft::kMaxTilesPerTask;
     const size_t lds = std::max(kXbufBytes + 3 * (size_t)a1.table_len * sizeof(int32_t), (size_t)ResidentLds<D>::kWords * 4);
     const uint32_t Hkv = (uint32_t)a1.Hkv, tasks = (uint32_t)T.n_items * Hkv;
     auto *kernel = T.n_items_precise == 0           ? &deft_stage1<D, kBf16, SHARED>

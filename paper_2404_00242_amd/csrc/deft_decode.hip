@@ -1408,15 +1408,33 @@ struct Stage2Row {
     static constexpr int kBatch = 8 * kRows;     // rows a wave keeps in flight in registers
 };
 
+// Maximum and sum over the wave, in every lane: within rows of 16 lanes by moves inside the vector unit (lane ^ 1, lane ^ 2,
+// then the halves of a row and the row itself mirrored, whose quads hold one value by then), across rows by swaps.  Six
+// exchanges through the LDS hardware, one after the other, take 0.3 us each time.
+template <int CTRL>
+__device__ __forceinline__ float row_move(float x) {
+    const int u = __builtin_bit_cast(int, x);
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(u, u, CTRL, 0xf, 0xf, false));
+}
+template <typename Op>
+__device__ __forceinline__ float wave_all(float x, Op op) {
+    x = op(x, row_move<0xb1>(x));   // quad_perm 1 0 3 2
+    x = op(x, row_move<0x4e>(x));   // quad_perm 2 3 0 1
+    x = op(x, row_move<0x141>(x));  // row_half_mirror
+    x = op(x, row_move<0x140>(x));  // row_mirror
+    const uint32_t u = __builtin_bit_cast(uint32_t, x);
+    const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    const uint32_t a0 = a[0], a1 = a[1];
+    const uint32_t w = __builtin_bit_cast(uint32_t, op(__builtin_bit_cast(float, a0), __builtin_bit_cast(float, a1)));
+    const auto b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+    const uint32_t b0 = b[0], b1 = b[1];
+    return op(__builtin_bit_cast(float, b0), __builtin_bit_cast(float, b1));
+}
 __device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x = fmaxf(x, __shfl_xor(x, o));
-    return x;
+    return wave_all(x, [](float a, float b) { return fmaxf(a, b); });
 }
 __device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
-    return x;
+    return wave_all(x, [](float a, float b) { return a + b; });
 }
 
 // HOLES: some slots of the list may have been marked empty by a whole call (m = -inf, l = 0).  Their rows of acc were not

@@ -357,9 +357,11 @@ def deft_tree_attn_decode(plan: Plan, q, k, v, out=None, scale: float = 0.0, out
     bf16 = torch.bfloat16
     if not (q.is_cuda and k.is_cuda and v.is_cuda):
         raise DeftError(-1, "deft_tree_attn_decode: q, k, v must be device tensors (there is no CPU path)")
-    for name, t in (("q", q), ("k", k), ("v", v)):
-        if t.dtype != bf16 or not t.is_contiguous() or t.dim() != 3:
-            raise DeftError(-1, f"deft_tree_attn_decode: {name} must be a contiguous 3-d bf16 tensor")
+    if not (q.dtype == k.dtype == v.dtype == bf16 and q.dim() == k.dim() == v.dim() == 3 and q.is_contiguous()
+            and k.is_contiguous() and v.is_contiguous()):
+        for name, t in (("q", q), ("k", k), ("v", v)):
+            if t.dtype != bf16 or not t.is_contiguous() or t.dim() != 3:
+                raise DeftError(-1, f"deft_tree_attn_decode: {name} must be a contiguous 3-d bf16 tensor")
     nq, Hq, d = q.shape
     ntok, Hkv, d2 = shape = k.shape
     if v.shape != shape or d2 != d:
@@ -371,7 +373,8 @@ def deft_tree_attn_decode(plan: Plan, q, k, v, out=None, scale: float = 0.0, out
         raise DeftError(-1, "deft_tree_attn_decode: the plan addresses rows beyond the KV cache")
     dev = q.device
     if out is None:
-        out = torch.empty((nq, Hq, d), dtype=out_dtype or bf16, device=dev)
+        # (empty_like costs half a microsecond less than naming shape, type and device)
+        out = torch.empty_like(q) if out_dtype is None or out_dtype == bf16 else torch.empty_like(q, dtype=out_dtype)
     elif out.shape != (nq, Hq, d) or not out.is_contiguous() or out.device != dev:
         raise DeftError(-1, "deft_tree_attn_decode: out must be a contiguous [nq, Hq, d] tensor on q's device")
     if out.dtype == bf16:
@@ -391,5 +394,6 @@ def deft_tree_attn_decode(plan: Plan, q, k, v, out=None, scale: float = 0.0, out
     rc = (_lib or load_library()).deft_tree_attn_decode(
         plan._h, img.data_ptr(), q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), Hq, Hkv, d, float(scale), flags,
         ws.data_ptr(), ws.numel() * ws.element_size(), raw)
-    _check(rc, "deft_tree_attn_decode")
+    if rc != 0:
+        _check(rc, "deft_tree_attn_decode")
     return out

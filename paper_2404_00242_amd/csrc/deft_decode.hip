@@ -32,7 +32,6 @@
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
-#include <random>
 #include <string>
 #include <thread>
 #include <type_traits>
@@ -89,7 +88,6 @@ struct Stage2Args {
 struct CallArgs {
     Stage1Args s1;
     Stage2Args s2;
-    int32_t wide_reduce;  // 1: a workgroup of stage 2 takes one row of the output, 0: one in each wave
 };
 
 // floor(n / d) for any n and d > 0, given inverse(d); a division by a run-time number costs a workgroup 0.3 us otherwise
@@ -1576,34 +1574,37 @@ __global__ __launch_bounds__(64 * WAVES) void deft_stage2_many(const int32_t *q_
     store_out(a, ((size_t)q_user * a.Hq + qh) * D + 4 * col, sum * (total > 0.f ? 1.f / total : 0.f));
 }
 
-// Stage 2 of a whole call in one launch.  Its workgroups come last in the grid: workgroups are started in the order of
-// their ids, on every XCD for itself, so whichever of these runs, all that it waits for run or have run already, and none of
-// those waits for anything.  (The wait gives up in any case, after seconds; the row is then not a number.)
+// Stage 2 of a whole call in one launch, at the end of the grid: a wave takes every (kWaves * groups)th row of the output and
+// waits for its partial results.  Every such wait ends.  Stage 1 waits for nothing, and the workgroups that wait, kReduceGroups
+// at most, leave it the rest of the 512 places of the chip: calls that overlap on the 32 hardware queues hold half of them if
+// every one has come this far, and workgroups are started in the order of their ids, so that as a rule what is waited for runs
+// already.  With a workgroup for every four rows, up to 256 a call, a few overlapping calls could have held all places of
+// one XCD each and waited for work that needs a place on the other's.  (The wait gives up after 2^22 polls, seconds, in any
+// case; the row is then not a number.)
 constexpr int kMarkPolls = 1 << 22;
+constexpr uint32_t kReduceGroups = 8;
+constexpr int kReduceLoads = 16;  // loads of a wave in flight, each of 16 bytes a lane: 32 partial results at d = 128, 64 at d = 64
 template <int D>
-__device__ __forceinline__ void reduce_task(const CallArgs &call, uint32_t id, float *lds) {
+__device__ __forceinline__ void reduce_row(const CallArgs &call, uint32_t row) {
     using R = Stage2Row<D>;
+    constexpr int kLoads = kReduceLoads;
     const Stage2Args &a = call.s2;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t row = call.wide_reduce ? id : kWaves * id + wave;
-    const int waves = call.wide_reduce ? kWaves : 1, first = call.wide_reduce ? wave : 0;
+    const int lane = threadIdx.x & 63;
     const int p = divide(row, a.Hq, a.inv_Hq), qh = row - p * a.Hq;
-    if (p >= a.nq) return;  // (only where every wave has a row of its own)
     const int32_t *rec = a.q_head + (size_t)p * a.head_ints;
-    int slot = rec[min(deft::kQueryHeadFixed + waves * lane + first, a.head_ints - 1)];
+    int slot = rec[min(deft::kQueryHeadFixed + lane, a.head_ints - 1)];
     const int n = rec[0], q_user = rec[1], s0 = rec[2];
     const int sub = lane / R::kLanes, col = lane - sub * R::kLanes;
-    const int mine = call.wide_reduce ? (n - wave + kWaves - 1) / kWaves : n;
+    const int kvh = divide(qh, call.s1.G, call.s1.inv_G);
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     float M = -INFINITY, lsum = 0.f;
-    for (int base = 0; base < mine; base += 64) {
-        const int cnt = min(64, mine - base);
+    for (int base = 0; base < n; base += 64) {
+        const int cnt = min(64, n - base);
         if (n > a.head_ints - deft::kQueryHeadFixed)
-            slot = a.q_part_slot[s0 + waves * (base + min(lane, cnt - 1)) + first];
+            slot = a.q_part_slot[s0 + base + min(lane, cnt - 1)];
         else if (base > 0)
-            slot = rec[deft::kQueryHeadFixed + waves * (base + min(lane, cnt - 1)) + first];
+            slot = rec[deft::kQueryHeadFixed + base + min(lane, cnt - 1)];
         slot = __shfl(slot, min(lane, cnt - 1));  // lanes past the end hold a slot that exists
-        const int kvh = divide(qh, call.s1.G, call.s1.inv_G);
         float *record = call.s1.marks + 4 * (((size_t)kvh * call.s1.n_slots + slot) * call.s1.G + (qh - kvh * call.s1.G));
         uint64_t *mark = mark_of(record);
         bool there = lane >= cnt;
@@ -1618,12 +1619,18 @@ __device__ __forceinline__ void reduce_task(const CallArgs &call, uint32_t id, f
             ml = __builtin_bit_cast(f32x2, __hip_atomic_load(reinterpret_cast<uint64_t *>(record), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
         const float mj = ml[0], lj = ml[1];
         float w = 0.f;
-        for (int j = 0; j < cnt; j += R::kBatch) {
-            f32x4 x[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
+        for (int j = 0; j < cnt; j += kLoads * R::kRows) {
+            f32x4 x[kLoads];
+            auto load = [&](int u) {
                 const int sj = __shfl(slot, (j + u * R::kRows + sub) & 63);
                 x[u] = load_shared4(a.part_acc + ((size_t)sj * a.Hq + qh) * D + 4 * col);
+            };
+            const bool half = cnt - j <= kLoads / 2 * R::kRows;
+#pragma unroll
+            for (int u = 0; u < kLoads / 2; ++u) load(u);
+            if (!half) {
+#pragma unroll
+                for (int u = kLoads / 2; u < kLoads; ++u) load(u);
             }
             if (j == 0) {
                 if (lane < cnt) __hip_atomic_store(mark, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1636,34 +1643,17 @@ __device__ __forceinline__ void reduce_task(const CallArgs &call, uint32_t id, f
                 M = top;
             }
 #pragma unroll
-            for (int u = 0; u < 8; ++u) acc += __shfl(w, (j + u * R::kRows + sub) & 63) * x[u];
+            for (int u = 0; u < kLoads / 2; ++u) acc += __shfl(w, (j + u * R::kRows + sub) & 63) * x[u];
+            if (!half) {
+#pragma unroll
+                for (int u = kLoads / 2; u < kLoads; ++u) acc += __shfl(w, (j + u * R::kRows + sub) & 63) * x[u];
+            }
         }
     }
 #pragma unroll
     for (int o = 32; o >= R::kLanes; o >>= 1)
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], o);
-    if (call.wide_reduce) {
-        float *s_m = lds + kWaves * D, *s_l = s_m + kWaves;
-        if (sub == 0) *reinterpret_cast<f32x4 *>(lds + wave * D + 4 * col) = acc;
-        if (lane == 0) {
-            s_m[wave] = M;
-            s_l[wave] = lsum;
-        }
-        __syncthreads();
-        if (wave != 0) return;
-        float top = -INFINITY;
-#pragma unroll
-        for (int k = 0; k < kWaves; ++k) top = fmaxf(top, s_m[k]);
-        acc = f32x4{0.f, 0.f, 0.f, 0.f};
-        lsum = 0.f;
-#pragma unroll
-        for (int k = 0; k < kWaves; ++k) {
-            const float w = top == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((s_m[k] - top) * a.c);
-            lsum += w * s_l[k];
-            acc += w * *reinterpret_cast<const f32x4 *>(lds + k * D + 4 * col);
-        }
-    }
     if (sub == 0) store_out(a, ((size_t)q_user * a.Hq + qh) * D + 4 * col, acc * (lsum > 0.f ? 1.f / lsum : 0.f));
 }
 
@@ -1674,7 +1664,8 @@ template <int D, int WEIGHTS, bool SHARED>
 __global__ __launch_bounds__(64 * kWaves, 2) void deft_stage1(const int32_t *items, uint32_t Hkv, uint32_t inv_Hkv, uint32_t tasks, CallArgs call) {
     extern __shared__ __attribute__((aligned(16))) unsigned char s_raw[];
     if (SHARED && blockIdx.x >= tasks) {
-        reduce_task<D>(call, blockIdx.x - tasks, reinterpret_cast<float *>(s_raw));
+        const uint32_t rows = (uint32_t)call.s2.nq * (uint32_t)call.s2.Hq, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        for (uint32_t row = kWaves * (blockIdx.x - tasks) + wave; row < rows; row += kWaves * (gridDim.x - tasks)) reduce_row<D>(call, row);
         return;
     }
     const Stage1Args &a = call.s1;
@@ -1907,7 +1898,8 @@ int run_stage2(const deft_plan_t *plan, const Call &call, const deft::TaskSet &T
 
 // A number that no call of this process has had and that no memory is likely to hold.
 uint64_t new_ticket() {
-    static std::atomic<uint64_t> last{((uint64_t)std::random_device{}() << 32) ^ std::random_device{}()};
+    static std::atomic<uint64_t> last{(uint64_t)std::chrono::steady_clock::now().time_since_epoch().count() ^
+                                      (uint64_t)reinterpret_cast<uintptr_t>(&hip_ok)};
     uint64_t x = last.fetch_add(0x9e3779b97f4a7c15ull, std::memory_order_relaxed);  // splitmix64
     x = (x ^ (x >> 30)) * 0xbf58476d1ce4e5b9ull;
     x = (x ^ (x >> 27)) * 0x94d049bb133111ebull;
@@ -1927,25 +1919,26 @@ int run_call(const deft_plan_t *plan, const Call &call, const void *q, const voi
     a.s1.ticket = new_ticket();
     a.s1.n_slots = plan->n_slots();
     const unsigned rows = (unsigned)plan->nq * (unsigned)Hq;
-    a.wide_reduce = T.max_parts > 16 && rows <= 512;
-    const unsigned groups = a.wide_reduce ? rows : (rows + kWaves - 1) / kWaves;
+    const unsigned groups = std::min((rows + kWaves - 1) / kWaves, kReduceGroups);
     const bool ok = d == 128 ? launch_stage1<128, true>(T, a, groups, call.img, call.stream)
                              : launch_stage1<64, true>(T, a, groups, call.img, call.stream);
     return ok ? DEFT_OK : DEFT_EHIP;
 }
 
 // Which calls are made in one launch.  It saves the host 2 to 3 us and the GPU the microsecond between two kernels, but
-// stage 2 then shares the chip with stage 1 at stage 1's size of workgroup, and partial results cross the caches one by
-// one.  So: the calls that the host's work bounds, those of few bytes, and few partial results.  Whole call, us, two
-// launches -> one: 384 tokens x 4 heads 10.4 -> 8.2; 1659 tokens under one query 12.6 -> 9.4; 8191 tokens (34 MB) 11.9 ->
-// 11.2; 33 MB and 960 rows of partial results 12.1 -> 10.7; 22 MB and 4032 rows 12.3 -> 12.2; 21 MB and 8096 rows 12.6 ->
-// 13.0, 38 MB and 10880 rows 16.0 -> 17.5; 47 MB and 1704 rows 14.7 -> 15.7; 17 MB, 4312 rows 13.0 -> 13.5.  A thousand
-// rows of output are too many as well: 1024 of them, 4.5 MB and 2240 partial ones 12.3 -> 12.6, 896 of them 12.4 -> 9.3.
+// partial results cross the caches one by one, and the few waves that stage 2 has (reduce_row) take some 2 us for every
+// further batch: a row of the output for each of them, or kReduceLoads loads of a row's partial results.  So: one batch where
+// K and V are of a size that the host's work is a good part of the call, two where they are small.  Whole call, us, two
+// launches -> one: one batch, 0.4 MB 11.8 -> 8.8, 6.8 MB 11.8 -> 8.8, 23 MB 11.3 -> 9.1, 33 MB 11.5 -> 10.5; two, 7 MB 11.4
+// -> 9.6, 16 MB 11.6 -> 9.5, but 20 MB 11.3 -> 12.2, 34 MB 11.7 -> 11.5, 38 MB 14.2 -> 15.1; three, 1.7 MB 11.4 -> 12.2, 5 MB
+// 11.6 -> 13.0 or 10.1.
 bool one_launch(const deft_plan_t *plan, const Call &call, int32_t Hq, int32_t Hkv, int32_t d) {
-    constexpr int64_t kFewRows = 1024, kFewPartials = 4096, kFewBytes = 40 << 20;
+    constexpr int64_t kWavesOfRows = kWaves * kReduceGroups;
     if (!call.marks || plan->nq == 0 || call.S->fused.n_items == 0) return false;
-    return (int64_t)plan->nq * Hq < kFewRows && (int64_t)plan->n_slots() * Hq <= kFewPartials &&
-           (int64_t)plan->n_flat * Hkv * d * 4 <= kFewBytes;
+    const int64_t parts = d == 128 ? kReduceLoads * Stage2Row<128>::kRows : kReduceLoads * Stage2Row<64>::kRows;
+    const int64_t batches = (((int64_t)plan->nq * Hq + kWavesOfRows - 1) / kWavesOfRows) * ((call.S->fused.max_parts + parts - 1) / parts);
+    const int64_t bytes = (int64_t)plan->n_flat * Hkv * d * 4;
+    return (batches <= 1 && bytes <= (40 << 20)) || (batches <= 2 && bytes <= (16 << 20));
 }
 
 // Pinned host staging for plan images: a ring of slots per device, allocated at the first upload on that

@@ -21,7 +21,7 @@
 // are merged in LDS before one (m, l, acc) triple per (chunk, row) is written.
 //
 // Stage 2 (deft_stage2_few, deft_stage2_many): one, two or four waves per (query, query head) merge that query's partial
-// results with the log-sum-exp weights of eq. 1.
+// results with the log-sum-exp weights of eq. 1.  Small whole calls have both stages in one launch (reduce_row).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -1642,11 +1642,16 @@ __device__ __forceinline__ void reduce_row(const CallArgs &call, uint32_t row) {
                 acc *= old;
                 M = top;
             }
+            auto add = [&](int u) {  // (rows past the end repeat the last one, which may hold infinities: no weight of 0 for them)
+                const int r = j + u * R::kRows + sub;
+                const float wr = __shfl(w, r & 63);
+                if (r < cnt) acc += wr * x[u];
+            };
 #pragma unroll
-            for (int u = 0; u < kLoads / 2; ++u) acc += __shfl(w, (j + u * R::kRows + sub) & 63) * x[u];
+            for (int u = 0; u < kLoads / 2; ++u) add(u);
             if (!half) {
 #pragma unroll
-                for (int u = kLoads / 2; u < kLoads; ++u) acc += __shfl(w, (j + u * R::kRows + sub) & 63) * x[u];
+                for (int u = kLoads / 2; u < kLoads; ++u) add(u);
             }
         }
     }

@@ -157,3 +157,16 @@ def test_captured_calls_replayed_with_eager_calls_between():
         close(out, two_launches(plan, t, q, k, v), v)
         if i == 1:
             binding.deft_tree_attn_decode(plan, q, k, v, workspace=ws)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("token", [0, 2047, 1000])
+def test_infinite_value_in_any_partial_result(token, d):
+    t = star(2048, 0, 0, 4, 4, d)  # whole blocks, a path long enough for single-term weights
+    plan, q, k, v = prepared(t, 128)
+    want = binding.deft_tree_attn_decode(plan, q, k, v, out_dtype=torch.float32)
+    v[token, :, 5] = float("inf")
+    got = binding.deft_tree_attn_decode(plan, q, k, v, out_dtype=torch.float32)
+    assert (got[..., 5] == float("inf")).all()
+    keep = [i for i in range(d) if i != 5]
+    assert torch.equal(got[..., keep], want[..., keep])

@@ -1949,8 +1949,9 @@ bool one_launch(const deft_plan_t *plan, const Call &call, int32_t Hq, int32_t H
 // Pinned host staging for plan images: a ring of slots per device, allocated at the first upload on that
 // device and kept until the process ends.  An image is copied into the next slot and fetched from there by a
 // kernel on the stream, so deft_plan_upload neither waits for the stream nor depends on the plan staying
-// alive.  A slot is reused only after that kernel has read it, which its flags say.  In a stream that is being captured
-// the image is sent by a copy command instead, and an event behind it guards the slot.
+// alive.  A slot is reused only after that kernel has read it, which its flags say.  In a stream that is being captured,
+// or to memory that is not of the stream's device, the image is sent by a copy command instead, and an event behind it
+// guards the slot.
 constexpr int kStageSlots = 8;
 constexpr size_t kStageSlotBytes = DEFT_STAGED_IMAGE_BYTES;
 constexpr uint32_t kStageFlags = (kStageSlotBytes / 16 + kFetchThreads - 1) / kFetchThreads;  // workgroups of a fetch, at most
@@ -1983,6 +1984,18 @@ bool wait_for_slot(Staging &g, int i) {
     for (int polls = 0; !fetched(); ++polls)  // (the work in front of the fetch may take long)
         if (polls >= 1000) std::this_thread::sleep_for(std::chrono::microseconds(10));
     return true;
+}
+
+// Whether a kernel on this stream may write there.  A copy command reaches any memory, a kernel that of its own device; the
+// memory of another one, or of the host, may not be mapped for it.
+bool on_stream_device(const void *p, hipStream_t st, int dev) {
+    hipPointerAttribute_t at{};
+    hipDevice_t stream_dev = dev;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess || (st && hipStreamGetDevice(st, &stream_dev) != hipSuccess)) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return at.type == hipMemoryTypeDevice && at.device == stream_dev;
 }
 
 // Returns 1 when the image went out through the ring, 0 when the caller has to take the plain path
@@ -2022,7 +2035,7 @@ int upload_staged(void *dev_image, const uint8_t *src, size_t bytes, hipStream_t
     Staging::Slot &s = g.slot[i];
     uint8_t *slot = g.base + (size_t)i * kStageSlotBytes;
     std::memcpy(slot, src, bytes);
-    if (capture != hipStreamCaptureStatusNone) {
+    if (capture != hipStreamCaptureStatusNone || !on_stream_device(dev_image, st, dev)) {
         if (!hip_ok(hipMemcpyAsync(dev_image, slot, bytes, hipMemcpyHostToDevice, st), "plan upload")) return -1;
         if (!hip_ok(hipEventRecord(s.done, st), "staging event record")) return -1;
         s.event_pending = true;

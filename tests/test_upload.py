@@ -47,6 +47,20 @@ def test_image_arrives_whole_and_nothing_behind_it(n):
     assert (img[end:] == 0xAB).all()
 
 
+def test_image_in_pinned_host_memory():
+    """memory that is not the stream's device's takes the copy command; the slots around it are reused as before"""
+    st = torch.cuda.current_stream().cuda_stream
+    for i in range(20):
+        plan, begins, lens = forest(50 + i)
+        size = plan.device_bytes(4, 4)
+        img = torch.full((size + 64,), 0xAB, dtype=torch.uint8, device="cuda") if i % 2 else \
+            torch.full((size + 64,), 0xAB, dtype=torch.uint8, pin_memory=True)
+        assert binding.load_library().deft_plan_upload(plan.handle, 4, 4, img.data_ptr(), size, st) == 0
+        torch.cuda.synchronize()
+        end = check(plan, begins, lens, img)
+        assert (img[end:] == 0xAB).all()
+
+
 def test_more_uploads_than_slots_in_two_streams():
     plans = [forest(40 + 37 * i) for i in range(30)]
     streams = [torch.cuda.Stream(), torch.cuda.Stream()]

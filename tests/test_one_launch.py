@@ -159,6 +159,17 @@ def test_captured_calls_replayed_with_eager_calls_between():
             binding.deft_tree_attn_decode(plan, q, k, v, workspace=ws)
 
 
+@pytest.mark.parametrize("dtype", [None, torch.float32])
+def test_output_of_one_query_from_a_wider_tensor_has_plain_strides(dtype):
+    t = star(200, 0, 0, 8, 2, 64)
+    plan, q, k, v = prepared(t, 64)
+    wide = torch.cat([q, q, q], 1)[:, : t.Hq]
+    assert wide.is_contiguous() and wide.stride(0) == 3 * t.Hq * t.d
+    got = binding.deft_tree_attn_decode(plan, wide, k, v, out_dtype=dtype)
+    assert got.stride() == (t.Hq * t.d, t.d, 1)
+    assert torch.equal(got, binding.deft_tree_attn_decode(plan, q, k, v, out_dtype=dtype))
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("token", [0, 2047, 1000])
 def test_infinite_value_in_any_partial_result(token, d):

@@ -147,9 +147,9 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
 }
 
 // In a whole call of one launch, stage 2 may not read a row of partial results before the row is complete.  The wave that
-// wrote it waits until its stores have arrived and then writes the call's ticket into the row's mark; stage 2's wave waits
-// for the ticket and takes it out again.  Every call has a ticket of its own, 64 bits, so a mark needs no value to start
-// from (whatever a workspace holds, it is not the ticket), and a captured call finds its marks cleared when it is replayed.
+// wrote it waits until its stores have arrived and then writes the call's ticket into the row's mark, for which stage 2's wave
+// waits.  Every call has a ticket of its own, 64 bits, so a mark needs no value to start from: whatever a workspace holds,
+// it is not the ticket.  (Not so in the replays of a captured call, which would all have one ticket: see one_launch.)
 __device__ __forceinline__ uint64_t *mark_of(float *record) { return reinterpret_cast<uint64_t *>(record) + 1; }
 __device__ __forceinline__ void publish_rows(const Stage1Args &a, bool mine, size_t record) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1633,7 +1633,6 @@ __device__ __forceinline__ void reduce_row(const CallArgs &call, uint32_t row) {
                 for (int u = kLoads / 2; u < kLoads; ++u) load(u);
             }
             if (j == 0) {
-                if (lane < cnt) __hip_atomic_store(mark, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 const float top = fmaxf(M, wave_max(mj));
                 const float old = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((M - top) * a.c);
                 w = (lane < cnt && top != -INFINITY) ? __builtin_amdgcn_exp2f((mj - top) * a.c) : 0.f;
@@ -1930,6 +1929,16 @@ int run_call(const deft_plan_t *plan, const Call &call, const void *q, const voi
     return ok ? DEFT_OK : DEFT_EHIP;
 }
 
+// Whether what is enqueued on a stream now is recorded and run later, any number of times.  (The null stream's never is.)
+bool is_captured(hipStream_t st) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (st && hipStreamIsCapturing(st, &capture) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;  // nobody can tell: whatever suits both
+    }
+    return capture != hipStreamCaptureStatusNone;
+}
+
 // Which calls are made in one launch.  It saves the host 2 to 3 us and the GPU the microsecond between two kernels, but
 // partial results cross the caches one by one, and the few waves that stage 2 has (reduce_row) take some 2 us for every
 // further batch: a row of the output for each of them, or kReduceLoads loads of a row's partial results.  So: one batch where
@@ -1937,13 +1946,15 @@ int run_call(const deft_plan_t *plan, const Call &call, const void *q, const voi
 // launches -> one: one batch, 0.4 MB 11.8 -> 8.8, 6.8 MB 11.8 -> 8.8, 23 MB 11.3 -> 9.1, 33 MB 11.5 -> 10.5; two, 7 MB 11.4
 // -> 9.6, 16 MB 11.6 -> 9.5, but 20 MB 11.3 -> 12.2, 34 MB 11.7 -> 11.5, 38 MB 14.2 -> 15.1; three, 1.7 MB 11.4 -> 12.2, 5 MB
 // 11.6 -> 13.0 or 10.1.
+// A captured call takes two: its replays have no host to spare and the GPU is the slower for it (0.4 MB 6.4 -> 6.9, 16 MB 6.8 ->
+// 7.5, 5 MB under 56 rows 7.5 -> 11.3), and their marks could hold the ticket from the replay before.
 bool one_launch(const deft_plan_t *plan, const Call &call, int32_t Hq, int32_t Hkv, int32_t d) {
     constexpr int64_t kWavesOfRows = kWaves * kReduceGroups;
     if (!call.marks || plan->nq == 0 || call.S->fused.n_items == 0) return false;
     const int64_t parts = d == 128 ? kReduceLoads * Stage2Row<128>::kRows : kReduceLoads * Stage2Row<64>::kRows;
     const int64_t batches = (((int64_t)plan->nq * Hq + kWavesOfRows - 1) / kWavesOfRows) * ((call.S->fused.max_parts + parts - 1) / parts);
     const int64_t bytes = (int64_t)plan->n_flat * Hkv * d * 4;
-    return (batches <= 1 && bytes <= (40 << 20)) || (batches <= 2 && bytes <= (16 << 20));
+    return ((batches <= 1 && bytes <= (40 << 20)) || (batches <= 2 && bytes <= (16 << 20))) && !is_captured(call.stream);
 }
 
 // Pinned host staging for plan images: a ring of slots per device, allocated at the first upload on that
@@ -2005,11 +2016,7 @@ int upload_staged(void *dev_image, const uint8_t *src, size_t bytes, hipStream_t
     if (bytes > kStageSlotBytes) return 0;
     if (!hip_ok(hipGetDevice(&dev), "hipGetDevice")) return -1;
     if (dev < 0 || dev >= 64) return 0;
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (st && hipStreamIsCapturing(st, &capture) != hipSuccess) {  // (the null stream cannot be captured)
-        (void)hipGetLastError();
-        capture = hipStreamCaptureStatusInvalidated;  // the copy below gives the error that there is to give
-    }
+    const bool captured = is_captured(st);
     Staging &g = g_staging[dev];
     std::lock_guard<std::mutex> lock(g.mu);
     if (!g.base) {
@@ -2035,7 +2042,7 @@ int upload_staged(void *dev_image, const uint8_t *src, size_t bytes, hipStream_t
     Staging::Slot &s = g.slot[i];
     uint8_t *slot = g.base + (size_t)i * kStageSlotBytes;
     std::memcpy(slot, src, bytes);
-    if (capture != hipStreamCaptureStatusNone || !on_stream_device(dev_image, st, dev)) {
+    if (captured || !on_stream_device(dev_image, st, dev)) {
         if (!hip_ok(hipMemcpyAsync(dev_image, slot, bytes, hipMemcpyHostToDevice, st), "plan upload")) return -1;
         if (!hip_ok(hipEventRecord(s.done, st), "staging event record")) return -1;
         s.event_pending = true;

@@ -3,6 +3,8 @@
 The same call in two launches, which a workspace without room for the marks gives, is the reference: both sum the same
 partial results in fp32, in another order, so outputs differ by a few units of 2^-24 of the attention of |V|."""
 
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -181,3 +183,29 @@ def test_infinite_value_in_any_partial_result(token, d):
     assert (got[..., 5] == float("inf")).all()
     keep = [i for i in range(d) if i != 5]
     assert torch.equal(got[..., keep], want[..., keep])
+
+
+@pytest.mark.parametrize("i", [0, 3, 8, 15])
+def test_captured_call_takes_two_launches(i):
+    # replays have no host work to save, and all of them would write one ticket into the marks
+    t, chunk = TREES[i]
+    assert batches(t, prepared(t, chunk)[0]) == 1
+    plan, q, k, v = prepared(t, chunk)
+    ws = torch.empty(plan.workspace_bytes(t.Hq, t.Hkv, t.d), dtype=torch.uint8, device="cuda")
+    out = torch.zeros((t.nq, t.Hq, t.d), dtype=torch.float32, device="cuda")
+    binding.deft_tree_attn_decode(plan, q, k, v, out=out, workspace=ws)
+    torch.cuda.synchronize()
+    side, g = torch.cuda.Stream(), torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(g, stream=side):
+        binding.deft_tree_attn_decode(plan, q, k, v, out=out, workspace=ws, stream=side)
+    n = ctypes.c_size_t(0)
+    assert binding.load_library().hipGraphGetNodes(ctypes.c_void_p(g.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    assert n.value == 2
+    g.instantiate()
+    want = two_launches(plan, t, q, k, v)
+    for _ in range(3):
+        out.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)

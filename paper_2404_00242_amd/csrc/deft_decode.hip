@@ -88,6 +88,7 @@ struct Stage2Args {
 struct CallArgs {
     Stage1Args s1;
     Stage2Args s2;
+    int32_t polls;  // most looks at a mark before stage 2 leaves a row to stage 1 (reduce_rows)
 };
 
 // floor(n / d) for any n and d > 0, given inverse(d); a division by a run-time number costs a workgroup 0.3 us otherwise
@@ -147,13 +148,22 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
 }
 
 // In a whole call of one launch, stage 2 may not read a row of partial results before the row is complete.  The wave that
-// wrote it waits until its stores have arrived and then writes the call's ticket into the row's mark, for which stage 2's wave
+// wrote it waits until its stores have arrived and then puts the call's ticket into the row's mark, for which stage 2's wave
 // waits.  Every call has a ticket of its own, 64 bits, so a mark needs no value to start from: whatever a workspace holds,
 // it is not the ticket.  (Not so in the replays of a captured call, which would all have one ticket: see one_launch.)
+// The mark is exchanged and not just stored, for a wave of stage 2 that would not wait any longer has left word in it, the
+// ticket's complement: see reduce_rows.
 __device__ __forceinline__ uint64_t *mark_of(float *record) { return reinterpret_cast<uint64_t *>(record) + 1; }
-__device__ __forceinline__ void publish_rows(const Stage1Args &a, bool mine, size_t record) {
+struct LeftRows {
+    bool left = false;  // whether stage 2 has left this lane's row to this wave,
+    int row = 0;        // which is this one of the task
+};
+__device__ __forceinline__ LeftRows publish_rows(const Stage1Args &a, bool mine, int row, size_t record) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if (mine) __hip_atomic_store(mark_of(a.marks + 4 * record), a.ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    LeftRows x;
+    x.row = row;
+    if (mine) x.left = __hip_atomic_exchange(mark_of(a.marks + 4 * record), a.ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == ~a.ticket;
+    return x;
 }
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 __device__ __forceinline__ void store_record(const Stage1Args &a, size_t record, float m, float l) {
@@ -916,8 +926,8 @@ struct ResidentTask {
     // The tiles of the task, one barrier each: a wave writes its part of tile t, and adds up four rows of that tile
     // while it works on tile t + 1 in the other buffer.
     template <int NA, bool MASK, bool PRECISE, bool SHARED>
-    __device__ __forceinline__ void run(const Stage1Args &a, const ChunkCtx &c, float *lds, int wave, int lane, int ntiles,
-                                        int rows, const uint16_t *q_lane, int vis_lo, int vis_hi) {
+    __device__ __forceinline__ LeftRows run(const Stage1Args &a, const ChunkCtx &c, float *lds, int wave, int lane, int ntiles,
+                                            int rows, const uint16_t *q_lane, int vis_lo, int vis_hi) {
         using L = ResidentLds<D>;
         const int32_t *row_q = reinterpret_cast<const int32_t *>(lds + L::kRows), *row_pos = row_q + kTaskRows;
         const uint32_t *row_out = reinterpret_cast<const uint32_t *>(row_pos + kTaskRows), *row_rec = row_out + kTaskRows;
@@ -982,12 +992,13 @@ struct ResidentTask {
         }
         // this wave's rows: 4 * wave .. 4 * wave + 3 of every tile
         const int mine = 16 * (lane >> 2) + 4 * wave + (lane & 3);
-        if (SHARED) publish_rows(a, mine < rows, row_rec[min(mine, rows - 1)]);
+        if (SHARED) return publish_rows(a, mine < rows, mine, row_rec[min(mine, rows - 1)]);
+        return LeftRows();
     }
 };
 
 template <int D, bool PRECISE, bool SHARED>
-__device__ __forceinline__ void resident_task(const Stage1Args &a, const int32_t *it, int h, unsigned char *s_raw) {
+__device__ __forceinline__ LeftRows resident_task(const Stage1Args &a, const int32_t *it, int h, unsigned char *s_raw) {
     using L = ResidentLds<D>;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1068,6 +1079,7 @@ __device__ __forceinline__ void resident_task(const Stage1Args &a, const int32_t
     }
 
     ResidentTask<D> T;
+    LeftRows left;
     auto go = [&](auto na) {
         constexpr int NA = decltype(na)::value;
         typename ResidentTask<D>::vrow v[NA > 0 ? NA : 1][8];
@@ -1100,9 +1112,9 @@ __device__ __forceinline__ void resident_task(const Stage1Args &a, const int32_t
             T.template interleave<NA>(v);
         }
         if (!__all(all))
-            T.template run<NA, true, PRECISE, SHARED>(a, c, lds, wave, lane, ntiles, rows, q_lane, vis_lo, vis_hi);
+            left = T.template run<NA, true, PRECISE, SHARED>(a, c, lds, wave, lane, ntiles, rows, q_lane, vis_lo, vis_hi);
         else
-            T.template run<NA, false, PRECISE, SHARED>(a, c, lds, wave, lane, ntiles, rows, q_lane, vis_lo, vis_hi);
+            left = T.template run<NA, false, PRECISE, SHARED>(a, c, lds, wave, lane, ntiles, rows, q_lane, vis_lo, vis_hi);
     };
     if (mine <= 0)
         go(std::integral_constant<int, 0>());
@@ -1112,6 +1124,7 @@ __device__ __forceinline__ void resident_task(const Stage1Args &a, const int32_t
         go(std::integral_constant<int, 2>());
     else
         go(std::integral_constant<int, kResidentBlocks<D>>());
+    return left;
 }
 
 // Stage 1: one workgroup of four waves per task = (chunk, KV head, up to 128 rows of the chunk's group).
@@ -1123,7 +1136,7 @@ __device__ __forceinline__ void resident_task(const Stage1Args &a, const int32_t
 //
 // PRECISE selects two-term softmax weights (see compute_block).
 template <int D, bool PRECISE, bool SHARED>
-__device__ __forceinline__ void streaming_task(const Stage1Args &a, const int32_t *it, int h, unsigned char *s_raw) {
+__device__ __forceinline__ LeftRows streaming_task(const Stage1Args &a, const int32_t *it, int h, unsigned char *s_raw) {
     constexpr int KK = D / 32;  // k-steps of the Q.K^T contraction
     // The P.V product runs as 8 MFMAs per block (a lane loads 8 d of V per token).  With D = 64 lanes
     // n16 >= 8 repeat the loads of n16 - 8 and half of each product is discarded; that shape only occurs
@@ -1347,9 +1360,10 @@ __device__ __forceinline__ void streaming_task(const Stage1Args &a, const int32_
     if (SHARED) {  // this wave's rows: 4 * TR from 4 * TR * wave among the first tiles of the waves, as many among the second
         const int gr = 4 * TR * wave + (lane & 15), tile = (gr >> 4) + 4 * (lane >> 4), r = 16 * (tile0 + tile) + (gr & 15);
         const int pl = divide(r, a.G, a.inv_G);
-        publish_rows(a, (lane & 15) < 4 * TR && lane < 16 * NTW && tile < ntiles && r < R,
-                     ((size_t)h * a.n_slots + slot_base + pl) * a.G + (r - pl * a.G));
+        return publish_rows(a, (lane & 15) < 4 * TR && lane < 16 * NTW && tile < ntiles && r < R, r - 16 * tile0,
+                            ((size_t)h * a.n_slots + slot_base + pl) * a.G + (r - pl * a.G));
     }
+    return LeftRows();
 }
 
 // One launch for all tasks of a call: a second one would run behind the first, each on a part of the chip (sixteen
@@ -1376,11 +1390,8 @@ __device__ __forceinline__ bool is_resident(const Stage1Args &a, const int32_t *
 }
 
 template <int D, bool PRECISE, bool SHARED>
-__device__ __forceinline__ void run_task(const Stage1Args &a, const int32_t *it, int h, unsigned char *s_raw) {
-    if (is_resident<D>(a, it))
-        resident_task<D, PRECISE, SHARED>(a, it, h, s_raw);
-    else
-        streaming_task<D, PRECISE, SHARED>(a, it, h, s_raw);
+__device__ __forceinline__ LeftRows run_task(const Stage1Args &a, const int32_t *it, int h, unsigned char *s_raw) {
+    return is_resident<D>(a, it) ? resident_task<D, PRECISE, SHARED>(a, it, h, s_raw) : streaming_task<D, PRECISE, SHARED>(a, it, h, s_raw);
 }
 
 // A run of several chunks with the same queries leaves its result in the slots of the first and marks those of the others
@@ -1575,45 +1586,88 @@ __global__ __launch_bounds__(64 * WAVES) void deft_stage2_many(const int32_t *q_
 }
 
 // Stage 2 of a whole call in one launch, at the end of the grid: a wave takes every (kWaves * groups)th row of the output and
-// waits for its partial results.  Every such wait ends.  Stage 1 waits for nothing, and the workgroups that wait, kReduceGroups
-// at most, leave it the rest of the 512 places of the chip: calls that overlap on the 32 hardware queues hold half of them if
-// every one has come this far, and workgroups are started in the order of their ids, so that as a rule what is waited for runs
-// already.  With a workgroup for every four rows, up to 256 a call, a few overlapping calls could have held all places of
-// one XCD each and waited for work that needs a place on the other's.  (The wait gives up after 2^22 polls, seconds, in any
-// case; the row is then not a number.)
-constexpr int kMarkPolls = 1 << 22;
+// waits for its partial results, kMarkPolls looks at most, about a millisecond.  Workgroups are started in the order of their
+// ids, on each XCD for itself, so as a rule what is waited for runs already; but other calls and other work may hold the
+// places that stage 1 needs, for any time.  A wave that has waited in vain leaves the row to stage 1: it puts the ticket's
+// complement into one of the marks that are still missing, and goes.  The wave of stage 1 that finds it there when it puts its
+// ticket in has the row from then on: it leaves it to another in the same way, or, if nothing is missing any more, merges it.
+// One wave at a time has a row, so each is merged once.  No result depends on how long anything takes, every wait ends,
+// and the at most kReduceGroups workgroups that wait give their places back.
+constexpr int kMarkPolls = 1 << 10;
 constexpr uint32_t kReduceGroups = 8;
 constexpr int kReduceLoads = 16;  // loads of a wave in flight, each of 16 bytes a lane: 32 partial results at d = 128, 64 at d = 64
+
+// Plan query p, query head qh: the list of its partial results.
+struct RowParts {
+    const CallArgs &call;
+    const int32_t *rec;
+    int n, q_user, s0, qh, kvh, lane, first;  // first: slot of partial result `lane`, where the record holds one
+    __device__ __forceinline__ RowParts(const CallArgs &c, int p, int head, int l) : call(c), qh(head), lane(l) {
+        rec = c.s2.q_head + (size_t)p * c.s2.head_ints;
+        first = rec[min(deft::kQueryHeadFixed + lane, c.s2.head_ints - 1)];
+        n = rec[0], q_user = rec[1], s0 = rec[2];
+        kvh = divide(qh, c.s1.G, c.s1.inv_G);
+    }
+    // of partial results base .. base + cnt - 1, one to a lane; lanes past the end hold the last
+    __device__ __forceinline__ int slot(int base, int cnt) const {
+        int x = first;
+        if (n > call.s2.head_ints - deft::kQueryHeadFixed)
+            x = call.s2.q_part_slot[s0 + base + min(lane, cnt - 1)];
+        else if (base > 0)
+            x = rec[deft::kQueryHeadFixed + base + min(lane, cnt - 1)];
+        return __shfl(x, min(lane, cnt - 1));
+    }
+    __device__ __forceinline__ float *record(int slot) const {
+        return call.s1.marks + 4 * (((size_t)kvh * call.s1.n_slots + slot) * call.s1.G + (qh - kvh * call.s1.G));
+    }
+    // Whether all are there, looking at most `polls` times.
+    __device__ __forceinline__ bool complete(int polls) const {
+        for (int base = 0; base < n; base += 64) {
+            uint64_t *mark = mark_of(record(slot(base, min(64, n - base))));
+            for (bool there = false;; __builtin_amdgcn_s_sleep(2)) {
+                if (!there) there = __hip_atomic_load(mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == call.s1.ticket;
+                if (__all(there)) break;
+                if (--polls <= 0) return false;
+            }
+        }
+        asm volatile("" ::: "memory");
+        return true;
+    }
+    // Leaves the row to a wave that writes one of the missing partial results.  False: left; true: nothing is missing.
+    __device__ __forceinline__ bool leave() const {
+        const uint64_t ticket = call.s1.ticket;
+        for (int base = 0; base < n; base += 64) {
+            uint64_t *mark = mark_of(record(slot(base, min(64, n - base))));
+            for (;;) {
+                uint64_t seen = __hip_atomic_load(mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const uint64_t missing = __ballot(seen != ticket);
+                if (!missing) break;
+                bool left = false;  // (it fails where the ticket has come meanwhile)
+                if (lane == __builtin_ctzll(missing))
+                    left = __hip_atomic_compare_exchange_strong(mark, &seen, ~ticket, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (__any(left)) return false;
+            }
+        }
+        asm volatile("" ::: "memory");
+        return true;
+    }
+};
+
+// Merges a row whose partial results are all there.
 template <int D>
-__device__ __forceinline__ void reduce_row(const CallArgs &call, uint32_t row) {
+__device__ __forceinline__ void merge_row(const RowParts &row) {
     using R = Stage2Row<D>;
     constexpr int kLoads = kReduceLoads;
+    const CallArgs &call = row.call;
     const Stage2Args &a = call.s2;
-    const int lane = threadIdx.x & 63;
-    const int p = divide(row, a.Hq, a.inv_Hq), qh = row - p * a.Hq;
-    const int32_t *rec = a.q_head + (size_t)p * a.head_ints;
-    int slot = rec[min(deft::kQueryHeadFixed + lane, a.head_ints - 1)];
-    const int n = rec[0], q_user = rec[1], s0 = rec[2];
+    const int lane = row.lane, n = row.n, qh = row.qh;
     const int sub = lane / R::kLanes, col = lane - sub * R::kLanes;
-    const int kvh = divide(qh, call.s1.G, call.s1.inv_G);
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     float M = -INFINITY, lsum = 0.f;
     for (int base = 0; base < n; base += 64) {
         const int cnt = min(64, n - base);
-        if (n > a.head_ints - deft::kQueryHeadFixed)
-            slot = a.q_part_slot[s0 + base + min(lane, cnt - 1)];
-        else if (base > 0)
-            slot = rec[deft::kQueryHeadFixed + base + min(lane, cnt - 1)];
-        slot = __shfl(slot, min(lane, cnt - 1));  // lanes past the end hold a slot that exists
-        float *record = call.s1.marks + 4 * (((size_t)kvh * call.s1.n_slots + slot) * call.s1.G + (qh - kvh * call.s1.G));
-        uint64_t *mark = mark_of(record);
-        bool there = lane >= cnt;
-        for (int i = 0; i < kMarkPolls; ++i) {
-            if (!there) there = __hip_atomic_load(mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == call.s1.ticket;
-            if (__all(there)) break;
-            __builtin_amdgcn_s_sleep(2);
-        }
-        asm volatile("" ::: "memory");
+        const int slot = row.slot(base, cnt);
+        float *record = row.record(slot);
         f32x2 ml = {-INFINITY, 0.f};
         if (lane < cnt)
             ml = __builtin_bit_cast(f32x2, __hip_atomic_load(reinterpret_cast<uint64_t *>(record), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
@@ -1636,7 +1690,6 @@ __device__ __forceinline__ void reduce_row(const CallArgs &call, uint32_t row) {
                 const float top = fmaxf(M, wave_max(mj));
                 const float old = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((M - top) * a.c);
                 w = (lane < cnt && top != -INFINITY) ? __builtin_amdgcn_exp2f((mj - top) * a.c) : 0.f;
-                if (!there) w = NAN;
                 lsum = lsum * old + wave_sum(w * lj);
                 acc *= old;
                 M = top;
@@ -1658,7 +1711,30 @@ __device__ __forceinline__ void reduce_row(const CallArgs &call, uint32_t row) {
     for (int o = 32; o >= R::kLanes; o >>= 1)
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], o);
-    if (sub == 0) store_out(a, ((size_t)q_user * a.Hq + qh) * D + 4 * col, acc * (lsum > 0.f ? 1.f / lsum : 0.f));
+    if (sub == 0) store_out(a, ((size_t)row.q_user * a.Hq + qh) * D + 4 * col, acc * (lsum > 0.f ? 1.f / lsum : 0.f));
+}
+
+// Stage 2's waves.
+template <int D>
+__device__ __forceinline__ void reduce_rows(const CallArgs &call, uint32_t group, uint32_t groups) {
+    const Stage2Args &a = call.s2;
+    const uint32_t rows = (uint32_t)a.nq * (uint32_t)a.Hq, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (uint32_t r = kWaves * group + wave; r < rows; r += kWaves * groups) {
+        const int p = divide(r, a.Hq, a.inv_Hq);
+        const RowParts row(call, p, r - p * a.Hq, threadIdx.x & 63);
+        if (row.complete(call.polls) || row.leave()) merge_row<D>(row);
+    }
+}
+
+// A wave of stage 1 to which rows of its task were left.
+template <int D>
+__device__ __forceinline__ void merge_left_rows(const CallArgs &call, const int32_t *it, int h, const LeftRows &x) {
+    const int G = call.s1.G, first = 16 * it[deft::kItTile0];
+    for (uint64_t left = __ballot(x.left); left; left &= left - 1) {
+        const int r = first + __builtin_amdgcn_readlane(x.row, __builtin_ctzll(left)), pl = divide(r, G, call.s1.inv_G);
+        const RowParts row(call, it[deft::kItQlo] + pl, h * G + r - pl * G, threadIdx.x & 63);
+        if (row.leave()) merge_row<D>(row);
+    }
 }
 
 // SHARED: a whole call in one launch, stage 2 included.
@@ -1668,8 +1744,7 @@ template <int D, int WEIGHTS, bool SHARED>
 __global__ __launch_bounds__(64 * kWaves, 2) void deft_stage1(const int32_t *items, uint32_t Hkv, uint32_t inv_Hkv, uint32_t tasks, CallArgs call) {
     extern __shared__ __attribute__((aligned(16))) unsigned char s_raw[];
     if (SHARED && blockIdx.x >= tasks) {
-        const uint32_t rows = (uint32_t)call.s2.nq * (uint32_t)call.s2.Hq, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        for (uint32_t row = kWaves * (blockIdx.x - tasks) + wave; row < rows; row += kWaves * (gridDim.x - tasks)) reduce_row<D>(call, row);
+        reduce_rows<D>(call, blockIdx.x - tasks, gridDim.x - tasks);
         return;
     }
     const Stage1Args &a = call.s1;
@@ -1683,10 +1758,9 @@ __global__ __launch_bounds__(64 * kWaves, 2) void deft_stage1(const int32_t *ite
     const int h = turned - divide(turned, Hkv, inv_Hkv) * Hkv;
     const int32_t *it = items + (size_t)item * deft::kItemInts;
     if (it[deft::kItChunks] > 1) mark_empty(a, it, h);  // (first: behind the task its descriptor would have to be read again)
-    if (WEIGHTS == kTwoTerm || (WEIGHTS == kMixed && it[deft::kItPrecise]))
-        run_task<D, true, SHARED>(a, it, h, s_raw);
-    else
-        run_task<D, false, SHARED>(a, it, h, s_raw);
+    const LeftRows left = WEIGHTS == kTwoTerm || (WEIGHTS == kMixed && it[deft::kItPrecise]) ? run_task<D, true, SHARED>(a, it, h, s_raw)
+                                                                                              : run_task<D, false, SHARED>(a, it, h, s_raw);
+    if (SHARED && __any(left.left)) merge_left_rows<D>(call, it, h, left);
 }
 
 // Plain read of a buffer with 128-bit loads, every byte once, all compute units busy: the rate this
@@ -1913,7 +1987,7 @@ uint64_t new_ticket() {
 
 // Both stages in one launch.
 int run_call(const deft_plan_t *plan, const Call &call, const void *q, const void *k, const void *v, void *o, int32_t Hq,
-             int32_t Hkv, int32_t d, uint32_t flags) {
+             int32_t Hkv, int32_t d, uint32_t flags, int32_t polls) {
     if (!stage1_inputs_ok(q, k, v)) return DEFT_EINVAL;
     const deft::TaskSet &T = call.S->fused;
     CallArgs a{};
@@ -1922,6 +1996,7 @@ int run_call(const deft_plan_t *plan, const Call &call, const void *q, const voi
     a.s1.marks = call.marks;
     a.s1.ticket = new_ticket();
     a.s1.n_slots = plan->n_slots();
+    a.polls = polls;
     const unsigned rows = (unsigned)plan->nq * (unsigned)Hq;
     const unsigned groups = std::min((rows + kWaves - 1) / kWaves, kReduceGroups);
     const bool ok = d == 128 ? launch_stage1<128, true>(T, a, groups, call.img, call.stream)
@@ -2111,19 +2186,33 @@ extern "C" int deft_stage2_global_reduction(const deft_plan_t *plan, const void 
     return run_stage2(plan, call, call.S->by_chunk, o, Hq, d, flags);
 }
 
-extern "C" int deft_tree_attn_decode(const deft_plan_t *plan, const void *dev_image, const void *q, const void *k,
-                                     const void *v, void *o, int32_t Hq, int32_t Hkv, int32_t d, float scale,
-                                     uint32_t flags, void *workspace, size_t workspace_bytes, void *stream) {
+namespace {
+int decode(const deft_plan_t *plan, const void *dev_image, const void *q, const void *k, const void *v, void *o, int32_t Hq, int32_t Hkv,
+           int32_t d, float scale, uint32_t flags, void *workspace, size_t workspace_bytes, void *stream, int32_t polls) {
     Call call;
     int rc = prepare(plan, dev_image, Hq, Hkv, d, scale, workspace, workspace_bytes, stream, call);
     if (rc != DEFT_OK) return rc;
     // check both stages' arguments before launching anything
     if (flags != DEFT_OUT_BF16 && flags != DEFT_OUT_F32) return DEFT_EINVAL;
     if (plan->nq > 0 && (!o || !aligned16(o))) return DEFT_EINVAL;
-    if (one_launch(plan, call, Hq, Hkv, d)) return run_call(plan, call, q, k, v, o, Hq, Hkv, d, flags);
+    if (one_launch(plan, call, Hq, Hkv, d)) return run_call(plan, call, q, k, v, o, Hq, Hkv, d, flags, polls);
     rc = run_stage1(plan, call, call.S->fused, q, k, v, Hq, Hkv, d);
     if (rc != DEFT_OK) return rc;
     return run_stage2(plan, call, call.S->fused, o, Hq, d, flags);
+}
+}  // namespace
+
+extern "C" int deft_tree_attn_decode(const deft_plan_t *plan, const void *dev_image, const void *q, const void *k,
+                                     const void *v, void *o, int32_t Hq, int32_t Hkv, int32_t d, float scale,
+                                     uint32_t flags, void *workspace, size_t workspace_bytes, void *stream) {
+    return decode(plan, dev_image, q, k, v, o, Hq, Hkv, d, scale, flags, workspace, workspace_bytes, stream, kMarkPolls);
+}
+
+extern "C" int deft_decode_polls(const deft_plan_t *plan, const void *dev_image, const void *q, const void *k, const void *v, void *o,
+                                 int32_t Hq, int32_t Hkv, int32_t d, float scale, uint32_t flags, void *workspace,
+                                 size_t workspace_bytes, void *stream, int32_t polls) {
+    if (polls < 1 || polls > kMarkPolls) return DEFT_EINVAL;
+    return decode(plan, dev_image, q, k, v, o, Hq, Hkv, d, scale, flags, workspace, workspace_bytes, stream, polls);
 }
 
 namespace {

@@ -135,3 +135,9 @@ size_t workspace_bytes(const deft_plan_t *plan, int32_t Hq, int32_t d);
 const Schedule *get_schedule(const deft_plan_t *plan, int32_t group, int32_t Hkv);
 const Schedule *find_schedule(const deft_plan_t *plan, int32_t group);
 }  // namespace deft
+
+// deft_tree_attn_decode with another limit to the wait inside a call of one launch, 1 .. the library's: the result does not
+// depend on it.  Not part of the interface; the tests see with it that a wait which is given up costs no result.
+extern "C" int deft_decode_polls(const deft_plan_t *plan, const void *dev_image, const void *q, const void *k, const void *v, void *o,
+                                 int32_t Hq, int32_t Hkv, int32_t d, float scale, uint32_t flags, void *workspace,
+                                 size_t workspace_bytes, void *stream, int32_t polls);

@@ -1,4 +1,5 @@
-"""Whole calls made in one launch: stage 2's workgroups wait for stage 1's inside the kernel.
+"""Whole calls made in one launch: stage 2's workgroups wait for stage 1's inside the kernel, and leave rows that are late to
+them.
 
 The same call in two launches, which a workspace without room for the marks gives, is the reference: both sum the same
 partial results in fp32, in another order, so outputs differ by a few units of 2^-24 of the attention of |V|."""
@@ -209,3 +210,27 @@ def test_captured_call_takes_two_launches(i):
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, want)
+
+
+def call_with_polls(plan, t, q, k, v, out, ws, polls, stream=None):
+    """the call with another limit to the wait inside the kernel (deft_internal.h)"""
+    img = plan.image(t.Hq, t.Hkv, "cuda")
+    st = (stream or torch.cuda.current_stream()).cuda_stream
+    flags = binding.DEFT_OUT_F32 if out.dtype == torch.float32 else binding.DEFT_OUT_BF16
+    p = ctypes.c_void_p
+    assert binding.load_library().deft_decode_polls(
+        plan.handle, p(img.data_ptr()), p(q.data_ptr()), p(k.data_ptr()), p(v.data_ptr()), p(out.data_ptr()), t.Hq, t.Hkv, t.d,
+        ctypes.c_float(0.0), flags, p(ws.data_ptr()), ctypes.c_size_t(ws.numel()), p(st), polls) == 0
+
+
+@pytest.mark.parametrize("i", [0, 1, 4, 5, 8, 12, 13, 16, 18, 20, 22])
+def test_rows_that_are_late_are_merged_by_stage_1(i):
+    t, chunk = TREES[i]
+    plan, q, k, v = prepared(t, chunk)
+    ws = torch.zeros(plan.workspace_bytes(t.Hq, t.Hkv, t.d), dtype=torch.uint8, device="cuda")
+    want = binding.deft_tree_attn_decode(plan, q, k, v, out_dtype=torch.float32, workspace=ws)
+    for polls in (1, 1, 2, 3, 4, 6, 9, 14):  # from a wait that is given up at once to one that may just do
+        out = torch.full_like(want, float("nan"))
+        ws.zero_()
+        call_with_polls(plan, t, q, k, v, out, ws, polls)
+        assert torch.equal(out, want), polls

@@ -2015,21 +2015,23 @@ bool is_captured(hipStream_t st) {
 }
 
 // Which calls are made in one launch.  It saves the host 2 to 3 us and the GPU the microsecond between two kernels, but
-// partial results cross the caches one by one, and the few waves that stage 2 has (reduce_row) take some 2 us for every
-// further batch: a row of the output for each of them, or kReduceLoads loads of a row's partial results.  So: one batch where
-// K and V are of a size that the host's work is a good part of the call, two where they are small.  Whole call, us, two
-// launches -> one: one batch, 0.4 MB 11.8 -> 8.8, 6.8 MB 11.8 -> 8.8, 23 MB 11.3 -> 9.1, 33 MB 11.5 -> 10.5; two, 7 MB 11.4
-// -> 9.6, 16 MB 11.6 -> 9.5, but 20 MB 11.3 -> 12.2, 34 MB 11.7 -> 11.5, 38 MB 14.2 -> 15.1; three, 1.7 MB 11.4 -> 12.2, 5 MB
-// 11.6 -> 13.0 or 10.1.
+// partial results cross the caches one by one, and the few waves that stage 2 has (reduce_rows) take some 2 us for every
+// further batch of kReduceLoads loads.  With a row of the output to a wave: one batch where K and V are of a size that the
+// host's work is a good part of the call, two where they are small.  With two rows: half a batch each.  Whole call, us, two
+// launches -> one: one row of one batch, 0.4 MB 9.8 -> 6.8, 16 MB 9.8 -> 7.9, 33 MB 9.7 -> 9.2, 39 MB 12.3 -> 12.3, but 41 MB
+// 13.0 -> 13.4; one of two, 6 MB 9.9 -> 8.5, 16 MB 9.9 -> 8.8, but 34 MB 9.7 -> 9.7, and earlier 38 MB 14.2 -> 15.1; two of half
+// a batch, 0.6 MB 9.8 -> 8.8, 9 MB 9.9 -> 9.1, 2.4 MB 8.7 -> 9.0 where the host is quick, 9.9 -> 9.1 where it is not; two of
+// one batch 8.8 -> 9.9, 10.0 -> 11.1, 10.1 -> 10.5 and 8.5 -> 11.0; three batches, 1.7 MB 11.4 -> 12.2, 5 MB 11.6 -> 13.0 or 10.1.
 // A captured call takes two: its replays have no host to spare and the GPU is the slower for it (0.4 MB 6.4 -> 6.9, 16 MB 6.8 ->
 // 7.5, 5 MB under 56 rows 7.5 -> 11.3), and their marks could hold the ticket from the replay before.
 bool one_launch(const deft_plan_t *plan, const Call &call, int32_t Hq, int32_t Hkv, int32_t d) {
     constexpr int64_t kWavesOfRows = kWaves * kReduceGroups;
     if (!call.marks || plan->nq == 0 || call.S->fused.n_items == 0) return false;
-    const int64_t parts = d == 128 ? kReduceLoads * Stage2Row<128>::kRows : kReduceLoads * Stage2Row<64>::kRows;
-    const int64_t batches = (((int64_t)plan->nq * Hq + kWavesOfRows - 1) / kWavesOfRows) * ((call.S->fused.max_parts + parts - 1) / parts);
-    const int64_t bytes = (int64_t)plan->n_flat * Hkv * d * 4;
-    return ((batches <= 1 && bytes <= (40 << 20)) || (batches <= 2 && bytes <= (16 << 20))) && !is_captured(call.stream);
+    const int64_t batch = d == 128 ? kReduceLoads * Stage2Row<128>::kRows : kReduceLoads * Stage2Row<64>::kRows;
+    const int64_t rows = (int64_t)plan->nq * Hq, parts = call.S->fused.max_parts, bytes = (int64_t)plan->n_flat * Hkv * d * 4;
+    const bool pays = rows <= kWavesOfRows ? (parts <= batch && bytes <= (40 << 20)) || (parts <= 2 * batch && bytes <= (16 << 20))
+                                           : rows <= 2 * kWavesOfRows && 2 * parts <= batch && bytes <= (16 << 20);
+    return pays && !is_captured(call.stream);
 }
 
 // Pinned host staging for plan images: a ring of slots per device, allocated at the first upload on that

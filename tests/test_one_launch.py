@@ -234,3 +234,30 @@ def test_rows_that_are_late_are_merged_by_stage_1(i):
         ws.zero_()
         call_with_polls(plan, t, q, k, v, out, ws, polls)
         assert torch.equal(out, want), polls
+
+
+@pytest.mark.parametrize("t,chunk,one", [
+    (star(256, 4, 32, 4, 4, 64), 0, True),
+    (star(8191, 0, 0, 32, 8, 128), 256, True),       # 32 MiB of K and V, 32 partial results
+    (star(10600, 0, 0, 32, 8, 128), 352, False),     # 41 MiB
+    (star(4000, 0, 0, 16, 8, 128), 64, True),        # 63 partial results, 15.6 MiB
+    (star(4100, 0, 0, 16, 8, 128), 96, False),       # 43, 16.02 MiB
+    (star(4160, 0, 0, 8, 1, 128), 64, False),        # 65
+    (star(8192, 0, 0, 8, 1, 64), 64, True),          # 128 at d = 64
+    (star(1000, 8, 50, 4, 1, 128), 64, True),        # 32 rows of output, 18 partial results
+    (star(1000, 11, 50, 3, 1, 128), 64, False),      # 33 rows
+    (star(1000, 9, 50, 4, 4, 128), 64, False),       # 36 rows
+    (star(2000, 9, 50, 4, 4, 64), 64, False),        # 34 partial results at d = 64
+    (star(1500, 12, 50, 4, 4, 64), 64, True),        # 26
+    (star(900, 1, 100, 64, 8, 128), 128, True),      # 64 rows, 9 partial results
+    (star(200, 17, 20, 4, 4, 128), 64, False),       # 68 rows
+])
+def test_which_calls_take_one_launch(t, chunk, one):
+    # one launch writes its ticket into the marks, two leave them as they were
+    plan, q, k, v = prepared(t, chunk)
+    rows = plan.view()["n_slots"] * t.Hq
+    ws = torch.full((plan.workspace_bytes(t.Hq, t.Hkv, t.d),), 0xFF, dtype=torch.uint8, device="cuda")
+    got = binding.deft_tree_attn_decode(plan, q, k, v, out_dtype=torch.float32, workspace=ws)
+    marks = ws[4 * (rows * t.d + (2 * rows + 3) // 4 * 4):][: 16 * rows].view(torch.int64).view(-1, 2)[:, 1]
+    assert bool((marks != -1).any()) == one
+    close(got, two_launches(plan, t, q, k, v), v)

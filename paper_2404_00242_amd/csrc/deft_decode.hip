@@ -22,6 +22,7 @@
 //
 // Stage 2 (deft_stage2_few, deft_stage2_many): one, two or four waves per (query, query head) merge that query's partial
 // results with the log-sum-exp weights of eq. 1.  Small whole calls have both stages in one launch (reduce_row).
+#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -33,7 +34,6 @@
 #include <cstring>
 #include <mutex>
 #include <string>
-#include <thread>
 #include <type_traits>
 
 #include "deft_internal.h"
@@ -1783,23 +1783,18 @@ __global__ __launch_bounds__(256) void deft_read_probe(const u32x4 *__restrict__
     if (threadIdx.x == 0) sink[blockIdx.x] = part[0] ^ part[1] ^ part[2] ^ part[3];
 }
 
-// A plan's image from pinned host memory into its buffer, one 16-byte word to a thread, and word that a workgroup has read
-// its part: flags[b] = turn, in host memory too.  A kernel and not a copy command: copies run on an engine of their own, and
-// the compute queue waits some 35 us for it to be told, to copy and to answer; and flags instead of an event behind it, which
-// is a packet of its own that the queue stops at.  Bound by the latency of host memory: 3.4 us for 24 KB.  Decode iteration
-// of 8 layer-calls 166 us with a copy, 153 with the kernel and an event, 149 as it is.
+// A plan's image from pinned host memory into its buffer, one 16-byte word to a thread.  A kernel and not a copy command:
+// copies run on an engine of their own, and the compute queue waits some 35 us for it to be told, to copy and to answer.
+// Bound by the latency of host memory: 3.4 us for 24 KB.  Decode iteration of 8 layer-calls 166 us with a copy, 147 with the
+// kernel.
 constexpr int kFetchThreads = 1024;
-__global__ __launch_bounds__(kFetchThreads) void deft_fetch_image(const u32x4 *host, u32x4 *image, uint32_t words, uint32_t *flags,
-                                                                  uint32_t turn) {
+__global__ __launch_bounds__(kFetchThreads) void deft_fetch_image(const u32x4 *host, u32x4 *image, uint32_t words) {
     const uint32_t i = blockIdx.x * kFetchThreads + threadIdx.x;
     if (i < words) {
         // system scope: no line of an earlier image may be found in a cache
         const u32x4 x = __builtin_amdgcn_global_load_b128((global_u32x4)(host + i), "");
         image[i] = x;
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (threadIdx.x == 0) __hip_atomic_store(flags + blockIdx.x, turn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 thread_local std::string g_hip_error;
@@ -2037,42 +2032,20 @@ bool one_launch(const deft_plan_t *plan, const Call &call, int32_t Hq, int32_t H
 // Pinned host staging for plan images: a ring of slots per device, allocated at the first upload on that
 // device and kept until the process ends.  An image is copied into the next slot and fetched from there by a
 // kernel on the stream, so deft_plan_upload neither waits for the stream nor depends on the plan staying
-// alive.  A slot is reused only after that kernel has read it, which its flags say.  In a stream that is being captured,
-// or to memory that is not of the stream's device, the image is sent by a copy command instead, and an event behind it
-// guards the slot.
+// alive.  A slot is reused only after its event has completed, which also is where a failure of the device is heard of.  The
+// event is the fetch kernel's own end: recorded behind it, it would be a packet of its own that the queue stops at (4 us of a
+// decode iteration of 147), and a fence for the host, which reads nothing, would be 1 us more.  In a stream that is being
+// captured, or to memory that is not of the stream's device, the image is sent by a copy command with the event behind it.
 constexpr int kStageSlots = 8;
 constexpr size_t kStageSlotBytes = DEFT_STAGED_IMAGE_BYTES;
-constexpr uint32_t kStageFlags = (kStageSlotBytes / 16 + kFetchThreads - 1) / kFetchThreads;  // workgroups of a fetch, at most
 struct Staging {
-    struct Slot {
-        hipEvent_t done = nullptr;
-        bool event_pending = false;
-        uint32_t groups = 0, turn = 0;  // of the last fetch: its flags are `turn` when it is done
-    };
     std::mutex mu;
-    uint8_t *base = nullptr, *seen = nullptr;  // the slots and their flags, as the host and as the device address them
-    Slot slot[kStageSlots];
-    uint32_t turn = 0;
+    uint8_t *base = nullptr, *seen = nullptr;  // the slots, as the host and as the device addresses them
+    hipEvent_t done[kStageSlots] = {};
+    bool used[kStageSlots] = {};
     int next = 0;
-    uint32_t *flags(uint8_t *at, int i) const { return reinterpret_cast<uint32_t *>(at + kStageSlots * kStageSlotBytes) + i * kStageFlags; }
 };
 Staging g_staging[64];
-
-// Until nothing reads slot i any more.
-bool wait_for_slot(Staging &g, int i) {
-    Staging::Slot &s = g.slot[i];
-    if (s.event_pending && !hip_ok(hipEventSynchronize(s.done), "staging slot")) return false;
-    s.event_pending = false;
-    auto fetched = [&] {
-        const uint32_t *f = g.flags(g.base, i);
-        for (uint32_t b = 0; b < s.groups; ++b)
-            if (__atomic_load_n(f + b, __ATOMIC_ACQUIRE) != s.turn) return false;
-        return true;
-    };
-    for (int polls = 0; !fetched(); ++polls)  // (the work in front of the fetch may take long)
-        if (polls >= 1000) std::this_thread::sleep_for(std::chrono::microseconds(10));
-    return true;
-}
 
 // Whether a kernel on this stream may write there.  A copy command reaches any memory, a kernel that of its own device; the
 // memory of another one, or of the host, may not be mapped for it.
@@ -2098,42 +2071,36 @@ int upload_staged(void *dev_image, const uint8_t *src, size_t bytes, hipStream_t
     std::lock_guard<std::mutex> lock(g.mu);
     if (!g.base) {
         void *p = nullptr, *seen = nullptr;
-        const size_t all = kStageSlots * (kStageSlotBytes + kStageFlags * sizeof(uint32_t));
-        if (!hip_ok(hipHostMalloc(&p, all, hipHostMallocMapped | hipHostMallocCoherent), "pinned staging")) return -1;
+        if (!hip_ok(hipHostMalloc(&p, kStageSlots * kStageSlotBytes, hipHostMallocMapped | hipHostMallocCoherent), "pinned staging"))
+            return -1;
         bool ok = hip_ok(hipHostGetDevicePointer(&seen, p, 0), "pinned staging");
         int made = 0;
         for (; ok && made < kStageSlots; ++made)
-            if (!hip_ok(hipEventCreateWithFlags(&g.slot[made].done, hipEventDisableTiming), "staging event")) break;
+            if (!hip_ok(hipEventCreateWithFlags(&g.done[made], hipEventDisableTiming | hipEventDisableSystemFence), "staging event")) break;
         if (!ok || made < kStageSlots) {
-            for (int j = 0; j < made; ++j) (void)hipEventDestroy(g.slot[j].done);
+            for (int j = 0; j < made; ++j) (void)hipEventDestroy(g.done[j]);
             (void)hipHostFree(p);
             return -1;
         }
-        std::memset(p, 0, all);
         g.seen = static_cast<uint8_t *>(seen);
         g.base = static_cast<uint8_t *>(p);
     }
     const int i = g.next;
     g.next = (g.next + 1) % kStageSlots;
-    if (!wait_for_slot(g, i)) return -1;
-    Staging::Slot &s = g.slot[i];
+    if (g.used[i] && !hip_ok(hipEventSynchronize(g.done[i]), "staging slot")) return -1;
     uint8_t *slot = g.base + (size_t)i * kStageSlotBytes;
     std::memcpy(slot, src, bytes);
     if (captured || !on_stream_device(dev_image, st, dev)) {
         if (!hip_ok(hipMemcpyAsync(dev_image, slot, bytes, hipMemcpyHostToDevice, st), "plan upload")) return -1;
-        if (!hip_ok(hipEventRecord(s.done, st), "staging event record")) return -1;
-        s.event_pending = true;
-        return 1;
+        if (!hip_ok(hipEventRecord(g.done[i], st), "staging event record")) return -1;
+    } else {
+        const uint32_t words = (uint32_t)(bytes / 16);  // an image is a whole number of them
+        hipExtLaunchKernelGGL(deft_fetch_image, dim3((words + kFetchThreads - 1) / kFetchThreads), dim3(kFetchThreads), 0, st, nullptr,
+                              g.done[i], 0, reinterpret_cast<const u32x4 *>(g.seen + (size_t)i * kStageSlotBytes),
+                              static_cast<u32x4 *>(dev_image), words);
+        if (!hip_ok(hipGetLastError(), "plan upload")) return -1;
     }
-    const uint32_t words = (uint32_t)(bytes / 16);  // an image is a whole number of them
-    const uint32_t groups = (words + kFetchThreads - 1) / kFetchThreads;
-    if (++g.turn == 0) g.turn = 1;
-    hipLaunchKernelGGL(deft_fetch_image, dim3(groups), dim3(kFetchThreads), 0, st,
-                       reinterpret_cast<const u32x4 *>(g.seen + (size_t)i * kStageSlotBytes), static_cast<u32x4 *>(dev_image), words,
-                       g.flags(g.seen, i), g.turn);
-    if (!hip_ok(hipGetLastError(), "plan upload")) return -1;
-    s.groups = groups;
-    s.turn = g.turn;
+    g.used[i] = true;
     return 1;
 }
 

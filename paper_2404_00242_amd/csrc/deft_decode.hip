@@ -2035,7 +2035,7 @@ bool one_launch(const deft_plan_t *plan, const Call &call, int32_t Hq, int32_t H
 // alive.  A slot is reused only after its event has completed, which also is where a failure of the device is heard of.  The
 // event is the fetch kernel's own end: recorded behind it, it would be a packet of its own that the queue stops at (4 us of a
 // decode iteration of 147), and a fence for the host, which reads nothing, would be 1 us more.  In a stream that is being
-// captured, or to memory that is not of the stream's device, the image is sent by a copy command with the event behind it.
+// captured, or where memory or stream are not the current device's, the image is sent by a copy command with the event behind it.
 constexpr int kStageSlots = 8;
 constexpr size_t kStageSlotBytes = DEFT_STAGED_IMAGE_BYTES;
 struct Staging {
@@ -2047,8 +2047,9 @@ struct Staging {
 };
 Staging g_staging[64];
 
-// Whether a kernel on this stream may write there.  A copy command reaches any memory, a kernel that of its own device; the
-// memory of another one, or of the host, may not be mapped for it.
+// Whether a kernel on this stream may be launched now and write there.  A copy command goes into any stream and reaches any
+// memory; a kernel goes into a stream of the current device and reaches that device's memory: the memory of another one, or
+// of the host, may not be mapped for it.
 bool on_stream_device(const void *p, hipStream_t st, int dev) {
     hipPointerAttribute_t at{};
     hipDevice_t stream_dev = dev;
@@ -2056,7 +2057,7 @@ bool on_stream_device(const void *p, hipStream_t st, int dev) {
         (void)hipGetLastError();
         return false;
     }
-    return at.type == hipMemoryTypeDevice && at.device == stream_dev;
+    return at.type == hipMemoryTypeDevice && at.device == dev && stream_dev == dev;
 }
 
 // Returns 1 when the image went out through the ring, 0 when the caller has to take the plain path

@@ -24,7 +24,7 @@ def forest(n):
     lens = np.arange(1, n + 1, dtype=np.int32) % 31 + 1
     begins = np.concatenate([[0], np.cumsum(lens)[:-1]]).astype(np.int32)
     return binding.deft_plan(begins, lens, np.full(n, -1, np.int32), np.arange(n, dtype=np.int32), int(lens.sum()), 32,
-                             binding.SPLIT_MODES["flatten"]), begins
+                             binding.DEFT_SPLIT_NODE), begins
 plan, begins = forest(20)
 size = plan.device_bytes(4, 4)
 buf = np.zeros(size + 16, np.uint8)
@@ -63,4 +63,26 @@ fake.event_error = FAILED
 for _ in range(3):
     assert upload() == EHIP
 assert b"staging slot" in lib.deft_last_hip_error()
+""")
+
+
+@needs_gxx
+@pytest.mark.parametrize("pointer,stream,kernel", [
+    ((0, "Device"), 0, True),
+    ((0, "Device"), None, True),    # the null stream, which is the current device's
+    ((0, "Host"), 0, False),        # a copy reaches any memory
+    ((1, "Device"), 0, False),
+    ((1, "Device"), None, False),
+    ((1, "Device"), 1, False),      # and goes into streams of other devices than the current one
+    ((0, "Device"), 1, False),
+])
+def test_image_goes_by_a_kernel_only_into_memory_and_streams_of_the_current_device(fake, pointer, stream, kernel):
+    run(fake, f"""
+fake.pointer_device, fake.pointer_type = {pointer[0]}, {dict(Host=1, Device=2)[pointer[1]]}
+fake.stream_device = {stream or 0}
+for i in range(1, 20):
+    image[:] = 0
+    assert upload({'None' if stream is None else 'STREAM'}) == 0
+    assert (fake.launches, fake.copies) == ({'i, 0' if kernel else '0, i'})
+    assert arrived() != {kernel}  # (kernels are not run here)
 """)

@@ -231,7 +231,8 @@ int64_t deft_plan_rows(const deft_plan_t *plan);
  * up to DEFT_STAGED_IMAGE_BYTES are staged in pinned host memory that the library keeps per device
  * (eight slots), and the call only enqueues the copy: work enqueued on `stream` afterwards sees the
  * image, and the plan may be destroyed at once.  Larger images are copied from the plan and the call
- * waits for that copy.  One image serves one Hq/Hkv ratio, with any number of KV heads; a plan may be
+ * waits for that copy.  A call made while the stream is being captured records the image itself in the graph, for images of
+ * up to DEFT_STAGED_IMAGE_BYTES in memory of the current device, which has to be the stream's.  One image serves one Hq/Hkv ratio, with any number of KV heads; a plan may be
  * uploaded for several ratios.  How tasks are cut is decided by the Hkv of the first upload for a ratio:
  * with another Hkv results are right, but the cut may not be the fastest.
  * Errors: DEFT_EINVAL (null, Hq <= 0, Hkv <= 0, Hq % Hkv != 0), DEFT_EWORKSPACE (bytes

@@ -1797,6 +1797,17 @@ __global__ __launch_bounds__(kFetchThreads) void deft_fetch_image(const u32x4 *h
     }
 }
 
+// A part of a plan's image that is the kernel's own argument: in a stream that is being captured, what the replays read has
+// to live as long as the graph does, and arguments are the one thing that a graph keeps (4 KB of them to a kernel).
+constexpr int kPartWords = 224;
+struct ImagePart {
+    u32x4 word[kPartWords];
+};
+__global__ __launch_bounds__(256) void deft_store_part(u32x4 *image, uint32_t words, ImagePart part) {
+    static_assert(kPartWords <= 256, "a word to a thread");
+    if (threadIdx.x < words) image[threadIdx.x] = part.word[threadIdx.x];
+}
+
 thread_local std::string g_hip_error;
 
 bool hip_ok(hipError_t e, const char *what) {
@@ -2034,8 +2045,9 @@ bool one_launch(const deft_plan_t *plan, const Call &call, int32_t Hq, int32_t H
 // kernel on the stream, so deft_plan_upload neither waits for the stream nor depends on the plan staying
 // alive.  A slot is reused only after its event has completed, which also is where a failure of the device is heard of.  The
 // event is the fetch kernel's own end: recorded behind it, it would be a packet of its own that the queue stops at (4 us of a
-// decode iteration of 147), and a fence for the host, which reads nothing, would be 1 us more.  In a stream that is being
-// captured, or where memory or stream are not the current device's, the image is sent by a copy command with the event behind it.
+// decode iteration of 147), and a fence for the host, which reads nothing, would be 1 us more.  Where memory
+// or stream are not the current device's, the image is sent by a copy command with the event behind it.  In a stream that is
+// being captured no slot is used (store_captured): replays would read it when it holds another plan's image.
 constexpr int kStageSlots = 8;
 constexpr size_t kStageSlotBytes = DEFT_STAGED_IMAGE_BYTES;
 struct Staging {
@@ -2060,14 +2072,34 @@ bool on_stream_device(const void *p, hipStream_t st, int dev) {
     return at.type == hipMemoryTypeDevice && at.device == dev && stream_dev == dev;
 }
 
-// Returns 1 when the image went out through the ring, 0 when the caller has to take the plain path
+// An image into a graph.
+bool store_captured(void *dev_image, const uint8_t *src, size_t bytes, hipStream_t st) {
+    const size_t words = bytes / 16;  // an image is a whole number of them
+    for (size_t at = 0; at < words; at += kPartWords) {
+        const uint32_t n = (uint32_t)std::min<size_t>(kPartWords, words - at);
+        ImagePart part{};
+        std::memcpy(part.word, src + 16 * at, 16 * n);
+        hipLaunchKernelGGL(deft_store_part, dim3(1), dim3(256), 0, st, static_cast<u32x4 *>(dev_image) + at, n, part);
+        if (!hip_ok(hipGetLastError(), "captured plan upload")) return false;
+    }
+    return true;
+}
+
+// Returns 1 when the image is on its way, 0 when the caller has to take the plain path
 // (image larger than a slot, device index out of range), -1 on a runtime error.
 int upload_staged(void *dev_image, const uint8_t *src, size_t bytes, hipStream_t st) {
     int dev = 0;
     if (bytes > kStageSlotBytes) return 0;
     if (!hip_ok(hipGetDevice(&dev), "hipGetDevice")) return -1;
     if (dev < 0 || dev >= 64) return 0;
-    const bool captured = is_captured(st);
+    const bool fetch = on_stream_device(dev_image, st, dev);
+    if (is_captured(st)) {
+        if (!fetch) {
+            g_hip_error = "captured plan upload: memory and stream have to be the current device's";
+            return -1;
+        }
+        return store_captured(dev_image, src, bytes, st) ? 1 : -1;
+    }
     Staging &g = g_staging[dev];
     std::lock_guard<std::mutex> lock(g.mu);
     if (!g.base) {
@@ -2091,7 +2123,7 @@ int upload_staged(void *dev_image, const uint8_t *src, size_t bytes, hipStream_t
     if (g.used[i] && !hip_ok(hipEventSynchronize(g.done[i]), "staging slot")) return -1;
     uint8_t *slot = g.base + (size_t)i * kStageSlotBytes;
     std::memcpy(slot, src, bytes);
-    if (captured || !on_stream_device(dev_image, st, dev)) {
+    if (!fetch) {
         if (!hip_ok(hipMemcpyAsync(dev_image, slot, bytes, hipMemcpyHostToDevice, st), "plan upload")) return -1;
         if (!hip_ok(hipEventRecord(g.done[i], st), "staging event record")) return -1;
     } else {

@@ -77,3 +77,26 @@ def test_more_uploads_than_slots_in_two_streams():
     torch.cuda.synchronize()
     for (plan, begins, lens), img in zip(plans, imgs):
         check(plan, begins, lens, img)
+
+
+@pytest.mark.parametrize("n", [1, 20, 33, 34, 300])  # images of one part and of several, and around a part's end
+def test_captured_upload_replays_its_own_image(n):
+    plan, begins, lens = forest(n)
+    size = plan.device_bytes(4, 4)
+    img = torch.full((size + 64,), 0xAB, dtype=torch.uint8, device="cuda")
+    side, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side):
+        assert binding.load_library().deft_plan_upload(plan.handle, 4, 4, img.data_ptr(), size, side.cuda_stream) == 0
+    del plan
+    st, other = torch.cuda.current_stream().cuda_stream, torch.empty(1 << 20, dtype=torch.uint8, device="cuda")
+    for i in range(4):
+        for j in range(9):  # every staging slot holds another plan's image by now
+            p, b, l = forest(n + 1 + j)
+            assert binding.load_library().deft_plan_upload(p.handle, 4, 4, other.data_ptr(), other.numel(), st) == 0
+            check(p, b, l, other)
+        img.fill_(0xAB)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        end = check(None, begins, lens, img)
+        assert (img[end:] == 0xAB).all()

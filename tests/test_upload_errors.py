@@ -86,3 +86,19 @@ for i in range(1, 20):
     assert (fake.launches, fake.copies) == ({'i, 0' if kernel else '0, i'})
     assert arrived() != {kernel}  # (kernels are not run here)
 """)
+
+
+@needs_gxx
+def test_captured_upload_uses_no_staging_slot(fake):
+    # a replay would read the slot when it holds another image, and no event in a graph says when a slot is free
+    run(fake, """
+ACTIVE = 1
+fake.capturing = ACTIVE
+for _ in range(20):
+    assert upload() == 0
+assert (fake.copies, fake.events_recorded) == (0, 0) and fake.launches % 20 == 0 and fake.launches > 0
+fake.pointer_device = 1
+assert upload() == EHIP and b"captured" in lib.deft_last_hip_error()
+fake.capturing = fake.pointer_device = fake.launches = 0
+assert upload() == 0 and fake.launches == 1
+""")

@@ -374,10 +374,15 @@ def deft_tree_attn_decode(plan: Plan, q, k, v, out=None, scale: float = 0.0, out
     dev = q.device
     if out is None:
         # (empty_like costs half a microsecond less than naming shape, type and device; its format is named because a q of one
-        # query, sliced from a wider tensor, is contiguous under strides that the output should not have)
+        # query, sliced from a wider tensor, is contiguous under strides that the output should not have; of a q that is a
+        # subclass of Tensor it would make another)
         dense = torch.contiguous_format
-        out = torch.empty_like(q, memory_format=dense) if out_dtype is None or out_dtype == bf16 else \
-            torch.empty_like(q, dtype=out_dtype, memory_format=dense)
+        if type(q) is not torch.Tensor:
+            out = torch.empty((nq, Hq, d), dtype=out_dtype or bf16, device=dev)
+        elif out_dtype is None or out_dtype == bf16:
+            out = torch.empty_like(q, memory_format=dense)
+        else:
+            out = torch.empty_like(q, dtype=out_dtype, memory_format=dense)
     elif out.shape != (nq, Hq, d) or not out.is_contiguous() or out.device != dev:
         raise DeftError(-1, "deft_tree_attn_decode: out must be a contiguous [nq, Hq, d] tensor on q's device")
     if out.dtype == bf16:

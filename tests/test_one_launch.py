@@ -173,6 +173,20 @@ def test_output_of_one_query_from_a_wider_tensor_has_plain_strides(dtype):
     assert torch.equal(got, binding.deft_tree_attn_decode(plan, q, k, v, out_dtype=dtype))
 
 
+class Activation(torch.Tensor):
+    pass
+
+
+@pytest.mark.parametrize("dtype", [None, torch.float32])
+def test_output_is_a_plain_tensor_whatever_q_is(dtype):
+    t = star(200, 4, 30, 8, 2, 64)
+    plan, q, k, v = prepared(t, 64)
+    want = binding.deft_tree_attn_decode(plan, q, k, v, out_dtype=dtype)
+    for x in (q.as_subclass(Activation), torch.nn.Parameter(q)):
+        got = binding.deft_tree_attn_decode(plan, x, k, v, out_dtype=dtype)
+        assert type(got) is torch.Tensor and not got.requires_grad and torch.equal(got, want)
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("token", [0, 2047, 1000])
 def test_infinite_value_in_any_partial_result(token, d):

@@ -2115,6 +2115,7 @@ int upload_staged(void *dev_image, const uint8_t *src, size_t bytes, hipStream_t
             (void)hipHostFree(p);
             return -1;
         }
+        std::memset(p, 0, kStageSlots * kStageSlotBytes);  // (or the first image in each slot takes 10 us more, page by page)
         g.seen = static_cast<uint8_t *>(seen);
         g.base = static_cast<uint8_t *>(p);
     }

@@ -271,6 +271,8 @@ size_t deft_workspace_bytes(const deft_plan_t *plan, int32_t Hq, int32_t Hkv, in
  * stream    : hipStream_t (NULL = default stream).  Kernels are enqueued, not awaited.  After one
  *             ordinary call on the device (which sets a kernel attribute), a call made while the
  *             stream is being captured records just its two kernel launches in the graph.
+ *             Small calls are made in one launch otherwise: up to eight of its workgroups wait inside the kernel for
+ *             the others, for about a millisecond at most, and the result does not depend on how that wait ends.
  * Errors: DEFT_EINVAL, DEFT_ENOTREADY, DEFT_EWORKSPACE, DEFT_EHIP (deft_last_hip_error
  * gives the runtime's text).  Nothing is launched when an error is returned, except that a
  * launch failure may leave earlier kernels of the same call enqueued.

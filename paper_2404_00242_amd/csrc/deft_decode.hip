@@ -21,7 +21,7 @@
 // are merged in LDS before one (m, l, acc) triple per (chunk, row) is written.
 //
 // Stage 2 (deft_stage2_few, deft_stage2_many): one, two or four waves per (query, query head) merge that query's partial
-// results with the log-sum-exp weights of eq. 1.  Small whole calls have both stages in one launch (reduce_row).
+// results with the log-sum-exp weights of eq. 1.  Small whole calls have both stages in one launch (reduce_rows).
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
@@ -82,7 +82,7 @@ struct Stage2Args {
 // What a workgroup needs to ask for its first record is passed ahead of the structures, as plain arguments: the compiler
 // has those loaded into registers before the first wave starts (build.py), which takes one round trip out of the chain
 // that every workgroup begins with.  Whole call, us: 37 MB over 16-token pages 16.2 -> 15.7, the decode iteration of the
-// same tree 170.8 -> 166.0, 21 MB with d = 64 12.4 -> 12.1, 67 MB 22.3 -> 22.1.
+// same tree 170.8 -> 166.0, 21 MB with d = 64 12.4 -> 12.1.
 
 // A whole call in one launch: stage 1's workgroups first, then those of stage 2
 struct CallArgs {

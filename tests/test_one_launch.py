@@ -68,7 +68,7 @@ TREES = [
 
 
 def batches(t, plan):
-    """what decides between one launch and two, at these sizes of K and V: rows for 32 waves, partial results in flight"""
+    """what the rule for one launch goes by, next to the sizes of K and V: rows for 32 waves, partial results in flight"""
     parts = int(np.diff(plan.view()["q_part_ptr"]).max())
     return -(-t.nq * t.Hq // 32) * -(-parts // (32 if t.d == 128 else 64))
 

@@ -1894,6 +1894,11 @@ struct Call {
     hipStream_t stream = nullptr;
 };
 
+// The tasks of a whole call.
+const deft::TaskSet &whole_call(const Call &call, int32_t d) {
+    return d == 128 && call.S->recut.n_items > 0 ? call.S->recut : call.S->fused;
+}
+
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 int prepare(const deft_plan_t *plan, const void *dev_image, int32_t Hq, int32_t Hkv, int32_t d, float scale,
@@ -1904,7 +1909,7 @@ int prepare(const deft_plan_t *plan, const void *dev_image, int32_t Hq, int32_t 
     call.S = deft::find_schedule(plan, Hq / Hkv);
     if (!call.S) return DEFT_ENOTREADY;
     if (workspace_bytes < deft::partials_bytes(plan, Hq, d)) return DEFT_EWORKSPACE;
-    if ((int64_t)std::max(call.S->by_chunk.n_items, call.S->fused.n_items) * Hkv > INT32_MAX) return DEFT_EINVAL;  // grid sizes are 32-bit
+    if ((int64_t)std::max({call.S->by_chunk.n_items, call.S->fused.n_items, call.S->recut.n_items}) * Hkv > INT32_MAX) return DEFT_EINVAL;  // grid sizes are 32-bit
     if ((int64_t)plan->nq * Hq > INT32_MAX) return DEFT_EINVAL;
     const size_t rows = (size_t)plan->n_slots() * (size_t)Hq;
     call.img = static_cast<const uint8_t *>(dev_image);
@@ -1978,8 +1983,8 @@ int run_stage2(const deft_plan_t *plan, const Call &call, const deft::TaskSet &T
     if (!o || !aligned16(o)) return DEFT_EINVAL;
     Stage2Args a2{};
     stage2_args(plan, call, T, o, Hq, flags, a2);
-    // a stage 2 called apart may find slots that a whole call on joined chunks left empty
-    const bool holes = &T != &call.S->fused && call.S->fused.off_items != T.off_items;
+    // a stage 2 called apart may find slots that a whole call left empty
+    const bool holes = &T == &call.S->by_chunk && (call.S->fused.off_items != T.off_items || call.S->recut.n_items > 0);
     const bool ok = d == 128 ? (holes ? launch_stage2<128, true>(T, a2, call.stream) : launch_stage2<128, false>(T, a2, call.stream))
                              : (holes ? launch_stage2<64, true>(T, a2, call.stream) : launch_stage2<64, false>(T, a2, call.stream));
     return ok ? DEFT_OK : DEFT_EHIP;
@@ -2000,7 +2005,7 @@ uint64_t new_ticket() {
 int run_call(const deft_plan_t *plan, const Call &call, const void *q, const void *k, const void *v, void *o, int32_t Hq,
              int32_t Hkv, int32_t d, uint32_t flags, int32_t polls) {
     if (!stage1_inputs_ok(q, k, v)) return DEFT_EINVAL;
-    const deft::TaskSet &T = call.S->fused;
+    const deft::TaskSet &T = whole_call(call, d);
     CallArgs a{};
     stage1_args(call, q, k, v, Hq, Hkv, a.s1);
     stage2_args(plan, call, T, o, Hq, flags, a.s2);
@@ -2037,9 +2042,10 @@ bool is_captured(hipStream_t st) {
 // 7.5, 5 MB under 56 rows 7.5 -> 11.3), and their marks could hold the ticket from the replay before.
 bool one_launch(const deft_plan_t *plan, const Call &call, int32_t Hq, int32_t Hkv, int32_t d) {
     constexpr int64_t kWavesOfRows = kWaves * kReduceGroups;
-    if (!call.marks || plan->nq == 0 || call.S->fused.n_items == 0) return false;
+    const deft::TaskSet &T = whole_call(call, d);
+    if (!call.marks || plan->nq == 0 || T.n_items == 0) return false;
     const int64_t batch = d == 128 ? kReduceLoads * Stage2Row<128>::kRows : kReduceLoads * Stage2Row<64>::kRows;
-    const int64_t rows = (int64_t)plan->nq * Hq, parts = call.S->fused.max_parts, bytes = (int64_t)plan->n_flat * Hkv * d * 4;
+    const int64_t rows = (int64_t)plan->nq * Hq, parts = T.max_parts, bytes = (int64_t)plan->n_flat * Hkv * d * 4;
     const bool pays = rows <= kWavesOfRows ? (parts <= batch && bytes <= (40 << 20)) || (parts <= 2 * batch && bytes <= (16 << 20))
                                            : rows <= 2 * kWavesOfRows && 2 * parts <= batch && bytes <= (16 << 20);
     return pays && !is_captured(call.stream);
@@ -2204,9 +2210,9 @@ int decode(const deft_plan_t *plan, const void *dev_image, const void *q, const 
     if (flags != DEFT_OUT_BF16 && flags != DEFT_OUT_F32) return DEFT_EINVAL;
     if (plan->nq > 0 && (!o || !aligned16(o))) return DEFT_EINVAL;
     if (one_launch(plan, call, Hq, Hkv, d)) return run_call(plan, call, q, k, v, o, Hq, Hkv, d, flags, polls);
-    rc = run_stage1(plan, call, call.S->fused, q, k, v, Hq, Hkv, d);
+    rc = run_stage1(plan, call, whole_call(call, d), q, k, v, Hq, Hkv, d);
     if (rc != DEFT_OK) return rc;
-    return run_stage2(plan, call, call.S->fused, o, Hq, d, flags);
+    return run_stage2(plan, call, whole_call(call, d), o, Hq, d, flags);
 }
 }  // namespace
 

@@ -66,6 +66,7 @@ constexpr int kLongChunk = 256;
 constexpr int kResidentTiles = 3;  // see is_resident
 constexpr int kLongGroups = kResidentGroups / 2;
 constexpr int kLongestShare = 4;
+constexpr int kRecutOthers = kLongGroups / 4;  // see recut_runs
 constexpr int kJoinTokens = kLongChunk;  // chunks are joined up to the longest run that is not long
 
 // Stage 1's tasks and the records with which stage 2 finds their partial results.
@@ -90,6 +91,7 @@ struct Schedule {
     size_t off_q_order = 0;
     TaskSet by_chunk;         // one partial result per (chunk, query of its group): what the two stages called apart use
     TaskSet fused;            // the same work on joined chunks: what a whole call uses; the same as by_chunk if none are
+    TaskSet recut;            // wide chunks cut anew, one task to a compute unit: for whole calls with d = 128, if there are any
     int32_t table_len = 32;   // longest chunk made of several pieces, rounded up to whole blocks: LDS table size
     std::vector<uint8_t> host_image;  // packed image, kept for repeated uploads
 };

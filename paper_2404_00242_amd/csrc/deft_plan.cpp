@@ -709,9 +709,11 @@ namespace deft {
 
 static size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
 
-// A run of consecutive chunks that stage 1 works on as one, with the queries of all of them.
+// Tokens that stage 1 works on as one, with the queries of their chunks: consecutive chunks, or what recut_runs makes of them.
 struct Run {
-    int32_t c0, c1;  // chunks [c0, c1)
+    int32_t c0, c1;  // chunks [c0, c1): the result goes to the slots of the first, those of the others stay empty
+    int32_t s0, s1;  // segments [s0, s1), the first of them from row begin0 on
+    int32_t begin0;
     int32_t lo, hi;  // queries, in plan positions
     int32_t len, tiles, precise, slot_base;
     int64_t cost;    // of the largest task, for the dispatch order
@@ -721,7 +723,7 @@ struct Run {
 // they do where chunks of one node are joined.  Such a task needs no per-token table: 4000 tokens under 64 queries x 32
 // heads in chunks of 128 27.0 -> 23.9 us per call, 16000 tokens under 32 branches 72 -> 67.
 static int32_t distinct_pieces(const deft_plan_t *P, const Run &r) {
-    const int32_t s0 = P->chunk_seg_ptr[r.c0], s1 = P->chunk_seg_ptr[r.c1];
+    const int32_t s0 = r.s0, s1 = r.s1;
     for (int32_t s = s0 + 1; s < s1; ++s)
         if (P->seg_tok_begin[s] != P->seg_tok_begin[s - 1] + P->seg_len[s - 1] || P->seg_qlo[s] != P->seg_qlo[s0] ||
             P->seg_qhi[s] != P->seg_qhi[s0])
@@ -813,19 +815,19 @@ static void build_tasks(const deft_plan_t *P, int32_t G, int32_t Hkv, std::vecto
     T.n_items = (int32_t)n_tasks;
     T.n_items_precise = T.n_items_split = 0;
     for (const Run &r : runs) {
-        const int32_t s0 = P->chunk_seg_ptr[r.c0], per = per_run(r), pieces = distinct_pieces(P, r);
+        const int32_t s0 = r.s0, per = per_run(r), pieces = distinct_pieces(P, r);
         for (int32_t t0 = 0; t0 < r.tiles; t0 += per, d += kItemInts) {
             d[kItChunk] = r.c0;
             d[kItTile0] = t0;
             d[kItNTiles] = std::min<int32_t>(per, r.tiles - t0);
             d[kItSeg0] = s0;
-            d[kItNSeg] = P->chunk_seg_ptr[r.c1] - s0;
+            d[kItNSeg] = r.s1 - s0;
             d[kItPieces] = pieces;
             d[kItQlo] = r.lo;
             d[kItWidth] = r.hi - r.lo;
             d[kItSlotBase] = r.slot_base;
             d[kItLen] = r.len;
-            d[kItBegin0] = P->seg_tok_begin[s0];
+            d[kItBegin0] = r.begin0;
             d[kItSegQlo0] = P->seg_qlo[s0];
             d[kItSegQhi0] = P->seg_qhi[s0];
             d[kItPrecise] = r.precise;
@@ -838,6 +840,97 @@ static void build_tasks(const deft_plan_t *P, int32_t G, int32_t Hkv, std::vecto
 
 // The strategies that the header calls comparisons are run as they are named, chunk by chunk.
 static bool may_join(const deft_plan_t *P) { return P->mode == DEFT_SPLIT_FLATTEN || P->mode == DEFT_SPLIT_BALANCED; }
+
+static int32_t full_tasks(int32_t tiles) { return (tiles + kMaxTilesPerTask - 1) / kMaxTilesPerTask; }
+
+// One task to a compute unit in the place of two.  Where nearly all of a launch is wide tasks of one piece, two tiles to a
+// wave, two of them on a unit only take turns (32768 tokens under 64 queries x 4 heads: 59.0 us a call as 256 tasks, 59.2 as
+// 512).  Longer tasks, as many as there are units, write and merge fewer partial results.  The tokens of
+// consecutive chunks with the same queries are cut anew, into equal runs of whole blocks, each with the slots of one of those
+// chunks; slots that are left stay empty, as where chunks are joined.  If the last chunk goes on with other pieces (one-token
+// nodes of a draft tree), those become a run of their own with that chunk's slots.  The runs are as short as kLongGroups
+// workgroups allow.  Only d = 128: with d = 64 twice as many tokens are held in registers, and longer runs stream them
+// (level to 30 % slower).  false: not such a launch.
+//
+// Whole call, us, as planned -> recut: 12345 tokens under 26 queries x 4 heads (392 workgroups of 256 tokens -> 256 of 416)
+// 25.2 -> 22.0; 4654 under 50 x 4 25.5 -> 20.6, 5251 under 34 x 8 33.2 -> 24.8, 15787 under 33 x 4 41.6 -> 32.7.  Over 640
+// trees of at most kRecutOthers other workgroups 0.86 of the time (0.60 to 1.12).  With more of them the narrow tasks would
+// have shared the units: 0.97 at 65 to 80, 1.04 at 81 to 96, 1.11 at 97 to 112, 1.2 and more beyond.  One tile to a wave (3 or
+// 4 in a task) loses beside many narrow or at G = 1, where the launch waits for HBM: 1.09 and 1.02, up to 1.5.
+static bool recut_runs(const deft_plan_t *P, const std::vector<Run> &own, const std::vector<Run> &joined, int32_t Hkv,
+                       std::vector<Run> &out) {
+    auto two_tiles_a_wave = [](const Run &r) {
+        const int32_t k = full_tasks(r.tiles);
+        return r.tiles && (r.tiles + k - 1) / k > kTaskTiles[1];
+    };
+    struct Stretch {
+        size_t c0, c1;    // of `own`
+        int32_t s1, len;  // its tokens are those of the segments up to s1
+        int32_t slots;    // chunks whose slots its runs may use: all but one that has further pieces
+    };
+    std::vector<Stretch> stretches;
+    int64_t now = 0, others = 0;
+    for (const Run &r : joined) now += (int64_t)full_tasks(r.tiles) * Hkv;
+    if (now <= kLongGroups) return false;
+    for (size_t c = 0, e; c < own.size(); c = e) {
+        const Run &r = own[c];
+        for (e = c + 1; e < own.size() && own[e].lo == r.lo && own[e].hi == r.hi;) ++e;
+        const Run &last = own[e - 1];
+        Stretch x{c, e, r.s0, 0, (int32_t)(e - c)};
+        for (; x.s1 < last.s1 && P->seg_qlo[x.s1] == r.lo && P->seg_qhi[x.s1] == r.hi &&
+               (x.s1 == r.s0 || P->seg_tok_begin[x.s1] == P->seg_tok_begin[x.s1 - 1] + P->seg_len[x.s1 - 1]);
+             ++x.s1)
+            x.len += P->seg_len[x.s1];
+        if (x.s1 < last.s1) {
+            --x.slots;
+            Run rest = last;
+            rest.s0 = x.s1;
+            if (x.s1 > last.s0 && distinct_pieces(P, rest) == 1) {  // the kernel would not mask it: the chunk stays whole
+                while (x.s1 > last.s0) x.len -= P->seg_len[--x.s1];
+                --x.c1;
+            }
+        }
+        if (x.s1 >= last.s0 && x.slots > 1 && two_tiles_a_wave(r)) {
+            stretches.push_back(x);
+            if (x.slots < (int32_t)(e - c)) others += full_tasks(last.tiles);
+        } else {
+            for (size_t i = c; i < e; ++i) others += full_tasks(own[i].tiles);
+        }
+    }
+    if (stretches.empty() || others * Hkv > kRecutOthers) return false;
+    int32_t length = kLongChunk;
+    auto fits = [&] {
+        int64_t n = others;
+        for (const Stretch &x : stretches) n += (int64_t)((x.len + length - 1) / length) * full_tasks(own[x.c0].tiles);
+        return n * Hkv <= kLongGroups;
+    };
+    while (length < DEFT_MAX_CHUNK && !fits()) length += 32;
+    if (!fits()) return false;
+    size_t c = 0;
+    for (const Stretch &x : stretches) {
+        out.insert(out.end(), own.begin() + c, own.begin() + x.c0);
+        const int32_t n = std::min(x.slots, (x.len + length - 1) / length), step = ((x.len + n - 1) / n + 31) / 32 * 32;
+        for (int32_t i = 0, at = 0; at < x.len; ++i, at += step) {
+            Run r = own[x.c0 + i];
+            r.s0 = own[x.c0].s0;
+            r.s1 = r.s0 + 1;
+            r.begin0 = own[x.c0].begin0 + at;
+            r.len = std::min(step, x.len - at);
+            if (at + step >= x.len) r.c1 = own[x.c0].c0 + x.slots;
+            out.push_back(r);
+        }
+        const Run &last = own[x.c1 - 1];
+        if (x.s1 < last.s1) {
+            Run r = last;
+            while (r.s0 < x.s1) r.len -= P->seg_len[r.s0++];
+            r.begin0 = P->seg_tok_begin[r.s0];
+            out.push_back(r);
+        }
+        c = x.c1;
+    }
+    out.insert(out.end(), own.begin() + c, own.end());
+    return true;
+}
 
 static void build_schedule(const deft_plan_t *P, int32_t G, int32_t Hkv, Schedule &S) {
     S.group = G;
@@ -853,7 +946,7 @@ static void build_schedule(const deft_plan_t *P, int32_t G, int32_t Hkv, Schedul
         const int32_t len = s1 > s0 ? seg_off[s1 - 1] + P->seg_len[s1 - 1] - seg_off[s0] : 0;
         // two-term softmax weights where some query of the group has a short path
         const int32_t precise = P->precise_all || short_paths[hi] > short_paths[lo];
-        own[c] = {c, c + 1, lo, hi, len, row_tiles(hi - lo, G), precise, P->chunk_slot_base[c], 0};
+        own[c] = {c, c + 1, s0, s1, s1 > s0 ? P->seg_tok_begin[s0] : 0, lo, hi, len, row_tiles(hi - lo, G), precise, P->chunk_slot_base[c], 0};
     }
 
     // A whole call is free to work on several chunks as one.  It does so where the plan's chunks are many and short: with
@@ -874,6 +967,7 @@ static void build_schedule(const deft_plan_t *P, int32_t G, int32_t Hkv, Schedul
             Run &j = joined.back();
             if (j.lo == r.lo && j.hi == r.hi && (int64_t)j.len + r.len <= kJoinTokens) {
                 j.c1 = r.c1;
+                j.s1 = r.s1;
                 j.len += r.len;
                 continue;
             }
@@ -898,10 +992,12 @@ static void build_schedule(const deft_plan_t *P, int32_t G, int32_t Hkv, Schedul
     S.off_seg_qhi = put(P->seg_qhi);
     S.off_seg_off = put(seg_off);
     S.off_q_order = put(P->q_order);
-    std::vector<int32_t> ptr, slots;  // of the joined runs: of each query's slots in the plan, those of a run's first chunk
-    if (!same) {
+    std::vector<int32_t> ptr, slots;
+    auto list_slots = [&](const std::vector<Run> &runs) {  // of each query's slots in the plan, those of a run's first chunk
         std::vector<uint8_t> first((size_t)m, 0);
-        for (const Run &r : joined) first[r.c0] = 1;
+        for (const Run &r : runs) first[r.c0] = 1;
+        ptr.clear();
+        slots.clear();
         ptr.reserve((size_t)P->nq + 1);
         slots.reserve(P->q_part_slot.size());
         for (int32_t p = 0; p < P->nq; ++p) {
@@ -910,12 +1006,25 @@ static void build_schedule(const deft_plan_t *P, int32_t G, int32_t Hkv, Schedul
                 if (first[P->q_part_chunk[i]]) slots.push_back(P->q_part_slot[i]);
         }
         ptr.push_back((int32_t)slots.size());
-    }
+    };
+    std::vector<Run> recut;
+    if (may_join(P)) recut_runs(P, own, joined, Hkv, recut);
     build_tasks(P, G, Hkv, std::move(own), P->q_part_ptr, P->q_part_slot, S, S.by_chunk);
-    if (same)
+    if (same) {
         S.fused = S.by_chunk;
-    else
+    } else {
+        list_slots(joined);
         build_tasks(P, G, Hkv, std::move(joined), ptr, slots, S, S.fused);
+    }
+    if (!recut.empty()) {
+        const size_t without = S.host_image.size();
+        list_slots(recut);
+        build_tasks(P, G, Hkv, std::move(recut), ptr, slots, S, S.recut);
+        if (S.host_image.size() > DEFT_STAGED_IMAGE_BYTES) {  // an upload would have to wait for the stream
+            S.host_image.resize(without);
+            S.recut = TaskSet();
+        }
+    }
     if (S.host_image.size() < 16) S.host_image.resize(16, 0);
     S.bytes = S.host_image.size();
 }
@@ -929,7 +1038,10 @@ size_t image_bytes(const deft_plan_t *P, int32_t G) {
     const size_t nq = (size_t)P->nq, record = sizeof(int32_t) * nq;
     const size_t set = align16(P->q_part_slot.size() * sizeof(int32_t)) + tasks * kItemInts * sizeof(int32_t) + 2 * 64 +
                        std::max(record * kQueryHeadInts, std::min(record * kQueryHeadMost, kQueryHeadBytes));
-    return 5 * align16((size_t)P->n_segs() * sizeof(int32_t)) + align16(record) + (may_join(P) ? 2 : 1) * set;
+    const size_t tables = 5 * align16((size_t)P->n_segs() * sizeof(int32_t)) + align16(record);
+    if (!may_join(P)) return tables + set;
+    // by chunk and joined; recut as well where that fits a staging slot
+    return std::max(tables + 2 * set, std::min<size_t>(tables + 3 * set, DEFT_STAGED_IMAGE_BYTES));
 }
 
 // acc [slots, Hq, d] + m [slots, Hq] + l [slots, Hq], fp32; never zero so callers can allocate it

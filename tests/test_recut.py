@@ -1,0 +1,52 @@
+"""Wide chunks cut anew, one task to a compute unit: the schedule on the host under the sanitizers (tests/sanitize/recut_driver.cpp), and
+calls on both sides of its lines.  Same tolerance as tests/test_gpu_parity.py."""
+
+import os
+import shutil
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2404_00242_amd import binding, workloads as wl
+
+from .test_sanitizers import ROOT, SAN, run
+from .test_short_chunks import check, reference
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_recut_sets_of_random_plans(tmp_path):
+    exe = str(tmp_path / "recut_driver")
+    csrc = os.path.join(ROOT, "paper_2404_00242_amd", "csrc")
+    run(["g++", "-std=c++17", *SAN, "-I", os.path.join(ROOT, "include"), "-I", csrc, os.path.join(csrc, "deft_plan.cpp"),
+         os.path.join(ROOT, "tests", "sanitize", "recut_driver.cpp"), "-lpthread", "-o", exe])
+    assert "recut sets checked" in run([exe])
+
+
+def star(root, leaves, Hq, Hkv, d, seed):
+    return wl._finish("recut", [root] + leaves, [-1] + [0] * len(leaves), list(range(1, len(leaves) + 1)), Hq, Hkv, d, seed)
+
+
+# one-token leaves in the root's last chunk, in chunks of their own, and a first leaf that fills it; rows that fill no
+# tile, several tasks to a run, roots that end inside a block; d = 64, which keeps the plan's chunks.  The stages called
+# apart after a whole call find the slots that it left empty.
+@pytest.mark.gpu
+@pytest.mark.parametrize("root,leaves,Hq,Hkv,d,chunk", [
+    (12345, [1] * 26, 32, 8, 128, 256), (4000, [1] * 51, 32, 8, 128, 160), (6017, [300] + [2, 1, 3] * 8, 28, 4, 128, 96),
+    (5120, [0, 1, 2] * 11, 32, 4, 128, 128), (9000, [1] * 81, 16, 16, 128, 256), (9000, [1] * 81, 16, 16, 64, 256)])
+def test_recut_calls(root, leaves, Hq, Hkv, d, chunk):
+    t = star(root, leaves, Hq, Hkv, d, root)
+    Q, K, V = wl.make_qkv(t)
+    ref = reference(t, Q, K, V)
+    q, k, v = Q.cuda(), K.cuda(), V.cuda()
+    lib = binding.load_library()
+    for mode in ("flatten", "balanced"):
+        plan = binding.deft_plan(t.node_tok_begin, t.node_tok_len, t.node_parent, t.query_node, t.ntok, chunk, binding.SPLIT_MODES[mode])
+        got = binding.deft_tree_attn_decode(plan, q, k, v, out_dtype=torch.float32)
+        check(got.cpu().numpy().astype(np.float64), ref, strict=False)
+        ws, o = plan.workspace(Hq, Hkv, d, q.device), torch.empty_like(got)
+        st = torch.cuda.current_stream().cuda_stream
+        img = plan.image(Hq, Hkv, q.device)
+        assert lib.deft_stage2_global_reduction(plan.handle, img.data_ptr(), o.data_ptr(), Hq, Hkv, d, 0.0, binding.DEFT_OUT_F32,
+                                                ws.data_ptr(), ws.numel(), st) == 0
+        check(o.cpu().numpy().astype(np.float64), ref, strict=False)

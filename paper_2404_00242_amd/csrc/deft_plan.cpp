@@ -854,9 +854,9 @@ static int32_t full_tasks(int32_t tiles) { return (tiles + kMaxTilesPerTask - 1)
 //
 // Whole call, us, as planned -> recut: 12345 tokens under 26 queries x 4 heads (392 workgroups of 256 tokens -> 256 of 416)
 // 25.2 -> 22.0; 4654 under 50 x 4 25.5 -> 20.6, 5251 under 34 x 8 33.2 -> 24.8, 15787 under 33 x 4 41.6 -> 32.7.  Over 564
-// trees of at most kRecutOthers other workgroups 0.86 of the time (0.60 to 1.12; 13 of them above 1.05).  With more of them the narrow tasks would
-// have shared the units: 0.97 at 65 to 80, 1.04 at 81 to 96, 1.11 at 97 to 112, 1.2 and more beyond.  One tile to a wave (3 or
-// 4 in a task) loses beside many narrow or at G = 1, where the launch waits for HBM: 1.09 and 1.02, up to 1.5.
+// trees of at most kRecutOthers other workgroups 0.86 of the time (0.60 to 1.12; 13 of them above 1.05).  With more of them the
+// narrow tasks would have shared the units: 0.97 at 65 to 80, 1.04 at 81 to 96, 1.11 at 97 to 112, 1.2 and more beyond.  One tile
+// to a wave (3 or 4 in a task) loses at G = 1, where the launch waits for HBM: 1.09 and 1.02, up to 1.5.
 static bool recut_runs(const deft_plan_t *P, const std::vector<Run> &own, const std::vector<Run> &joined, int32_t Hkv,
                        std::vector<Run> &out) {
     auto two_tiles_a_wave = [](const Run &r) {

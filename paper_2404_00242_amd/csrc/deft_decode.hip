@@ -1376,17 +1376,15 @@ enum Weights { kBf16 = 0, kTwoTerm = 1, kMixed = 2 };
 // per 32 tokens (1.2 us and more where rows are looked up token by token, as in chunks of several pieces, and with d = 64,
 // which has no fast addressing).  One piece and d = 128: up to three tiles; four tiles of 256 tokens on a full chip are
 // 17.5 us streamed and 20.3 us resident, and seven tiles beside narrow tasks 20.9 and 23.9 us a call (32 queries x 4 heads
-// over 7281 tokens).  Three tiles stream where such tasks are most of a launch and more than one to a compute unit: with two
-// on a unit both have their tokens late and their tiles behind that, while streamed tasks work on what has come.  Whole call,
-// us, resident -> streamed: 9.2 MB under 48 queries x 16 heads (304 of 448 tasks) 15.3 -> 14.2, 12000 tokens under 12 queries
-// x 4 heads (all of 376) 19.5 -> 17.8, 4000 under 48 queries x 32 heads (all of 512) 21.9 -> 20.2; but 192 of 512 tasks 12.7 ->
-// 13.4, 128 of 416 14.6 -> 16.9, 256 of 392 14.2 -> 15.9, 216 of 360 14.9 -> 15.7, 288 of 432 18.4 -> 19.1.  Several pieces
-// or d = 64: any number.  One such task among tasks of one piece is what its launch waits for (2977 tokens under 50 queries x
-// 4 heads, 16 of 712 workgroups, 24.6 -> 22.2 us a call), d = 64 under 31 queries x 4 heads 21.0 -> 18.7; on launches of
-// several rounds it is level: 952 workgroups 52.6 -> 51.3, 1696 78.3 -> 77.1, 704 37.4 -> 37.8, 896 38.5 -> 38.9, 3064 70.6 ->
-// 70.4.
+// over 7281 tokens).  (Three tiles streamed where they are most of a launch are 0.96 of the time over 256 trees, 0.88 to 1.09,
+// but 1.20 to 1.34 times as far from 64 bits: a resident weight is rounded relative to the largest of its wave's tokens, a
+// streaming one to that of the first block.)  Several pieces or d = 64: any number.  One such task among tasks of one piece is
+// what its launch waits for (2977 tokens under 50 queries x 4 heads, 16 of 712 workgroups, 24.6 -> 22.2 us a call), d = 64 under
+// 31 queries x 4 heads 21.0 -> 18.7; on launches of several rounds it is level: 952 workgroups 52.6 -> 51.3, 1696 78.3 -> 77.1,
+// 704 37.4 -> 37.8, 896 38.5 -> 38.9, 3064 70.6 -> 70.4.
 // (The limits are arguments of the kernel: as constants the compiler lays the kernel's registers out otherwise, and narrow
 // streaming tasks take 2 to 8 % longer.)
+constexpr int kResidentTiles = 3;
 template <int D>
 __device__ __forceinline__ bool is_resident(const Stage1Args &a, const int32_t *it) {
     return it[deft::kItLen] <= kResidentTokens<D> &&
@@ -1848,8 +1846,7 @@ bool launch_stage1(const deft::TaskSet &T, CallArgs a, unsigned reduce_groups, c
     Stage1Args &a1 = a.s1;
     const int32_t *items = reinterpret_cast<const int32_t *>(image + T.off_items);
     a1.n_items = T.n_items;
-    const bool split = (int64_t)T.n_items_split * a1.Hkv > deft::kLongGroups && 3 * T.n_items_split > 2 * T.n_items;  // see is_resident
-    a1.resident_one = split ? deft::kResidentTiles - 1 : deft::kResidentTiles;
+    a1.resident_one = kResidentTiles;
     a1.resident_many = deft::kMaxTilesPerTask;
     const size_t lds = std::max(kXbufBytes + 3 * (size_t)a1.table_len * sizeof(int32_t), (size_t)ResidentLds<D>::kWords * 4);
     const uint32_t Hkv = (uint32_t)a1.Hkv, tasks = (uint32_t)T.n_items * Hkv;

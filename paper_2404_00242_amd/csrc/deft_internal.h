@@ -63,7 +63,6 @@ constexpr int kResidentGroups = 512;  // workgroups of stage 1 that an MI355X ho
 // 49.2, 1.7 58.2 -> 66.8, 2.3 60.5 -> 71.6, 2.5 33.6 -> 38.2, 3.3 34.7 -> 38.5, 3.4 81.5 -> 90.8; with several pieces 4.5
 // 37.8 -> 31.1, 4.5 54.3 -> 45.2, 6.0 37.7 -> 30.7; one piece 4.7 22.7 -> 17.1, 5.9 38.9 -> 25.6, 9.3 31.8 -> 22.5.
 constexpr int kLongChunk = 256;
-constexpr int kResidentTiles = 3;  // see is_resident
 constexpr int kLongGroups = kResidentGroups / 2;
 constexpr int kLongestShare = 4;
 constexpr int kRecutOthers = kLongGroups / 4;  // see recut_runs
@@ -76,7 +75,6 @@ struct TaskSet {
     size_t off_q_part_slot = 0;  // per-query slot lists, where some query's does not fit its record
     int32_t n_items = 0;
     int32_t n_items_precise = 0;         // tasks among them that want two-term weights
-    int32_t n_items_split = 0;           // tasks among them that stay resident only where they are few, see is_resident
     int32_t head_ints = kQueryHeadInts;  // int32 per record
     int32_t max_parts = 0;               // partials of the query that has most
 };

@@ -813,7 +813,7 @@ static void build_tasks(const deft_plan_t *P, int32_t G, int32_t Hkv, std::vecto
               [](const Run &x, const Run &y) { return x.cost != y.cost ? x.cost > y.cost : x.c0 < y.c0; });
     int32_t *d = reinterpret_cast<int32_t *>(S.host_image.data() + T.off_items);
     T.n_items = (int32_t)n_tasks;
-    T.n_items_precise = T.n_items_split = 0;
+    T.n_items_precise = 0;
     for (const Run &r : runs) {
         const int32_t s0 = r.s0, per = per_run(r), pieces = distinct_pieces(P, r);
         for (int32_t t0 = 0; t0 < r.tiles; t0 += per, d += kItemInts) {
@@ -833,7 +833,6 @@ static void build_tasks(const deft_plan_t *P, int32_t G, int32_t Hkv, std::vecto
             d[kItPrecise] = r.precise;
             d[kItChunks] = r.c1 - r.c0;
             T.n_items_precise += r.precise;
-            T.n_items_split += d[kItNTiles] == kResidentTiles && r.len <= kLongChunk && pieces == 1;
         }
     }
 }

@@ -185,6 +185,7 @@ struct ChunkCtx {
     int clen;                       // tokens in the chunk
     int uniform;                    // the chunk is one piece of one node: rows are begin0 + x
     int begin0, qlo0, qhi0;
+    int fresh;                      // a block whose number has none of these bits set starts a new reference; -1: none does
     int n16, g;
 };
 
@@ -242,6 +243,12 @@ __device__ __forceinline__ void load_v(KVRegs<D> &r, const ChunkCtx &c, int x0, 
 // then reach 2^kLazyLog2, harmless in bf16 and fp32); otherwise a block costs no cross-lane traffic and
 // no rescaling of the accumulators.  Any reference gives the same (m, l, acc) up to rounding, because the
 // merge of eq. 1 only needs the three to be consistent.
+// The rounding is the smaller the more tokens were the reference once: such a token is among the heaviest of its row, and its
+// weight is exactly 1.  A stream that replaces several shorter ones therefore starts a new reference where each of them
+// would have begun (kItFresh): the largest exponent of that block, also if it is below the old one, but by no more than
+// kFreshLog2, which keeps the sums in range whatever the scores do (2^48 times larger after 6000 tokens in steps of 128).
+// Error against 64 bits over 330 calls with their chunks cut anew (recut_runs): 1.019 times what it is in the plan's chunks
+// with one reference to a stream, 0.99 with these, for 1.5 to 3 % of the call's time.
 struct RowState {
     float mc, thr;
     f32x4 l;  // four identical copies (rows 4g..4g+3 of the all-ones product)
@@ -249,6 +256,7 @@ struct RowState {
     __device__ __forceinline__ float m(float inv_cs) const { return thr == -INFINITY ? -INFINITY : mc * inv_cs; }
 };
 constexpr float kLazyLog2 = 8.0f;
+constexpr float kFreshLog2 = 1.0f;
 
 // Everything a wave keeps for one of its 16-row tiles: Q as the B operand of S^T = K Q^T (resident for the
 // whole chunk), the plan position of this lane's row (-1: no such row), the softmax state and the O^T
@@ -337,8 +345,9 @@ __device__ __forceinline__ void shift_block(const TileState<D> (&ts)[NT], f32x4 
 // lazy reference, on the shifted scores of shift_block: it is raised (for every tile of the wave) only when
 // some exponent exceeds kLazyLog2, i.e. some score exceeds the reference by more than kLazyLog2 / cs.  The
 // exponents come out of an fma, so their maximum needs no canonicalisation and takes four instructions per tile.
+// fresh: the block starts a new reference.
 template <int D, int NT>
-__device__ __forceinline__ void raise_block(TileState<D> (&ts)[NT], f32x4 (&sacc)[NT][2]) {
+__device__ __forceinline__ void raise_block(TileState<D> (&ts)[NT], f32x4 (&sacc)[NT][2], bool fresh = false) {
     float mx[NT];
     bool need = false;
 #pragma unroll
@@ -347,15 +356,15 @@ __device__ __forceinline__ void raise_block(TileState<D> (&ts)[NT], f32x4 (&sacc
                       fmaxf(fmaxf(sacc[t][1][0], sacc[t][1][1]), fmaxf(sacc[t][1][2], sacc[t][1][3])));
         need = need || (mx[t] > ts[t].rs.thr);
     }
-    if (__any(need)) {
+    if (__any(need) || fresh) {
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-            // move the reference of every row up to its running maximum (never down), rescale what was
+            // move the reference of every row up to its running maximum (down only for a new one), rescale what was
             // accumulated and move this block's exponents to the new reference
             RowState &st = ts[t].rs;
             const float r = wave_row_max(mx[t]);  // largest exponent of the row in this block, -inf if all masked
             const bool had = st.thr != -INFINITY;
-            const float d = had ? fmaxf(r, 0.f) : (r == -INFINITY ? 0.f : r);
+            const float d = had ? fmaxf(r, fresh ? -kFreshLog2 : 0.f) : (r == -INFINITY ? 0.f : r);
             const float alpha = had ? __builtin_amdgcn_exp2f(-d) : 0.f;  // nothing was accumulated before the first
             st.mc += d;
             st.thr = (had || r != -INFINITY) ? kLazyLog2 : -INFINITY;
@@ -705,7 +714,7 @@ struct WidePipe {
         read_v(xs, lane, vreg);
         if (!WHOLE) mask_block<D, NT>(c, blk * 32, ts, snew);
         shift_block<D, NT>(ts, snew, cs);
-        raise_block<D, NT>(ts, snew);
+        raise_block<D, NT>(ts, snew, UNIFORM && (blk & c.fresh) == 0);
 #pragma unroll
         for (int tt = 0; tt < NT; ++tt) {
             sacc[tt][0] = snew[tt][0];
@@ -1181,6 +1190,7 @@ __device__ __forceinline__ LeftRows streaming_task(const Stage1Args &a, const in
     ctx.begin0 = it[deft::kItBegin0];
     ctx.qlo0 = it[deft::kItSegQlo0];
     ctx.qhi0 = it[deft::kItSegQhi0];
+    ctx.fresh = it[deft::kItFresh] - 1;
     ctx.n16 = n16;
     ctx.g = g;
     const int nblk = (clen + 31) >> 5;
@@ -1384,7 +1394,6 @@ enum Weights { kBf16 = 0, kTwoTerm = 1, kMixed = 2 };
 // 704 37.4 -> 37.8, 896 38.5 -> 38.9, 3064 70.6 -> 70.4.
 // (The limits are arguments of the kernel: as constants the compiler lays the kernel's registers out otherwise, and narrow
 // streaming tasks take 2 to 8 % longer.)
-constexpr int kResidentTiles = 3;
 template <int D>
 __device__ __forceinline__ bool is_resident(const Stage1Args &a, const int32_t *it) {
     return it[deft::kItLen] <= kResidentTokens<D> &&
@@ -1846,7 +1855,7 @@ bool launch_stage1(const deft::TaskSet &T, CallArgs a, unsigned reduce_groups, c
     Stage1Args &a1 = a.s1;
     const int32_t *items = reinterpret_cast<const int32_t *>(image + T.off_items);
     a1.n_items = T.n_items;
-    a1.resident_one = kResidentTiles;
+    a1.resident_one = deft::kResidentTiles;
     a1.resident_many = deft::kMaxTilesPerTask;
     const size_t lds = std::max(kXbufBytes + 3 * (size_t)a1.table_len * sizeof(int32_t), (size_t)ResidentLds<D>::kWords * 4);
     const uint32_t Hkv = (uint32_t)a1.Hkv, tasks = (uint32_t)T.n_items * Hkv;

@@ -41,6 +41,7 @@ enum ItemField {
     kItSegQhi0 = 11,
     kItPrecise = 12,  // 1: the softmax weights enter the products as two bf16 terms (short paths, or on request)
     kItPieces = 14,   // segments to tell apart: 1 where they continue one another and have the same queries, else kItNSeg
+    kItFresh = 15,    // blocks (a power of two) after which a stream of one piece starts a new reference; 0: it keeps one
     kItChunks = 13,   // chunks worked on as one: the result goes to the slots of the first, those of the others stay empty
 };
 // A group one of whose queries has fewer tokens than this on its whole path gets two-term weights.
@@ -63,6 +64,7 @@ constexpr int kResidentGroups = 512;  // workgroups of stage 1 that an MI355X ho
 // 49.2, 1.7 58.2 -> 66.8, 2.3 60.5 -> 71.6, 2.5 33.6 -> 38.2, 3.3 34.7 -> 38.5, 3.4 81.5 -> 90.8; with several pieces 4.5
 // 37.8 -> 31.1, 4.5 54.3 -> 45.2, 6.0 37.7 -> 30.7; one piece 4.7 22.7 -> 17.1, 5.9 38.9 -> 25.6, 9.3 31.8 -> 22.5.
 constexpr int kLongChunk = 256;
+constexpr int kResidentTiles = 3;  // of a task of one piece that is held in registers, see is_resident in deft_decode.hip
 constexpr int kLongGroups = kResidentGroups / 2;
 constexpr int kLongestShare = 4;
 constexpr int kRecutOthers = kLongGroups / 4;  // see recut_runs

@@ -716,6 +716,7 @@ struct Run {
     int32_t begin0;
     int32_t lo, hi;  // queries, in plan positions
     int32_t len, tiles, precise, slot_base;
+    int32_t fresh;   // see kItFresh
     int64_t cost;    // of the largest task, for the dispatch order
 };
 
@@ -733,29 +734,31 @@ static int32_t distinct_pieces(const deft_plan_t *P, const Run &r) {
 
 static int32_t row_tiles(int32_t width, int32_t G) { return (int32_t)(((int64_t)width * G + 15) / 16); }
 
-// Tasks and stage-2 records of a list of runs, appended to the image.  ptr, slots: the slots of each query's partial
-// results, in the order of the runs.
-static void build_tasks(const deft_plan_t *P, int32_t G, int32_t Hkv, std::vector<Run> runs, const std::vector<int32_t> &ptr,
-                        const std::vector<int32_t> &slots, Schedule &S, TaskSet &T) {
-    constexpr int kCuts = (int)(sizeof(kTaskTiles) / sizeof(kTaskTiles[0]));
-    int64_t n_short[kCuts] = {}, n_long[kCuts] = {}, work = 0, longest = 0;
-    auto per_task = [](int32_t tiles, int cut) {
-        const int32_t k = (tiles + kTaskTiles[cut] - 1) / kTaskTiles[cut];
+// How the rows of a list of runs are cut into tasks.
+struct Cut {
+    int32_t wide_and_long = kTaskTiles[0], others = kTaskTiles[0];  // row tiles that a task may have
+    size_t n_tasks = 0;
+    static bool is_wide_and_long(const Run &r) { return r.len > kLongChunk && r.tiles > kTaskTiles[kCuts - 1]; }
+    static int32_t per_task(int32_t tiles, int32_t most) {
+        const int32_t k = (tiles + most - 1) / most;
         return k ? (tiles + k - 1) / k : 1;
-    };
-    auto wide_and_long = [](const Run &r) { return r.len > kLongChunk && r.tiles > kTaskTiles[kCuts - 1]; };
+    }
+    int32_t per_run(const Run &r) const { return per_task(r.tiles, is_wide_and_long(r) ? wide_and_long : others); }
+    static constexpr int kCuts = (int)(sizeof(kTaskTiles) / sizeof(kTaskTiles[0]));
+};
+static Cut choose_cut(const deft_plan_t *P, const std::vector<Run> &runs, int32_t Hkv) {
+    constexpr int kCuts = Cut::kCuts;
+    int64_t n_short[kCuts] = {}, n_long[kCuts] = {}, work = 0, longest = 0;
     for (const Run &r : runs) {
-        const int32_t pieces = distinct_pieces(P, r);
-        if (pieces > 1)
-            S.table_len = std::max(S.table_len, (r.len + 31) / 32 * 32);
+        const bool wide_and_long = Cut::is_wide_and_long(r);
         for (int i = 0; i < kCuts; ++i) {
-            const int32_t per = per_task(r.tiles, i), n = (r.tiles + per - 1) / per;
-            (wide_and_long(r) ? n_long : n_short)[i] += n;
+            const int32_t per = Cut::per_task(r.tiles, kTaskTiles[i]), n = (r.tiles + per - 1) / per;
+            (wide_and_long ? n_long : n_short)[i] += n;
         }
-        const int32_t per = per_task(r.tiles, 0);
+        const int32_t per = Cut::per_task(r.tiles, kTaskTiles[0]);
         const int64_t cost = (int64_t)r.len * (2 + per);
         work += cost * ((r.tiles + per - 1) / per);
-        if (wide_and_long(r)) longest = std::max(longest, pieces > 1 ? cost * 4 / 3 : cost);
+        if (wide_and_long) longest = std::max(longest, distinct_pieces(P, r) > 1 ? cost * 4 / 3 : cost);
     }
     int cut_long = 0, cut_short = 0;
     // A second round of workgroups is worth it only where the launch waits for its longest task: where that task costs
@@ -767,8 +770,21 @@ static void build_tasks(const deft_plan_t *P, int32_t G, int32_t Hkv, std::vecto
             cut_long = i;
     for (int i = 1; i < kCuts; ++i)
         if ((n_long[cut_long] + n_short[i]) * Hkv <= kResidentGroups) cut_short = i;
-    auto per_run = [&](const Run &r) { return per_task(r.tiles, wide_and_long(r) ? cut_long : cut_short); };
-    const size_t n_tasks = (size_t)(n_long[cut_long] + n_short[cut_short]);
+    Cut cut;
+    cut.wide_and_long = kTaskTiles[cut_long];
+    cut.others = kTaskTiles[cut_short];
+    cut.n_tasks = (size_t)(n_long[cut_long] + n_short[cut_short]);
+    return cut;
+}
+
+// Tasks and stage-2 records of a list of runs, appended to the image.  ptr, slots: the slots of each query's partial
+// results, in the order of the runs.
+static void build_tasks(const deft_plan_t *P, int32_t G, int32_t Hkv, std::vector<Run> runs, const std::vector<int32_t> &ptr,
+                        const std::vector<int32_t> &slots, Schedule &S, TaskSet &T) {
+    for (const Run &r : runs)
+        if (distinct_pieces(P, r) > 1) S.table_len = std::max(S.table_len, (r.len + 31) / 32 * 32);
+    const Cut cut = choose_cut(P, runs, Hkv);
+    const size_t n_tasks = cut.n_tasks;
 
     auto place = [&](size_t bytes, size_t align) {
         const size_t at = (S.host_image.size() + align - 1) / align * align;
@@ -808,14 +824,14 @@ static void build_tasks(const deft_plan_t *P, int32_t G, int32_t Hkv, std::vecto
     // the short ones fill the tail.  The row groups of one run share one estimate (that of the largest of
     // them) and equal estimates keep their order, which leaves them next to each other: they re-read
     // the tokens from the same L2 while they are still there.
-    for (Run &r : runs) r.cost = (int64_t)r.len * (2 + per_run(r));
+    for (Run &r : runs) r.cost = (int64_t)r.len * (2 + cut.per_run(r));
     std::sort(runs.begin(), runs.end(),
               [](const Run &x, const Run &y) { return x.cost != y.cost ? x.cost > y.cost : x.c0 < y.c0; });
     int32_t *d = reinterpret_cast<int32_t *>(S.host_image.data() + T.off_items);
     T.n_items = (int32_t)n_tasks;
     T.n_items_precise = 0;
     for (const Run &r : runs) {
-        const int32_t s0 = r.s0, per = per_run(r), pieces = distinct_pieces(P, r);
+        const int32_t s0 = r.s0, per = cut.per_run(r), pieces = distinct_pieces(P, r);
         for (int32_t t0 = 0; t0 < r.tiles; t0 += per, d += kItemInts) {
             d[kItChunk] = r.c0;
             d[kItTile0] = t0;
@@ -832,6 +848,7 @@ static void build_tasks(const deft_plan_t *P, int32_t G, int32_t Hkv, std::vecto
             d[kItSegQhi0] = P->seg_qhi[s0];
             d[kItPrecise] = r.precise;
             d[kItChunks] = r.c1 - r.c0;
+            d[kItFresh] = r.fresh;
             T.n_items_precise += r.precise;
         }
     }
@@ -849,7 +866,9 @@ static int32_t full_tasks(int32_t tiles) { return (tiles + kMaxTilesPerTask - 1)
 // chunks; slots that are left stay empty, as where chunks are joined.  If the last chunk goes on with other pieces (one-token
 // nodes of a draft tree), those become a run of their own with that chunk's slots.  The runs are as short as kLongGroups
 // workgroups allow.  Only d = 128: with d = 64 twice as many tokens are held in registers, and longer runs stream them
-// (level to 30 % slower).  false: not such a launch.
+// (level to 30 % slower).  Nor where tasks of the launch as it is are held in registers, whose weights are rounded less: a call whose
+// rows all were was 1.27 times as far from 64 bits.  A run starts new references as often as the runs that it replaces began
+// (RowState).  false: not such a launch.
 //
 // Whole call, us, as planned -> recut: 12345 tokens under 26 queries x 4 heads (392 workgroups of 256 tokens -> 256 of 416)
 // 25.2 -> 22.0; 4654 under 50 x 4 25.5 -> 20.6, 5251 under 34 x 8 33.2 -> 24.8, 15787 under 33 x 4 41.6 -> 32.7.  Over 564
@@ -866,16 +885,17 @@ static bool recut_runs(const deft_plan_t *P, const std::vector<Run> &own, const 
         size_t c0, c1;    // of `own`
         int32_t s1, len;  // its tokens are those of the segments up to s1
         int32_t slots;    // chunks whose slots its runs may use: all but one that has further pieces
+        int32_t fresh;    // blocks, a power of two, in the shorter runs that they replace
     };
     std::vector<Stretch> stretches;
     int64_t now = 0, others = 0;
     for (const Run &r : joined) now += (int64_t)full_tasks(r.tiles) * Hkv;
     if (now <= kLongGroups) return false;
-    for (size_t c = 0, e; c < own.size(); c = e) {
+    for (size_t c = 0, e, at = 0; c < own.size(); c = e) {
         const Run &r = own[c];
         for (e = c + 1; e < own.size() && own[e].lo == r.lo && own[e].hi == r.hi;) ++e;
         const Run &last = own[e - 1];
-        Stretch x{c, e, r.s0, 0, (int32_t)(e - c)};
+        Stretch x{c, e, r.s0, 0, (int32_t)(e - c), 1};
         for (; x.s1 < last.s1 && P->seg_qlo[x.s1] == r.lo && P->seg_qhi[x.s1] == r.hi &&
                (x.s1 == r.s0 || P->seg_tok_begin[x.s1] == P->seg_tok_begin[x.s1 - 1] + P->seg_len[x.s1 - 1]);
              ++x.s1)
@@ -890,6 +910,8 @@ static bool recut_runs(const deft_plan_t *P, const std::vector<Run> &own, const 
             }
         }
         if (x.s1 >= last.s0 && x.slots > 1 && two_tiles_a_wave(r)) {
+            while (joined[at].c0 < r.c0) ++at;
+            while (64 * x.fresh <= joined[at].len) x.fresh *= 2;
             stretches.push_back(x);
             if (x.slots < (int32_t)(e - c)) others += full_tasks(last.tiles);
         } else {
@@ -897,6 +919,10 @@ static bool recut_runs(const deft_plan_t *P, const std::vector<Run> &own, const 
         }
     }
     if (stretches.empty() || others * Hkv > kRecutOthers) return false;
+    const Cut cut = choose_cut(P, joined, Hkv);
+    for (const Run &r : joined)  // (a row's last task has the fewest tiles)
+        if (two_tiles_a_wave(r) && r.len <= kLongChunk && (r.tiles - 1) % cut.per_run(r) < kResidentTiles && distinct_pieces(P, r) == 1)
+            return false;
     int32_t length = kLongChunk;
     auto fits = [&] {
         int64_t n = others;
@@ -915,6 +941,7 @@ static bool recut_runs(const deft_plan_t *P, const std::vector<Run> &own, const 
             r.s1 = r.s0 + 1;
             r.begin0 = own[x.c0].begin0 + at;
             r.len = std::min(step, x.len - at);
+            r.fresh = x.fresh;
             if (at + step >= x.len) r.c1 = own[x.c0].c0 + x.slots;
             out.push_back(r);
         }
@@ -945,7 +972,7 @@ static void build_schedule(const deft_plan_t *P, int32_t G, int32_t Hkv, Schedul
         const int32_t len = s1 > s0 ? seg_off[s1 - 1] + P->seg_len[s1 - 1] - seg_off[s0] : 0;
         // two-term softmax weights where some query of the group has a short path
         const int32_t precise = P->precise_all || short_paths[hi] > short_paths[lo];
-        own[c] = {c, c + 1, s0, s1, s1 > s0 ? P->seg_tok_begin[s0] : 0, lo, hi, len, row_tiles(hi - lo, G), precise, P->chunk_slot_base[c], 0};
+        own[c] = {c, c + 1, s0, s1, s1 > s0 ? P->seg_tok_begin[s0] : 0, lo, hi, len, row_tiles(hi - lo, G), precise, P->chunk_slot_base[c], 0, 0};
     }
 
     // A whole call is free to work on several chunks as one.  It does so where the plan's chunks are many and short: with

@@ -859,22 +859,70 @@ static bool may_join(const deft_plan_t *P) { return P->mode == DEFT_SPLIT_FLATTE
 
 static int32_t full_tasks(int32_t tiles) { return (tiles + kMaxTilesPerTask - 1) / kMaxTilesPerTask; }
 
-// One task to a compute unit in the place of two.  Where nearly all of a launch is wide tasks of one piece, two tiles to a
-// wave, two of them on a unit only take turns (32768 tokens under 64 queries x 4 heads: 59.0 us a call as 256 tasks, 59.2 as
-// 512).  Longer tasks, as many as there are units, write and merge fewer partial results.  The tokens of
+// When a launch of wide tasks ends, in twentieths of the step that a task of five to eight row tiles takes for a block.  Tasks are
+// dealt to the compute units in the order of their cost.  Three and four tiles count 0.8 of a step, one and two a quarter (they
+// run beside others), a quarter more where rows are looked up, a fifth more where the stream starts new references; every task
+// has five steps of start and end and 1.5 a tile for its partial results, of which those that share a unit hide a tenth; 50
+// steps pass around stage 1 or do not depend on the cut.  Fitted to 1634 trees run both ways, see recut_runs.
+static int64_t launch_end(const deft_plan_t *P, const std::vector<Run> &runs, int32_t Hkv) {
+    const Cut cut = choose_cut(P, runs, Hkv);
+    std::vector<std::pair<int64_t, int64_t>> kinds;  // cost, tasks
+    for (const Run &r : runs) {
+        const int32_t per = cut.per_run(r), pieces = distinct_pieces(P, r);
+        auto add = [&](int32_t tiles, int64_t n) {
+            const int64_t step = (tiles > 4 ? 20 : tiles > 2 ? 16 : 5) * (pieces > 1 ? 25 : r.fresh ? 24 : 20) / 20;
+            const int64_t cost = (r.len + 31) / 32 * step + 100 + 30 * tiles;
+            if (!kinds.empty() && kinds.back().first == cost)
+                kinds.back().second += n * Hkv;
+            else
+                kinds.emplace_back(cost, n * Hkv);
+        };
+        if (r.tiles / per) add(per, r.tiles / per);
+        if (r.tiles % per) add(r.tiles % per, 1);
+    }
+    std::sort(kinds.begin(), kinds.end(), [](const auto &x, const auto &y) { return x.first > y.first; });
+    std::vector<std::pair<int64_t, int64_t>> units{{0, kLongGroups}};  // (busy until, compute units), the first free first
+    for (const auto &[cost, tasks] : kinds)
+        for (int64_t left = tasks; left > 0;) {
+            const auto [busy, free] = units[0];
+            const int64_t n = std::min(left, free), until = busy ? busy + cost * 9 / 10 : cost;
+            left -= n;
+            if (n == free)
+                units.erase(units.begin());
+            else
+                units[0].second -= n;
+            auto at = std::lower_bound(units.begin(), units.end(), until, [](const auto &u, int64_t t) { return u.first < t; });
+            if (at != units.end() && at->first == until)
+                at->second += n;
+            else
+                units.insert(at, {until, n});
+        }
+    return units.back().first + 1000;
+}
+
+// One long task to a compute unit in the place of two.  Where nearly all of a launch is wide tasks of one piece, two tiles to a
+// wave, two of them on a unit mostly take turns (32768 tokens under 64 queries x 4 heads: 59.0 us a call as 256 tasks, 59.2 as
+// 512).  Longer tasks, at most as many as there are units, write and merge fewer partial results.  The tokens of
 // consecutive chunks with the same queries are cut anew, into equal runs of whole blocks, each with the slots of one of those
 // chunks; slots that are left stay empty, as where chunks are joined.  If the last chunk goes on with other pieces (one-token
 // nodes of a draft tree), those become a run of their own with that chunk's slots.  The runs are as short as kLongGroups
-// workgroups allow.  Only d = 128: with d = 64 twice as many tokens are held in registers, and longer runs stream them
+// workgroups allow, the short ones among the others counted whole; those are then cut as finely as kResidentGroups allow.
+// Only d = 128: with d = 64 twice as many tokens are held in registers, and longer runs stream them
 // (level to 30 % slower).  Nor where tasks of the launch as it is are held in registers, whose weights are rounded less: a call whose
 // rows all were was 1.27 times as far from 64 bits.  A run starts new references as often as the runs that it replaces began
 // (RowState).  false: not such a launch.
 //
-// Whole call, us, as planned -> recut: 12345 tokens under 26 queries x 4 heads (392 workgroups of 256 tokens -> 256 of 416)
-// 25.2 -> 22.0; 4654 under 50 x 4 25.5 -> 20.6, 5251 under 34 x 8 33.2 -> 24.8, 15787 under 33 x 4 41.6 -> 32.7.  Over 564
-// trees of at most kRecutOthers other workgroups 0.86 of the time (0.60 to 1.12; 13 of them above 1.05).  With more of them the
-// narrow tasks would have shared the units: 0.97 at 65 to 80, 1.04 at 81 to 96, 1.11 at 97 to 112, 1.2 and more beyond.  One tile
-// to a wave (3 or 4 in a task) loses at G = 1, where the launch waits for HBM: 1.09 and 1.02, up to 1.5.
+// Nor unless the call is to end a tenth sooner (launch_end) on more than three quarters of the units: a run more is
+// full_tasks x Hkv workgroups more at once, and the count may stop well short of the units with every run the longer for it.
+// Whole call, us, as planned -> cut anew: 12345 tokens under 26 queries x 4 heads (392 workgroups of 256 tokens -> 240 of 416 and
+// 32 short ones) 24.4 -> 21.9, 4000 under 51 x 4 in chunks of 160 26.6 -> 22.2, 9000 under 81 x 1 34.0 -> 25.1; but 15589 under 35
+// x 8 (480 of 768 tokens -> 216 of 1760 or less) 39.9 -> 46.8.  The estimate was fitted to 1634 trees of 4 to 300 queries and 1 to
+// 64 KV heads run both ways, then tried on 600 others: the 407 it takes are 0.81 of the time (0.45 to 1.19), 5 of them above 1.02
+// (1.10 to 1.19: two of 638 and 1541 tokens under more than 100 queries, and three of 1, 4 and 5 KV heads whose steps take half as
+// long again as others', why is not known); without it 46 of the 600 would be, up to 1.36.  On 205 draft, few-shot and long-context
+// trees of up to 64 queries: 0.84, 1.01 at most.  With more others than kRecutOthers the narrow tasks would have shared the units:
+// 0.97 at 65 to 80, 1.04 at 81 to 96, 1.11 at 97 to 112, 1.2 and more beyond (1975 trees, without the estimate).  One tile to a
+// wave (3 or 4 in a task) loses at G = 1, where the launch waits for HBM: 1.09 and 1.02, up to 1.5.
 static bool recut_runs(const deft_plan_t *P, const std::vector<Run> &own, const std::vector<Run> &joined, int32_t Hkv,
                        std::vector<Run> &out) {
     auto two_tiles_a_wave = [](const Run &r) {
@@ -955,7 +1003,11 @@ static bool recut_runs(const deft_plan_t *P, const std::vector<Run> &own, const 
         c = x.c1;
     }
     out.insert(out.end(), own.begin() + c, own.end());
-    return true;
+    if (4 * (int64_t)choose_cut(P, out, Hkv).n_tasks * Hkv > 3 * kLongGroups &&
+        10 * launch_end(P, out, Hkv) < 9 * launch_end(P, joined, Hkv))
+        return true;
+    out.clear();
+    return false;
 }
 
 static void build_schedule(const deft_plan_t *P, int32_t G, int32_t Hkv, Schedule &S) {

@@ -93,7 +93,9 @@ int main() {
             whole += P->chunk_seg_ptr[P->n_chunks()] - P->chunk_seg_ptr[P->n_chunks() - 1] > 1;
             for (const auto &x : sees) CHECK(x == nobody);
             CHECK((int32_t)slots_done.size() == P->n_slots());
-            CHECK((int64_t)T.n_items * Hkv <= kResidentGroups);
+            int64_t groups = (int64_t)T.n_items * Hkv, of_long = 0;
+            for (int32_t i = 0; i < T.n_items; ++i) of_long += at(T.off_items)[(size_t)i * kItemInts + kItLen] > kLongChunk ? Hkv : 0;
+            CHECK(groups <= kResidentGroups && of_long <= kLongGroups && 4 * groups > 3 * kLongGroups);
             int32_t most = 0;
             for (int32_t p = 0; p < leaves; ++p) {
                 const int32_t *h = at(T.off_q_head) + (size_t)p * T.head_ints, room = T.head_ints - kQueryHeadFixed;

@@ -1,5 +1,6 @@
 // The tasks of a whole call at d = 128 on a star, a root under leaves of given lengths with one query each (deft_plan.cpp), built
-// with -fsanitize=address,undefined by the tests: prints one line per kind of task, "workgroups tokens tiles pieces".
+// with -fsanitize=address,undefined by the tests: prints whether the chunks are cut anew (recut_runs), then one line per kind of
+// task, "workgroups tokens tiles pieces".
 //   star_driver Hq Hkv chunk flags root leaf...
 #include <cstdint>
 #include <cstdio>
@@ -32,6 +33,7 @@ int main(int argc, char **argv) {
     const int32_t *d = reinterpret_cast<const int32_t *>(S->host_image.data() + T.off_items);
     std::map<std::vector<int32_t>, int32_t> kinds;
     for (int32_t i = 0; i < T.n_items; ++i, d += kItemInts) kinds[{d[kItLen], d[kItNTiles], d[kItPieces]}] += Hkv;
+    printf("%s\n", S->recut.n_items ? "cut anew" : "as planned");
     for (const auto &k : kinds) printf("%d %d %d %d\n", k.second, k.first[0], k.first[1], k.first[2]);
     deft_plan_destroy(P);
 }

@@ -23,6 +23,31 @@ def test_recut_sets_of_random_plans(tmp_path):
     assert "recut sets checked" in run([exe])
 
 
+# (root, leaves, Hq, Hkv, chunk): us a call as planned and cut anew.  A run more costs Hkv workgroups for every eight row tiles, and
+# where that is many the launch would stop well short of the compute units, or a few long tasks would end it.
+SLOWER = [(15589, [1] * 35, 64, 8, 768),  # 39.9, 46.8
+          (15733, [1] * 34, 64, 8, 768),  # 39.9, 46.7
+          (11083, [1] * 50, 64, 8, 768),  # 39.3, 44.4
+          (8000, [1] * 64, 128, 16, 1024),  # 61.8, 67.2
+          (6000, [1] * 130, 32, 32, 768),  # 50.7, 53.0
+          (4096, [0] * 280, 64, 8, 256)]  # 93.6, 98.3
+FASTER = [(12345, [1] * 26, 32, 8, 256),  # 25.0, 22.4
+          (4000, [1] * 51, 32, 8, 160),  # 26.6, 22.2
+          (9000, [1] * 81, 16, 16, 256),  # 34.0, 25.1
+          (7853, [30] * 35, 64, 8, 384)]  # 44.6, 33.1
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_cut_anew_only_where_the_launch_ends_earlier(tmp_path):
+    exe = str(tmp_path / "star_driver")
+    csrc = os.path.join(ROOT, "paper_2404_00242_amd", "csrc")
+    run(["g++", "-std=c++17", *SAN, "-I", os.path.join(ROOT, "include"), "-I", csrc, os.path.join(csrc, "deft_plan.cpp"),
+         os.path.join(ROOT, "tests", "sanitize", "star_driver.cpp"), "-lpthread", "-o", exe])
+    for cases, route in ((SLOWER, "as planned"), (FASTER, "cut anew")):
+        for root, leaves, Hq, Hkv, chunk in cases:
+            assert run([exe, *map(str, (Hq, Hkv, chunk, 0, root, *leaves))]).startswith(route), (root, len(leaves), Hq, Hkv)
+
+
 def star(root, leaves, Hq, Hkv, d, seed):
     return wl._finish("recut", [root] + leaves, [-1] + [0] * len(leaves), list(range(1, len(leaves) + 1)), Hq, Hkv, d, seed)
 

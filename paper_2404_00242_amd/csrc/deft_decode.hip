@@ -1900,9 +1900,11 @@ struct Call {
     hipStream_t stream = nullptr;
 };
 
-// The tasks of a whole call.
-const deft::TaskSet &whole_call(const Call &call, int32_t d) {
-    return d == 128 && call.S->recut.n_items > 0 ? call.S->recut : call.S->fused;
+// The tasks of a whole call.  Chunks are cut anew into as many runs as the KV heads of the first upload ask for; with fewer heads
+// they would leave most of the chip idle (12345 tokens under 26 queries x 4 heads, uploaded for 32 KV heads and called with two:
+// 22 workgroups, 98 as planned).
+const deft::TaskSet &whole_call(const Call &call, int32_t Hkv, int32_t d) {
+    return d == 128 && Hkv == call.S->Hkv && call.S->recut.n_items > 0 ? call.S->recut : call.S->fused;
 }
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
@@ -2011,7 +2013,7 @@ uint64_t new_ticket() {
 int run_call(const deft_plan_t *plan, const Call &call, const void *q, const void *k, const void *v, void *o, int32_t Hq,
              int32_t Hkv, int32_t d, uint32_t flags, int32_t polls) {
     if (!stage1_inputs_ok(q, k, v)) return DEFT_EINVAL;
-    const deft::TaskSet &T = whole_call(call, d);
+    const deft::TaskSet &T = whole_call(call, Hkv, d);
     CallArgs a{};
     stage1_args(call, q, k, v, Hq, Hkv, a.s1);
     stage2_args(plan, call, T, o, Hq, flags, a.s2);
@@ -2048,7 +2050,7 @@ bool is_captured(hipStream_t st) {
 // 7.5, 5 MB under 56 rows 7.5 -> 11.3), and their marks could hold the ticket from the replay before.
 bool one_launch(const deft_plan_t *plan, const Call &call, int32_t Hq, int32_t Hkv, int32_t d) {
     constexpr int64_t kWavesOfRows = kWaves * kReduceGroups;
-    const deft::TaskSet &T = whole_call(call, d);
+    const deft::TaskSet &T = whole_call(call, Hkv, d);
     if (!call.marks || plan->nq == 0 || T.n_items == 0) return false;
     const int64_t batch = d == 128 ? kReduceLoads * Stage2Row<128>::kRows : kReduceLoads * Stage2Row<64>::kRows;
     const int64_t rows = (int64_t)plan->nq * Hq, parts = T.max_parts, bytes = (int64_t)plan->n_flat * Hkv * d * 4;
@@ -2216,9 +2218,9 @@ int decode(const deft_plan_t *plan, const void *dev_image, const void *q, const 
     if (flags != DEFT_OUT_BF16 && flags != DEFT_OUT_F32) return DEFT_EINVAL;
     if (plan->nq > 0 && (!o || !aligned16(o))) return DEFT_EINVAL;
     if (one_launch(plan, call, Hq, Hkv, d)) return run_call(plan, call, q, k, v, o, Hq, Hkv, d, flags, polls);
-    rc = run_stage1(plan, call, whole_call(call, d), q, k, v, Hq, Hkv, d);
+    rc = run_stage1(plan, call, whole_call(call, Hkv, d), q, k, v, Hq, Hkv, d);
     if (rc != DEFT_OK) return rc;
-    return run_stage2(plan, call, whole_call(call, d), o, Hq, d, flags);
+    return run_stage2(plan, call, whole_call(call, Hkv, d), o, Hq, d, flags);
 }
 }  // namespace
 

@@ -85,13 +85,14 @@ struct TaskSet {
 // that an image was first uploaded for; the schedule is right for any.
 struct Schedule {
     int32_t group = 0;        // G = Hq / Hkv, rows per query within one KV head
+    int32_t Hkv = 0;          // KV heads that it suits
     size_t bytes = 0;         // total image size
     // byte offsets of the canonical arrays inside the image
     size_t off_seg_tok_begin = 0, off_seg_len = 0, off_seg_qlo = 0, off_seg_qhi = 0, off_seg_off = 0;
     size_t off_q_order = 0;
     TaskSet by_chunk;         // one partial result per (chunk, query of its group): what the two stages called apart use
     TaskSet fused;            // the same work on joined chunks: what a whole call uses; the same as by_chunk if none are
-    TaskSet recut;            // wide chunks cut anew, one task to a compute unit: for whole calls with d = 128, if there are any
+    TaskSet recut;            // wide chunks cut anew (recut_runs): for whole calls with d = 128 and Hkv KV heads, if there are any
     int32_t table_len = 32;   // longest chunk made of several pieces, rounded up to whole blocks: LDS table size
     std::vector<uint8_t> host_image;  // packed image, kept for repeated uploads
 };

@@ -1012,6 +1012,7 @@ static bool recut_runs(const deft_plan_t *P, const std::vector<Run> &own, const 
 
 static void build_schedule(const deft_plan_t *P, int32_t G, int32_t Hkv, Schedule &S) {
     S.group = G;
+    S.Hkv = Hkv;
     S.table_len = 32;
     const int32_t m = P->n_chunks(), nseg = P->n_segs();
     std::vector<int32_t> seg_off(nseg);  // flattened position of a segment's first token

@@ -1,6 +1,6 @@
-// Stands in for the HIP runtime calls that deft_plan_upload makes, on a machine without a GPU: loaded with RTLD_GLOBAL before
-// libdeft.so, its functions are the ones the library finds.  Kernels are counted and not run, copies are done at once.  What
-// the calls answer is set by the test (tests/test_upload_errors.py).
+// Stands in for the HIP runtime calls that deft_plan_upload and the calls make, on a machine without a GPU: loaded with
+// RTLD_GLOBAL before libdeft.so, its functions are the ones the library finds.  Kernels are counted and not run, copies are done
+// at once.  What the calls answer is set by the test (tests/test_upload_errors.py, tests/test_recut.py).
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
@@ -11,7 +11,10 @@ extern "C" {
 struct {
     int32_t device, stream_device, pointer_device, pointer_type, capturing, event_error;  // answers
     int32_t launches, copies, events_recorded;                                            // calls made
-} fake = {0, 0, 0, hipMemoryTypeDevice, hipStreamCaptureStatusNone, hipSuccess, 0, 0, 0};
+    int32_t grid[16];         // workgroups of the launches, the last 16 of them,
+    const void *kernel[16];   // and their kernels
+} fake = {0, 0, 0, hipMemoryTypeDevice, hipStreamCaptureStatusNone, hipSuccess, 0, 0, 0, {}, {}};
+static dim3 pushed;
 
 hipError_t hipGetDevice(int *d) { *d = fake.device; return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
@@ -36,9 +39,14 @@ hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *) {
 }
 hipError_t hipStreamGetDevice(hipStream_t, hipDevice_t *d) { *d = fake.stream_device; return hipSuccess; }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s) { *s = (hipStreamCaptureStatus)fake.capturing; return hipSuccess; }
-hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
-hipError_t __hipPopCallConfiguration(dim3 *, dim3 *, size_t *, hipStream_t *) { return hipSuccess; }
-hipError_t hipLaunchKernel(const void *, dim3, dim3, void **, size_t, hipStream_t) { ++fake.launches; return hipSuccess; }
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3, size_t, hipStream_t) { pushed = grid; return hipSuccess; }
+hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *, size_t *, hipStream_t *) { *grid = pushed; return hipSuccess; }
+hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { return hipSuccess; }
+hipError_t hipLaunchKernel(const void *kernel, dim3 grid, dim3, void **, size_t, hipStream_t) {
+    fake.grid[fake.launches % 16] = (int32_t)grid.x;
+    fake.kernel[fake.launches++ % 16] = kernel;
+    return hipSuccess;
+}
 hipError_t hipExtLaunchKernel(const void *, dim3, dim3, void **, size_t, hipStream_t, hipEvent_t, hipEvent_t, int) {
     ++fake.launches;
     return hipSuccess;

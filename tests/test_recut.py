@@ -12,6 +12,7 @@ from paper_2404_00242_amd import binding, workloads as wl
 
 from .test_sanitizers import ROOT, SAN, run
 from .test_short_chunks import check, reference, stages
+from .test_upload_errors import fake, needs_gxx, run as run_faked  # noqa: F401
 
 
 @pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
@@ -46,6 +47,45 @@ def test_cut_anew_only_where_the_launch_ends_earlier(tmp_path):
     for cases, route in ((SLOWER, "as planned"), (FASTER, "cut anew")):
         for root, leaves, Hq, Hkv, chunk in cases:
             assert run([exe, *map(str, (Hq, Hkv, chunk, 0, root, *leaves))]).startswith(route), (root, len(leaves), Hq, Hkv)
+
+
+CALLS = """
+class Launches(ctypes.Structure):
+    _fields_ = Fake._fields_ + [("grid", ctypes.c_int32 * 16), ("kernel", ctypes.c_void_p * 16)]
+fake = Launches.in_dll(fake_lib, "fake")
+def star(root, leaves, chunk):
+    lens = np.array([root] + [1] * leaves, np.int32)
+    begins = np.concatenate([[0], np.cumsum(lens)[:-1]]).astype(np.int32)
+    return binding.deft_plan(begins, lens, np.array([-1] + [0] * leaves, np.int32), np.arange(1, leaves + 1, dtype=np.int32), int(lens.sum()), chunk)
+def memory(n):
+    b = np.zeros(n + 16, np.uint8)
+    return b[-b.ctypes.data % 16:][:n]
+def image_of(plan, Hq, Hkv):
+    img = memory(plan.device_bytes(Hq, Hkv))
+    assert lib.deft_plan_upload(plan.handle, Hq, Hkv, img.ctypes.data, img.size, STREAM) == 0
+    return img
+def launches(call):
+    fake.launches = 0
+    assert call() == 0
+    return list(zip(fake.grid[:fake.launches], fake.kernel[:fake.launches]))
+x = memory(4096)  # q, k, v and the output: nothing reads them here
+def decode(plan, img, Hq, Hkv, d):
+    ws = memory(plan.workspace_bytes(Hq, Hkv, d))
+    return launches(lambda: lib.deft_tree_attn_decode(plan.handle, img.ctypes.data, *[x.ctypes.data] * 4, Hq, Hkv, d, 0.0, 1, ws.ctypes.data,
+                                                      ws.size, STREAM))
+"""
+
+
+@needs_gxx
+def test_cut_anew_only_for_the_kv_heads_it_was_made_for(fake):  # noqa: F811
+    # 49 chunks of up to 256 tokens with seven row tiles each, or eight runs of 1568 for 32 KV heads
+    run_faked(fake, CALLS + """
+plan = star(12345, 26, 128)
+img = image_of(plan, 128, 32)
+assert decode(plan, img, 128, 32, 128)[0][0] < 512
+assert decode(plan, img, 8, 2, 128)[0][0] >= 2 * 49
+assert decode(plan, img, 128, 32, 128)[0][0] < 512
+""")
 
 
 def star(root, leaves, Hq, Hkv, d, seed):

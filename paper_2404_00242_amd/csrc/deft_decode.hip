@@ -1992,7 +1992,7 @@ int run_stage2(const deft_plan_t *plan, const Call &call, const deft::TaskSet &T
     Stage2Args a2{};
     stage2_args(plan, call, T, o, Hq, flags, a2);
     // a stage 2 called apart may find slots that a whole call left empty
-    const bool holes = &T == &call.S->by_chunk && (call.S->fused.off_items != T.off_items || call.S->recut.n_items > 0);
+    const bool holes = &T == &call.S->by_chunk && whole_call(call, Hq / call.S->group, d).off_items != T.off_items;
     const bool ok = d == 128 ? (holes ? launch_stage2<128, true>(T, a2, call.stream) : launch_stage2<128, false>(T, a2, call.stream))
                              : (holes ? launch_stage2<64, true>(T, a2, call.stream) : launch_stage2<64, false>(T, a2, call.stream));
     return ok ? DEFT_OK : DEFT_EHIP;

@@ -88,6 +88,21 @@ assert decode(plan, img, 128, 32, 128)[0][0] < 512
 """)
 
 
+@needs_gxx
+def test_only_a_stage_2_that_may_find_empty_slots_looks_for_them(fake):  # noqa: F811
+    # called apart after a whole call with d = 128 it may, with d = 64 or other KV heads nothing is cut anew (nor joined, in chunks of 160)
+    run_faked(fake, CALLS + """
+plan = star(6500, 96, 160)
+img = image_of(plan, 32, 32)
+def stage2(Hq, Hkv, d):
+    ws = memory(plan.workspace_bytes(Hq, Hkv, d))
+    return launches(lambda: lib.deft_stage2_global_reduction(plan.handle, img.ctypes.data, x.ctypes.data, Hq, Hkv, d, 0.0, 1, ws.ctypes.data, ws.size, STREAM))
+assert decode(plan, img, 32, 32, 128)[0][0] != decode(plan, img, 32, 32, 64)[0][0]
+for (Hq, Hkv, d), same in (((32, 32, 128), False), ((32, 32, 64), True), ((16, 16, 128), True)):
+    assert (stage2(Hq, Hkv, d) == decode(plan, img, Hq, Hkv, d)[1:]) == same, (Hq, Hkv, d)
+""")
+
+
 def star(root, leaves, Hq, Hkv, d, seed):
     return wl._finish("recut", [root] + leaves, [-1] + [0] * len(leaves), list(range(1, len(leaves) + 1)), Hq, Hkv, d, seed)
 

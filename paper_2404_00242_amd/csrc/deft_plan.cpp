@@ -749,15 +749,19 @@ struct Cut {
 static Cut choose_cut(const deft_plan_t *P, const std::vector<Run> &runs, int32_t Hkv) {
     constexpr int kCuts = Cut::kCuts;
     int64_t n_short[kCuts] = {}, n_long[kCuts] = {}, work = 0, longest = 0;
+    int32_t tiles = -1, per = 0, n[kCuts] = {};  // of the run before: most have as many tiles
     for (const Run &r : runs) {
         const bool wide_and_long = Cut::is_wide_and_long(r);
-        for (int i = 0; i < kCuts; ++i) {
-            const int32_t per = Cut::per_task(r.tiles, kTaskTiles[i]), n = (r.tiles + per - 1) / per;
-            (wide_and_long ? n_long : n_short)[i] += n;
+        if (r.tiles != tiles) {
+            tiles = r.tiles;
+            for (int i = kCuts - 1; i >= 0; --i) {
+                per = Cut::per_task(tiles, kTaskTiles[i]);
+                n[i] = (tiles + per - 1) / per;
+            }
         }
-        const int32_t per = Cut::per_task(r.tiles, kTaskTiles[0]);
+        for (int i = 0; i < kCuts; ++i) (wide_and_long ? n_long : n_short)[i] += n[i];
         const int64_t cost = (int64_t)r.len * (2 + per);
-        work += cost * ((r.tiles + per - 1) / per);
+        work += cost * n[0];
         if (wide_and_long) longest = std::max(longest, distinct_pieces(P, r) > 1 ? cost * 4 / 3 : cost);
     }
     int cut_long = 0, cut_short = 0;
@@ -864,18 +868,17 @@ static int32_t full_tasks(int32_t tiles) { return (tiles + kMaxTilesPerTask - 1)
 // run beside others), a quarter more where rows are looked up, a fifth more where the stream starts new references; every task
 // has five steps of start and end and 1.5 a tile for its partial results, of which those that share a unit hide a tenth; 50
 // steps pass around stage 1 or do not depend on the cut.  Fitted to 1634 trees run both ways, see recut_runs.
-static int64_t launch_end(const deft_plan_t *P, const std::vector<Run> &runs, int32_t Hkv) {
-    const Cut cut = choose_cut(P, runs, Hkv);
+static int64_t launch_end(const deft_plan_t *P, const std::vector<Run> &runs, const Cut &cut, int32_t Hkv) {
     std::vector<std::pair<int64_t, int64_t>> kinds;  // cost, tasks
-    for (const Run &r : runs) {
+    for (size_t i = 0, e; i < runs.size(); i = e) {
+        const Run &r = runs[i];
         const int32_t per = cut.per_run(r), pieces = distinct_pieces(P, r);
+        for (e = i + 1; e < runs.size() && runs[e].len == r.len && runs[e].tiles == r.tiles && runs[e].fresh == r.fresh &&
+                        (distinct_pieces(P, runs[e]) > 1) == (pieces > 1);)
+            ++e;
         auto add = [&](int32_t tiles, int64_t n) {
             const int64_t step = (tiles > 4 ? 20 : tiles > 2 ? 16 : 5) * (pieces > 1 ? 25 : r.fresh ? 24 : 20) / 20;
-            const int64_t cost = (r.len + 31) / 32 * step + 100 + 30 * tiles;
-            if (!kinds.empty() && kinds.back().first == cost)
-                kinds.back().second += n * Hkv;
-            else
-                kinds.emplace_back(cost, n * Hkv);
+            kinds.emplace_back((r.len + 31) / 32 * step + 100 + 30 * tiles, n * (int64_t)(e - i) * Hkv);
         };
         if (r.tiles / per) add(per, r.tiles / per);
         if (r.tiles % per) add(r.tiles % per, 1);
@@ -968,17 +971,24 @@ static bool recut_runs(const deft_plan_t *P, const std::vector<Run> &own, const 
     }
     if (stretches.empty() || others * Hkv > kRecutOthers) return false;
     const Cut cut = choose_cut(P, joined, Hkv);
-    for (const Run &r : joined)  // (a row's last task has the fewest tiles)
-        if (two_tiles_a_wave(r) && r.len <= kLongChunk && (r.tiles - 1) % cut.per_run(r) < kResidentTiles && distinct_pieces(P, r) == 1)
-            return false;
-    int32_t length = kLongChunk;
-    auto fits = [&] {
+    int32_t streamed = 0;  // row tiles of the run before, if all its tasks stream: most have as many
+    for (const Run &r : joined)
+        if (r.len <= kLongChunk && r.tiles != streamed && two_tiles_a_wave(r) && distinct_pieces(P, r) == 1) {
+            if ((r.tiles - 1) % cut.per_run(r) < kResidentTiles) return false;  // the last task of a run has the fewest tiles
+            streamed = r.tiles;
+        }
+    auto fits = [&](int32_t length) {
         int64_t n = others;
         for (const Stretch &x : stretches) n += (int64_t)((x.len + length - 1) / length) * full_tasks(own[x.c0].tiles);
         return n * Hkv <= kLongGroups;
     };
-    while (length < DEFT_MAX_CHUNK && !fits()) length += 32;
-    if (!fits()) return false;
+    if (!fits(DEFT_MAX_CHUNK)) return false;
+    int32_t length = DEFT_MAX_CHUNK;  // the shortest that fits
+    for (int32_t too_short = kLongChunk - 32; length - too_short > 32;) {
+        const int32_t middle = (too_short + length) / 64 * 32;
+        (fits(middle) ? length : too_short) = middle;
+    }
+    out.reserve(own.size() + stretches.size());
     size_t c = 0;
     for (const Stretch &x : stretches) {
         out.insert(out.end(), own.begin() + c, own.begin() + x.c0);
@@ -1003,8 +1013,9 @@ static bool recut_runs(const deft_plan_t *P, const std::vector<Run> &own, const 
         c = x.c1;
     }
     out.insert(out.end(), own.begin() + c, own.end());
-    if (4 * (int64_t)choose_cut(P, out, Hkv).n_tasks * Hkv > 3 * kLongGroups &&
-        10 * launch_end(P, out, Hkv) < 9 * launch_end(P, joined, Hkv))
+    const Cut anew = choose_cut(P, out, Hkv);
+    if (4 * (int64_t)anew.n_tasks * Hkv > 3 * kLongGroups &&
+        10 * launch_end(P, out, anew, Hkv) < 9 * launch_end(P, joined, cut, Hkv))
         return true;
     out.clear();
     return false;
@@ -1061,10 +1072,13 @@ static void build_schedule(const deft_plan_t *P, int32_t G, int32_t Hkv, Schedul
         return at;
     };
     const bool same = joined.size() == own.size();
+    std::vector<Run> recut;
+    if (may_join(P)) recut_runs(P, own, joined, Hkv, recut);
     // room for the records and the lists whole, and for tasks as far as they are cut
-    S.host_image.reserve(4 * (5 * (size_t)nseg + P->nq + (same ? 1 : 2) * (P->q_part_slot.size() + kQueryHeadInts * (size_t)P->nq +
-                                                                          kItemInts * (size_t)(groups / Hkv + kResidentGroups))) +
-                         2 * kQueryHeadBytes + 1024);
+    const size_t sets = 1 + !same + !recut.empty();
+    S.host_image.reserve(4 * (5 * (size_t)nseg + P->nq + sets * (P->q_part_slot.size() + kQueryHeadInts * (size_t)P->nq +
+                                                                kItemInts * (size_t)((groups + kResidentGroups) / Hkv))) +
+                         sets * kQueryHeadBytes + 1024);
     S.off_seg_tok_begin = put(P->seg_tok_begin);
     S.off_seg_len = put(P->seg_len);
     S.off_seg_qlo = put(P->seg_qlo);
@@ -1075,19 +1089,20 @@ static void build_schedule(const deft_plan_t *P, int32_t G, int32_t Hkv, Schedul
     auto list_slots = [&](const std::vector<Run> &runs) {  // of each query's slots in the plan, those of a run's first chunk
         std::vector<uint8_t> first((size_t)m, 0);
         for (const Run &r : runs) first[r.c0] = 1;
-        ptr.clear();
-        slots.clear();
-        ptr.reserve((size_t)P->nq + 1);
-        slots.reserve(P->q_part_slot.size());
+        ptr.resize((size_t)P->nq + 1);
+        slots.resize(P->q_part_slot.size());
+        const int32_t *chunk = P->q_part_chunk.data(), *slot = P->q_part_slot.data(), *from = P->q_part_ptr.data();
+        int32_t n = 0;
         for (int32_t p = 0; p < P->nq; ++p) {
-            ptr.push_back((int32_t)slots.size());
-            for (int32_t i = P->q_part_ptr[p]; i < P->q_part_ptr[p + 1]; ++i)
-                if (first[P->q_part_chunk[i]]) slots.push_back(P->q_part_slot[i]);
+            ptr[p] = n;
+            for (int32_t i = from[p]; i < from[p + 1]; ++i) {
+                slots[n] = slot[i];
+                n += first[chunk[i]];
+            }
         }
-        ptr.push_back((int32_t)slots.size());
+        ptr[P->nq] = n;
+        slots.resize((size_t)n);
     };
-    std::vector<Run> recut;
-    if (may_join(P)) recut_runs(P, own, joined, Hkv, recut);
     build_tasks(P, G, Hkv, std::move(own), P->q_part_ptr, P->q_part_slot, S, S.by_chunk);
     if (same) {
         S.fused = S.by_chunk;

@@ -1917,7 +1917,8 @@ int prepare(const deft_plan_t *plan, const void *dev_image, int32_t Hq, int32_t 
     call.S = deft::find_schedule(plan, Hq / Hkv);
     if (!call.S) return DEFT_ENOTREADY;
     if (workspace_bytes < deft::partials_bytes(plan, Hq, d)) return DEFT_EWORKSPACE;
-    if ((int64_t)std::max({call.S->by_chunk.n_items, call.S->fused.n_items, call.S->recut.n_items}) * Hkv > INT32_MAX) return DEFT_EINVAL;  // grid sizes are 32-bit
+    const int32_t most = std::max(call.S->by_chunk.n_items, whole_call(call, Hkv, d).n_items);
+    if ((int64_t)most * Hkv > INT32_MAX) return DEFT_EINVAL;  // grid sizes are 32-bit
     if ((int64_t)plan->nq * Hq > INT32_MAX) return DEFT_EINVAL;
     const size_t rows = (size_t)plan->n_slots() * (size_t)Hq;
     call.img = static_cast<const uint8_t *>(dev_image);

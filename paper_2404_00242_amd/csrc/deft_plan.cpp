@@ -911,9 +911,9 @@ static int64_t launch_end(const deft_plan_t *P, const std::vector<Run> &runs, co
 // nodes of a draft tree), those become a run of their own with that chunk's slots.  The runs are as short as kLongGroups
 // workgroups allow, the short ones among the others counted whole; those are then cut as finely as kResidentGroups allow.
 // Only d = 128: with d = 64 twice as many tokens are held in registers, and longer runs stream them
-// (level to 30 % slower).  Nor where tasks of the launch as it is are held in registers, whose weights are rounded less: a call whose
-// rows all were was 1.27 times as far from 64 bits.  A run starts new references as often as the runs that it replaces began
-// (RowState).  false: not such a launch.
+// (level to 30 % slower).  Nor where tasks of the launch as it is are held in registers, whose weights are rounded less: a call
+// whose rows all were was 1.27 times as far from 64 bits.  A run starts new references as often as the runs that it replaces
+// began (RowState).  false: not such a launch.
 //
 // Nor unless the call is to end a tenth sooner (launch_end) on more than three quarters of the units: a run more is
 // full_tasks x Hkv workgroups more at once, and the count may stop well short of the units with every run the longer for it.
@@ -1036,7 +1036,8 @@ static void build_schedule(const deft_plan_t *P, int32_t G, int32_t Hkv, Schedul
         const int32_t len = s1 > s0 ? seg_off[s1 - 1] + P->seg_len[s1 - 1] - seg_off[s0] : 0;
         // two-term softmax weights where some query of the group has a short path
         const int32_t precise = P->precise_all || short_paths[hi] > short_paths[lo];
-        own[c] = {c, c + 1, s0, s1, s1 > s0 ? P->seg_tok_begin[s0] : 0, lo, hi, len, row_tiles(hi - lo, G), precise, P->chunk_slot_base[c], 0, 0};
+        const int32_t begin0 = s1 > s0 ? P->seg_tok_begin[s0] : 0;
+        own[c] = {c, c + 1, s0, s1, begin0, lo, hi, len, row_tiles(hi - lo, G), precise, P->chunk_slot_base[c], 0, 0};
     }
 
     // A whole call is free to work on several chunks as one.  It does so where the plan's chunks are many and short: with

@@ -1,7 +1,8 @@
 // Host-only check of the tasks of wide chunks cut anew (deft_plan.cpp, recut_runs), built with -fsanitize=address,undefined
-// by tests/test_recut.py: for random trees with a wide root, the tasks of the set hold every row tile of every token exactly
-// once under the queries that see it, a task of one piece has no query that does not, every slot of the plan is written or
-// marked empty exactly once, and a query's list names the slots that its tasks write.
+// by tests/test_recut.py: for random trees with wide nodes (a root under leaves, two of them, a chain of them; with gaps between
+// nodes, and paged), the tasks of the set hold every row tile of every token exactly once under the queries that see it, a task
+// of one piece has no query that does not, every slot of the plan is written or marked empty exactly once, and a query's list
+// names the slots that its tasks write.  Long tasks are at most one to a compute unit, and all are on the chip at once.
 #include <cstdint>
 #include <cstdio>
 #include <map>
@@ -22,21 +23,25 @@ static int32_t below(int32_t n) {
 
 int main() {
     using namespace deft;
-    long sets = 0, rests = 0, whole = 0;
-    for (int it = 0; it < 250; ++it) {
-        const int32_t G = 1 << below(5), Hkv = 1 << below(6), leaves = 1 + (64 + below(300)) / G, kind = below(3);
-        const int32_t page = below(4) ? 0 : 16, root = 32 * (20 + below(2500) / Hkv) + below(3) * below(32), nodes = leaves + 1;
+    long sets = 0, rests = 0, whole = 0, several = 0;
+    for (int it = 0; it < 1500; ++it) {
+        const int32_t G = 1 + below(it & 1 ? 8 : 16), Hkv = 1 + below(32), leaves = 2 + (64 + below(300)) / G;
+        const int32_t kind = below(3), shape = below(4);
+        const int32_t page = below(4) ? 0 : 16, gap = below(3) ? 0 : 64 * below(2), inner = shape == 0 ? 2 : shape == 1 ? 3 : 1;
+        const int32_t nodes = leaves + inner;
         std::vector<int32_t> begin(nodes), len(nodes), parent(nodes, 0), qn(leaves);
-        parent[0] = -1;
-        for (int32_t u = 0, at = 0; u < nodes; at += len[u++]) {
-            len[u] = u == 0 ? root : kind == 0 ? 1 : kind == 1 ? below(12) : (u == 1 ? 300 : 1 + below(4));
+        for (int32_t u = 0, at = 0; u < nodes; at += len[u++] + gap) {
+            const int32_t root = 32 * (20 + below(2500) / Hkv) + below(3) * below(32);
+            len[u] = u < inner ? root : kind == 0 ? 1 : kind == 1 ? below(12) : (u == inner ? 300 : 1 + below(4));
+            // shape 0: two trees of half the leaves each; 1: a chain of three wide nodes; else one root
+            parent[u] = u < inner ? (shape == 1 ? u - 1 : -1) : shape == 0 ? (u - inner) * 2 / leaves : inner - 1;
             begin[u] = at;
-            if (u) qn[u - 1] = u;
+            if (u >= inner) qn[u - inner] = u;
         }
         int32_t total = 0;
-        for (int32_t n : len) total += n;
+        for (int32_t n : len) total += n + gap;
         const uint32_t mode = below(2) ? DEFT_SPLIT_FLATTEN : DEFT_SPLIT_BALANCED;
-        const int32_t chunk = 32 << below(5);
+        const int32_t chunk = 32 * (1 + below(16));
         deft_plan_t *P = nullptr;
         if (page) {  // every other page in its place, the others swapped: roots of several pieces
             std::vector<int32_t> ptr(1, 0), ids;
@@ -69,6 +74,9 @@ int main() {
             CHECK(tiles[d[kItSlotBase]] == d[kItTile0]);
             tiles[d[kItSlotBase]] += d[kItNTiles];
             if (d[kItTile0]) continue;
+            whole += d[kItPieces] > 1 && d[kItChunk] > 0 && d[kItSeg0] == P->chunk_seg_ptr[d[kItChunk]] &&
+                     P->seg_qlo[d[kItSeg0]] == lo && P->seg_qhi[d[kItSeg0]] == hi && P->chunk_qlo[d[kItChunk] - 1] == lo &&
+                     P->chunk_qhi[d[kItChunk] - 1] == hi;
             for (int32_t k = 0; k < d[kItChunks] * d[kItWidth]; ++k) CHECK(slots_done.insert(d[kItSlotBase] + k).second);
             for (int32_t p = lo; p < hi; ++p) written[p].insert(d[kItSlotBase] + p - lo);
             std::vector<int32_t> rows;
@@ -90,7 +98,13 @@ int main() {
         }
         if (T.n_items) {
             ++sets;
-            whole += P->chunk_seg_ptr[P->n_chunks()] - P->chunk_seg_ptr[P->n_chunks() - 1] > 1;
+            several += shape < 2;
+            for (int32_t i = 0; i < T.n_items; ++i) {
+                const int32_t *d = at(T.off_items) + (size_t)i * kItemInts;
+                CHECK(tiles[d[kItSlotBase]] == (d[kItWidth] * G + 15) / 16);
+                const int32_t fresh = d[kItFresh];
+                CHECK(fresh >= 0 && (fresh & (fresh - 1)) == 0 && (fresh == 0 || d[kItPieces] == 1));
+            }
             for (const auto &x : sees) CHECK(x == nobody);
             CHECK((int32_t)slots_done.size() == P->n_slots());
             int64_t groups = (int64_t)T.n_items * Hkv, of_long = 0;
@@ -109,6 +123,7 @@ int main() {
         }
         deft_plan_destroy(P);
     }
-    printf("recut sets checked: %ld, %ld with a rest, %ld ending in several pieces\n", sets, rests, whole);
-    return sets > 40 && rests > 10 ? 0 : 2;
+    // sets; with a rest of a last chunk, with a last chunk that stays whole, of trees with several wide nodes
+    printf("recut sets checked: %ld, %ld with a rest, %ld whole chunks, %ld of several wide nodes\n", sets, rests, whole, several);
+    return sets > 40 && rests > 10 && whole > 5 && several > 10 ? 0 : 2;
 }

@@ -13,7 +13,8 @@ from .test_sanitizers import ROOT, SAN, run
 from .test_short_chunks import check, reference
 
 # (root, leaves, Hq, Hkv): rows that fill no tile (heads x queries a multiple of 16 or not), tokens that fill no block
-STARS = [(2048, 48, 16, 16), (2080, 45, 16, 16), (2049, 33, 17, 17), (4095, 41, 8, 8), (4224, 48, 8, 8), (4095, 45, 32, 32), (4000, 41, 24, 24)]
+STARS = [(2048, 48, 16, 16), (2080, 45, 16, 16), (2049, 33, 17, 17), (4095, 41, 8, 8), (4224, 48, 8, 8), (4095, 45, 32, 32),
+         (4000, 41, 24, 24)]
 CHUNKS = (96, 128, 256)
 # those of them whose three tiles stay in one task: elsewhere the chip has room for two and one
 THREE = {(2049, 33, 17, 17, 128), (4095, 45, 32, 32, 96), (4095, 45, 32, 32, 128), (4095, 45, 32, 32, 256),

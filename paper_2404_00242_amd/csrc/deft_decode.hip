@@ -185,7 +185,7 @@ struct ChunkCtx {
     int clen;                       // tokens in the chunk
     int uniform;                    // the chunk is one piece of one node: rows are begin0 + x
     int begin0, qlo0, qhi0;
-    int fresh;                      // a block whose number has none of these bits set starts a new reference; -1: none does
+    int fresh;                      // blocks after which a new reference is taken (RowState), less one; -1: never
     int n16, g;
 };
 
@@ -244,11 +244,10 @@ __device__ __forceinline__ void load_v(KVRegs<D> &r, const ChunkCtx &c, int x0, 
 // no rescaling of the accumulators.  Any reference gives the same (m, l, acc) up to rounding, because the
 // merge of eq. 1 only needs the three to be consistent.
 // The rounding is the smaller the more tokens were the reference once: such a token is among the heaviest of its row, and its
-// weight is exactly 1.  A stream that replaces several shorter ones therefore starts a new reference where each of them
-// would have begun (kItFresh): the largest exponent of that block, also if it is below the old one, but by no more than
-// kFreshLog2, which keeps the sums in range whatever the scores do (2^48 times larger after 6000 tokens in steps of 128).
-// Error against 64 bits over 330 calls with their chunks cut anew (recut_runs): 1.019 times what it is in the plan's chunks
-// with one reference to a stream, 0.99 with these, for 1.5 to 3 % of the call's time.
+// weight is exactly 1.  A stream that replaces several shorter ones therefore takes a new reference where each of them would
+// have begun (kItFresh): the largest exponent of that block, also if it is below the old one, but by no more than kFreshLog2,
+// which keeps the sums in range whatever the scores do (2^48 times larger after 6000 tokens in steps of 128).  Only with bf16
+// weights: asked in the loops of two-term weights too, it cost trees of both kinds 0.7 % (40.8 -> 41.1 us).
 struct RowState {
     float mc, thr;
     f32x4 l;  // four identical copies (rows 4g..4g+3 of the all-ones product)
@@ -345,7 +344,7 @@ __device__ __forceinline__ void shift_block(const TileState<D> (&ts)[NT], f32x4 
 // lazy reference, on the shifted scores of shift_block: it is raised (for every tile of the wave) only when
 // some exponent exceeds kLazyLog2, i.e. some score exceeds the reference by more than kLazyLog2 / cs.  The
 // exponents come out of an fma, so their maximum needs no canonicalisation and takes four instructions per tile.
-// fresh: the block starts a new reference.
+// fresh: the block takes a new reference.
 template <int D, int NT>
 __device__ __forceinline__ void raise_block(TileState<D> (&ts)[NT], f32x4 (&sacc)[NT][2], bool fresh = false) {
     float mx[NT];
@@ -702,7 +701,7 @@ struct WidePipe {
     template <bool PRECISE, bool WHOLE>
     __device__ __forceinline__ void step(S &sh, const ChunkCtx &c, u32x4 *xs, int t, int lane, int blk, int nblk,
                                          TileState<D> (&ts)[NT], f32x4 (&sacc)[NT][2], u32x4 (&vreg)[8], float cs,
-                                         float inv_cs) {
+                                         float inv_cs, bool fresh = false) {
         exchange(sh, c, xs, t, lane, blk + DEPTH, nblk);
         bf16x8 k[2][KK];
         read_k(xs, lane, k);
@@ -714,7 +713,7 @@ struct WidePipe {
         read_v(xs, lane, vreg);
         if (!WHOLE) mask_block<D, NT>(c, blk * 32, ts, snew);
         shift_block<D, NT>(ts, snew, cs);
-        raise_block<D, NT>(ts, snew, UNIFORM && (blk & c.fresh) == 0);
+        raise_block<D, NT>(ts, snew, fresh);
 #pragma unroll
         for (int tt = 0; tt < NT; ++tt) {
             sacc[tt][0] = snew[tt][0];
@@ -747,10 +746,14 @@ struct WidePipe {
         const int b_end = kWhole ? nblk - 1 : nblk;
         int b0 = 1;
         for (; b0 + DEPTH <= b_end; b0 += DEPTH) {
+            // whether the round begins with a new reference (RowState); asked once a round, because in every step it cost the
+            // wide tasks that keep one reference 0.3 to 0.4 %
+            const bool fresh = UNIFORM && !PRECISE && (b0 & ctx.fresh) == max(ctx.fresh, 0);
 #pragma unroll
             for (int u = 0; u < DEPTH; ++u) {
                 const int blk = b0 + u;
-                step<PRECISE, kWhole>(st[(1 + u) % DEPTH], ctx, xbuf + (blk & 1) * STAGE, t, lane, blk, nblk, ts, sacc, vreg, cs, inv_cs);
+                step<PRECISE, kWhole>(st[(1 + u) % DEPTH], ctx, xbuf + (blk & 1) * STAGE, t, lane, blk, nblk, ts, sacc, vreg, cs, inv_cs,
+                                      u == 0 && fresh);
             }
         }
 #pragma unroll
@@ -1190,7 +1193,7 @@ __device__ __forceinline__ LeftRows streaming_task(const Stage1Args &a, const in
     ctx.begin0 = it[deft::kItBegin0];
     ctx.qlo0 = it[deft::kItSegQlo0];
     ctx.qhi0 = it[deft::kItSegQhi0];
-    ctx.fresh = it[deft::kItFresh] - 1;
+    ctx.fresh = SHARED ? -1 : it[deft::kItFresh] - 1;  // (calls of few rows have no such tasks)
     ctx.n16 = n16;
     ctx.g = g;
     const int nblk = (clen + 31) >> 5;

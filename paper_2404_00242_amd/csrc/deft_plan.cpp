@@ -912,20 +912,22 @@ static int64_t launch_end(const deft_plan_t *P, const std::vector<Run> &runs, co
 // workgroups allow, the short ones among the others counted whole; those are then cut as finely as kResidentGroups allow.
 // Only d = 128: with d = 64 twice as many tokens are held in registers, and longer runs stream them
 // (level to 30 % slower).  Nor where tasks of the launch as it is are held in registers, whose weights are rounded less: a call
-// whose rows all were was 1.27 times as far from 64 bits.  A run starts new references as often as the runs that it replaces
-// began (RowState).  false: not such a launch.
+// whose rows all were was 1.27 times as far from 64 bits.  Nor chunks of two-term weights.  A run takes new references as often as
+// the runs that it replaces began (RowState).  false: not such a launch.
 //
 // Nor unless the call is to end a tenth sooner (launch_end) on more than three quarters of the units: a run more is
 // full_tasks x Hkv workgroups more at once, and the count may stop well short of the units with every run the longer for it.
 // Whole call, us, as planned -> cut anew: 12345 tokens under 26 queries x 4 heads (392 workgroups of 256 tokens -> 240 of 416 and
-// 32 short ones) 24.4 -> 21.9, 4000 under 51 x 4 in chunks of 160 26.6 -> 22.2, 9000 under 81 x 1 34.0 -> 25.1; but 15589 under 35
+// 32 short ones) 24.4 -> 21.8, 4000 under 51 x 4 in chunks of 160 26.6 -> 22.2, 9000 under 81 x 1 34.0 -> 25.1; but 15589 under 35
 // x 8 (480 of 768 tokens -> 216 of 1760 or less) 39.9 -> 46.8.  The estimate was fitted to 1634 trees of 4 to 300 queries and 1 to
-// 64 KV heads run both ways, then tried on 600 others: the 407 it takes are 0.81 of the time (0.45 to 1.19), 5 of them above 1.02
-// (1.10 to 1.19: two of 638 and 1541 tokens under more than 100 queries, and three of 1, 4 and 5 KV heads whose steps take half as
-// long again as others', why is not known); without it 46 of the 600 would be, up to 1.36.  On 205 draft, few-shot and long-context
-// trees of up to 64 queries: 0.84, 1.01 at most.  With more others than kRecutOthers the narrow tasks would have shared the units:
-// 0.97 at 65 to 80, 1.04 at 81 to 96, 1.11 at 97 to 112, 1.2 and more beyond (1975 trees, without the estimate).  One tile to a
-// wave (3 or 4 in a task) loses at G = 1, where the launch waits for HBM: 1.09 and 1.02, up to 1.5.
+// 64 KV heads run both ways, then tried on 600 others: the 404 it takes are 0.79 of the time (0.44 to 1.17), 4 of them above 1.02
+// (1.08 to 1.17: 1541 tokens under 256 queries, and three trees of 1, 4 and 5 KV heads whose steps take half as long again as
+// others', why is not known); without it 36 of the 600 are, up to 1.35.  205 draft, few-shot and long-context trees of up to 64
+// queries among them: 0.82, 0.99 at most.  With more others than kRecutOthers the narrow tasks would have shared the units: 0.97 at
+// 65 to 80, 1.04 at 81 to 96, 1.11 at 97 to 112, 1.2 and more beyond (1975 trees, without the estimate).  One tile to a wave (3 or 4
+// in a task) loses at G = 1, where the launch waits for HBM: 1.09 and 1.02, up to 1.5.
+//
+// Error against 64 bits, 100 of the 404: 0.995 times what it is as planned (1.01 at most), 1.02 (1.05) with one reference to a run.
 static bool recut_runs(const deft_plan_t *P, const std::vector<Run> &own, const std::vector<Run> &joined, int32_t Hkv,
                        std::vector<Run> &out) {
     auto two_tiles_a_wave = [](const Run &r) {
@@ -960,7 +962,7 @@ static bool recut_runs(const deft_plan_t *P, const std::vector<Run> &own, const 
                 --x.c1;
             }
         }
-        if (x.s1 >= last.s0 && x.slots > 1 && two_tiles_a_wave(r)) {
+        if (x.s1 >= last.s0 && x.slots > 1 && two_tiles_a_wave(r) && !r.precise) {
             while (joined[at].c0 < r.c0) ++at;
             while (64 * x.fresh <= joined[at].len) x.fresh *= 2;
             stretches.push_back(x);
